@@ -213,7 +213,7 @@ sc_status sparse_conv_plan_tiles(const sc_plan* plan, int32_t which, int32_t* ti
 
 /* Name of the kernel the sparse (which = 0) or dense (which = 1) launch uses: "band",
  * "band_alternating", "band_tap", "band_stream", "band_row_segments", "tile_row_panel", "tile_slab", "tile_split_k", "tile_masked_store", "tile_stream_k", "tile_lds_direct",
- * "tile_registers", "tile_row_segments", "tile_elements" or "depthwise".
+ * "tile_registers", "tile_staged", "tile_row_segments", "tile_elements" or "depthwise".
  * A static string; NULL for a NULL plan or an unknown `which`. */
 const char* sparse_conv_plan_kernel(const sc_plan* plan, int32_t which);
 /* The same for a launch fused with a shortcut sum (sparse_conv_run_residual / dense_conv_run_residual with dense
@@ -247,7 +247,12 @@ sc_status sparse_conv_plan_tune(sc_plan* plan, const void* x_dev, const float* b
  *                                                matrix work; the one whose filters arrive window row by
  *                                                window row under the matrix work (both: 3x3 windows, 16-bit
  *                                                types, 32 or 64 input channels); the automatic choice
- *                                                without the last; automatic otherwise */
+ *                                                without the last; automatic otherwise
+ *   SPARSE_CONV_STAGE_TILE=<rows>x<couts>[x<groups>]
+ *                                                tile of the kernel reported as "tile_staged" (float layers, channel
+ *                                                counts off the 16-byte group, SC_NCHW) and how many groups of
+ *                                                wavefronts share its K tiles (float NHWC); 0x0 = other kernels;
+ *                                                automatic otherwise */
 
 /* Tuning hook: SC_OPT_GATHER_PIPELINE selects how the tiled gather kernel moves its K tiles:
  * 0 = automatic, 1 = global -> registers -> LDS, 2 = global -> LDS directly (NHWC with 16-byte

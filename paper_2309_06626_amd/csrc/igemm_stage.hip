@@ -1,0 +1,150 @@
+// Instantiations of the register-staged tiled kernel, and the plan-time kernels that pack its filters and its gather table.
+#include "igemm_stage_kernel.hpp"
+
+namespace sc {
+
+template <int DT, int GATHER, bool NCHW>
+static LaunchFn stage_tile(int bm, int bn) {
+  if (bm == 128 && bn == 64) return igemm_stage_launch<DT, 128, 64, 2, 2, GATHER, NCHW>;
+  if (bm == 128 && bn == 32) return igemm_stage_launch<DT, 128, 32, 4, 1, GATHER, NCHW>;
+  if (bm == 64 && bn == 128) return igemm_stage_launch<DT, 64, 128, 2, 2, GATHER, NCHW>;
+  if (bm == 64 && bn == 64) return igemm_stage_launch<DT, 64, 64, 2, 2, GATHER, NCHW>;
+  return nullptr;
+}
+
+template <int DT>
+static LaunchFn stage_gather(int gather, bool nchw, int bm, int bn) {
+  if (gather == kStageRaggedGroups) return stage_tile<DT, kStageRaggedGroups, false>(bm, bn);
+  if (gather == kStageChunks) return stage_tile<DT, kStageChunks, true>(bm, bn);
+  if (gather == kStageEntries) return nchw ? stage_tile<DT, kStageEntries, true>(bm, bn) : stage_tile<DT, kStageEntries, false>(bm, bn);
+  if constexpr (DT == kF32) {
+    if (gather == kStageGroups) return stage_tile<DT, kStageGroups, false>(bm, bn);
+  }
+  return nullptr;          // (16-byte groups of a 16-bit type go straight into LDS: other kernels)
+}
+
+LaunchFn stage_kernel(int dtype, int gather, bool nchw, int bm, int bn) {
+  if (dtype == kF32) return stage_gather<kF32>(gather, nchw, bm, bn);
+  if (dtype == kF16) return stage_gather<kF16>(gather, nchw, bm, bn);
+  return stage_gather<kBF16>(gather, nchw, bm, bn);
+}
+
+// The K order of a gather: entry k of the tiles is channel `ci` of tap `tap`, or a filter entry that stays zero.
+struct StageOrder {
+  int gather, v, c_in, taps, cpad;
+  __device__ bool at(int k, int* tap, int* ci) const {
+    if (gather <= kStageRaggedGroups) {
+      *tap = k / cpad;
+      int e = k - *tap * cpad;
+      if (e + v >= cpad && cpad > c_in) {              // the pixel's last group ends at its last channel
+        e += c_in - cpad;
+        *ci = e;
+        return *tap < taps && e >= cpad - v;          // (what it repeats of the group before meets zeros)
+      }
+      *ci = e;
+    } else {
+      *tap = k / c_in;
+      *ci = k - *tap * c_in;
+    }
+    return *tap < taps;
+  }
+};
+
+// One thread per 16 bytes of the packed filters: [32 channels][K tile][part][K step][lane].  Channel rows are permuted so
+// that a lane of the MFMA result owns 16 consecutive channels.
+template <int DT>
+__global__ void stage_pack_kernel(const typename Elem<DT>::T* __restrict__ w, v4i* __restrict__ wp, StageOrder o, int c_out,
+                                  int blocks, int k_tiles, int kh, int kw, int nchw) {
+  using D = StageDims<DT>;
+  using T = typename Elem<DT>::T;
+  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= (int64_t)blocks * k_tiles * D::KSTEPS * 64) return;
+  const int lane = (int)(idx & 63);
+  const int64_t unit = idx >> 6;
+  const int ks = (int)(unit % D::KSTEPS);
+  const int64_t tile = unit / D::KSTEPS;
+  const int kt = (int)(tile % k_tiles), nb = (int)(tile / k_tiles);
+  const int m = lane & 31, half = lane >> 5;
+  const int co = nb * 32 + 16 * ((m >> 2) & 1) + 4 * (m >> 3) + (m & 3);
+  T e[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    int tap, ci;
+    const bool real = o.at(kt * D::K_TILE + (2 * ks + half) * 8 + i, &tap, &ci) && co < c_out;
+    e[i] = !real ? (T)0.0f : nchw ? w[((int64_t)co * o.c_in + ci) * o.taps + tap] : w[((int64_t)co * o.taps + tap) * o.c_in + ci];
+  }
+  v4i* dst = wp + tile * (D::BLOCK_BYTES / 16) + ks * 64 + lane;
+  if constexpr (DT == kF32) {
+    uint16_t parts[3][8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const float f = e[i];
+      const uint32_t bits = __builtin_bit_cast(uint32_t, f);
+      const bool finite = (bits & 0x7f800000u) != 0x7f800000u;
+      float a = (float)(__bf16)f;
+      // a finite value that would round to infinity is cut instead; one that is not finite is its own first part and
+      // its second one is not a number, so that every sum it enters asks for the careful pass
+      if (finite && (__builtin_bit_cast(uint32_t, a) & 0x7f800000u) == 0x7f800000u) a = __builtin_bit_cast(float, bits & 0xffff0000u);
+      const float r = f - a;
+      const float b = finite ? (float)(__bf16)r : __builtin_nanf("");
+      const float c = finite ? r - b : 0.0f;
+      parts[0][i] = (uint16_t)(__builtin_bit_cast(uint32_t, a) >> 16);
+      parts[1][i] = (uint16_t)(__builtin_bit_cast(uint32_t, b) >> 16);
+      parts[2][i] = (uint16_t)(__builtin_bit_cast(uint32_t, c) >> 16);
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      v4i v;
+      __builtin_memcpy(&v, parts[q], 16);
+      dst[q * D::KSTEPS * 64] = v;
+    }
+  } else {
+    v4i v;
+    __builtin_memcpy(&v, e, 16);
+    dst[0] = v;
+  }
+}
+
+// Table entry: byte offset from the window's corner, and the validity bits its tap needs.
+__global__ void stage_table_kernel(KEntry* __restrict__ tab, int entries, int per, StageOrder o, int kw, int dil_h, int dil_w,
+                                   int eb, int xs_h, int xs_w, int xs_c) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= entries) return;
+  int tap, ci;
+  // (of a last group the entry that counts is its last one: the group ends there)
+  o.at(i * per, &tap, &ci);
+  KEntry e;
+  e.off = 0;
+  e.dydx = (int32_t)kStageNoTap;
+  if (tap < o.taps) {
+    const int ky = tap / kw, kx = tap % kw;
+    e.off = (ky * dil_h * xs_h + kx * dil_w * xs_w + ci * xs_c) * eb;
+    uint32_t bits = (1u << ky) | (1u << (8 + kx));
+    if (o.gather == kStageRaggedGroups && (i * per) % o.cpad + per == o.cpad) bits |= kStageTail;
+    e.dydx = (int32_t)bits;
+  }
+  tab[i] = e;
+}
+
+hipError_t stage_pack(int dtype, int gather, const void* w, void* wp, KEntry* tab, int c_out, int blocks, int c_in, int kh, int kw,
+                      int dil_h, int dil_w, int k_tiles, bool nchw, int h, int w_cols, hipStream_t stream) {
+  const int v = dtype == kF32 ? 4 : 8, eb = dtype == kF32 ? 4 : 2;
+  const StageOrder o = {gather, v, c_in, kh * kw, (c_in + v - 1) / v * v};
+  const int ksteps = dtype == kF32 ? StageDims<kF32>::KSTEPS : StageDims<kBF16>::KSTEPS;
+  const int64_t total = (int64_t)blocks * k_tiles * ksteps * 64;
+  const dim3 grid((unsigned)((total + 255) / 256)), block(256);
+  if (dtype == kF32)
+    hipLaunchKernelGGL(stage_pack_kernel<kF32>, grid, block, 0, stream, (const float*)w, (v4i*)wp, o, c_out, blocks, k_tiles, kh, kw, nchw ? 1 : 0);
+  else      // 16-bit patterns are moved verbatim
+    hipLaunchKernelGGL(stage_pack_kernel<kF16>, grid, block, 0, stream, (const _Float16*)w, (v4i*)wp, o, c_out, blocks, k_tiles, kh, kw, nchw ? 1 : 0);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !tab) return e;
+  const int per = gather <= kStageRaggedGroups ? v : gather == kStageChunks ? 8 : 1;
+  const int entries = k_tiles * (dtype == kF32 ? StageDims<kF32>::K_TILE : StageDims<kBF16>::K_TILE) / per;
+  const int xs_h = nchw ? w_cols : w_cols * c_in, xs_w = nchw ? 1 : c_in, xs_c = nchw ? h * w_cols : 1;
+  hipLaunchKernelGGL(stage_table_kernel, dim3((entries + 255) / 256), dim3(256), 0, stream, tab, entries, per, o, kw, dil_h, dil_w, eb,
+                     xs_h, xs_w, xs_c);
+  return hipGetLastError();
+}
+
+}  // namespace sc

@@ -1,0 +1,546 @@
+// Tiled masked-convolution kernel whose operand tiles pass through registers on their way into LDS.
+//
+// Serves the layers whose rows cannot be transferred as they lie in memory:
+//   * float operands.  The float MFMA runs at a sixteenth of the 16-bit rate, so a float tile is staged as three bf16
+//     parts: x = x1 + x2 + x3 with x1 = bf16(x), x2 = bf16(x - x1), x3 = x - x1 - x2.  The split is exact (24 significand
+//     bits in three times 8, the remainders are representable), and of the nine products of a pair of parts the six
+//     largest are contracted: x1w1, x1w2, x2w1, x2w2, x1w3, x3w1.  What is left out (x2w3, x3w2, x3w3) is below 2^-25 of
+//     |x w|, less than the rounding of one float addition; the products themselves are exact in the matrix unit, x1w1
+//     and the five small ones go to accumulators of their own, and one MFMA adds sixteen of them, so fewer roundings
+//     happen than with the float MFMA (two per addition step).  A value that is not finite makes its remainder
+//     not-a-number and with it the sums it enters: a workgroup that finds one contracts its tile again with the float
+//     MFMA on the unsplit values (`careful` pass), which gives the infinities of the plain sum.
+//   * NHWC channel counts that are no multiple of the 16-byte group (a pruned network run as it is): a group is an
+//     element-aligned 16-byte load inside one pixel.  The last group of a pixel is the one that ENDS at its last
+//     channel; the entries it repeats meet zero filter entries, and the careful pass clears them.
+//   * channels-first tensors, and pixels with fewer channels than a group: one load per entry.  A wavefront's lanes are
+//     64 rows of the tile and the entry is the same for all of them, so what a lane adds is one 32-bit offset, and a
+//     load touches the few cache lines that hold the row's neighbours along a map row.
+//
+// K is cut into chunks of eight entries; a K tile is four chunks of floats or eight of a 16-bit type.  In LDS a tile
+// lies in the order in which the MFMA reads it -- [part][32 rows][K step][lane] of 16 bytes -- with the row exchanged by
+// a multiple of the chunk number so that the sixteen lanes of a write phase hit sixteen different bank groups.  The
+// filters are packed in the same order at plan time, so their transfer is a plain copy.
+//
+// What bounds it: a K tile passes LDS twice (written by the threads that fetched it, read by the wavefronts), and one load per
+// entry keeps a channels-first tile at the rate of the address units.  Loads run two tiles ahead in registers; the table that
+// says where they go runs three ahead, because waiting for a load waits for all that were issued before it.  Measured at
+// s = 0.5 (element gather before / this kernel, us): 32 x 128 -> 128 @28 channels first in float 115 / 46, in bf16 84 / 27.5;
+// 64 x 102 -> 102 @28 in fp16 at s = 0.3 98 / 27.5, 51 -> 51 @56 110 / 44, 410 -> 410 @7 186 / 27.
+//
+// Workgroup = BM kept rows x BN channels, four wavefronts; zero-fill ownership and the order of the epilogue are those
+// of the other tiled kernels.
+#pragma once
+#include "igemm_buf_kernel.hpp"
+
+namespace sc {
+
+// how window entries reach a tile
+enum StageGather { kStageGroups = 0,         // NHWC, Cin a multiple of the 16-byte group
+                   kStageRaggedGroups = 1,   // NHWC, Cin at least one group, not a multiple of it
+                   kStageChunks = 2,         // one load per entry, eight channels of a tap per table entry (NCHW, Cin % 8 == 0)
+                   kStageEntries = 3 };      // one load per entry, a table entry each (any layout, any Cin)
+
+constexpr uint32_t kStageNoTap = 1u << 30;       // a validity bit no row has: entries beyond the last one
+constexpr uint32_t kStageTail = 1u << 31;        // the group repeats entries of the one before it
+
+template <int DT> struct StageDims {
+  static constexpr int PARTS = DT == kF32 ? 3 : 1;
+  static constexpr int CHUNKS = DT == kF32 ? 4 : 8;        // chunks of eight entries in a K tile
+  static constexpr int KSTEPS = CHUNKS / 2;                // 32x32x16 steps
+  static constexpr int SWZ = 16 / CHUNKS;                  // row exchanged with (chunk * SWZ)
+  static constexpr int BLOCK_BYTES = PARTS * KSTEPS * 1024;   // 32 rows (or channels) x one K tile
+  static constexpr int K_TILE = 8 * CHUNKS;
+};
+template <int DT, int BM, int BN> constexpr size_t stage_lds_bytes() {
+  return 2 * (size_t)((BM + BN) / 32) * StageDims<DT>::BLOCK_BYTES + (BM + BN) * 4;
+}
+
+// (the two float halves of a packed pair of bf16, exactly)
+__device__ __forceinline__ float bf16_lo(uint32_t v) { return __builtin_bit_cast(float, v << 16); }
+__device__ __forceinline__ float bf16_hi(uint32_t v) { return __builtin_bit_cast(float, v & 0xffff0000u); }
+// upper halves of two registers side by side
+__device__ __forceinline__ uint32_t upper_halves(uint32_t lo, uint32_t hi) { return __builtin_amdgcn_perm(hi, lo, 0x07060302u); }
+// Eight floats -> three parts of eight bf16.  The first part rounds to nearest (half away from zero: one integer addition;
+// it leaves remainders of either sign, so that the products left out have no common sign), the second one truncates; both
+// remainders are exact, and the last one has at most eight significand bits.
+__device__ __forceinline__ void split3(const float (&f)[8], v4i& p1, v4i& p2, v4i& p3) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    uint32_t h[2], m[2], l[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const float v = f[2 * i + e];
+      h[e] = __builtin_bit_cast(uint32_t, v) + 0x8000u;
+      const float r = v - __builtin_bit_cast(float, h[e] & 0xffff0000u);
+      m[e] = __builtin_bit_cast(uint32_t, r);
+      l[e] = __builtin_bit_cast(uint32_t, r - __builtin_bit_cast(float, m[e] & 0xffff0000u));
+    }
+    p1[i] = (int)upper_halves(h[0], h[1]);
+    p2[i] = (int)upper_halves(m[0], m[1]);
+    p3[i] = (int)upper_halves(l[0], l[1]);
+  }
+}
+// the float a triple of parts stands for (a value that is not finite has itself as the first part)
+__device__ __forceinline__ float join3(float a, float b, float c) {
+  return (__builtin_bit_cast(uint32_t, a) & 0x7f800000u) == 0x7f800000u ? a : (a + b) + c;
+}
+
+// Bias, activation, shortcut and store of a lane's 16 channels c0 .. c0 + 15 of output row rr, for any layout: 16-byte
+// groups at element alignment for NHWC, elements for NCHW.
+template <int DT, bool NCHW>
+__device__ __forceinline__ void stage_store_row(const float (&acc)[16], int rr, int c0, const ConvParams& p, const float* s_bias_at) {
+  using T = typename Elem<DT>::T;
+  constexpr int V = Elem<DT>::V;
+  int64_t at;
+  if constexpr (!NCHW) at = (int64_t)rr * p.c_out + c0;
+  else {
+    const int n = fast_div(rr, p.div_howo_mul, p.div_howo_shift);
+    at = n * p.ys_n + (rr - n * p.ho_wo) + (int64_t)c0 * p.ys_c;
+  }
+  const int ok = min(16, p.c_out - c0);
+  T* y = static_cast<T*>(p.y) + at;
+  const T* res = p.residual ? static_cast<const T*>(p.residual) + at : nullptr;
+  T out[16];
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    float f = acc[v] + (s_bias_at ? s_bias_at[v] : 0.0f);
+    if (p.relu) f = fmaxf(f, 0.0f);
+    if (res && v < ok) f += (float)(NCHW ? res[(int64_t)v * p.ys_c] : res[v]);
+    if (p.residual_relu) f = fmaxf(f, 0.0f);
+    out[v] = Elem<DT>::from_float(f);
+  }
+  if constexpr (NCHW) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+      if (v < ok) y[(int64_t)v * p.ys_c] = out[v];
+  } else {
+#pragma unroll
+    for (int g = 0; g < 16 / V; ++g) {
+      if (V * g + V <= ok) __builtin_memcpy(y + V * g, out + V * g, 16);
+      else {
+#pragma unroll
+        for (int e = 0; e < V; ++e)
+          if (V * g + e < ok) y[V * g + e] = out[V * g + e];
+      }
+    }
+  }
+}
+
+template <int DT, int BM, int BN, int WAVES_M, int WAVES_N, int GATHER, bool NCHW>
+__global__ __launch_bounds__(kThreads, 2) void igemm_stage_kernel(const ConvParams p) {
+  using D = StageDims<DT>;
+  using E = Elem<DT>;
+  using T = typename E::T;
+  constexpr int V = E::V, EB = sizeof(T);
+  constexpr int PARTS = D::PARTS, CHUNKS = D::CHUNKS, KSTEPS = D::KSTEPS, SWZ = D::SWZ;
+  constexpr bool SPLIT = PARTS == 3;
+  constexpr bool BY_ENTRY = GATHER >= kStageChunks;
+  constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
+  constexpr int MI = WM / 32, NI = WN / 32;
+  constexpr int A_BYTES = (BM / 32) * D::BLOCK_BYTES, B_BYTES = (BN / 32) * D::BLOCK_BYTES;
+  constexpr int PART_A = (BM / 32) * KSTEPS * 1024;             // one part of the A tile
+  constexpr int B_UNITS = B_BYTES / 1024;                       // 1 KiB a wavefront copies at a time
+  constexpr int B_LOADS = (B_UNITS + 3) / 4;
+  constexpr int AHEAD = PARTS * (MI + NI) <= 6 && MI * NI < 4 ? 2 : 1;      // (as the registers allow)
+  static_assert(WAVES_M * WAVES_N == 4 && WM % 32 == 0 && WN % 32 == 0 && BM % 64 == 0, "four wavefronts of 32x32 blocks");
+
+  extern __shared__ __align__(16) unsigned char smem[];
+  unsigned char* s_a = smem;                                    // [2][A_BYTES]
+  unsigned char* s_b = smem + 2 * A_BYTES;                      // [2][B_BYTES]
+  int32_t* s_rows = reinterpret_cast<int32_t*>(smem + 2 * (A_BYTES + B_BYTES));   // [BM]
+  float* s_bias = reinterpret_cast<float*>(s_rows + BM);        // [BN]
+
+  const int nwg = p.m_tiles * p.n_tiles;
+  const int per_xcd = (nwg + 7) >> 3;
+  const int logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (logical >= nwg) return;
+  const int tile_m = logical / p.n_tiles;
+  const int tile_n = logical - tile_m * p.n_tiles;
+  const int m0 = tile_m * BM, n0 = tile_n * BN;
+  const int t = threadIdx.x;
+  const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int wm0 = (wave / WAVES_N) * WM, wn0 = (wave % WAVES_N) * WN;
+  const int fp = lane & 31, fh = lane >> 5;
+
+  // ---- the rows this thread stages and the chunks of a K tile it fetches for each of them -----------------------------
+  //   groups:  CHUNKS lanes side by side hold the chunks of one row; rows 256 / CHUNKS apart
+  //   entries: lane = row, the chunk is the same for the whole wavefront
+  constexpr int ROWS = BY_ENTRY ? 1 : BM * CHUNKS / kThreads;
+  constexpr int ROW_STEP = kThreads / CHUNKS;
+  constexpr int PER_ROW = BY_ENTRY ? BM * CHUNKS / kThreads : 1;
+  const int row0 = BY_ENTRY ? t % BM : t / CHUNKS;
+  const int chunk0 = BY_ENTRY ? __builtin_amdgcn_readfirstlane(t / BM) * PER_ROW : t % CHUNKS;
+  int32_t a_at[ROWS];           // byte offset of the window's corner, possibly negative
+  uint32_t a_taps[ROWS];        // bit ky: that window row lies inside the image; bit 8 + kx: that window column
+#pragma unroll
+  for (int j = 0; j < ROWS; ++j) {
+    const int ic = m0 + row0 + ROW_STEP * j;
+    const bool present = ic < p.rows;
+    const int icc = present ? ic : p.rows - 1;
+    const int rr = p.row_idx ? p.row_idx[icc] : icc;
+    if (BY_ENTRY ? t < BM : chunk0 == 0) s_rows[row0 + ROW_STEP * j] = !present ? -1 : p.y_compact ? ic : rr;
+    const int rc = p.x_compact ? icc : rr;
+    const int n = fast_div(rc, p.div_howo_mul, p.div_howo_shift), rem = rc - n * p.ho_wo;
+    const int oy = fast_div(rem, p.div_wo_mul, p.div_wo_shift), ox = rem - oy * p.wo;
+    const int iy0 = oy * p.sh - p.ph, ix0 = ox * p.sw - p.pw;
+    a_at[j] = (int32_t)((n * p.xs_n + (int64_t)iy0 * p.xs_h + (int64_t)ix0 * p.xs_w) * EB);
+    uint32_t bits = 0;
+    for (int ky = 0; ky < p.kh; ++ky) bits |= ((unsigned)(iy0 + ky * p.dil_h) < (unsigned)p.h ? 1u : 0u) << ky;
+    for (int kx = 0; kx < p.kw; ++kx) bits |= ((unsigned)(ix0 + kx * p.dil_w) < (unsigned)p.w ? 1u : 0u) << (8 + kx);
+    a_taps[j] = present ? bits : 0u;
+  }
+  if (t < BN) s_bias[t] = p.bias && n0 + t < p.c_out ? p.bias[n0 + t] : 0.0f;
+  const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.x), 0, (int)p.x_bytes, kBufferWord3);
+  const unsigned char* xb = static_cast<const unsigned char*>(p.x);
+  const unsigned char* wb = static_cast<const unsigned char*>(p.wp) + ((int64_t)(n0 / 32) * p.k_tiles) * D::BLOCK_BYTES + lane * 16;
+
+  // what a thread holds of a K tile: 16-byte groups, or one register per entry
+  constexpr int A_REGS = BY_ENTRY ? PER_ROW * 8 : ROWS * (8 * EB / 4);
+  struct Regs { uint32_t a[A_REGS]; v4i b[B_LOADS]; uint32_t tails; };
+  constexpr int GPC = 8 / V;          // 16-byte groups per chunk
+  const int last = p.k_tiles - 1;
+
+  // The table entries of the next tile to be loaded.  They are fetched a tile ahead of the loads that need them, so that
+  // waiting for them (loads return in order) never waits for a tile that is still on its way.
+  constexpr int TABS = BY_ENTRY ? (GATHER == kStageChunks ? PER_ROW : 1) : GPC;
+  KEntry ke[TABS];
+  auto load_table = [&](int kt) {
+    if constexpr (!BY_ENTRY) {
+#pragma unroll
+      for (int g = 0; g < GPC; ++g) ke[g] = p.ktab[(kt * CHUNKS + chunk0) * GPC + g];
+    } else if constexpr (GATHER == kStageChunks) {
+#pragma unroll
+      for (int c = 0; c < PER_ROW; ++c) ke[c] = p.ktab[kt * CHUNKS + chunk0 + c];
+    }
+  };
+  auto load_tile = [&](int kt_want, Regs& r) {      // (unconditional: past the last tile it is loaded again, and not used)
+    const int kt = min(kt_want, last);
+    KEntry now[TABS];
+#pragma unroll
+    for (int i = 0; i < TABS; ++i) now[i] = ke[i];
+    load_table(min(kt_want + 1, last));
+    if constexpr (!BY_ENTRY) {
+      r.tails = 0;
+#pragma unroll
+      for (int g = 0; g < GPC; ++g) {
+        const uint32_t need = (uint32_t)now[g].dydx & ~kStageTail;
+        if constexpr (GATHER == kStageRaggedGroups) r.tails |= ((uint32_t)now[g].dydx >> 31) << g;
+#pragma unroll
+        for (int j = 0; j < ROWS; ++j) {
+          const bool ok = (a_taps[j] & need) == need;
+          v4i v;
+          if constexpr (GATHER == kStageGroups) {
+            v = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rx, ok ? (uint32_t)(a_at[j] + now[g].off) : kOutOfRange, 0, 0));
+          } else {
+            const unsigned char* src = ok ? xb + (int64_t)(a_at[j] + now[g].off) : static_cast<const unsigned char*>(p.zeros);
+            __builtin_memcpy(&v, src, 16);          // element-aligned
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i) r.a[(j * GPC + g) * 4 + i] = (uint32_t)v[i];
+        }
+      }
+    } else {
+#pragma unroll
+      for (int c = 0; c < PER_ROW; ++c) {
+        auto fetch = [&](uint32_t voff, int soff) -> uint32_t {
+          if constexpr (EB == 4) return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rx, voff, soff, 0);
+          else return (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rx, voff, soff, 0);
+        };
+        if constexpr (GATHER == kStageChunks) {
+          const uint32_t need = (uint32_t)now[c].dydx;
+          const uint32_t voff = (a_taps[0] & need) == need ? (uint32_t)(a_at[0] + now[c].off) : kOutOfRange;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) r.a[c * 8 + e] = fetch(voff, e * p.h * p.w * EB);
+        } else {
+          const KEntry* te = p.ktab + (kt * CHUNKS + chunk0 + c) * 8;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const uint32_t need = (uint32_t)te[e].dydx;
+            r.a[c * 8 + e] = fetch((a_taps[0] & need) == need ? (uint32_t)(a_at[0] + te[e].off) : kOutOfRange, 0);
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < B_LOADS; ++j) {
+      const int u = wave + 4 * j;
+      if (B_UNITS % 4 == 0 || u < B_UNITS) {
+        constexpr int PER = D::BLOCK_BYTES / 1024;
+        const int nb = u / PER, in = u - nb * PER;
+        r.b[j] = *reinterpret_cast<const v4i*>(wb + ((int64_t)nb * p.k_tiles + kt) * D::BLOCK_BYTES + in * 1024);
+      }
+    }
+  };
+
+  // LDS byte offset of (row, chunk) inside one part of a tile
+  auto a_place = [&](int row, int chunk) {
+    return ((row >> 5) * KSTEPS + (chunk >> 1)) * 1024 + (chunk & 1) * 512 + (((row ^ (chunk * SWZ)) & 31) << 4);
+  };
+  auto store_tile = [&](int buf, const Regs& r, auto careful_c) {
+    constexpr bool CAREFUL = decltype(careful_c)::value;
+    unsigned char* pa = s_a + buf * A_BYTES;
+#pragma unroll
+    for (int j = 0; j < ROWS; ++j)
+#pragma unroll
+      for (int c = 0; c < PER_ROW; ++c) {
+        unsigned char* dst = pa + a_place(row0 + ROW_STEP * j, chunk0 + c);
+        if constexpr (SPLIT) {
+          float f[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) f[e] = __builtin_bit_cast(float, r.a[(j * PER_ROW + c) * 8 + e]);
+          if constexpr (CAREFUL) {
+            if constexpr (GATHER == kStageRaggedGroups) {
+#pragma unroll
+              for (int e = 0; e < 8; ++e)
+                if (((r.tails >> (e / 4)) & 1u) && (e & 3) < p.seg_tail) f[e] = 0.0f;
+            }
+            v4f lo = {f[0], f[1], f[2], f[3]}, hi = {f[4], f[5], f[6], f[7]};
+            *reinterpret_cast<v4f*>(dst) = lo;
+            *reinterpret_cast<v4f*>(dst + PART_A) = hi;
+          } else {
+            v4i p1, p2, p3;
+            split3(f, p1, p2, p3);
+            *reinterpret_cast<v4i*>(dst) = p1;
+            *reinterpret_cast<v4i*>(dst + PART_A) = p2;
+            *reinterpret_cast<v4i*>(dst + 2 * PART_A) = p3;
+          }
+        } else {
+          v4i v;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            if constexpr (BY_ENTRY) v[i] = (int)((r.a[c * 8 + 2 * i] & 0xffffu) | (r.a[c * 8 + 2 * i + 1] << 16));
+            else v[i] = (int)r.a[j * 4 + i];
+            if constexpr (CAREFUL && GATHER == kStageRaggedGroups) {
+              if (r.tails & 1u) {
+                if (2 * i < p.seg_tail) v[i] &= (int)0xffff0000u;
+                if (2 * i + 1 < p.seg_tail) v[i] &= 0xffff;
+              }
+            }
+          }
+          *reinterpret_cast<v4i*>(dst) = v;
+        }
+      }
+    unsigned char* pb = s_b + buf * B_BYTES + lane * 16;
+#pragma unroll
+    for (int j = 0; j < B_LOADS; ++j) {
+      const int u = wave + 4 * j;
+      if (B_UNITS % 4 == 0 || u < B_UNITS) *reinterpret_cast<v4i*>(pb + u * 1024) = r.b[j];
+    }
+  };
+
+  floatx16 acc[MI][NI], small[SPLIT ? MI : 1][SPLIT ? NI : 1];
+  auto clear = [&]() {
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          acc[mi][ni][v] = 0.0f;
+          if constexpr (SPLIT) small[mi][ni][v] = 0.0f;
+        }
+  };
+
+  int frag_a[KSTEPS];
+#pragma unroll
+  for (int ks = 0; ks < KSTEPS; ++ks) frag_a[ks] = a_place(wm0 + fp, 2 * ks + fh);
+
+  auto compute_tile = [&](int buf, auto careful_c) {
+    constexpr bool CAREFUL = decltype(careful_c)::value;
+    const unsigned char* a = s_a + buf * A_BYTES;
+    const unsigned char* b = s_b + buf * B_BYTES + (wn0 / 32) * D::BLOCK_BYTES + lane * 16;
+#pragma unroll
+    for (int k2 = 0; k2 < KSTEPS; k2 += AHEAD) {      // AHEAD K steps of fragments are read before their products start
+      v4i xf[AHEAD][MI][PARTS], wf[AHEAD][NI][PARTS];
+#pragma unroll
+      for (int i = 0; i < AHEAD; ++i) {
+#pragma unroll
+        for (int q = 0; q < PARTS; ++q) {
+#pragma unroll
+          for (int ni = 0; ni < NI; ++ni)
+            wf[i][ni][q] = *reinterpret_cast<const v4i*>(b + ni * D::BLOCK_BYTES + (q * KSTEPS + k2 + i) * 1024);
+#pragma unroll
+          for (int mi = 0; mi < MI; ++mi)
+            xf[i][mi][q] = *reinterpret_cast<const v4i*>(a + q * PART_A + mi * KSTEPS * 1024 + frag_a[k2 + i]);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < AHEAD; ++i) {
+        auto each = [&](auto fn) {
+#pragma unroll
+          for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni) fn(mi, ni);
+        };
+        if constexpr (!SPLIT) {
+          each([&](int mi, int ni) { E::mma(acc[mi][ni], wf[i][ni][0], xf[i][mi][0]); });
+        } else if constexpr (CAREFUL) {
+          each([&](int mi, int ni) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              auto part = [&](int q) {
+                const uint32_t v = (uint32_t)wf[i][ni][q][e >> 1];
+                return (e & 1) ? bf16_hi(v) : bf16_lo(v);
+              };
+              const float w = join3(part(0), part(1), part(2));
+              const float x = __builtin_bit_cast(v4f, xf[i][mi][e >> 2])[e & 3];
+              acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(w, x, acc[mi][ni], 0, 0, 0);
+            }
+          });
+        } else {
+          using H = Elem<kBF16>;
+          each([&](int mi, int ni) { H::mma(acc[mi][ni], wf[i][ni][0], xf[i][mi][0]); });
+          each([&](int mi, int ni) { H::mma(small[mi][ni], wf[i][ni][1], xf[i][mi][0]); });
+          each([&](int mi, int ni) { H::mma(small[mi][ni], wf[i][ni][0], xf[i][mi][1]); });
+          each([&](int mi, int ni) { H::mma(small[mi][ni], wf[i][ni][1], xf[i][mi][1]); });
+          each([&](int mi, int ni) { H::mma(small[mi][ni], wf[i][ni][2], xf[i][mi][0]); });
+          each([&](int mi, int ni) { H::mma(small[mi][ni], wf[i][ni][0], xf[i][mi][2]); });
+        }
+      }
+    }
+  };
+
+  // ---- zero fill of the dropped rows this workgroup owns (Alg. 2, mask == 0 branch), behind the first K tile: the stores
+  // drain under the others.  Mask bytes are fetched several passes at a time.
+  auto fill_zeros = [&]() {
+    const int lo = tile_m == 0 ? 0 : p.row_idx[m0];
+    const int hi = (m0 + BM >= p.rows) ? p.m_total : p.row_idx[m0 + BM];
+    auto mask_of = [&](int r) -> unsigned {
+      if (p.mask_spatial) r -= fast_div(r, p.div_howo_mul, p.div_howo_shift) * p.ho_wo;
+      return p.mask[r];
+    };
+    T* y = static_cast<T*>(p.y);
+    const T* res = static_cast<const T*>(p.residual);
+    auto fill_one = [&](int64_t at) {
+      float f = 0.0f;
+      if (res) {
+        f += (float)res[at];
+        if (p.residual_relu) f = fmaxf(f, 0.0f);
+      }
+      y[at] = E::from_float(f);
+    };
+    const int cols = min(BN, p.c_out - n0);
+    if constexpr (!NCHW) {      // lanes side by side on the 16-byte groups of a row
+      constexpr int CPR = BN / V, RPI = kThreads / CPR, ZB = 8;
+      const int c = (t % CPR) * V;
+      if (c >= cols) return;
+      for (int r0 = lo + t / CPR; r0 < hi; r0 += ZB * RPI) {
+        unsigned mk[ZB];
+#pragma unroll
+        for (int u = 0; u < ZB; ++u) mk[u] = mask_of(min(r0 + u * RPI, hi - 1));
+#pragma unroll
+        for (int u = 0; u < ZB; ++u) {
+          const int r = r0 + u * RPI;
+          if (r >= hi || mk[u] != 0) continue;
+          const int64_t at = (int64_t)r * p.c_out + n0 + c;
+          if (!res && c + V <= cols) {
+            const v4i z = {0, 0, 0, 0};
+            __builtin_memcpy(y + at, &z, 16);
+          } else {
+            for (int e = 0; e < min(V, cols - c); ++e) fill_one(at + e);
+          }
+        }
+      }
+    } else {                    // lanes side by side on the positions of a channel's map
+      constexpr int ZB = 4;
+      for (int r0 = lo + lane; r0 < hi; r0 += ZB * 64) {
+        unsigned mk[ZB];
+#pragma unroll
+        for (int u = 0; u < ZB; ++u) mk[u] = mask_of(min(r0 + u * 64, hi - 1));
+#pragma unroll
+        for (int u = 0; u < ZB; ++u) {
+          const int r = r0 + u * 64;
+          if (r >= hi || mk[u] != 0) continue;
+          const int n = fast_div(r, p.div_howo_mul, p.div_howo_shift);
+          const int64_t at = n * p.ys_n + (r - n * p.ho_wo) + (int64_t)n0 * p.ys_c;
+          for (int c = wave; c < cols; c += 4) fill_one(at + (int64_t)c * p.ys_c);
+        }
+      }
+    }
+  };
+
+  // ---- K loop: two tiles ahead in registers, one ahead in LDS ------------------------------------------------------------
+  auto contract = [&](auto careful_c) {
+    Regs r0, r1;
+    load_table(0);
+    load_tile(0, r0);
+    load_tile(1, r1);
+    store_tile(0, r0, careful_c);
+    __syncthreads();
+    // (two tiles per turn and no way out in the middle: the accumulators and the register slots keep their places)
+#pragma unroll 1
+    for (int kt = 0; kt + 1 < p.k_tiles; kt += 2) {
+      load_tile(kt + 2, r0);
+      compute_tile(0, careful_c);
+      if (!decltype(careful_c)::value && kt == 0 && p.zero_fill) fill_zeros();
+      store_tile(1, r1, careful_c);
+      __syncthreads();
+      load_tile(kt + 3, r1);
+      compute_tile(1, careful_c);
+      store_tile(0, r0, careful_c);
+      __syncthreads();
+    }
+    if (p.k_tiles & 1) compute_tile(0, careful_c);
+    if (!decltype(careful_c)::value && p.k_tiles == 1 && p.zero_fill) fill_zeros();
+  };
+  clear();
+  contract(std::false_type{});
+  if constexpr (SPLIT || GATHER == kStageRaggedGroups) {
+    bool odd = false;
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          if constexpr (SPLIT) acc[mi][ni][v] += small[mi][ni][v];
+          odd |= acc[mi][ni][v] != acc[mi][ni][v];
+        }
+    if (__syncthreads_or(odd)) {
+      clear();
+      contract(std::true_type{});
+    }
+  }
+  __syncthreads();
+
+  // ---- epilogue --------------------------------------------------------------------------------------------------------------
+#pragma unroll
+  for (int mi = 0; mi < MI; ++mi) {
+    const int rr = s_rows[wm0 + mi * 32 + fp];
+    if (rr < 0) continue;
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni) {
+      const int c0 = wn0 + ni * 32 + 16 * fh;
+      if (n0 + c0 >= p.c_out) continue;
+      float vals[16];
+#pragma unroll
+      for (int v = 0; v < 16; ++v) vals[v] = acc[mi][ni][v];
+      stage_store_row<DT, NCHW>(vals, rr, n0 + c0, p, p.bias ? s_bias + c0 : nullptr);
+    }
+  }
+}
+
+template <int DT, int BM, int BN, int WAVES_M, int WAVES_N, int GATHER, bool NCHW>
+hipError_t igemm_stage_launch(const ConvParams& p, hipStream_t stream) {
+  constexpr size_t lds = stage_lds_bytes<DT, BM, BN>();
+  auto kern = igemm_stage_kernel<DT, BM, BN, WAVES_M, WAVES_N, GATHER, NCHW>;
+  static std::atomic<bool> attr_set{false};
+  if (lds > 64 * 1024 && !attr_set) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  const int nwg = p.m_tiles * p.n_tiles;
+  hipLaunchKernelGGL(kern, dim3(((nwg + 7) / 8) * 8), dim3(kThreads), lds, stream, p);
+  return hipGetLastError();
+}
+
+// the kernel of tile bm x bn for a dtype and a gather, or null (igemm_stage.hip)
+LaunchFn stage_kernel(int dtype, int gather, bool nchw, int bm, int bn);
+// filters into the order of the kernel's tiles, and the gather's table (igemm_stage.hip)
+hipError_t stage_pack(int dtype, int gather, const void* w, void* wp, KEntry* tab, int c_out, int blocks, int c_in, int kh, int kw,
+                      int dil_h, int dil_w, int k_tiles, bool nchw, int h, int w_cols, hipStream_t stream);
+
+}  // namespace sc

@@ -7,6 +7,7 @@
 
 #include <atomic>
 #include <cmath>
+#include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <new>
@@ -19,6 +20,8 @@
 #include "conv_params.hpp"
 #include "igemm_buf_kernel.hpp"
 #include "igemm_slab_kernel.hpp"
+#include "igemm_split_kernel.hpp"
+#include "igemm_stage_kernel.hpp"
 #include "igemm_streamk_kernel.hpp"
 #include "igemm_panel_kernel.hpp"
 
@@ -425,6 +428,10 @@ struct Geometry {
   bool rowseg;
   int32_t epad, hp, wp_cols;   // K entries per window row (padded to 8), padded input height and width
   size_t off_xpad;
+  // register-staged tiled kernel (igemm_stage_kernel.hpp): its gather (-1: the layer does not run it), K tiles in that
+  // gather's order, repeated entries of a pixel's last group, 32-channel blocks of its packed filters
+  int32_t stage_gather, stage_k_tiles, stage_tail, stage_blocks;
+  size_t off_stage_w, off_stage_tab;
   size_t off_xrank, off_xcounts;   // depthwise layers with windows: rank map of a compact input, its segment counts
 };
 
@@ -523,6 +530,24 @@ static sc_status check_desc(const sc_conv_desc* d, Geometry* g) {
     const size_t tiles = (size_t)((g->m + 63) / 64) * ((d->c_out + 63) / 64);
     g->off_counters = off; off = align_up(off + tiles * 4, 256);
     g->off_partial = off;  off = align_up(off + kSplitKPartialBytes, 256);
+  }
+  // Register-staged kernel: float layers, and layers whose tensors the 16-byte gathers do not fit (channels first, or
+  // channel counts off the 16-byte group).  Windows up to 8 x 8 (validity bits), x below 2 GiB (32-bit byte offsets).
+  g->stage_gather = -1;
+  g->stage_k_tiles = g->stage_tail = g->stage_blocks = 0;
+  g->off_stage_w = g->off_stage_tab = off;
+  if (!depthwise && !g->rowseg && (d->dtype == SC_F32 || !g->vec_gather) && d->kh <= 8 && d->kw <= 8 && g->x_elems * eb < lim) {
+    const bool nhwc = d->layout == SC_NHWC;
+    g->stage_gather = nhwc ? (g->vec_gather ? kStageGroups : d->c_in >= g->vec ? kStageRaggedGroups : kStageEntries)
+                           : (d->c_in % 8 == 0 ? kStageChunks : kStageEntries);
+    const int cpad = g->stage_gather == kStageRaggedGroups ? (d->c_in + g->vec - 1) / g->vec * g->vec : d->c_in;
+    const int tile = d->dtype == SC_F32 ? StageDims<kF32>::K_TILE : StageDims<kBF16>::K_TILE;
+    const int block_bytes = d->dtype == SC_F32 ? StageDims<kF32>::BLOCK_BYTES : StageDims<kBF16>::BLOCK_BYTES;
+    g->stage_tail = cpad - d->c_in;
+    g->stage_k_tiles = (int32_t)(((int64_t)d->kh * d->kw * cpad + tile - 1) / tile);
+    g->stage_blocks = (d->c_out + 127) / 128 * 4;      // (tiles are up to 128 channels wide)
+    g->off_stage_w = off;   off = align_up(off + (size_t)g->stage_blocks * g->stage_k_tiles * block_bytes, 256);
+    g->off_stage_tab = off; off = align_up(off + (size_t)g->stage_k_tiles * tile * sizeof(KEntry), 256);
   }
   g->total = off;
   return SC_OK;
@@ -810,6 +835,9 @@ static bool tap_is_automatic(const sc_conv_desc& d, const Geometry& g, const Ban
 
 using namespace sc;
 
+// tile of the register-staged kernel; groups of wavefronts that share K (direct form); asked for by the environment
+struct StageTile { int bm, bn, groups; bool asked; };
+
 struct sc_plan {
   sc_conv_desc desc;
   Geometry geo;
@@ -839,6 +867,7 @@ struct sc_plan {
   bool x_rank_set;                 // sparse_conv_plan_set_input_mask has filled the rank map of a compact input
   // slab form of the tiled kernel (deep 3x3 layers)
   struct Slab { int bm, splits; };
+  StageTile stage_pick[2];         // tile of the register-staged kernel for the sparse / dense run (bm == 0: another kernel)
   bool slab_ok;                    // the layer's geometry admits it
   int slab;                        // 0 = automatic, 1 = never, 2 = wherever it applies, 128 / 256 = with tiles of that many rows
   int slab_span[2][2];             // [sparse, dense run][128-row, 256-row tiles]: virtual rows of the widest tile's slab
@@ -1063,6 +1092,77 @@ static sc_plan::Slab slab_pick(const sc_plan* pl, int which, int64_t rows) {
   }
   return none;
 }
+// ---- register-staged kernel ------------------------------------------------------------------------------
+// The direct-to-LDS form serves the float NHWC layers whose rows are whole 16-byte groups.
+static bool stage_is_direct(const sc_conv_desc& d, const Geometry& g) {
+  return g.stage_gather == kStageGroups && d.c_out % 4 == 0 &&
+         (int64_t)g.stage_blocks * g.stage_k_tiles * StageDims<kF32>::BLOCK_BYTES < ((int64_t)1 << 31);
+}
+static LaunchFn stage_launcher(const sc_conv_desc& d, const Geometry& g, StageTile t) {
+  if (stage_is_direct(d, g))
+    return split_kernel(t.bm, t.bn, t.groups, d.c_in % StageDims<kF32>::K_TILE == 0, d.c_out % 16 == 0 ? 1 : 2);
+  return t.groups != 1 ? nullptr : stage_kernel(d.dtype == SC_BF16 ? kBF16 : d.dtype == SC_F16 ? kF16 : kF32, g.stage_gather, d.layout == SC_NCHW, t.bm, t.bn);
+}
+// Its tile for a run of `rows` rows.  SPARSE_CONV_STAGE_TILE=<bm>x<bn>[x<groups>] overrides (tuning and tests), 0x0 switches the
+// kernel off.
+// `groups` > 0 fixes the number of groups: the dense run takes that of the sparse one, so that both add a row's products in
+// the same order and a kept row carries the same bits in either.
+static StageTile stage_tile_for(const sc_conv_desc& d, const Geometry& g, int64_t rows, int groups = 0) {
+  StageTile none = {0, 0, 1, false};
+  if (g.stage_gather < 0 || rows == 0) return none;
+  int fbm = 0, fbn = 0, fgr = 1;
+  if (const char* env = std::getenv("SPARSE_CONV_STAGE_TILE"); env && std::sscanf(env, "%dx%dx%d", &fbm, &fbn, &fgr) >= 2)
+    return fbm > 0 && stage_launcher(d, g, {fbm, fbn, fgr, true}) ? StageTile{fbm, fbn, fgr, true} : none;
+  const int kt = g.stage_k_tiles;
+  if (stage_is_direct(d, g)) {
+    // Priced like the other tiled launches, with quantities measured on this kernel (us, MI355X): what a K tile costs a
+    // compute unit with enough workgroups on it, what it costs a workgroup alone, and a round of workgroups beyond its K
+    // loop.  Sparse runs at s = 0.5, chosen tile / 128 x 64 in one group / the float-MFMA kernel:  32 x 64 -> 64 @56
+    // 33 / 33 / 60;  128 -> 128 @28 31 / 38 / 55;  256 -> 256 @14 38 / 62 / 61;  16 x 384 -> 384 @12 32 / 87 / 88;
+    // 1 x 128 -> 128 @28 15 / 34 / 32 (batch 32 where not said; where few workgroups walk a long K, groups share it).
+    struct Shape { StageTile t; double per_tile, alone; int waves; };
+    static const Shape shapes[] = {{{128, 64, 1, false}, 0.53, 0.69, 4}, {{128, 64, 2, false}, 0.53, 0.71, 8}, {{128, 32, 1, false}, 0.35, 0.50, 4},
+                                   {{128, 32, 2, false}, 0.35, 0.70, 8}, {{64, 64, 2, false}, 0.29, 0.70, 4},  {{64, 32, 1, false}, 0.21, 0.48, 2},
+                                   {{64, 32, 2, false}, 0.205, 0.48, 4}, {{64, 32, 4, false}, 0.205, 0.50, 8}};
+    const int cus = device_cus();
+    StageTile best = none;
+    double best_us = 1e300;
+    for (const Shape& sh : shapes) {
+      if (groups > 0 && sh.t.groups != groups) continue;
+      const int64_t wgs = ((rows + sh.t.bm - 1) / sh.t.bm) * ((d.c_out + sh.t.bn - 1) / sh.t.bn);
+      const int lds = sh.t.groups * 2 * (sh.t.bm * kRowBytes + sh.t.bn / 32 * StageDims<kF32>::BLOCK_BYTES);
+      const int resident = std::max(1, std::min((int)(kLdsLimit / lds), (sh.t.bn == 64 ? 8 : 12) / sh.waves));
+      const int steps = (kt + sh.t.groups - 1) / sh.t.groups;
+      auto round_us = [&](int64_t on_cu) {
+        double step = std::max(sh.alone, (double)on_cu * sh.t.groups * sh.per_tile);
+        if (sh.waves == 2 && on_cu >= 2) step = std::max(step, 0.95);       // (their wavefronts share two of the four SIMDs)
+        return 4.0 + steps * step;
+      };
+      const int64_t full = wgs / ((int64_t)cus * resident), rest = wgs - full * cus * resident;
+      const double us = full * round_us(resident) + (rest ? round_us((rest + cus - 1) / cus) : 0.0);
+      if (us < best_us) { best_us = us; best = sh.t; }
+    }
+    return best;
+  }
+  // Through registers: 64 rows keep most workgroups in flight (us, 64 x 64 / 128 x 64: 128 -> 128 @28 channels first in float
+  // 46 / 59; 51 -> 51 @56 in bf16 44 / 50; 410 -> 410 @7 27 / 39).  Two channel tiles' worth of 16-bit channels in one
+  // workgroup save half of the gathers where that still covers the compute units (128 -> 128 @28 channels first in bf16
+  // 27.5 against 32.6).
+  if (d.c_out <= 32) return {128, 32, 1, false};
+  if (kt <= 2 && (rows + 127) / 128 * ((d.c_out + 63) / 64) >= device_cus()) return {128, 64, 1, false};
+  if (d.dtype != SC_F32 && d.c_out > 64 && (d.c_out % 128 == 0 || d.c_out % 128 > 64) &&
+      (rows + 63) / 64 * ((d.c_out + 127) / 128) >= device_cus() * 3 / 4) return {64, 128, 1, false};
+  return {64, 64, 1, false};
+}
+// does a run take it?  (not where a tile, a band kernel or another form of the tiled kernel was asked for)
+// (float layers that a band kernel serves keep it while they are small: 16 -> 16 @16, one image, 6.4 against 7.1 us;
+// 16 -> 16 @56, four images, 6.9 against 7.3; with 2.3e8 multiply-adds in all rows 10.4 and 11.4 against 9.5 and 10.8; one
+// line for the sparse and the dense run, see above)
+static bool use_stage(const sc_plan* pl, int which) {
+  if (!pl->stage_pick[which].asked && pl->band.ok && (double)pl->geo.m * pl->geo.k * pl->desc.c_out < 8e7) return false;
+  return pl->stage_pick[which].bm > 0 && pl->forced[which] == -1 && pl->gather_pipeline == 0 &&
+         !(pl->masked_store == 2 && which == 0) && !pl->prefer_tiled[which];
+}
 static TilePick pick_tile(const sc_plan* pl, int which, int64_t rows) {
   TilePick tp;
   tp.masked = false;
@@ -1167,7 +1267,7 @@ static sc_status launch_conv(const sc_plan* pl, bool dense, const void* x, const
   const sc_plan::Slab slab = x_compact ? sc_plan::Slab{0, 1} : slab_pick(pl, which, rows);
   const bool use_band = band.ok && !x_compact && !y_compact && (!residual || ((band.pp || band.tap) && !band.stream)) &&
                         (pl->forced[which] == kForceBand || (pl->forced[which] == -1 && !band.stream && !pl->prefer_tiled[which])) &&
-                        !(slab.bm && pl->slab >= 2);
+                        !(slab.bm && pl->slab >= 2) && !use_stage(pl, which);
   if (use_band) {
     const BandPlan& b = band;
     BandParams q;
@@ -1292,6 +1392,51 @@ static sc_status launch_conv(const sc_plan* pl, bool dense, const void* x, const
     SC_HIP(fn(p, stream));
     return SC_OK;
   }
+  if (use_stage(pl, which)) {
+    ConvParams p;
+    std::memset(&p, 0, sizeof(p));
+    const StageTile tile = pl->stage_pick[which];
+    p.x = x;
+    p.wp = pl->ws + g.off_stage_w;
+    p.bias = d.has_bias ? bias : nullptr;
+    p.y = y;
+    p.row_idx = identity ? nullptr : reinterpret_cast<const int32_t*>(pl->ws + g.off_rows);
+    p.mask = pl->ws + g.off_mask;
+    p.ktab = reinterpret_cast<const KEntry*>(pl->ws + g.off_stage_tab);
+    p.zeros = pl->ws + g.off_zeros;
+    p.rows = (int32_t)rows;
+    p.m_total = (int32_t)g.m;
+    p.h = d.h; p.w = d.w; p.ho_wo = g.ho * g.wo; p.wo = g.wo;
+    magic_div((uint32_t)p.ho_wo, &p.div_howo_mul, &p.div_howo_shift);
+    magic_div((uint32_t)p.wo, &p.div_wo_mul, &p.div_wo_shift);
+    p.sh = d.stride_h; p.sw = d.stride_w; p.ph = d.pad_h; p.pw = d.pad_w;
+    p.c_in = d.c_in; p.kh = d.kh; p.kw = d.kw; p.dil_h = d.dil_h; p.dil_w = d.dil_w;
+    p.c_out = d.c_out;
+    p.k_tiles = g.stage_k_tiles;
+    p.seg_tail = g.stage_tail;
+    if (d.layout == SC_NHWC) {
+      p.xs_n = (int64_t)d.h * d.w * d.c_in; p.xs_h = d.w * d.c_in; p.xs_w = d.c_in;
+      p.ys_n = (int64_t)p.ho_wo * d.c_out; p.ys_p = d.c_out; p.ys_c = 1;
+    } else {
+      p.xs_n = (int64_t)d.c_in * d.h * d.w; p.xs_h = d.w; p.xs_w = 1;
+      p.ys_n = (int64_t)d.c_out * p.ho_wo; p.ys_p = 1; p.ys_c = p.ho_wo;
+    }
+    p.x_bytes = (uint32_t)(g.x_elems * eb);
+    p.relu = d.relu;
+    p.zero_fill = zero_fill ? 1 : 0;
+    p.mask_spatial = d.mask_mode == SC_MASK_SPATIAL;
+    p.x_compact = compact && x_compact ? 1 : 0;
+    p.y_compact = compact && y_compact ? 1 : 0;
+    p.residual = residual;
+    p.residual_relu = residual && residual_relu ? 1 : 0;
+    p.m_tiles = (int32_t)((rows + tile.bm - 1) / tile.bm);
+    p.n_tiles = (d.c_out + tile.bn - 1) / tile.bn;
+    p.w_bytes = (uint32_t)((uint64_t)g.stage_blocks * g.stage_k_tiles * (d.dtype == SC_F32 ? StageDims<kF32>::BLOCK_BYTES : StageDims<kBF16>::BLOCK_BYTES));
+    LaunchFn fn = stage_launcher(d, g, tile);
+    if (!fn) return SC_ERR_UNSUPPORTED;      // cannot happen: the pick checked it
+    SC_HIP(fn(p, stream));
+    return SC_OK;
+  }
   TilePick tp = pick_tile(pl, which, rows);
   // every row contracted, the mask looked at only at the store: plain sparse runs of dense operands without a shortcut
   const bool masked = tp.masked && !dense && !identity && !compact && !x_compact && !y_compact && !residual &&
@@ -1409,7 +1554,7 @@ static sc_status check_run_args(const sc_plan* plan, const void* x, const float*
 }
 
 // Everything of a plan that depends on the filters: the packed filter matrix (and, once, the gather table).
-static sc_status pack_filters(const sc_conv_desc& d, const Geometry& g, unsigned char* ws, const void* w_dev,
+static sc_status pack_filters(const sc_conv_desc& d, const Geometry& g, unsigned char* ws, const void* w_dev, bool tables,
                               hipStream_t stream) {
   if (g.depthwise) {
     const int dt = d.dtype == SC_BF16 ? kBF16 : d.dtype == SC_F16 ? kF16 : kF32;
@@ -1428,8 +1573,13 @@ static sc_status pack_filters(const sc_conv_desc& d, const Geometry& g, unsigned
                          (_Float16*)(ws + g.off_wp), d.c_out, d.c_in, d.kh, d.kw, g.k, g.k_stride, g.cout_pad, nchw, g.rowseg ? g.epad : 0);
     SC_HIP(hipGetLastError());
   }
-  // gather table (depends on the geometry only; rebuilt with the filters for simplicity, it is tiny)
-  {
+  if (g.stage_gather >= 0) {
+    const int dt = d.dtype == SC_BF16 ? kBF16 : d.dtype == SC_F16 ? kF16 : kF32;
+    SC_HIP(stage_pack(dt, g.stage_gather, w_dev, ws + g.off_stage_w, tables ? reinterpret_cast<KEntry*>(ws + g.off_stage_tab) : nullptr,
+                      d.c_out, g.stage_blocks, d.c_in, d.kh, d.kw, d.dil_h, d.dil_w, g.stage_k_tiles, d.layout == SC_NCHW, d.h, d.w, stream));
+  }
+  // gather table (depends on the geometry only)
+  if (tables) {
     const int vec = g.vec_gather ? g.vec : 1;
     const int entries = g.k_pad / vec;
     int xs_h, xs_w, xs_c;
@@ -1553,7 +1703,7 @@ sc_status sparse_conv_plan(const sc_conv_desc* desc, const uint8_t* mask_dev, co
   const int64_t rows_hint = d.sparsity >= 0.0f ? (int64_t)((1.0 - (double)d.sparsity) * (double)g.m + 0.5) : g.m / 2;
   BandPlan bp = plan_band(d, g, rows_hint);
   int32_t kept_host = 0;
-  s = pack_filters(d, g, ws, w_dev, stream);
+  s = pack_filters(d, g, ws, w_dev, true, stream);
   if (s != SC_OK) return s;
   int32_t slab_span[2] = {0, 0};
   s = build_row_tables(d, g, ws, mask_dev, stream, &bp, &kept_host, slab_span);   // synchronises the stream
@@ -1585,6 +1735,8 @@ sc_status sparse_conv_plan(const sc_conv_desc* desc, const uint8_t* mask_dev, co
   pl->pick[1] = model_pick(pl, 1, g.m);
   pl->band = bp;
   pl->band_dense = plan_band(d, g, g.m);
+  pl->stage_pick[0] = stage_tile_for(d, g, pl->kept);
+  pl->stage_pick[1] = stage_tile_for(d, g, g.m, pl->stage_pick[0].bm ? pl->stage_pick[0].groups : 0);
   pl->slab = 0;
   pl->slab_ok = slab_geometry_ok(d, g) && slab_kernel(d.dtype == SC_BF16 ? kBF16 : kF16, 128, false);
   pl->slab_span[0][0] = slab_span[0]; pl->slab_span[0][1] = slab_span[1];
@@ -1616,6 +1768,8 @@ sc_status sparse_conv_plan_set_mask(sc_plan* plan, const uint8_t* mask_dev, void
   plan->band = bp;
   plan->pick[0] = model_pick(plan, 0, plan->kept);      // (a measured choice belonged to the previous mask's row count)
   plan->prefer_tiled[0] = false;
+  plan->stage_pick[0] = stage_tile_for(d, g, plan->kept);
+  plan->stage_pick[1] = stage_tile_for(d, g, g.m, plan->stage_pick[0].bm ? plan->stage_pick[0].groups : 0);
   plan->slab_span[0][0] = slab_span[0]; plan->slab_span[0][1] = slab_span[1];
   plan->slab_auto[0] = sc_plan::Slab{0, 1};
   return SC_OK;
@@ -1651,7 +1805,7 @@ sc_status sparse_conv_plan_set_input_mask(sc_plan* plan, const uint8_t* mask_in_
 sc_status sparse_conv_plan_set_filters(sc_plan* plan, const void* w_dev, void* hip_stream) {
   if (!plan || !w_dev) return SC_ERR_NULL;
   if ((uintptr_t)w_dev & 15) return SC_ERR_ALIGN;
-  return pack_filters(plan->desc, plan->geo, plan->ws, w_dev, static_cast<hipStream_t>(hip_stream));
+  return pack_filters(plan->desc, plan->geo, plan->ws, w_dev, false, static_cast<hipStream_t>(hip_stream));
 }
 
 sc_status sparse_conv_run(const sc_plan* plan, const void* x_dev, const float* bias_dev, void* y_dev,
@@ -1885,7 +2039,7 @@ sc_status sparse_conv_plan_tiles(const sc_plan* plan, int32_t which, int32_t* ti
   }
   const BandPlan& band = which ? plan->band_dense : plan->band;
   if (band.ok && (plan->forced[which] == kForceBand || (plan->forced[which] == -1 && !band.stream && !plan->prefer_tiled[which])) &&
-      !(plan->slab >= 2 && slab_pick(plan, which, which ? plan->geo.m : plan->kept).bm)) {
+      !(plan->slab >= 2 && slab_pick(plan, which, which ? plan->geo.m : plan->kept).bm) && !use_stage(plan, which)) {
     if (tile_m) *tile_m = -band.bh;     // (rows per run; split bands hold half a run each)
     if (tile_n) *tile_n = 32 * band.ni;
     if (workgroups) *workgroups = band.pp && !band.tap ? band.pp_grid : (int64_t)band.n_bands * band.n_tiles;
@@ -1896,6 +2050,13 @@ sc_status sparse_conv_plan_tiles(const sc_plan* plan, int32_t which, int32_t* ti
     if (tile_m) *tile_m = sl.bm;
     if (tile_n) *tile_n = kSlabBN;
     if (workgroups) *workgroups = ((rows + sl.bm - 1) / sl.bm) * ((plan->desc.c_out + kSlabBN - 1) / kSlabBN) * std::min(sl.splits, plan->desc.c_in / kSlabCh);
+    return SC_OK;
+  }
+  if (use_stage(plan, which)) {
+    const StageTile st = plan->stage_pick[which];
+    if (tile_m) *tile_m = st.bm;
+    if (tile_n) *tile_n = st.bn;
+    if (workgroups) *workgroups = ((rows + st.bm - 1) / st.bm) * ((plan->desc.c_out + st.bn - 1) / st.bn);
     return SC_OK;
   }
   if (use_panel(plan, which, rows)) {
@@ -1919,6 +2080,7 @@ sc_status sparse_conv_plan_tiles(const sc_plan* plan, int32_t which, int32_t* ti
 // name of the tiled kernel a launch of this plan takes when no band or row-panel kernel applies
 static const char* tiled_kernel_name(const sc_plan* plan, int32_t which) {
   const Geometry& g = plan->geo;
+  if (use_stage(plan, which)) return "tile_staged";
   const TilePick tp = pick_tile(plan, which, which ? g.m : plan->kept);
   if (tp.masked) return "tile_masked_store";
   if (tp.splits > 1) return "tile_split_k";
@@ -1933,7 +2095,7 @@ const char* sparse_conv_plan_kernel(const sc_plan* plan, int32_t which) {
   if (plan->geo.depthwise) return "depthwise";
   const BandPlan& band = which ? plan->band_dense : plan->band;
   if (band.ok && (plan->forced[which] == kForceBand || (plan->forced[which] == -1 && !band.stream && !plan->prefer_tiled[which])) &&
-      !(plan->slab >= 2 && slab_pick(plan, which, which ? plan->geo.m : plan->kept).bm))
+      !(plan->slab >= 2 && slab_pick(plan, which, which ? plan->geo.m : plan->kept).bm) && !use_stage(plan, which))
     return band.rowband ? "band_row_segments" : band.stream ? "band_stream" : band.tap ? "band_tap" : band.pp ? "band_alternating" : "band";
   const Geometry& g = plan->geo;
   if (slab_pick(plan, which, which ? g.m : plan->kept).bm) return "tile_slab";

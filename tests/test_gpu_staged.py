@@ -1,0 +1,113 @@
+"""The register-staged tiled kernel (float operands in three 16-bit parts, ragged channel counts, channels-first tensors)
+against the oracle, over its gathers and tiles, and its answers for values that are not finite."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from oracle import oracle
+from paper_2309_06626_amd import binding as B
+from paper_2309_06626_amd import runtime as R
+from parity import check_layer, rows_view
+from test_gpu_compact import check_compact_output
+from test_gpu_parity import spec_of
+from test_gpu_residual import check as check_residual
+
+pytestmark = pytest.mark.gpu
+
+TILES = ["128x64", "128x32", "64x64", "64x128", "64x32", "128x64x2", "64x64x2", "64x32x4"]
+CASES = [
+    dict(n=2, cin=16, h=19, w=17, cout=160, k=3),                      # float: K tiles that span taps; two ragged channel tiles
+    dict(n=2, cin=32, h=11, w=13, cout=33, k=3, s=2, sp=0.3),          # float: a K tile per tap; output rows at odd addresses
+    dict(n=1, cin=13, h=12, w=10, cout=51, k=3, p=2, d=2, sp=0.4),     # ragged last group, dilation
+    dict(n=3, cin=51, h=9, w=9, cout=102, k=1, p=0, sp=0.5),           # ragged pointwise
+    dict(n=1, cin=9, h=15, w=11, cout=8, k=5, p=2, sp=0.0),            # one entry past a group; every row kept
+    dict(n=2, cin=3, h=14, w=14, cout=24, k=8, s=2, p=3, sp=0.6),      # fewer channels than a group, the widest window
+    dict(n=1, cin=72, h=3, w=2, cout=5, k=3, sp=0.5),                  # three rows
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("layout", ["nhwc", "nchw"])
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_gathers_and_tiles(case, layout, dtype, monkeypatch):
+    spec = spec_of(dtype=dtype, layout=layout, **CASES[case])
+    staged = dtype == "f32" or layout == "nchw" or spec.c_in % 8
+    for tile in TILES:
+        direct = dtype == "f32" and layout == "nhwc" and spec.c_in % 4 == 0 and spec.c_out % 4 == 0     # straight into LDS
+        if not staged or (direct and tile == "64x128") or (tile not in TILES[:4] and not direct):
+            continue
+        monkeypatch.setenv("SPARSE_CONV_STAGE_TILE", tile)
+        layer = check_layer(W.make_conv_inputs(spec, 1500 + case))
+        if B.sparse_conv_plan_kernel(layer.plan, 0) == "band_row_segments" or "row_segments" in B.sparse_conv_plan_kernel(layer.plan, 0):
+            return                                                     # (small-channel 16-bit stems have a kernel of their own)
+        assert B.sparse_conv_plan_kernel(layer.plan, 0) == "tile_staged"
+        assert ["%d" % v for v in B.sparse_conv_plan_tiles(layer.plan, 0)[:2]] == tile.split("x")[:2]
+    if staged:
+        monkeypatch.delenv("SPARSE_CONV_STAGE_TILE")
+        check_layer(W.make_conv_inputs(spec.with_(mask_mode="spatial"), 1520 + case), out_mode=B.SC_OUT_SCATTER_ONLY)
+
+
+@pytest.mark.parametrize("dtype,cin,layout", [("f32", 32, "nhwc"), ("f32", 7, "nhwc"), ("bf16", 21, "nhwc"), ("f16", 16, "nchw")])
+def test_shortcut_and_compact_rows(dtype, cin, layout):
+    for cout in (16, 27):
+        spec = spec_of(2, cin, 9, 12, cout, k=1, p=0, dtype=dtype, layout=layout, relu=False)
+        check_residual(spec, 1540, True, want_kernel=("tile_staged",))
+        if layout == "nhwc":
+            check_residual(spec, 1541, False, y_compact=True)
+            check_residual(spec, 1542, True, y_compact=True, x_compact=True)
+            check_compact_output(spec.with_(kh=3, kw=3, pad_h=1, pad_w=1), 1543)
+
+
+@pytest.mark.parametrize("sx,sw", [(2.0 ** -60, 2.0 ** -50), (2.0 ** 60, 2.0 ** 50), (2.0 ** -110, 2.0 ** 100)])
+def test_float_parts_at_the_ends_of_the_range(sx, sw):
+    spec = spec_of(1, 24, 10, 10, 32, dtype="f32", bias=False)
+    ci = W.make_conv_inputs(spec, 1560)
+    ci.x, ci.w = ci.x * np.float32(sx), ci.w * np.float32(sw)
+    check_layer(ci)
+
+
+VALUES = [np.inf, -np.inf, np.nan, 3.4e38, -3.4028235e38]
+
+
+@pytest.mark.parametrize("dtype,cin,layout", [("f32", 32, "nhwc"), ("f32", 13, "nhwc"), ("f32", 8, "nchw"), ("bf16", 13, "nhwc"),
+                                              ("f16", 27, "nhwc"), ("bf16", 8, "nchw")])
+@pytest.mark.parametrize("where", ["x", "w"])
+def test_values_that_are_not_finite(dtype, cin, layout, where):
+    """The same finite, infinite and not-a-number results as the kernel that gathers element by element or in 16-byte
+    groups (a forced tile), which adds the plain products; what stays finite agrees with it."""
+    for i, value in enumerate(VALUES):
+        if abs(value) > 6e4 and np.isfinite(value) and dtype == "f16":
+            continue
+        spec = spec_of(1, cin, 9, 9, 40, dtype=dtype, layout=layout, relu=False, sp=0.2)
+        ci = W.make_conv_inputs(spec, 1570 + i)
+        x, w = ci.x.copy(), ci.w.copy()
+        flat = (x if where == "x" else w).reshape(-1)
+        with np.errstate(all="ignore"):
+            flat[[flat.size // 2, flat.size - 1]] = W.quantize(np.array([value, value], np.float32), dtype) if np.isfinite(value) else value
+        w.reshape(-1)[::7] = 0.5                    # filters whose later parts are zero
+        layer = R.ConvLayer(spec, w, ci.bias, ci.mask)
+        assert B.sparse_conv_plan_kernel(layer.plan, 0) == "tile_staged"
+        dev = R.to_device(x, dtype)
+        a = layer.sparse(dev).float()
+        B.sparse_conv_plan_set_tiles(layer.plan, 0, 64, 64)
+        assert B.sparse_conv_plan_kernel(layer.plan, 0) != "tile_staged"
+        b = layer.sparse(dev).float()
+        torch.cuda.synchronize()
+        assert torch.equal(a.isnan(), b.isnan()), (value, where)
+        assert torch.equal(a.isinf(), b.isinf()) and torch.equal(a[a.isinf()], b[b.isinf()]), (value, where)
+        fin = a.isfinite()
+        tol = {"f32": 2e-5, "bf16": 2e-2, "f16": 4e-3}[dtype]
+        assert torch.allclose(a[fin], b[fin], rtol=tol, atol=tol * float(b[fin].abs().max().clamp(max=100)))
+
+
+def test_plan_refresh_reaches_the_staged_filters_and_tile():
+    spec = spec_of(2, 40, 12, 12, 48, dtype="f32", sp=0.5)
+    a, b = W.make_conv_inputs(spec, 1590), W.make_conv_inputs(spec, 1591)
+    layer = R.ConvLayer(spec, a.w, b.bias, a.mask)
+    layer.sparse(R.to_device(a.x, "f32"))
+    B.sparse_conv_plan_set_filters(layer.plan, R.to_device(b.w, "f32"))
+    B.sparse_conv_plan_set_mask(layer.plan, torch.from_numpy(b.mask).cuda())
+    y = rows_view(spec, R.to_host_f32(layer.sparse(R.to_device(b.x, "f32"))))
+    ref = rows_view(spec, oracle.masked_conv2d(spec, b.x, b.w, b.bias, b.mask))
+    assert np.linalg.norm(y - ref) <= 1e-5 * np.linalg.norm(ref)
