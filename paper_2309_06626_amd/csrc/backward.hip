@@ -24,6 +24,7 @@
 #include "conv_params.hpp"
 #include "igemm_buf_kernel.hpp"
 #include "mma_common.hpp"
+#include "wgrad_split.hpp"
 
 namespace sc {
 
@@ -766,6 +767,50 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* __restri
   }
 }
 
+// Both reductions of the float path in one launch (4.7 + 5.8 us apart, 6.2 us together at 51 splits of 64 x 576): the first `dw_blocks` workgroups are wgrad_reduce_kernel's, the others
+// colsum_final_kernel's (either may be none).
+__global__ __launch_bounds__(256) void float_reduce_kernel(const float* __restrict__ partial, int splits, int64_t count,
+                                                           float* __restrict__ dw, int dw_blocks, const float* __restrict__ sums,
+                                                           int slabs, int c, float* __restrict__ db) {
+  __shared__ __align__(16) unsigned char s_mem[sizeof(v4f) * 16 * 17];
+  if ((int)blockIdx.x < dw_blocks) {
+    v4f (*s_sub)[17] = reinterpret_cast<v4f (*)[17]>(s_mem);
+    const int e = threadIdx.x & 15, sl = threadIdx.x >> 4;
+    const int64_t i = ((int64_t)blockIdx.x * 16 + e) * 4;
+    v4f acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (i < count)
+      for (int s = sl; s < splits; s += 16) {
+        const v4f v = *reinterpret_cast<const v4f*>(partial + (int64_t)s * count + i);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[j] += v[j];
+      }
+    s_sub[sl][e] = acc;
+    __syncthreads();
+    if (threadIdx.x < 16 && i < count) {
+      v4f tot = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int l = 0; l < 16; ++l)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) tot[j] += s_sub[l][threadIdx.x][j];
+      *reinterpret_cast<v4f*>(dw + i) = tot;
+    }
+  } else {
+    float (*s_sub)[5] = reinterpret_cast<float (*)[5]>(s_mem);
+    const int e = threadIdx.x & 3, sl = threadIdx.x >> 2;
+    const int col = ((int)blockIdx.x - dw_blocks) * 4 + e;
+    float acc = 0.0f;
+    if (col < c)
+      for (int s = sl; s < slabs; s += 64) acc += sums[(int64_t)s * c + col];
+    s_sub[sl][e] = acc;
+    __syncthreads();
+    if (threadIdx.x < 4 && col < c) {
+      float tot = 0.0f;
+      for (int l = 0; l < 64; ++l) tot += s_sub[l][threadIdx.x];
+      db[col] = tot;
+    }
+  }
+}
+
 // The same for the partial results of wgrad2_kernel: per split Cout * K filter-gradient sums, then Cout bias-gradient
 // sums (`stride` floats in all); dw and db may each be null.
 __global__ __launch_bounds__(256) void wgrad2_reduce_kernel(const float* __restrict__ partial, int splits, int64_t stride,
@@ -959,7 +1004,8 @@ static sc_status backward_layout(const sc_conv_desc* d, sc_bwd_plan* L, sc_conv_
   *off_colsum = off; off = align_up(off + (size_t)((*m + kSumRowsLeast - 1) / kSumRowsLeast) * d->c_out * 4, 256);
   *off_partial = off;
   // (the dense row count bounds every mask's; both forms of the kernel fit)
-  off = align_up(off + std::max(std::max((size_t)wgrad_splits(*m, d->c_out, (int)k), (size_t)wgrad_f32_splits(*m, d->c_out, (int)k)) * d->c_out * k * 4,
+  off = align_up(off + std::max(std::max(std::max((size_t)wgrad_splits(*m, d->c_out, (int)k), (size_t)wgrad_f32_splits(*m, d->c_out, (int)k)),
+                                         (size_t)wgrad_split_splits(*m, d->c_out, (int)k, kWgradPartialBytes)) * d->c_out * k * 4,
                                 (size_t)wgrad2_splits(*m, d->c_out, (int)k, d->relu != 0) * ((size_t)d->c_out * k + d->c_out) * 4), 256);
   *off_ones = *off_wrot = *off_inner = *off_gup = off;
   if (*has_inner) {
@@ -1091,34 +1137,56 @@ sc_status sparse_conv_backward_run(const sc_bwd_plan* plan, const void* x_dev, c
     float* colsum = reinterpret_cast<float*>(plan->ws + plan->off_colsum);
     hipLaunchKernelGGL(sc::grad_map_kernel<float>, dim3(slabs), dim3(256), 0, stream, (const float*)y_dev, (const float*)dy_dev,
                        mask, gf, m, d.c_out, slab_rows, d.relu, period, colsum);
-    if (db_dev)
-      hipLaunchKernelGGL(sc::colsum_final_kernel, dim3((d.c_out + 3) / 4), dim3(256), 0, stream, colsum, slabs, d.c_out, db_dev);
-    if (dw_dev) {
-      const int k = d.kh * d.kw * d.c_in;
-      const int64_t count = (int64_t)d.c_out * k;
+    const int k = d.kh * d.kw * d.c_in;
+    const int64_t count = (int64_t)d.c_out * k;
+    float* partial = reinterpret_cast<float*>(plan->ws + plan->off_partial);
+    int splits = 0;              // (no kept row: zero splits, the reduction writes zeros)
+    const uint64_t x_bytes = (uint64_t)d.n * d.h * d.w * d.c_in * 4, g_bytes = (uint64_t)m * d.c_out * 4;
+    if (dw_dev && kept > 0 && sc::wgrad_split_applies(d.kh, d.kw, x_bytes, g_bytes)) {
+      sc::WgradSplitParams p;
+      std::memset(&p, 0, sizeof(p));
+      p.x = x_dev; p.g = gf;
+      p.row_idx = kept == m ? nullptr : rows_dev;
+      p.out = partial;
+      p.rows = (int32_t)kept;
+      splits = sc::wgrad_split_splits(kept, d.c_out, k, sc::kWgradPartialBytes);
+      p.rows_per_split = (int32_t)(((kept + splits - 1) / splits + sc::kWsRows - 1) / sc::kWsRows * sc::kWsRows);
+      p.splits = splits = (int32_t)((kept + p.rows_per_split - 1) / p.rows_per_split);
+      p.h = d.h; p.w = d.w; p.c_in = d.c_in; p.ho_wo = plan->ho * plan->wo; p.wo = plan->wo; p.c_out = d.c_out;
+      p.kh = d.kh; p.kw = d.kw; p.sh = d.stride_h; p.sw = d.stride_w; p.ph = d.pad_h; p.pw = d.pad_w;
+      p.dil_h = d.dil_h; p.dil_w = d.dil_w;
+      p.k = k;
+      p.co_tiles = (d.c_out + sc::kWsTile - 1) / sc::kWsTile;
+      p.k_tiles = (k + sc::kWsTile - 1) / sc::kWsTile;
+      p.x_bytes = (uint32_t)x_bytes; p.g_bytes = (uint32_t)g_bytes;
+      sc::magic_div((uint32_t)p.ho_wo, &p.div_howo_mul, &p.div_howo_shift);
+      sc::magic_div((uint32_t)p.wo, &p.div_wo_mul, &p.div_wo_shift);
+      hipError_t e = sc::wgrad_split_launch(p, stream);
+      if (e != hipSuccess) { sc::note_hip_error((int32_t)e); return SC_ERR_HIP; }
+    } else if (dw_dev && kept > 0) {
       sc::WgradParams p;
       std::memset(&p, 0, sizeof(p));
       p.x = x_dev; p.g = gf;
       p.row_idx = kept == m ? nullptr : rows_dev;
       p.rows = (int32_t)kept;
-      p.splits = kept > 0 ? sc::wgrad_f32_splits(kept, d.c_out, k) : 0;
-      if (p.splits > 0) {
-        p.rows_per_split = (int32_t)(((kept + p.splits - 1) / p.splits + sc::kWfRows - 1) / sc::kWfRows * sc::kWfRows);
-        p.splits = (int32_t)((kept + p.rows_per_split - 1) / p.rows_per_split);
-        p.out = reinterpret_cast<float*>(plan->ws + plan->off_partial);
-        p.h = d.h; p.w = d.w; p.c_in = d.c_in; p.ho_wo = plan->ho * plan->wo; p.wo = plan->wo; p.c_out = d.c_out;
-        p.kh = d.kh; p.kw = d.kw; p.sh = d.stride_h; p.sw = d.stride_w; p.ph = d.pad_h; p.pw = d.pad_w;
-        p.dil_h = d.dil_h; p.dil_w = d.dil_w;
-        p.k = k;
-        p.co_tiles = (d.c_out + sc::kWfTile - 1) / sc::kWfTile;
-        p.k_tiles = (k + sc::kWfTile - 1) / sc::kWfTile;
-        sc::magic_div((uint32_t)p.ho_wo, &p.div_howo_mul, &p.div_howo_shift);
-        sc::magic_div((uint32_t)p.wo, &p.div_wo_mul, &p.div_wo_shift);
-        hipLaunchKernelGGL(sc::wgrad_f32_kernel, dim3((unsigned)(p.co_tiles * p.k_tiles * p.splits)), dim3(256), 0, stream, p);
-      }
-      // (no kept row: zero splits, the reduction writes zeros)
-      hipLaunchKernelGGL(sc::wgrad_reduce_kernel, dim3((unsigned)((count + 63) / 64)), dim3(256), 0, stream,
-                         (const float*)p.out, p.splits, count, dw_dev);
+      splits = sc::wgrad_f32_splits(kept, d.c_out, k);
+      p.rows_per_split = (int32_t)(((kept + splits - 1) / splits + sc::kWfRows - 1) / sc::kWfRows * sc::kWfRows);
+      p.splits = splits = (int32_t)((kept + p.rows_per_split - 1) / p.rows_per_split);
+      p.out = partial;
+      p.h = d.h; p.w = d.w; p.c_in = d.c_in; p.ho_wo = plan->ho * plan->wo; p.wo = plan->wo; p.c_out = d.c_out;
+      p.kh = d.kh; p.kw = d.kw; p.sh = d.stride_h; p.sw = d.stride_w; p.ph = d.pad_h; p.pw = d.pad_w;
+      p.dil_h = d.dil_h; p.dil_w = d.dil_w;
+      p.k = k;
+      p.co_tiles = (d.c_out + sc::kWfTile - 1) / sc::kWfTile;
+      p.k_tiles = (k + sc::kWfTile - 1) / sc::kWfTile;
+      sc::magic_div((uint32_t)p.ho_wo, &p.div_howo_mul, &p.div_howo_shift);
+      sc::magic_div((uint32_t)p.wo, &p.div_wo_mul, &p.div_wo_shift);
+      hipLaunchKernelGGL(sc::wgrad_f32_kernel, dim3((unsigned)(p.co_tiles * p.k_tiles * p.splits)), dim3(256), 0, stream, p);
+    }
+    if (dw_dev || db_dev) {
+      const int dw_blocks = dw_dev ? (int)((count + 63) / 64) : 0, db_blocks = db_dev ? (d.c_out + 3) / 4 : 0;
+      hipLaunchKernelGGL(sc::float_reduce_kernel, dim3((unsigned)(dw_blocks + db_blocks)), dim3(256), 0, stream, (const float*)partial,
+                         splits, count, dw_dev, dw_blocks, (const float*)colsum, slabs, d.c_out, db_dev);
     }
     hipError_t ef = hipGetLastError();
     if (ef != hipSuccess) { sc::note_hip_error((int32_t)ef); return SC_ERR_HIP; }

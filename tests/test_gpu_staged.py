@@ -111,3 +111,38 @@ def test_plan_refresh_reaches_the_staged_filters_and_tile():
     y = rows_view(spec, R.to_host_f32(layer.sparse(R.to_device(b.x, "f32"))))
     ref = rows_view(spec, oracle.masked_conv2d(spec, b.x, b.w, b.bias, b.mask))
     assert np.linalg.norm(y - ref) <= 1e-5 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("shape", [
+    dict(n=1, c_in=8, hw=5, c_out=8, k=1, sparsity=0.0),             # one ragged tile, fewer rows than a step
+    dict(n=3, c_in=72, hw=17, c_out=136, k=3, sparsity=0.4),          # ragged tiles both ways, several splits, a ragged last step
+    dict(n=2, c_in=24, hw=12, c_out=64, k=5, s=2, d=2, w=19, sparsity=0.7, mask_mode="spatial"),
+    dict(n=1, c_in=16, hw=16, c_out=16, k=9, sparsity=0.5),           # a window past the validity bits: the float MFMA kernel
+])
+def test_float_filter_gradient(shape, monkeypatch):
+    import test_gpu_backward as TB
+    monkeypatch.setattr(TB, "TOL_F32_SUMS", 1e-5)
+    TB.run_backward(TB.spec_of(dtype="f32", **shape), 1600)
+
+
+@pytest.mark.parametrize("value", [np.inf, np.nan, 3.4e38])
+def test_float_filter_gradient_of_values_that_are_not_finite(value):
+    """dw has the finite, infinite and not-a-number entries of the plain sum over the kept rows."""
+    spec = W.ConvSpec("wnf", n=2, c_in=16, h=9, w=9, c_out=24, dtype="f32", sparsity=0.3, relu=False)
+    ci = W.make_conv_inputs(spec, 1620)
+    x = ci.x.copy()
+    x[0, 4, 4, 3] = x[1, 2, 7, 0] = value
+    dy = np.random.default_rng(1621).standard_normal(spec.y_shape()).astype(np.float32)
+    dy.reshape(-1)[::5] = 0.0
+    layer = R.ConvLayer(spec, ci.w, ci.bias, ci.mask)
+    bwd = B.sparse_conv_backward_plan(layer.plan, layer.w)
+    dw = torch.empty(spec.w_shape(), dtype=torch.float32, device="cuda:0")
+    B.sparse_conv_backward_run(bwd, R.to_device(x, "f32"), None, R.to_device(dy, "f32"), dw=dw)
+    cols = torch.nn.functional.unfold(torch.from_numpy(x).permute(0, 3, 1, 2), 3, padding=1)        # [N, C * 9, L]
+    a = cols.view(2, 16, 9, 81).permute(0, 3, 2, 1).reshape(162, 144)
+    kept = torch.from_numpy(ci.mask).bool()
+    want = (torch.from_numpy(dy).reshape(162, 24)[kept].t() @ a[kept]).view(24, 3, 3, 16)
+    got = dw.cpu()
+    assert torch.equal(got.isnan(), want.isnan()) and torch.equal(got.isinf(), want.isinf())
+    fin = want.isfinite()
+    assert torch.allclose(got[fin], want[fin], rtol=1e-4, atol=1e-4)
