@@ -962,6 +962,9 @@ static inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; 
 
 }  // namespace sc
 
+// plan.hip
+extern "C" __attribute__((visibility("hidden"))) sc_status sc_plan_set_rotated_filters(sc_plan* plan, const void* w_dev, void* hip_stream);
+
 struct sc_bwd_plan {
   const sc_plan* fwd;
   sc_conv_desc desc;
@@ -1105,7 +1108,9 @@ sc_status sparse_conv_backward_set_filters(sc_bwd_plan* plan, const void* w_dev,
   if (!plan || !w_dev) return SC_ERR_NULL;
   if ((uintptr_t)w_dev & 15) return SC_ERR_ALIGN;
   if (!plan->inner) return SC_OK;            // only the input gradient uses the filters
-  sc_status s = sc::rotate_filters(plan, w_dev, static_cast<hipStream_t>(hip_stream));
+  sc_status s = sc_plan_set_rotated_filters(plan->inner, w_dev, hip_stream);
+  if (s != SC_ERR_UNSUPPORTED) return s;
+  s = sc::rotate_filters(plan, w_dev, static_cast<hipStream_t>(hip_stream));
   if (s != SC_OK) return s;
   return sparse_conv_plan_set_filters(plan->inner, plan->ws + plan->off_wrot, hip_stream);
 }

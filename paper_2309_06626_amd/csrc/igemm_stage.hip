@@ -50,6 +50,34 @@ struct StageOrder {
   }
 };
 
+// eight filter entries in three parts, K steps of a part apart
+__device__ __forceinline__ void store_filter_parts(const float (&e)[8], v4i* __restrict__ dst) {
+  using D = StageDims<kF32>;
+  uint16_t parts[3][8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const float f = e[i];
+    const uint32_t bits = __builtin_bit_cast(uint32_t, f);
+    const bool finite = (bits & 0x7f800000u) != 0x7f800000u;
+    float a = (float)(__bf16)f;
+    // a finite value that would round to infinity is cut instead; one that is not finite is its own first part and
+    // its second one is not a number, so that every sum it enters asks for the careful pass
+    if (finite && (__builtin_bit_cast(uint32_t, a) & 0x7f800000u) == 0x7f800000u) a = __builtin_bit_cast(float, bits & 0xffff0000u);
+    const float r = f - a;
+    const float b = finite ? (float)(__bf16)r : __builtin_nanf("");
+    const float c = finite ? r - b : 0.0f;
+    parts[0][i] = (uint16_t)(__builtin_bit_cast(uint32_t, a) >> 16);
+    parts[1][i] = (uint16_t)(__builtin_bit_cast(uint32_t, b) >> 16);
+    parts[2][i] = (uint16_t)(__builtin_bit_cast(uint32_t, c) >> 16);
+  }
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    v4i v;
+    __builtin_memcpy(&v, parts[q], 16);
+    dst[q * D::KSTEPS * 64] = v;
+  }
+}
+
 // One thread per 16 bytes of the packed filters: [32 channels][K tile][part][K step][lane].  Channel rows are permuted so
 // that a lane of the MFMA result owns 16 consecutive channels.
 template <int DT>
@@ -75,29 +103,7 @@ __global__ void stage_pack_kernel(const typename Elem<DT>::T* __restrict__ w, v4
   }
   v4i* dst = wp + tile * (D::BLOCK_BYTES / 16) + ks * 64 + lane;
   if constexpr (DT == kF32) {
-    uint16_t parts[3][8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const float f = e[i];
-      const uint32_t bits = __builtin_bit_cast(uint32_t, f);
-      const bool finite = (bits & 0x7f800000u) != 0x7f800000u;
-      float a = (float)(__bf16)f;
-      // a finite value that would round to infinity is cut instead; one that is not finite is its own first part and
-      // its second one is not a number, so that every sum it enters asks for the careful pass
-      if (finite && (__builtin_bit_cast(uint32_t, a) & 0x7f800000u) == 0x7f800000u) a = __builtin_bit_cast(float, bits & 0xffff0000u);
-      const float r = f - a;
-      const float b = finite ? (float)(__bf16)r : __builtin_nanf("");
-      const float c = finite ? r - b : 0.0f;
-      parts[0][i] = (uint16_t)(__builtin_bit_cast(uint32_t, a) >> 16);
-      parts[1][i] = (uint16_t)(__builtin_bit_cast(uint32_t, b) >> 16);
-      parts[2][i] = (uint16_t)(__builtin_bit_cast(uint32_t, c) >> 16);
-    }
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      v4i v;
-      __builtin_memcpy(&v, parts[q], 16);
-      dst[q * D::KSTEPS * 64] = v;
-    }
+    store_filter_parts(e, dst);
   } else {
     v4i v;
     __builtin_memcpy(&v, e, 16);
@@ -133,7 +139,8 @@ hipError_t stage_pack(int dtype, int gather, const void* w, void* wp, KEntry* ta
   const int ksteps = dtype == kF32 ? StageDims<kF32>::KSTEPS : StageDims<kBF16>::KSTEPS;
   const int64_t total = (int64_t)blocks * k_tiles * ksteps * 64;
   const dim3 grid((unsigned)((total + 255) / 256)), block(256);
-  if (dtype == kF32)
+  if (!w) (void)0;      // (the table alone)
+  else if (dtype == kF32)
     hipLaunchKernelGGL(stage_pack_kernel<kF32>, grid, block, 0, stream, (const float*)w, (v4i*)wp, o, c_out, blocks, k_tiles, kh, kw, nchw ? 1 : 0);
   else      // 16-bit patterns are moved verbatim
     hipLaunchKernelGGL(stage_pack_kernel<kF16>, grid, block, 0, stream, (const _Float16*)w, (v4i*)wp, o, c_out, blocks, k_tiles, kh, kw, nchw ? 1 : 0);
@@ -144,6 +151,84 @@ hipError_t stage_pack(int dtype, int gather, const void* w, void* wp, KEntry* ta
   const int xs_h = nchw ? w_cols : w_cols * c_in, xs_w = nchw ? 1 : c_in, xs_c = nchw ? h * w_cols : 1;
   hipLaunchKernelGGL(stage_table_kernel, dim3((entries + 255) / 256), dim3(256), 0, stream, tab, entries, per, o, kw, dil_h, dil_w, eb,
                      xs_h, xs_w, xs_c);
+  return hipGetLastError();
+}
+
+// Filters of an NHWC layer whose channels are whole 16-byte groups, into the layout of the tiled and band kernels
+// ([channel row][K], rows permuted like above) and, for float, into the parts of the direct-to-LDS kernel: one launch, 16
+// bytes a thread.  ROT: `w` holds the filters of the layer whose input gradient this is ([Cin][kh][kw][Cout], rotated by 180
+// degrees); lanes then run over the channel rows, along which those lie.
+template <int DT, bool ROT>
+__global__ void repack_kernel(const typename Elem<DT>::T* __restrict__ w, v4i* __restrict__ wp, v4i* __restrict__ parts, int c_out,
+                              int c_in, int taps, int k_stride, int rows, int row_blocks, int part_blocks, int k_tiles) {
+  using D = StageDims<DT>;
+  using T = typename Elem<DT>::T;
+  constexpr int V = Elem<DT>::V;
+  const int k = taps * c_in;
+  auto channel = [](int row) { return (row & ~31) + 16 * ((row >> 2) & 1) + 4 * ((row & 31) >> 3) + (row & 3); };
+  auto group = [&](int co, int kk, T* dst) {        // V entries from kk on: one tap
+    if (co >= c_out || kk >= k) {
+#pragma unroll
+      for (int i = 0; i < V; ++i) dst[i] = (T)0.0f;
+      return;
+    }
+    if constexpr (ROT) {
+      const int tap = kk / c_in, ci = kk - tap * c_in;
+#pragma unroll
+      for (int i = 0; i < V; ++i) dst[i] = w[((int64_t)(ci + i) * taps + taps - 1 - tap) * c_out + co];
+    } else {
+      const v4i v = *reinterpret_cast<const v4i*>(w + (int64_t)co * k + kk);
+      __builtin_memcpy(dst, &v, 16);
+    }
+  };
+  if ((int)blockIdx.x < row_blocks) {
+    const int idx = blockIdx.x * blockDim.x + threadIdx.x, per_row = k_stride / V;
+    int row, g;
+    if constexpr (ROT) {
+      const int rest = idx >> 5;
+      g = rest % per_row;
+      row = rest / per_row * 32 + (idx & 31);
+    } else {
+      row = idx / per_row;
+      g = idx - row * per_row;
+    }
+    if (row >= rows) return;
+    T e[V];
+    group(channel(row), g * V, e);
+    v4i v;
+    __builtin_memcpy(&v, e, 16);
+    wp[(int64_t)row * per_row + g] = v;
+    return;
+  }
+  if constexpr (DT == kF32) {
+    const int idx = (blockIdx.x - row_blocks) * blockDim.x + threadIdx.x;
+    const int lane = idx & 63, unit = idx >> 6, ks = unit % D::KSTEPS, tile = unit / D::KSTEPS;
+    const int kt = tile % k_tiles, nb = tile / k_tiles;
+    if (nb >= part_blocks) return;
+    const int co = nb * 32 + channel(lane & 31), kk = kt * D::K_TILE + (2 * ks + (lane >> 5)) * 8;
+    float e[8];
+    group(co, kk, e);
+    group(co, kk + 4, e + 4);
+    store_filter_parts(e, parts + (int64_t)tile * (D::BLOCK_BYTES / 16) + ks * 64 + lane);
+  }
+}
+
+hipError_t repack_filters(int dtype, const void* w, void* wp, void* parts, int c_out, int c_in, int taps, int k_stride, int rows,
+                          int part_blocks, int k_tiles, bool rotated, hipStream_t stream) {
+  const int v = dtype == kF32 ? 4 : 8;
+  const int row_blocks = (int)(((int64_t)rows * (k_stride / v) + 255) / 256);
+  const int blocks = row_blocks + (parts ? (int)(((int64_t)part_blocks * k_tiles * StageDims<kF32>::KSTEPS * 64 + 255) / 256) : 0);
+  auto launch = [&](auto kern, auto* src) {
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, stream, src, (v4i*)wp, (v4i*)parts, c_out, c_in, taps, k_stride, rows, row_blocks,
+                       part_blocks, k_tiles);
+  };
+  if (dtype == kF32) {
+    if (rotated) launch(repack_kernel<kF32, true>, (const float*)w);
+    else launch(repack_kernel<kF32, false>, (const float*)w);
+  } else {       // 16-bit patterns are moved verbatim
+    if (rotated) launch(repack_kernel<kF16, true>, (const _Float16*)w);
+    else launch(repack_kernel<kF16, false>, (const _Float16*)w);
+  }
   return hipGetLastError();
 }
 

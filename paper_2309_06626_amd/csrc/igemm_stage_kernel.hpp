@@ -542,5 +542,9 @@ LaunchFn stage_kernel(int dtype, int gather, bool nchw, int bm, int bn);
 // filters into the order of the kernel's tiles, and the gather's table (igemm_stage.hip)
 hipError_t stage_pack(int dtype, int gather, const void* w, void* wp, KEntry* tab, int c_out, int blocks, int c_in, int kh, int kw,
                       int dil_h, int dil_w, int k_tiles, bool nchw, int h, int w_cols, hipStream_t stream);
+// the filters of an NHWC layer with whole 16-byte groups of channels into the tiled layout and (parts not null) the float
+// parts; rotated: from the filters of the layer whose input gradient this is (igemm_stage.hip)
+hipError_t repack_filters(int dtype, const void* w, void* wp, void* parts, int c_out, int c_in, int taps, int k_stride, int rows,
+                          int part_blocks, int k_tiles, bool rotated, hipStream_t stream);
 
 }  // namespace sc

@@ -146,3 +146,27 @@ def test_float_filter_gradient_of_values_that_are_not_finite(value):
     assert torch.equal(got.isnan(), want.isnan()) and torch.equal(got.isinf(), want.isinf())
     fin = want.isfinite()
     assert torch.allclose(got[fin], want[fin], rtol=1e-4, atol=1e-4)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("cin,cout,k", [(8, 40, 3), (64, 264, 1), (72, 16, 5)])
+def test_refreshed_filters_equal_those_of_a_new_plan(cin, cout, k, dtype):
+    """Forward and input gradient after set_filters (one launch each, the rotation folded in): the bits of fresh plans."""
+    spec = spec_of(2, cin, 9, 11, cout, k=k, p=k // 2, dtype=dtype, relu=False)
+    a, b = W.make_conv_inputs(spec, 1630), W.make_conv_inputs(spec, 1631)
+    x, dy = R.to_device(b.x, dtype), torch.randn(spec.y_shape(), device="cuda:0").to(B.TORCH_DTYPE[dtype])
+    got = []
+    for first in (a.w, b.w):
+        layer = R.ConvLayer(spec, first, b.bias, b.mask)
+        bwd = B.sparse_conv_backward_plan(layer.plan, layer.w)
+        if first is a.w:
+            w = R.to_device(b.w, dtype)
+            B.sparse_conv_plan_set_filters(layer.plan, w)
+            B.sparse_conv_backward_set_filters(bwd, w)
+        y, dx = layer.sparse(x), torch.empty_like(x)
+        B.sparse_conv_plan_set_tiles(layer.plan, 0, 64, 64)          # and the layout of the other kernels
+        y2 = layer.sparse(x)
+        B.sparse_conv_backward_run(bwd, x, y, dy, dx=dx)
+        got.append([R.bits_of(t) for t in (y, y2, dx)])
+    for p, q in zip(*got):
+        assert np.array_equal(p, q)
