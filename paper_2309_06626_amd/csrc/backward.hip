@@ -45,8 +45,8 @@ static inline int colsum_slab_rows(int64_t rows) {
 template <typename T>
 __global__ __launch_bounds__(256) void grad_map_kernel(const T* __restrict__ y, const T* __restrict__ dy,
                                                        const uint8_t* __restrict__ mask, T* __restrict__ g, int64_t rows,
-                                                       int c, int slab_rows, int relu, int period,
-                                                       float* __restrict__ partial) {
+                                                       int c, int slab_rows, int relu, int period, uint32_t period_mul,
+                                                       uint32_t period_shift, float* __restrict__ partial) {
   __shared__ float s_acc[256][9];                       // (padded: the final adds walk a column of it)
   struct alignas(16) Grp { T v[8]; };
   const int groups = c / 8;
@@ -58,36 +58,48 @@ __global__ __launch_bounds__(256) void grad_map_kernel(const T* __restrict__ y, 
     float acc[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] = 0.0f;
+    // (a few rows at a time: their mask bytes first, then the loads of the kept ones together -- row by row each waited
+    // for its own byte and then for its own values)
+    constexpr int AHEAD = sizeof(T) == 2 ? 4 : 2;      // (64 x 128 channels @28 in bf16 at s = 0.5: 11.4 -> 9.9 us)
     if (rl < lanes_per_group)
-      for (int64_t r = r0 + rl; r < r1; r += lanes_per_group) {
-        const int64_t at = r * c + (int64_t)(gbase + gi) * 8;
-        Grp out;
+      for (int64_t rb = r0 + rl; rb < r1; rb += AHEAD * lanes_per_group) {
+        bool keep[AHEAD];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) out.v[j] = (T)0.0f;
-        if (mask[period ? r % period : r] != 0) {
-          out = *reinterpret_cast<const Grp*>(dy + at);
-          if (relu) {
-            const Grp f = *reinterpret_cast<const Grp*>(y + at);
+        for (int u = 0; u < AHEAD; ++u) {
+          const int r = (int)min(rb + (int64_t)u * lanes_per_group, r1 - 1);
+          keep[u] = mask[period ? r - fast_div(r, period_mul, period_shift) * period : r] != 0;
+        }
+        Grp out[AHEAD], f[AHEAD];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) out.v[j] = (float)f.v[j] > 0.0f ? out.v[j] : (T)0.0f;
+        for (int u = 0; u < AHEAD; ++u) {
+          const int64_t r = rb + (int64_t)u * lanes_per_group, at = r * c + (int64_t)(gbase + gi) * 8;
+#pragma unroll
+          for (int j = 0; j < 8; ++j) { out[u].v[j] = (T)0.0f; f[u].v[j] = (T)0.0f; }
+          if (r < r1 && keep[u]) {
+            out[u] = *reinterpret_cast<const Grp*>(dy + at);
+            if (relu) f[u] = *reinterpret_cast<const Grp*>(y + at);
           }
         }
-        *reinterpret_cast<Grp*>(g + at) = out;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j] += (float)out.v[j];
+        for (int u = 0; u < AHEAD; ++u) {
+          const int64_t r = rb + (int64_t)u * lanes_per_group;
+          if (r >= r1) break;
+          if (relu) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) out[u].v[j] = (float)f[u].v[j] > 0.0f ? out[u].v[j] : (T)0.0f;
+          }
+          *reinterpret_cast<Grp*>(g + r * c + (int64_t)(gbase + gi) * 8) = out[u];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) acc[j] += (float)out[u].v[j];
+        }
       }
 #pragma unroll
     for (int j = 0; j < 8; ++j) s_acc[threadIdx.x][j] = acc[j];
     __syncthreads();
-    if (threadIdx.x < gcount) {
-      float tot[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) tot[j] = 0.0f;
-      for (int l = 0; l < lanes_per_group; ++l)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) tot[j] += s_acc[l * gcount + threadIdx.x][j];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) partial[(int64_t)blockIdx.x * c + (int64_t)(gbase + threadIdx.x) * 8 + j] = tot[j];
+    for (int i = threadIdx.x; i < gcount * 8; i += 256) {      // a thread per channel: the row lanes in lane order
+      float tot = 0.0f;
+      for (int l = 0; l < lanes_per_group; ++l) tot += s_acc[l * gcount + (i >> 3)][i & 7];
+      partial[(int64_t)blockIdx.x * c + (int64_t)gbase * 8 + i] = tot;
     }
     __syncthreads();
   }
@@ -1132,6 +1144,8 @@ sc_status sparse_conv_backward_run(const sc_bwd_plan* plan, const void* x_dev, c
   const uint8_t* mask = sparse_conv_plan_mask(plan->fwd);
   const int dt = d.dtype == SC_BF16 ? sc::kBF16 : d.dtype == SC_F16 ? sc::kF16 : sc::kF32;
   const int period = d.mask_mode == SC_MASK_SPATIAL ? plan->ho * plan->wo : 0;
+  uint32_t period_mul = 0, period_shift = 0;
+  if (period) sc::magic_div((uint32_t)period, &period_mul, &period_shift);
   _Float16* g = reinterpret_cast<_Float16*>(plan->ws + plan->off_g);    // 16-bit patterns; compared as the real type below
 
   if (dt == sc::kF32) {
@@ -1141,7 +1155,7 @@ sc_status sparse_conv_backward_run(const sc_bwd_plan* plan, const void* x_dev, c
     const int slabs = (int)((m + slab_rows - 1) / slab_rows);
     float* colsum = reinterpret_cast<float*>(plan->ws + plan->off_colsum);
     hipLaunchKernelGGL(sc::grad_map_kernel<float>, dim3(slabs), dim3(256), 0, stream, (const float*)y_dev, (const float*)dy_dev,
-                       mask, gf, m, d.c_out, slab_rows, d.relu, period, colsum);
+                       mask, gf, m, d.c_out, slab_rows, d.relu, period, period_mul, period_shift, colsum);
     const int k = d.kh * d.kw * d.c_in;
     const int64_t count = (int64_t)d.c_out * k;
     float* partial = reinterpret_cast<float*>(plan->ws + plan->off_partial);
@@ -1232,10 +1246,10 @@ sc_status sparse_conv_backward_run(const sc_bwd_plan* plan, const void* x_dev, c
   if (want_g) {
     if (dt == sc::kBF16)
       hipLaunchKernelGGL(sc::grad_map_kernel<__bf16>, dim3(slabs), dim3(256), 0, stream, (const __bf16*)y_dev,
-                         (const __bf16*)dy_dev, mask, (__bf16*)g, m, d.c_out, slab_rows, d.relu, period, colsum);
+                         (const __bf16*)dy_dev, mask, (__bf16*)g, m, d.c_out, slab_rows, d.relu, period, period_mul, period_shift, colsum);
     else
       hipLaunchKernelGGL(sc::grad_map_kernel<_Float16>, dim3(slabs), dim3(256), 0, stream, (const _Float16*)y_dev,
-                         (const _Float16*)dy_dev, mask, g, m, d.c_out, slab_rows, d.relu, period, colsum);
+                         (const _Float16*)dy_dev, mask, g, m, d.c_out, slab_rows, d.relu, period, period_mul, period_shift, colsum);
   }
   if (direct) {
     sc::Wgrad2Params p;

@@ -10,6 +10,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <new>
 
 #include "band_kernel.hpp"
@@ -103,9 +104,13 @@ __global__ __launch_bounds__(256) void mask_scatter_kernel(const uint8_t* __rest
 }
 
 // Slab kernel (igemm_slab_kernel.hpp): virtual rows between the window corner of the first and of the last kept row of
-// every tile of 128 and of 256 kept rows, plus the window height; the maximum over the tiles sizes the LDS slab.
+// every tile of 128 and of 256 kept rows, plus the window height; the maximum over the tiles sizes the LDS slab.  per_wg:
+// each workgroup leaves its own two maxima (one workgroup covers the tiles of 32 768 rows), else all raise the same two.
 __global__ __launch_bounds__(256) void slab_span_kernel(const int32_t* __restrict__ row_idx, const int32_t* __restrict__ kept_dev,
-                                                        int ho_wo, int wo, int hp, int kh, int32_t* __restrict__ span_out) {
+                                                        int ho_wo, int wo, int hp, int kh, int32_t* __restrict__ span_out, int per_wg) {
+  __shared__ int s_span[2];
+  if (threadIdx.x < 2) s_span[threadIdx.x] = 0;
+  __syncthreads();
   const int kept = kept_dev[0];
   const int tile = blockIdx.x * 256 + threadIdx.x;
   auto vrow = [&](int r) { return (r / ho_wo) * hp + (r % ho_wo) / wo; };
@@ -114,7 +119,12 @@ __global__ __launch_bounds__(256) void slab_span_kernel(const int32_t* __restric
     const int64_t m0 = (int64_t)tile * bm;
     if (m0 >= kept) continue;
     const int last = (int)min((int64_t)kept, m0 + bm) - 1;
-    atomicMax(span_out + b, vrow(row_idx[last]) + kh - vrow(row_idx[m0]));
+    atomicMax(&s_span[b], vrow(row_idx[last]) + kh - vrow(row_idx[m0]));
+  }
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    if (per_wg) span_out[blockIdx.x * 2 + threadIdx.x] = s_span[threadIdx.x];
+    else atomicMax(span_out + threadIdx.x, s_span[threadIdx.x]);
   }
 }
 
@@ -262,6 +272,200 @@ __global__ void band_rows_kernel(const int32_t* __restrict__ row_idx, const int3
   band_rows[img * ho_wo + first + (i - i0)] = r;
   if (i == i0) atomicMax(band_max, band_i0[band + 1] - i0);
 }
+
+// ------------------------------------------------------------------------------------------------
+// The same tables -- row list, private mask copy, band starts, band-ordered rows, and for one workgroup the slab spans -- in
+// ONE launch, for maps of up to kTableMostRows rows.  A workgroup owns 1 024 rows and counts the ones in front of them by
+// itself (16-byte loads of a mask that lies in L2) instead of waiting for a pass of its own, so a refresh of a small map is
+// one launch in place of four or five.  Every workgroup leaves what the host wants to know -- its kept rows, the fullest
+// band that ends in its rows, the spans -- in host memory (`result`, four words each), where the host finds it behind the
+// synchronisation without a copy.
+// ------------------------------------------------------------------------------------------------
+constexpr int kTableThreads = 256, kTableRows = 4 * kTableThreads;
+constexpr int kTableMostRows = 1 << 17, kTableMostWgs = kTableMostRows / kTableRows;
+
+struct TableParams {
+  const uint8_t* mask;
+  uint8_t* copy;
+  int32_t *row_idx, *kept_out, *band_i0, *band_rows, *result;
+  int32_t m, period, mask_len;
+  int32_t n_bands, bands_per_image, bh, split, ho, wo;      // n_bands == 0: no band tables
+  int32_t slab_hp, slab_kh;                                 // slab_hp == 0: no spans
+  uint32_t howo_mul, howo_shift, wo_mul, wo_shift, bh_mul, bh_shift;
+};
+
+__global__ __launch_bounds__(kTableThreads) void row_tables_kernel(const TableParams p) {
+  __shared__ unsigned long long s_bits[kTableRows / 64];    // which rows of the segment are kept
+  __shared__ int s_before[kTableRows / 64];                 // kept rows of the segment in front of each word
+  __shared__ int s_wave[4], s_red[3];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int r0 = blockIdx.x * kTableRows;
+  const int ho_wo = p.ho * p.wo;
+
+  // the segment's rows, and where a band that began in front of it started
+  unsigned char v[4];
+#pragma unroll
+  for (int it = 0; it < 4; ++it) {
+    const int r = r0 + wave * 256 + it * 64 + lane;
+    const int q = p.period ? r - fast_div(r, p.howo_mul, p.howo_shift) * p.period : r;
+    v[it] = r < p.m ? p.mask[q] : (uint8_t)0;
+    if (r < p.mask_len) p.copy[r] = v[it];
+  }
+  auto band_at = [&](int r, int* band, int* first, int* end) {      // rows [first, end) of the band that row r lies in
+    const int img = fast_div(r, p.howo_mul, p.howo_shift), pix = r - img * ho_wo;
+    const int run = fast_div(fast_div(pix, p.wo_mul, p.wo_shift), p.bh_mul, p.bh_shift);
+    const int p0 = run * p.bh * p.wo, px = min(p.ho - run * p.bh, p.bh) * p.wo, half = (px + 1) >> 1;
+    const int second = p.split && pix - p0 >= half ? 1 : 0;
+    *band = img * p.bands_per_image + (p.split ? 2 * run + second : run);
+    *first = img * ho_wo + p0 + (second ? half : 0);
+    *end = img * ho_wo + p0 + (p.split && !second ? half : px);
+  };
+  int start = r0;
+  if (p.n_bands && r0 > 0) {
+    int band, end;
+    band_at(r0, &band, &start, &end);
+  }
+  // kept rows in [0, start) and in [start, r0)
+  auto kept_in = [&](int from, int to) {       // this thread's share of mask[from .. to)
+    int n = 0;
+    const uintptr_t base = (uintptr_t)p.mask;
+    const int a = (int)min((int64_t)to, (int64_t)((from + base + 15) / 16 * 16 - base)), b = (int)max((int64_t)a, (int64_t)((to + base) / 16 * 16 - base));
+    for (int i = from + t; i < a; i += kTableThreads) n += p.mask[i] != 0;
+    for (int i = a + 16 * t; i < b; i += 4 * 16 * kTableThreads) {      // four loads on their way
+      uint4 w[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int at = i + u * 16 * kTableThreads;
+        w[u] = at < b ? *reinterpret_cast<const uint4*>(p.mask + at) : make_uint4(0, 0, 0, 0);
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const uint32_t d[4] = {w[u].x, w[u].y, w[u].z, w[u].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) n += __popc((((d[e] & 0x7f7f7f7fu) + 0x7f7f7f7fu) | d[e]) & 0x80808080u);
+      }
+    }
+    for (int i = b + t; i < to; i += kTableThreads) n += p.mask[i] != 0;
+    return n;
+  };
+  auto kept_before = [&](int r) {              // this thread's share of the kept rows in front of row r
+    if (!p.period) return kept_in(0, r);
+    const int img = fast_div(r, p.howo_mul, p.howo_shift), rem = r - img * p.period;
+    return (img ? img * kept_in(0, p.period) : 0) + kept_in(0, rem);
+  };
+  if (t < 3) s_red[t] = 0;
+  __syncthreads();
+  if (r0 > 0) {
+    const int to_start = wave_sum(kept_before(start)), to_r0 = wave_sum(start == r0 ? 0 : kept_before(r0));
+    if (lane == 0) {
+      atomicAdd(&s_red[0], to_start);
+      atomicAdd(&s_red[1], start == r0 ? to_start : to_r0);
+    }
+  }
+  int own = 0;
+#pragma unroll
+  for (int it = 0; it < 4; ++it) {
+    const unsigned long long bits = __ballot(v[it] != 0);
+    if (lane == 0) { s_bits[wave * 4 + it] = bits; s_before[wave * 4 + it] = own; }
+    own += __popcll(bits);
+  }
+  if (lane == 0) s_wave[wave] = own;
+  __syncthreads();
+  int before_wave = 0, total = 0;
+  for (int w = 0; w < 4; ++w) {
+    if (w < wave) before_wave += s_wave[w];
+    total += s_wave[w];
+  }
+  if (lane < 4) s_before[wave * 4 + lane] += before_wave;
+  const int start_rank = s_red[0], base = s_red[1];
+  __syncthreads();
+  auto rank_at = [&](int r) {                  // kept rows in front of row r, a row of the segment or `start`
+    if (r < r0) return start_rank;
+    const int q = r - r0;
+    return base + s_before[q >> 6] + (int)__popcll(s_bits[q >> 6] & ((1ull << (q & 63)) - 1ull));
+  };
+  int fullest = 0;
+#pragma unroll
+  for (int it = 0; it < 4; ++it) {
+    const int r = r0 + wave * 256 + it * 64 + lane;
+    if (r >= p.m) break;
+    const bool keep = v[it] != 0;
+    const int rank = rank_at(r);
+    if (keep) p.row_idx[rank] = r;
+    if (p.n_bands) {
+      int band, first, end;
+      band_at(r, &band, &first, &end);
+      const int i0 = rank_at(first);
+      if (r == first) p.band_i0[band] = rank;
+      if (keep) p.band_rows[first + (rank - i0)] = r;
+      if (r == end - 1) fullest = max(fullest, rank + (keep ? 1 : 0) - i0);
+    }
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) fullest = max(fullest, __shfl_xor(fullest, off, 64));
+  if (lane == 0) atomicMax(&s_red[2], fullest);
+  const bool last = blockIdx.x == gridDim.x - 1;
+  const int kept = base + total;
+  __syncthreads();                             // (also: this workgroup's row list is in memory for its own readers)
+  int span[2] = {0, 0};
+  if (p.slab_hp && gridDim.x == 1) {
+    auto vrow = [&](int r) {
+      const int img = fast_div(r, p.howo_mul, p.howo_shift);
+      return img * p.slab_hp + fast_div(r - img * ho_wo, p.wo_mul, p.wo_shift);
+    };
+    for (int b = 0; b < 2; ++b)
+      for (int m0 = t * (128 << b); m0 < kept; m0 += kTableThreads * (128 << b))
+        span[b] = max(span[b], vrow(p.row_idx[min(kept, m0 + (128 << b)) - 1]) + p.slab_kh - vrow(p.row_idx[m0]));
+    if (t < 2) s_wave[t] = 0;
+    __syncthreads();
+    for (int b = 0; b < 2; ++b) atomicMax(&s_wave[b], span[b]);
+    __syncthreads();
+    span[0] = s_wave[0];
+    span[1] = s_wave[1];
+  }
+  if (t == 0) {
+    int32_t* out = p.result + blockIdx.x * 4;
+    out[0] = total;
+    out[1] = s_red[2];
+    out[2] = span[0];
+    out[3] = span[1];
+    if (last) {
+      p.kept_out[0] = kept;
+      p.kept_out[1] = p.kept_out[2] = p.kept_out[3] = 0;
+      if (p.n_bands) p.band_i0[p.n_bands] = kept;
+    }
+  }
+}
+
+// Host memory that kernels write their few words for the host into: kHostSlots slots in one allocation, made on first use and
+// held until the process ends.  A call holds a slot from its launch to its synchronisation; one that finds none free (or no
+// such memory) copies from the device instead.
+constexpr int kTableSpanWgs = kTableMostRows / (128 * 256);
+constexpr int kHostSlots = 32, kHostSlotWords = kTableMostWgs * 4 + kTableSpanWgs * 2;
+struct HostSlots {
+  std::mutex lock;
+  int32_t* base = nullptr;
+  bool tried = false;
+  uint32_t used = 0;
+  int32_t* take() {
+    std::lock_guard<std::mutex> hold(lock);
+    if (!tried) {
+      tried = true;
+      void* mem = nullptr;
+      if (hipHostMalloc(&mem, sizeof(int32_t) * kHostSlots * kHostSlotWords, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess) base = static_cast<int32_t*>(mem);
+      else (void)hipGetLastError();
+    }
+    if (!base) return nullptr;
+    for (int i = 0; i < kHostSlots; ++i)
+      if (!(used >> i & 1u)) { used |= 1u << i; return base + i * kHostSlotWords; }
+    return nullptr;
+  }
+  void give_back(int32_t* slot) {
+    std::lock_guard<std::mutex> hold(lock);
+    used &= ~(1u << ((slot - base) / kHostSlotWords));
+  }
+};
+static HostSlots g_host_slots;
 
 // ------------------------------------------------------------------------------------------------
 // Glue operators for network runs
@@ -506,7 +710,7 @@ static sc_status check_desc(const sc_conv_desc* d, Geometry* g) {
   g->nseg = (int32_t)((g->m + kSeg - 1) / kSeg);
   size_t off = 0;
   g->off_rows = off;   off = align_up(off + (size_t)g->m * 4, 256);
-  g->off_counts = off; off = align_up(off + (size_t)g->nseg * 4, 256);
+  g->off_counts = off; off = align_up(off + ((size_t)g->nseg * 4 + 16) * 4, 256);      // (and the words of row_tables_kernel)
   g->off_kept = off;   off += 256;
   g->off_zeros = off;  off += 256;
   g->off_mask = off;   off = align_up(off + (size_t)g->mask_len, 256);
@@ -1609,43 +1813,99 @@ static sc_status pack_filters(const sc_conv_desc& d, const Geometry& g, unsigned
 static sc_status build_row_tables(const sc_conv_desc& d, const Geometry& g, unsigned char* ws, const uint8_t* mask_dev,
                                   hipStream_t stream, BandPlan* bp_io, int32_t* kept_out, int32_t* slab_span_out) {
   BandPlan& bp = *bp_io;
-  // compaction
   const int period = d.mask_mode == SC_MASK_SPATIAL ? g.ho * g.wo : 0;
   int32_t* counts = reinterpret_cast<int32_t*>(ws + g.off_counts);
   int32_t* rows = reinterpret_cast<int32_t*>(ws + g.off_rows);
   int32_t* kept_dev = reinterpret_cast<int32_t*>(ws + g.off_kept);
-  const int cgrid = (g.nseg + 3) / 4;
-  // pass 1 also leaves the plan's private copy of the mask (the zero fill of every run reads it)
-  hipLaunchKernelGGL(mask_count_kernel, dim3(cgrid), dim3(256), 0, stream, mask_dev, (int)g.m, period,
-                     g.nseg, counts, ws + g.off_mask, (int)g.mask_len);
-  SC_HIP(hipGetLastError());
-  hipLaunchKernelGGL(mask_scatter_kernel, dim3(cgrid), dim3(256), 0, stream, ws + g.off_mask, (int)g.m, period,
-                     g.nseg, counts, rows, kept_dev);
-  SC_HIP(hipGetLastError());
-  if (g.depthwise)   // position of every kept row in the row list (compact output of the LDS-tiled kernels)
-    SC_HIP(depthwise_rank(rows, kept_dev, reinterpret_cast<int32_t*>(ws + g.off_band_rows), g.m, stream));
-
-  if (bp.ok) {
-    hipLaunchKernelGGL(band_start_kernel, dim3((bp.n_bands + 1 + 255) / 256), dim3(256), 0, stream, rows, kept_dev,
-                       reinterpret_cast<int32_t*>(ws + g.off_band), bp.n_bands, bp.bands_per_image, bp.bh, bp.split, g.ho, g.wo);
-    SC_HIP(hipGetLastError());
-    // kept_dev + 1 holds the per-band maximum (zeroed by the scatter pass, raised by band_rows_kernel)
-    hipLaunchKernelGGL(band_rows_kernel, dim3((unsigned)((g.m + 255) / 256)), dim3(256), 0, stream, rows, kept_dev,
-                       reinterpret_cast<const int32_t*>(ws + g.off_band),
-                       reinterpret_cast<int32_t*>(ws + g.off_band_rows), bp.bands_per_image, bp.bh, bp.split, g.ho, g.wo,
-                       kept_dev + 1);
-    SC_HIP(hipGetLastError());
-  }
-
-  if (slab_geometry_ok(d, g)) {
-    hipLaunchKernelGGL(slab_span_kernel, dim3((unsigned)((g.m + 127) / 128 + 255) / 256), dim3(256), 0, stream, rows, kept_dev,
-                       g.ho * g.wo, g.wo, d.h + 2 * d.pad_h, d.kh, kept_dev + 2);
-    SC_HIP(hipGetLastError());
-  }
-
   int32_t host_vals[4] = {-1, 0, 0, 0};   // kept count, most kept rows in one band, widest slab of a 128-row / 256-row tile
-  SC_HIP(hipMemcpyAsync(host_vals, kept_dev, 4 * sizeof(int32_t), hipMemcpyDeviceToHost, stream));
-  SC_HIP(hipStreamSynchronize(stream));
+  const bool slab = slab_geometry_ok(d, g);
+  // One launch up to 2^17 rows (where a run of rows cut in two leaves both halves a pixel); beyond that every workgroup's count of the rows in front of it costs more than a pass of its own.  Measured per refresh on a
+  // 56 x 56 map of one image, us of GPU time: 13 in five launches and a copy, 5 in one.
+  if (g.m <= kTableMostRows && !(bp.ok && bp.split && g.wo == 1)) {
+    TableParams p;
+    std::memset(&p, 0, sizeof(p));
+    const int wgs = (int)((g.m + kTableRows - 1) / kTableRows);
+    p.mask = mask_dev;
+    p.copy = ws + g.off_mask;
+    p.row_idx = rows;
+    p.kept_out = kept_dev;
+    p.band_i0 = reinterpret_cast<int32_t*>(ws + g.off_band);
+    p.band_rows = reinterpret_cast<int32_t*>(ws + g.off_band_rows);
+    p.m = (int32_t)g.m; p.period = period; p.mask_len = (int32_t)g.mask_len;
+    p.ho = g.ho; p.wo = g.wo; p.bh = 1;
+    if (bp.ok) { p.n_bands = bp.n_bands; p.bands_per_image = bp.bands_per_image; p.bh = bp.bh; p.split = bp.split; }
+    if (slab && wgs == 1) { p.slab_hp = d.h + 2 * d.pad_h; p.slab_kh = d.kh; }
+    magic_div((uint32_t)(g.ho * g.wo), &p.howo_mul, &p.howo_shift);
+    magic_div((uint32_t)g.wo, &p.wo_mul, &p.wo_shift);
+    magic_div((uint32_t)p.bh, &p.bh_mul, &p.bh_shift);
+    int32_t* slot = g_host_slots.take();
+    p.result = slot ? slot : counts;
+    const int span_wgs = (int)((g.m + 128 * 256 - 1) / (128 * 256));
+    int32_t copied[kHostSlotWords];
+    const sc_status s = [&]() -> sc_status {
+      hipLaunchKernelGGL(row_tables_kernel, dim3(wgs), dim3(kTableThreads), 0, stream, p);
+      SC_HIP(hipGetLastError());
+      if (g.depthwise)
+        SC_HIP(depthwise_rank(rows, kept_dev, reinterpret_cast<int32_t*>(ws + g.off_band_rows), g.m, stream));
+      if (slab && wgs > 1) {
+        hipLaunchKernelGGL(slab_span_kernel, dim3(span_wgs), dim3(256), 0, stream, rows, kept_dev, g.ho * g.wo, g.wo, d.h + 2 * d.pad_h,
+                           d.kh, p.result + 4 * wgs, 1);
+        SC_HIP(hipGetLastError());
+      }
+      if (!slot) SC_HIP(hipMemcpyAsync(copied, counts, sizeof(int32_t) * (4 * wgs + 2 * span_wgs), hipMemcpyDeviceToHost, stream));
+      SC_HIP(hipStreamSynchronize(stream));
+      return SC_OK;
+    }();
+    if (s != SC_OK) {
+      // (a launch may still be on its way to the slot: it stays taken)
+      return s;
+    }
+    const int32_t* res = slot ? slot : copied;
+    int kept = 0, fullest = 0;
+    for (int i = 0; i < wgs; ++i) {
+      kept += res[4 * i];
+      fullest = std::max(fullest, (int)res[4 * i + 1]);
+      if (wgs == 1) { host_vals[2] = res[2]; host_vals[3] = res[3]; }
+    }
+    if (slab && wgs > 1)
+      for (int i = 0; i < span_wgs; ++i)
+        for (int b = 0; b < 2; ++b) host_vals[2 + b] = std::max(host_vals[2 + b], (int)res[4 * wgs + 2 * i + b]);
+    if (slot) g_host_slots.give_back(slot);
+    host_vals[0] = kept;
+    host_vals[1] = fullest;
+  } else {
+    const int cgrid = (g.nseg + 3) / 4;
+    // pass 1 also leaves the plan's private copy of the mask (the zero fill of every run reads it)
+    hipLaunchKernelGGL(mask_count_kernel, dim3(cgrid), dim3(256), 0, stream, mask_dev, (int)g.m, period,
+                       g.nseg, counts, ws + g.off_mask, (int)g.mask_len);
+    SC_HIP(hipGetLastError());
+    hipLaunchKernelGGL(mask_scatter_kernel, dim3(cgrid), dim3(256), 0, stream, ws + g.off_mask, (int)g.m, period,
+                       g.nseg, counts, rows, kept_dev);
+    SC_HIP(hipGetLastError());
+    if (g.depthwise)   // position of every kept row in the row list (compact output of the LDS-tiled kernels)
+      SC_HIP(depthwise_rank(rows, kept_dev, reinterpret_cast<int32_t*>(ws + g.off_band_rows), g.m, stream));
+
+    if (bp.ok) {
+      hipLaunchKernelGGL(band_start_kernel, dim3((bp.n_bands + 1 + 255) / 256), dim3(256), 0, stream, rows, kept_dev,
+                         reinterpret_cast<int32_t*>(ws + g.off_band), bp.n_bands, bp.bands_per_image, bp.bh, bp.split, g.ho, g.wo);
+      SC_HIP(hipGetLastError());
+      // kept_dev + 1 holds the per-band maximum (zeroed by the scatter pass, raised by band_rows_kernel)
+      hipLaunchKernelGGL(band_rows_kernel, dim3((unsigned)((g.m + 255) / 256)), dim3(256), 0, stream, rows, kept_dev,
+                         reinterpret_cast<const int32_t*>(ws + g.off_band),
+                         reinterpret_cast<int32_t*>(ws + g.off_band_rows), bp.bands_per_image, bp.bh, bp.split, g.ho, g.wo,
+                         kept_dev + 1);
+      SC_HIP(hipGetLastError());
+    }
+
+    if (slab) {
+      hipLaunchKernelGGL(slab_span_kernel, dim3((unsigned)((g.m + 127) / 128 + 255) / 256), dim3(256), 0, stream, rows, kept_dev,
+                         g.ho * g.wo, g.wo, d.h + 2 * d.pad_h, d.kh, kept_dev + 2, 0);
+      SC_HIP(hipGetLastError());
+    }
+
+    SC_HIP(hipMemcpyAsync(host_vals, kept_dev, 4 * sizeof(int32_t), hipMemcpyDeviceToHost, stream));
+    SC_HIP(hipStreamSynchronize(stream));
+  }
   *kept_out = host_vals[0];
   bp.max_kept = host_vals[1];
   slab_span_out[0] = host_vals[2];
