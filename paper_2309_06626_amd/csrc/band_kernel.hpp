@@ -42,6 +42,7 @@ struct BandParams {
   // residual in the dense layout of y; a dropped row receives post(residual)
   const void* residual;
   int32_t residual_relu;
+  int32_t share_k;           // float, bands of at most 32 pixels: the wavefronts divide the window's taps
   uint32_t div_wo_mul, div_wo_shift;   // n / wo as (n * mul) >> shift (tap-pipelined kernel)
 #ifdef SC_TIMING
   long long* dbg;            // development builds only: per-workgroup phase time stamps
@@ -125,6 +126,7 @@ __global__ __launch_bounds__(kThreads) void band_kernel(const BandParams p) {
   // kept rows of the band: count from the band table, row numbers from the band-ordered list (its
   // address depends only on the band, not on the count); 64*MI rows per block, blocks dealt to the
   // wavefronts round robin; the first RB blocks of a wavefront are fetched here.
+  constexpr bool SHARE = DT == kF32 && MI == 1;
   constexpr int RB = kBandMaxRows / (4 * 32 * MI);   // blocks per wavefront that cover the tallest band
   int cnt = r_hi - r_lo;
   if (p.row_idx) cnt = p.band_i0[band + 1] - p.band_i0[band];
@@ -133,7 +135,7 @@ __global__ __launch_bounds__(kThreads) void band_kernel(const BandParams p) {
   for (int b = 0; b < RB; ++b)
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi) {
-      const int j = ((b * 4 + wave) * MI + mi) * 32 + fp;     // position in the band's list (< band rows)
+      const int j = ((b * 4 + (SHARE && p.share_k ? 0 : wave)) * MI + mi) * 32 + fp;     // position in the band's list (< band rows)
       const int jc = min(j, r_hi - r_lo - 1);
       r_pre[b][mi] = p.row_idx ? p.band_rows[r_lo + jc] : r_lo + jc;
     }
@@ -211,6 +213,77 @@ __global__ __launch_bounds__(kThreads) void band_kernel(const BandParams p) {
   if (p.zero_fill) zero_fill();
 
   const int zq = p.x_groups;          // a zeroed 16-byte group behind the input slab
+  if constexpr (SHARE) {
+    // A band of one 32-row block: one wavefront's chain of float MFMAs (64 clocks each, four per 32 bytes of K) is what the
+    // launch waits for, and the other three idle.  The taps of the window are dealt to all four, whose sums meet in LDS in
+    // wavefront order.  (The smallest layer, 16 -> 16 @16, one image, s = 0.5: a pass 6.6 us with one wavefront's chain, 5.5 with four.)
+    if (p.share_k) {
+      if (cnt == 0) return;
+      int rr = -1, ly0 = 0, lx0 = -(1 << 28);
+      if (fp < cnt) {
+        rr = r_pre[0][0];
+        const int rem = rr - img * ho_wo, oy = rem / p.wo, ox = rem - oy * p.wo;
+        ly0 = oy * p.sh - p.ph - iy_base;
+        lx0 = ox * p.sw - p.pw;
+      }
+      floatx16 acc[NI];
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[ni][v] = 0.0f;
+      auto tap_products = [&](int tap) {
+        const int ky = tap / kw, kx = tap - ky * kw;
+        const int ly = ly0 + ky * p.dil_h, ix = lx0 + kx * p.dil_w;
+        const bool ok = (unsigned)(iy_base + ly) < (unsigned)p.h && (unsigned)ix < (unsigned)p.w;
+        auto pair = [&](int c) {
+          const v4i xf = s_x[ok ? swz((ly * p.w + ix) * cpp + c + fh) : (int)p.x_groups];
+#pragma unroll
+          for (int ni = 0; ni < NI; ++ni) E::mma(acc[ni], s_b[swz((ni * 32 + fp) * kgr + tap * cpp + c + fh)], xf);
+        };
+        if constexpr (CPP > 0) {
+#pragma unroll
+          for (int c = 0; c < CPP; c += 2) pair(c);
+        } else {
+          for (int c = 0; c < cpp; c += 2) pair(c);
+        }
+      };
+      if constexpr (KH > 0) {
+#pragma unroll
+        for (int i = 0; i < (KH * KW + 3) / 4; ++i)
+          if (wave + 4 * i < KH * KW) tap_products(wave + 4 * i);
+      } else {
+        for (int tap = wave; tap < kh * kw; tap += 4) tap_products(tap);
+      }
+      __syncthreads();                       // everybody has read the slabs: their place takes the sums
+      v4f* part = reinterpret_cast<v4f*>(smem) + lane;
+      if (wave > 0) {
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            part[((wave - 1) * NI * 4 + ni * 4 + q) * 64] = v4f{acc[ni][4 * q], acc[ni][4 * q + 1], acc[ni][4 * q + 2], acc[ni][4 * q + 3]};
+      }
+      __syncthreads();
+      if (wave > 0 || rr < 0) return;
+#pragma unroll
+      for (int w = 0; w < 3; ++w)
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const v4f v = part[(w * NI * 4 + ni * 4 + q) * 64];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[ni][4 * q + e] += v[e];
+          }
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni) {
+        const int c0 = n0 + ni * 32 + 16 * fh;
+        if (c0 < p.c_out)
+          store_kept_block<DT>(acc[ni], rr, c0, y, p.bias ? s_bias + (c0 - n0) : nullptr, 0, p.relu, 1, p.c_out, ho_wo, 0, 0, 0);
+      }
+      return;
+    }
+  }
   const int nblk = (cnt + 32 * MI - 1) / (32 * MI);
 #pragma unroll
   for (int bi = 0; bi < RB; ++bi) {

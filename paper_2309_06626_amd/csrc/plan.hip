@@ -1543,6 +1543,12 @@ static sc_status launch_conv(const sc_plan* pl, bool dense, const void* x, const
       SC_HIP(table[d.c_in / g.vec == 8 ? 0 : 1][b.ni - 1][mi_idx](q, b.lds, b.pp_grid, stream));
       return SC_OK;
     }
+    // (one line for the sparse and the dense run: both add a row's products in the same order)
+    if (d.dtype == SC_F32 && (int64_t)std::max(pl->band.bh, pl->band_dense.bh) * g.wo <= 32 &&
+        std::min(pl->band.b_bytes, pl->band_dense.b_bytes) >= (size_t)3 * 4096 * b.ni) {
+      q.share_k = 1;
+      mi_idx = 0;
+    }
     const int cpp = d.c_in / g.vec;
     const int shape = (d.kh == 3 && d.kw == 3 && cpp == 8) ? 1 : (d.kh == 3 && d.kw == 3 && cpp == 4) ? 2 : 0;
     SC_HIP(pl->band_table->fn[shape][b.ni_idx][mi_idx](q, b.lds, stream));

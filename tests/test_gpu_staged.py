@@ -170,3 +170,17 @@ def test_refreshed_filters_equal_those_of_a_new_plan(cin, cout, k, dtype):
         got.append([R.bits_of(t) for t in (y, y2, dx)])
     for p, q in zip(*got):
         assert np.array_equal(p, q)
+
+
+@pytest.mark.parametrize("case", [
+    dict(n=1, cin=16, h=16, w=16, cout=16),                          # unrolled window, one filter block
+    dict(n=3, cin=32, h=5, w=32, cout=48, sp=0.3),                   # a full 32-row block, two filter blocks
+    dict(n=2, cin=8, h=9, w=7, cout=80, k=3, s=2, p=1, sp=0.6),      # run-time window, four filter blocks
+    dict(n=1, cin=16, h=8, w=11, cout=16, k=3, p=2, d=2, sp=0.95),   # bands without a kept row
+])
+@pytest.mark.parametrize("mask_mode", ["row", "spatial"])
+def test_small_float_bands_share_the_window(case, mask_mode):
+    spec = spec_of(dtype="f32", mask_mode=mask_mode, **case)
+    for out_mode in (B.SC_OUT_ZERO_FILL, B.SC_OUT_SCATTER_ONLY):
+        layer = check_layer(W.make_conv_inputs(spec, 1640), tiles=(-1, 0), out_mode=out_mode)
+        assert B.sparse_conv_plan_kernel(layer.plan, 0) == "band"
