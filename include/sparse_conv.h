@@ -252,7 +252,9 @@ sc_status sparse_conv_plan_tune(sc_plan* plan, const void* x_dev, const float* b
  *                                                tile of the kernel reported as "tile_staged" (float layers, channel
  *                                                counts off the 16-byte group, SC_NCHW) and how many groups of
  *                                                wavefronts share its K tiles (float NHWC); 0x0 = other kernels;
- *                                                automatic otherwise */
+ *                                                automatic otherwise
+ *   SPARSE_CONV_TILE_GROUPS=<rows>x<couts>x<1|2> tile of the automatic tiled launch of 16-bit layers and how many
+ *                                                groups of wavefronts share its K tiles; automatic otherwise */
 
 /* Tuning hook: SC_OPT_GATHER_PIPELINE selects how the tiled gather kernel moves its K tiles:
  * 0 = automatic, 1 = global -> registers -> LDS, 2 = global -> LDS directly (NHWC with 16-byte

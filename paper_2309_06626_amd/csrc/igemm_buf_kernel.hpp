@@ -46,8 +46,13 @@ __device__ __forceinline__ v4i load16_device_scope(const void* src) {
 // are shared in its L2), each contracts its share of the K tiles and leaves float partial sums; the one that
 // arrives last at the tile's counter adds them in split order (the result does not depend on who was last) and
 // runs the epilogue.  Nobody waits for anybody.
-template <int DT, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, bool SPLITK = false>
-__global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void igemm_buf_kernel(const ConvParams p) {
+//
+// KG > 1: the K tiles are divided among KG groups of wavefronts inside the workgroup, each with a ring of its own; the first
+// group adds the others' sums out of LDS, in order.  For long K walks of few workgroups: a compute unit with one workgroup
+// of four wavefronts takes operands in at little more than half the rate it reaches with twice the wavefronts (see the
+// quantities of the cost model), and unlike SPLITK nothing crosses the memory system.
+template <int DT, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, bool SPLITK = false, int KG = 1>
+__global__ __launch_bounds__(WAVES_M * WAVES_N * 64 * KG) void igemm_buf_kernel(const ConvParams p) {
   using E = Elem<DT>;
   using T = typename E::T;
   constexpr int V = E::V;
@@ -55,7 +60,8 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void igemm_buf_kernel(const
   constexpr int BK = 8 * V;
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
   constexpr int MI = WM / 32, NI = WN / 32;
-  constexpr int NT = WAVES_M * WAVES_N * 64;   // threads: four wavefronts, or eight (two per SIMD) for the largest tile
+  constexpr int NT = WAVES_M * WAVES_N * 64;   // threads of a group: four wavefronts, or eight (two per SIMD) for the largest tile
+  constexpr int NTALL = NT * KG;
   constexpr int RPR = NT / 8;                  // tile rows one transfer of the whole workgroup covers
   constexpr int A_LOADS = BM / RPR, B_LOADS = BN / RPR;
   constexpr int LPT = A_LOADS + B_LOADS;
@@ -65,8 +71,9 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void igemm_buf_kernel(const
   static_assert(STAGES >= 2 && (STAGES - 2) * LPT <= 63, "vmcnt is a 6-bit counter");
   static_assert(EB == 2, "16-bit operands");
 
-  extern __shared__ __align__(16) unsigned char smem[];
-  int32_t* s_rows = reinterpret_cast<int32_t*>(smem + STAGES * STAGE_BYTES);   // [BM], then one spare group
+  static_assert(!SPLITK || KG == 1, "one way of dividing K at a time");
+  extern __shared__ __align__(16) unsigned char smem_all[];
+  int32_t* s_rows = reinterpret_cast<int32_t*>(smem_all + KG * STAGES * STAGE_BYTES);   // [BM], then one spare group
   float* s_bias = reinterpret_cast<float*>(s_rows + BM + 4);                   // [BN]
 
   const int splits = SPLITK ? p.splits : 1;
@@ -79,12 +86,15 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void igemm_buf_kernel(const
   const int tile_m = tile / p.n_tiles;
   const int tile_n = tile - tile_m * p.n_tiles;
   const int m0 = tile_m * BM, n0 = tile_n * BN;
-  const int kt_lo = SPLITK ? (int)((int64_t)split * p.k_tiles / splits) : 0;
-  const int kt_hi = SPLITK ? (int)((int64_t)(split + 1) * p.k_tiles / splits) : p.k_tiles;
-  const int n_kt = kt_hi - kt_lo;
-
   const int t = threadIdx.x;
-  const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int group = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane(t / NT);
+  unsigned char* smem = smem_all + group * (STAGES * STAGE_BYTES);
+  const int kt_lo = SPLITK ? (int)((int64_t)split * p.k_tiles / splits) : KG > 1 ? group * p.k_tiles / KG : 0;
+  const int kt_hi = SPLITK ? (int)((int64_t)(split + 1) * p.k_tiles / splits) : KG > 1 ? (group + 1) * p.k_tiles / KG : p.k_tiles;
+  const int n_kt = kt_hi - kt_lo;
+  const int n_steps = KG > 1 ? (p.k_tiles + KG - 1) / KG : n_kt;     // of the longest share: every wavefront passes every barrier
+
+  const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6) - group * (NT / 64);      // within the group
   const int wm0 = (wave / WAVES_N) * WM, wn0 = (wave % WAVES_N) * WN;
   const int fp = lane & 31, fh = lane >> 5;
   T* __restrict__ y = static_cast<T*>(p.y);
@@ -143,7 +153,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void igemm_buf_kernel(const
   const uint32_t b_voff = (uint32_t)((lrow * p.k_pad + lc * V) * EB);
 
   constexpr int CPR = BN * EB / 16;        // 16-byte groups per output row slice
-  constexpr int RPI = NT / CPR;           // dense rows per fill pass of the workgroup
+  constexpr int RPI = NTALL / CPR;        // dense rows per fill pass of the workgroup
   constexpr int ZB = 4;                    // passes whose mask bytes are fetched up front
   const int zc = t % CPR, zr = t / CPR;
   unsigned mk[ZB];
@@ -289,6 +299,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void igemm_buf_kernel(const
     else wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();   // landed for every wavefront; and all have left tile kt-1
     asm volatile("" ::: "memory");
+    if (KG > 1 && kt >= n_kt) return;      // (a shorter share: the barrier only)
     const bool more = issued < n_kt;
     if constexpr (!INTERLEAVE) {
       if (more) issue_tile(Refill{});
@@ -317,11 +328,43 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void igemm_buf_kernel(const
   if constexpr (STAGES >= 3) if (1 < n_kt) { issue_tile(std::integral_constant<int, 1>{}); ++issued; }
   if constexpr (STAGES >= 4) if (2 < n_kt) { issue_tile(std::integral_constant<int, 2>{}); ++issued; }
   static_assert(STAGES <= 4, "ring of at most four tiles");
-  for (int kt = 0; kt < n_kt; kt += STAGES) {
+  for (int kt = 0; kt < n_steps; kt += STAGES) {
     k_tile(std::integral_constant<int, 0>{}, kt);
-    if (kt + 1 < n_kt) k_tile(std::integral_constant<int, 1 % STAGES>{}, kt + 1);
-    if constexpr (STAGES >= 3) if (kt + 2 < n_kt) k_tile(std::integral_constant<int, 2 % STAGES>{}, kt + 2);
-    if constexpr (STAGES >= 4) if (kt + 3 < n_kt) k_tile(std::integral_constant<int, 3 % STAGES>{}, kt + 3);
+    if (kt + 1 < n_steps) k_tile(std::integral_constant<int, 1 % STAGES>{}, kt + 1);
+    if constexpr (STAGES >= 3) if (kt + 2 < n_steps) k_tile(std::integral_constant<int, 2 % STAGES>{}, kt + 2);
+    if constexpr (STAGES >= 4) if (kt + 3 < n_steps) k_tile(std::integral_constant<int, 3 % STAGES>{}, kt + 3);
+  }
+
+  if constexpr (KG > 1) {
+    __syncthreads();                                   // every wavefront has left the rings
+    v4f* part = reinterpret_cast<v4f*>(smem_all) + (wave * (MI * NI * 4)) * 64 + lane;
+    constexpr int SLOT = (NT / 64) * MI * NI * 4 * 64;
+    static_assert((KG - 1) * SLOT * 16 <= KG * STAGES * STAGE_BYTES, "the sums lie where the rings were");
+    if (group > 0) {
+#pragma unroll
+      for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            part[(group - 1) * SLOT + ((mi * NI + ni) * 4 + q) * 64] =
+                v4f{acc[mi][ni][4 * q], acc[mi][ni][4 * q + 1], acc[mi][ni][4 * q + 2], acc[mi][ni][4 * q + 3]};
+    }
+    __syncthreads();
+    if (group == 0) {
+#pragma unroll
+      for (int g = 0; g < KG - 1; ++g)
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+          for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const v4f v = part[g * SLOT + ((mi * NI + ni) * 4 + q) * 64];
+#pragma unroll
+              for (int e = 0; e < 4; ++e) acc[mi][ni][4 * q + e] += v[e];
+            }
+    }
   }
 
   // ---- split K: leave the partial sums; the last workgroup of the tile adds them up ----------------------
@@ -436,6 +479,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void igemm_buf_kernel(const
   }
 
   // ---- epilogue ----------------------------------------------------------------------------------------
+  if (KG > 1 && group > 0) return;
 #pragma unroll
   for (int mi = 0; mi < MI; ++mi) {
     const int rr = s_rows[wm0 + mi * 32 + fp];
@@ -451,10 +495,10 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void igemm_buf_kernel(const
   }
 }
 
-template <int DT, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, bool SPLITK = false>
+template <int DT, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, bool SPLITK = false, int KG = 1>
 hipError_t igemm_buf_launch(const ConvParams& p, hipStream_t stream) {
-  constexpr size_t lds = igemm_dma_lds_bytes<BM, BN, STAGES>();
-  auto kern = igemm_buf_kernel<DT, BM, BN, WAVES_M, WAVES_N, STAGES, SPLITK>;
+  constexpr size_t lds = igemm_dma_lds_bytes<BM, BN, STAGES * KG>();
+  auto kern = igemm_buf_kernel<DT, BM, BN, WAVES_M, WAVES_N, STAGES, SPLITK, KG>;
   static std::atomic<bool> attr_set{false};
   if (lds > 64 * 1024 && !attr_set) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -464,7 +508,7 @@ hipError_t igemm_buf_launch(const ConvParams& p, hipStream_t stream) {
   }
   const int nwg = p.m_tiles * p.n_tiles * (SPLITK ? p.splits : 1);
   const int grid = ((nwg + 7) / 8) * 8;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(WAVES_M * WAVES_N * 64), lds, stream, p);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(WAVES_M * WAVES_N * 64 * KG), lds, stream, p);
   return hipGetLastError();
 }
 
@@ -472,5 +516,7 @@ hipError_t igemm_buf_launch(const ConvParams& p, hipStream_t stream) {
 LaunchFn buf_kernel(int dtype, int bm, int bn, bool shallow);
 // its split-K form, or null
 LaunchFn buf_splitk_kernel(int dtype, int bm, int bn);
+// its form with two groups of wavefronts that share K, or null
+LaunchFn buf_groups_kernel(int dtype, int bm, int bn);
 
 }  // namespace sc

@@ -1055,7 +1055,7 @@ struct sc_plan {
   int64_t kept;
   const KernelEntry* table;
   int table_count;
-  struct Pick { int ti, splits; bool masked; };
+  struct Pick { int ti, splits; bool masked; int groups = 1; bool asked = false; };      // (groups of wavefronts that share K inside a workgroup; asked for by the environment)
   Pick pick[2];                    // tiled launch of the sparse / dense run when nothing is forced: tile, K splits, and
                                    // (sparse run) whether every row is contracted and the mask decides at the store
   bool prefer_tiled[2];            // measured by sparse_conv_plan_tune: the tiled launch beat the band / row-panel kernel
@@ -1096,7 +1096,9 @@ namespace sc {
 //                 stores and loads: across the fabric between the dies' L2 caches)
 // The model is good to about 15 %; sparse_conv_plan_tune replaces its choice by a measured one.
 constexpr double kLaunchUs = 3.0, kWgFixedUs = 1.0, kRowListUs = 0.6, kMfmaShare = 0.85, kExchangeKBus = 4000.0;
-constexpr double kIngestKBus[3] = {62.0, 110.0, 120.0};
+//   kGroupUs      what two groups of wavefronts that share K add to a workgroup: their sums through LDS; such a workgroup
+//                 alone on a compute unit takes in kIngestGroupsKBus
+constexpr double kIngestKBus[3] = {62.0, 110.0, 120.0}, kGroupUs = 0.2, kIngestGroupsKBus = 85.0;
 constexpr double kIngestEightWavesKBus = 76.0;      // one resident workgroup of eight wavefronts
 constexpr double kClockPerUs = 2100.0;
 
@@ -1112,7 +1114,7 @@ static size_t tile_lds_bytes(const sc_plan* pl, const KernelEntry& ke) {
 
 // predicted microseconds of one tiled launch: `rows` rows through tile ke with K cut into `splits`;
 // `listed`: rows come through the kept-row list and dropped rows are zero-filled by their owners
-static double predict_us(const sc_plan* pl, const KernelEntry& ke, int64_t rows, int splits, bool listed) {
+static double predict_us(const sc_plan* pl, const KernelEntry& ke, int64_t rows, int splits, bool listed, int groups = 1) {
   const Geometry& g = pl->geo;
   const sc_conv_desc& d = pl->desc;
   const int cus = device_cus();
@@ -1126,10 +1128,11 @@ static double predict_us(const sc_plan* pl, const KernelEntry& ke, int64_t rows,
   const bool eight_waves = ke.bm * ke.bn >= 128 * 128 && g.vec_gather && g.vec_out && d.dtype != SC_F32 && d.c_in % 64 == 0;
   int occ = (int)std::min<size_t>(kLdsLimit / std::max<size_t>(tile_lds_bytes(pl, ke), 1), eight_waves ? 2 : 4);
   occ = std::max(occ, 1);
+  if (groups > 1) occ = std::max<int>(1, (int)std::min<size_t>(kLdsLimit / (tile_lds_bytes(pl, ke) * groups), 2));
   const int c = (int)std::max<int64_t>(1, std::min<int64_t>(occ, (wgs + cus - 1) / cus));   // resident per compute unit
   const double rounds = std::ceil((double)wgs / ((double)cus * c));
-  const double ingest = c == 1 && eight_waves ? kIngestEightWavesKBus : kIngestKBus[std::min(c, 3) - 1];
-  const double round_us = kWgFixedUs + (listed ? kRowListUs : 0.0) + std::max(c * kb_wg / ingest, c * mfma_us);
+  const double ingest = c == 1 && groups > 1 ? kIngestGroupsKBus : c == 1 && eight_waves ? kIngestEightWavesKBus : kIngestKBus[std::min(c * groups, 3) - 1];
+  const double round_us = kWgFixedUs + (groups > 1 ? kGroupUs : 0.0) + (listed ? kRowListUs : 0.0) + std::max(c * kb_wg / ingest, c * mfma_us);
   double t = kLaunchUs + rounds * round_us;
   if (splits > 1)   // every split writes its tile of floats, the last arrival reads them all
     t += 2.0 * (double)tiles * splits * ke.bm * ke.bn * 4.0 / 1024.0 / kExchangeKBus;
@@ -1138,6 +1141,7 @@ static double predict_us(const sc_plan* pl, const KernelEntry& ke, int64_t rows,
 
 static int most_splits(const sc_plan* pl, const KernelEntry& ke, int64_t rows);
 static LaunchFn splitk_launcher(const sc_plan* pl, const KernelEntry& ke);
+static int group_candidates(const sc_plan* pl, const KernelEntry& ke, int64_t rows);
 static bool buf_applies(const sc_plan* pl, const KernelEntry& ke);
 
 // K splits the automatic choice considers for a tile: up to four, and only the buffer-load form of the split kernel
@@ -1146,6 +1150,16 @@ static int split_candidates(const sc_plan* pl, const KernelEntry& ke, int64_t ro
   if (pl->split_k == 1 || !buf_applies(pl, ke) || pl->geo.k_tiles <= 2) return 1;
   if (!buf_splitk_kernel(pl->desc.dtype == SC_BF16 ? kBF16 : kF16, ke.bm, ke.bn)) return 1;
   return std::min(4, most_splits(pl, ke, rows));
+}
+
+// groups of wavefronts the automatic choice considers for a tile: two, where the buffer-load kernel has that form and the
+// workgroups cover half to all of the compute units (fewer leave the filters, cold behind other layers, to too few of them:
+// a ResNet18 stack at batch 8 and 160 x 160 208 -> 212 us; more wait for a second round)
+static int group_candidates(const sc_plan* pl, const KernelEntry& ke, int64_t rows) {
+  const int64_t wgs = ((rows + ke.bm - 1) / ke.bm) * ((pl->desc.c_out + ke.bn - 1) / ke.bn);
+  if (wgs * 2 < device_cus() || wgs > device_cus()) return 1;
+  if (pl->split_k != 0 || pl->stream_k >= 2 || pl->geo.k_tiles < 8 || !buf_applies(pl, ke)) return 1;
+  return buf_groups_kernel(pl->desc.dtype == SC_BF16 ? kBF16 : kF16, ke.bm, ke.bn) ? 2 : 1;
 }
 
 // the cheapest tiled launch by the model.  Layers the fast gathers do not serve keep their one measured shape.
@@ -1160,6 +1174,12 @@ static sc_plan::Pick model_pick(const sc_plan* pl, int which, int64_t rows) {
   };
   if (g.rowseg) { best.ti = d.c_out <= 32 ? find(128, 32) : find(64, 64); return best; }   // window-row gather (stems)
   if (!g.vec_gather) { best.ti = find(128, 64); return best; }                              // element gather
+  // SPARSE_CONV_TILE_GROUPS=<bm>x<bn>x<1|2>: that tile with so many groups of wavefronts sharing K (tuning and tests)
+  int fbm = 0, fbn = 0, fgr = 0;
+  if (const char* env = std::getenv("SPARSE_CONV_TILE_GROUPS"); env && std::sscanf(env, "%dx%dx%d", &fbm, &fbn, &fgr) == 3) {
+    const int i = find(fbm, fbn);
+    if (pl->table[i].bm == fbm && pl->table[i].bn == fbn && (fgr == 1 || (fgr == 2 && buf_applies(pl, pl->table[i]) && buf_groups_kernel(d.dtype == SC_BF16 ? kBF16 : kF16, fbm, fbn)))) { best = {i, 1, false, fgr}; best.asked = fgr > 1; return best; }
+  }
   double best_us = 1e300;
   const bool can_mask = which == 0 && rows < g.m && rows > 0;
   for (int i = 0; i < pl->table_count; ++i) {
@@ -1170,6 +1190,10 @@ static sc_plan::Pick model_pick(const sc_plan* pl, int which, int64_t rows) {
     for (int sp = 1; sp <= most; ++sp) {
       const double t = predict_us(pl, ke, rows, sp, which == 0 && rows < g.m);
       if (t < best_us) { best_us = t; best = {i, sp, false}; }
+    }
+    if (group_candidates(pl, ke, rows) > 1) {
+      const double t = predict_us(pl, ke, rows, 1, which == 0 && rows < g.m, 2);
+      if (t < best_us) { best_us = t; best = {i, 1, false, 2}; }
     }
     if (can_mask && pl->masked_store != 1) {       // every row contracted, the mask decides at the store: the dense launch plus a mask byte per row
       const double t = predict_us(pl, ke, g.m, 1, false) + 0.1;
@@ -1182,7 +1206,7 @@ static sc_plan::Pick model_pick(const sc_plan* pl, int which, int64_t rows) {
 // Split K?  Layers deep in a network have few rows and a long K: large output tiles cannot fill
 // 256 CUs, and with small tiles every workgroup walks the whole K, one L2 round trip after the other.
 // Dividing K among workgroups shortens that walk and still gives every CU work.
-struct TilePick { int ti, splits; bool masked; };
+struct TilePick { int ti, splits; bool masked; int groups = 1; };
 
 // Row-panel kernel: short K (pointwise layers), several 64-channel tiles, enough rows to fill the
 // CUs with 128-row panels.  There the tiled kernels are bound by the instructions every
@@ -1379,6 +1403,7 @@ static TilePick pick_tile(const sc_plan* pl, int which, int64_t rows) {
   tp.ti = pl->pick[which].ti;
   tp.splits = pl->split_k == 1 ? 1 : std::min(pl->pick[which].splits, most_splits(pl, pl->table[tp.ti], rows));
   tp.masked = pl->masked_store == 2 ? which == 0 : pl->masked_store == 1 ? false : pl->pick[which].masked;
+  if (pl->pick[which].groups > 1 && !tp.masked) tp.groups = pl->pick[which].asked ? 2 : group_candidates(pl, pl->table[tp.ti], rows);
   if (pl->split_k >= 2 && pl->tile_splitk >= 0) {      // on request: that many splits of the 64 x 128 tile
     const int want = std::min(pl->split_k, most_splits(pl, pl->table[pl->tile_splitk], rows));
     if (want >= 2) { tp.ti = pl->tile_splitk; tp.splits = want; tp.masked = false; }
@@ -1740,6 +1765,8 @@ static sc_status launch_conv(const sc_plan* pl, bool dense, const void* x, const
       fn = sk;
     }
   }
+  if (tp.groups > 1 && fn_is_buf && splits == 1 && !panel && !masked && !p.stream_wgs)
+    fn = buf_groups_kernel(d.dtype == SC_BF16 ? kBF16 : kF16, ke.bm, ke.bn);
   if (splits > 1) {
     p.splits = splits;
     p.partial = reinterpret_cast<float*>(pl->ws + g.off_partial);
@@ -2221,6 +2248,10 @@ sc_status sparse_conv_plan_tune(sc_plan* plan, const void* x_dev, const float* b
       const int most = split_candidates(plan, ke, rows);
       for (int sp = 1; sp <= most; ++sp) {
         cands[n] = {{i, sp, false}, predict_us(plan, ke, rows, sp, which == 0 && rows < plan->geo.m)};
+        best_pred = std::min(best_pred, cands[n++].predicted);
+      }
+      if (group_candidates(plan, ke, rows) > 1) {
+        cands[n] = {{i, 1, false, 2}, predict_us(plan, ke, rows, 1, which == 0 && rows < plan->geo.m, 2)};
         best_pred = std::min(best_pred, cands[n++].predicted);
       }
       if (can_mask && plan->masked_store != 1) {

@@ -184,3 +184,22 @@ def test_small_float_bands_share_the_window(case, mask_mode):
     for out_mode in (B.SC_OUT_ZERO_FILL, B.SC_OUT_SCATTER_ONLY):
         layer = check_layer(W.make_conv_inputs(spec, 1640), tiles=(-1, 0), out_mode=out_mode)
         assert B.sparse_conv_plan_kernel(layer.plan, 0) == "band"
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("case", [
+    dict(n=2, cin=64, h=15, w=13, cout=80, sp=0.4),                   # nine K tiles: shares of five and four
+    dict(n=1, cin=128, h=9, w=20, cout=64, k=3, s=2, sp=0.0),          # every row kept
+    dict(n=1, cin=64, h=7, w=7, cout=160, k=5, p=2, sp=0.9),           # five kept rows, ragged channel tile
+])
+def test_groups_of_wavefronts_share_k(case, dtype, monkeypatch):
+    """Two groups of wavefronts of the buffer-load kernel: against the oracle, compact rows and shortcut sums included."""
+    monkeypatch.setenv("SPARSE_CONV_TILE_GROUPS", "64x64x2")
+    monkeypatch.setenv("SPARSE_CONV_BAND_KERNEL", "single")
+    spec = spec_of(dtype=dtype, **case)
+    for out_mode in (B.SC_OUT_ZERO_FILL, B.SC_OUT_SCATTER_ONLY):
+        layer = check_layer(W.make_conv_inputs(spec, 1650), out_mode=out_mode)
+        assert B.sparse_conv_plan_tiles(layer.plan, 0)[:2] == (64, 64)
+    check_residual(spec.with_(relu=False), 1651, True, want_kernel=("tile_lds_direct",))
+    if spec.sparsity > 0:
+        check_compact_output(spec, 1652)
