@@ -4,7 +4,13 @@
 namespace sc {
 
 template <int DT, int GATHER, bool NCHW>
-static LaunchFn stage_tile(int bm, int bn) {
+static LaunchFn stage_tile(int bm, int bn, int groups) {
+  if (groups == 2) {
+    if (bm == 64 && bn == 128) return igemm_stage_launch<DT, 64, 128, 2, 2, GATHER, NCHW, 2>;
+    if (bm == 64 && bn == 64) return igemm_stage_launch<DT, 64, 64, 2, 2, GATHER, NCHW, 2>;
+    return nullptr;
+  }
+  if (groups != 1) return nullptr;
   if (bm == 128 && bn == 64) return igemm_stage_launch<DT, 128, 64, 2, 2, GATHER, NCHW>;
   if (bm == 128 && bn == 32) return igemm_stage_launch<DT, 128, 32, 4, 1, GATHER, NCHW>;
   if (bm == 64 && bn == 128) return igemm_stage_launch<DT, 64, 128, 2, 2, GATHER, NCHW>;
@@ -13,20 +19,21 @@ static LaunchFn stage_tile(int bm, int bn) {
 }
 
 template <int DT>
-static LaunchFn stage_gather(int gather, bool nchw, int bm, int bn) {
-  if (gather == kStageRaggedGroups) return stage_tile<DT, kStageRaggedGroups, false>(bm, bn);
-  if (gather == kStageChunks) return stage_tile<DT, kStageChunks, true>(bm, bn);
-  if (gather == kStageEntries) return nchw ? stage_tile<DT, kStageEntries, true>(bm, bn) : stage_tile<DT, kStageEntries, false>(bm, bn);
+static LaunchFn stage_gather(int gather, bool nchw, int bm, int bn, int groups) {
+  if (gather == kStageRaggedGroups) return stage_tile<DT, kStageRaggedGroups, false>(bm, bn, groups);
+  if (gather == kStageChunks) return stage_tile<DT, kStageChunks, true>(bm, bn, groups);
+  if (gather == kStageEntries)
+    return nchw ? stage_tile<DT, kStageEntries, true>(bm, bn, groups) : stage_tile<DT, kStageEntries, false>(bm, bn, groups);
   if constexpr (DT == kF32) {
-    if (gather == kStageGroups) return stage_tile<DT, kStageGroups, false>(bm, bn);
+    if (gather == kStageGroups) return stage_tile<DT, kStageGroups, false>(bm, bn, groups);
   }
   return nullptr;          // (16-byte groups of a 16-bit type go straight into LDS: other kernels)
 }
 
-LaunchFn stage_kernel(int dtype, int gather, bool nchw, int bm, int bn) {
-  if (dtype == kF32) return stage_gather<kF32>(gather, nchw, bm, bn);
-  if (dtype == kF16) return stage_gather<kF16>(gather, nchw, bm, bn);
-  return stage_gather<kBF16>(gather, nchw, bm, bn);
+LaunchFn stage_kernel(int dtype, int gather, bool nchw, int bm, int bn, int groups) {
+  if (dtype == kF32) return stage_gather<kF32>(gather, nchw, bm, bn, groups);
+  if (dtype == kF16) return stage_gather<kF16>(gather, nchw, bm, bn, groups);
+  return stage_gather<kBF16>(gather, nchw, bm, bn, groups);
 }
 
 // The K order of a gather: entry k of the tiles is channel `ci` of tap `tap`, or a filter entry that stays zero.

@@ -22,18 +22,29 @@
 // a multiple of the chunk number so that the sixteen lanes of a write phase hit sixteen different bank groups.  The
 // filters are packed in the same order at plan time, so their transfer is a plain copy.
 //
-// What bounds it: a K tile passes LDS twice (written by the threads that fetched it, read by the wavefronts), and one load per
-// entry keeps a channels-first tile at the rate of the address units.  Loads run two tiles ahead in registers; the table that
-// says where they go runs three ahead, because waiting for a load waits for all that were issued before it.  Measured at
-// s = 0.5 (element gather before / this kernel, us): 32 x 128 -> 128 @28 channels first in float 115 / 46, in bf16 84 / 27.5;
-// 64 x 102 -> 102 @28 in fp16 at s = 0.3 98 / 27.5, 51 -> 51 @56 110 / 44, 410 -> 410 @7 186 / 27.
+// What bounds it: the rows of a K tile pass LDS twice (written by the threads that fetched them, read by the wavefronts), one
+// load per entry keeps a channels-first tile at the rate of the address units, and the phases of a workgroup (addresses,
+// products, split and stores) are one after the other.  Row loads run two tiles ahead in registers; the table that says where
+// they go runs three ahead, because waiting for a load waits for all that were issued before it, and is read by scalar loads
+// where a wavefront shares its entries.  The filters need no registers: they go from memory to LDS as they lie, a tile ahead.
+// Measured at s = 0.5 (element gather / all through registers / this kernel, us): 32 x 128 -> 128 @28 channels first in float
+// 115 / 45 / 39, in bf16 84 / 27.5 / 23, 32 x 51 -> 64 @28 in bf16 - / 19.6 / 13.8; at s = 0.3 64 x 102 -> 102 @28 in fp16
+// 98 / 27.5 / 26.5, 51 -> 51 @56 110 / 44 / 40, 410 -> 410 @7 186 / 27 / 24.
 //
-// Workgroup = BM kept rows x BN channels, four wavefronts; zero-fill ownership and the order of the epilogue are those
-// of the other tiled kernels.
+// Workgroup = BM kept rows x BN channels, four wavefronts (or KG groups of four); zero-fill ownership and the order of the
+// epilogue are those of the other tiled kernels.
 #pragma once
 #include "igemm_buf_kernel.hpp"
 
 namespace sc {
+
+// fn(integral_constant 0), ..., fn(integral_constant N - 1)
+template <int N, typename F> __device__ __forceinline__ void static_for(F fn) {
+  if constexpr (N > 0) {
+    static_for<N - 1>(fn);
+    fn(std::integral_constant<int, N - 1>{});
+  }
+}
 
 // how window entries reach a tile
 enum StageGather { kStageGroups = 0,         // NHWC, Cin a multiple of the 16-byte group
@@ -52,8 +63,8 @@ template <int DT> struct StageDims {
   static constexpr int BLOCK_BYTES = PARTS * KSTEPS * 1024;   // 32 rows (or channels) x one K tile
   static constexpr int K_TILE = 8 * CHUNKS;
 };
-template <int DT, int BM, int BN> constexpr size_t stage_lds_bytes() {
-  return 2 * (size_t)((BM + BN) / 32) * StageDims<DT>::BLOCK_BYTES + (BM + BN) * 4;
+template <int DT, int BM, int BN> constexpr size_t stage_lds_bytes(int groups) {
+  return 2 * (size_t)((BM + BN) / 32) * StageDims<DT>::BLOCK_BYTES * groups + (BM + BN) * 4;
 }
 
 // (the two float halves of a packed pair of bf16, exactly)
@@ -127,8 +138,11 @@ __device__ __forceinline__ void stage_store_row(const float (&acc)[16], int rr, 
   }
 }
 
-template <int DT, int BM, int BN, int WAVES_M, int WAVES_N, int GATHER, bool NCHW>
-__global__ __launch_bounds__(kThreads, 2) void igemm_stage_kernel(const ConvParams p) {
+// KG > 1: the K tiles are divided among KG groups of four wavefronts, each with LDS tiles of its own; the first group adds the
+// others' sums in order and stores.  For launches of at most a workgroup per compute unit, whose four wavefronts leave it idle
+// between their phases (measured where the launcher chooses).
+template <int DT, int BM, int BN, int WAVES_M, int WAVES_N, int GATHER, bool NCHW, int KG = 1>
+__global__ __launch_bounds__(kThreads * KG, 2) void igemm_stage_kernel(const ConvParams p) {
   using D = StageDims<DT>;
   using E = Elem<DT>;
   using T = typename E::T;
@@ -142,13 +156,16 @@ __global__ __launch_bounds__(kThreads, 2) void igemm_stage_kernel(const ConvPara
   constexpr int PART_A = (BM / 32) * KSTEPS * 1024;             // one part of the A tile
   constexpr int B_UNITS = B_BYTES / 1024;                       // 1 KiB a wavefront copies at a time
   constexpr int B_LOADS = (B_UNITS + 3) / 4;
-  constexpr int AHEAD = PARTS * (MI + NI) <= 6 && MI * NI < 4 ? 2 : 1;      // (as the registers allow)
+  constexpr int AHEAD = PARTS * (MI + NI) <= 9 && MI * NI < 4 ? 2 : 1;      // (as the registers allow)
   static_assert(WAVES_M * WAVES_N == 4 && WM % 32 == 0 && WN % 32 == 0 && BM % 64 == 0, "four wavefronts of 32x32 blocks");
 
-  extern __shared__ __align__(16) unsigned char smem[];
+  constexpr int RING = 2 * (A_BYTES + B_BYTES);
+  extern __shared__ __align__(16) unsigned char smem_all[];
+  const int t_all = threadIdx.x, group = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane(t_all / kThreads);
+  unsigned char* smem = smem_all + group * RING;
   unsigned char* s_a = smem;                                    // [2][A_BYTES]
   unsigned char* s_b = smem + 2 * A_BYTES;                      // [2][B_BYTES]
-  int32_t* s_rows = reinterpret_cast<int32_t*>(smem + 2 * (A_BYTES + B_BYTES));   // [BM]
+  int32_t* s_rows = reinterpret_cast<int32_t*>(smem_all + KG * RING);             // [BM]
   float* s_bias = reinterpret_cast<float*>(s_rows + BM);        // [BN]
 
   const int nwg = p.m_tiles * p.n_tiles;
@@ -158,8 +175,10 @@ __global__ __launch_bounds__(kThreads, 2) void igemm_stage_kernel(const ConvPara
   const int tile_m = logical / p.n_tiles;
   const int tile_n = logical - tile_m * p.n_tiles;
   const int m0 = tile_m * BM, n0 = tile_n * BN;
-  const int t = threadIdx.x;
+  const int t = t_all - group * kThreads;                        // within the group, like `wave`
   const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int kt_lo = group * p.k_tiles / KG, n_kt = (group + 1) * p.k_tiles / KG - kt_lo;
+  const int steps = (p.k_tiles + KG - 1) / KG;                   // of the longest share: every wavefront passes every barrier
   const int wm0 = (wave / WAVES_N) * WM, wn0 = (wave % WAVES_N) * WN;
   const int fp = lane & 31, fh = lane >> 5;
 
@@ -190,36 +209,56 @@ __global__ __launch_bounds__(kThreads, 2) void igemm_stage_kernel(const ConvPara
     for (int kx = 0; kx < p.kw; ++kx) bits |= ((unsigned)(ix0 + kx * p.dil_w) < (unsigned)p.w ? 1u : 0u) << (8 + kx);
     a_taps[j] = present ? bits : 0u;
   }
-  if (t < BN) s_bias[t] = p.bias && n0 + t < p.c_out ? p.bias[n0 + t] : 0.0f;
+  if (t_all < BN) s_bias[t_all] = p.bias && n0 + t_all < p.c_out ? p.bias[n0 + t_all] : 0.0f;
   const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.x), 0, (int)p.x_bytes, kBufferWord3);
   const unsigned char* xb = static_cast<const unsigned char*>(p.x);
-  const unsigned char* wb = static_cast<const unsigned char*>(p.wp) + ((int64_t)(n0 / 32) * p.k_tiles) * D::BLOCK_BYTES + lane * 16;
+  const unsigned char* wb = static_cast<const unsigned char*>(p.wp) + ((int64_t)(n0 / 32) * p.k_tiles) * D::BLOCK_BYTES;
 
   // what a thread holds of a K tile: 16-byte groups, or one register per entry
   constexpr int A_REGS = BY_ENTRY ? PER_ROW * 8 : ROWS * (8 * EB / 4);
-  struct Regs { uint32_t a[A_REGS]; v4i b[B_LOADS]; uint32_t tails; };
+  struct Regs { uint32_t a[A_REGS]; uint32_t tails; };
+  constexpr int A_LOADS = BY_ENTRY ? PER_ROW * 8 : ROWS * (8 / V);      // loads of a tile's rows
   constexpr int GPC = 8 / V;          // 16-byte groups per chunk
-  const int last = p.k_tiles - 1;
+  const int last = max(kt_lo + n_kt - 1, 0);
 
   // The table entries of the next tile to be loaded.  They are fetched a tile ahead of the loads that need them, so that
   // waiting for them (loads return in order) never waits for a tile that is still on its way.
-  constexpr int TABS = BY_ENTRY ? (GATHER == kStageChunks ? PER_ROW : 1) : GPC;
+  // Where they are the same for a wavefront they are scalar loads (named as such: behind the barriers' clobbers the compiler
+  // would use vector loads, or a branch around the offset of an entry outside the image).
+  constexpr int ENTRIES = GATHER == kStageChunks ? 1 : 8;       // of a chunk
+  constexpr bool TABLE_AHEAD = PER_ROW * ENTRIES <= 16;         // (as the scalar registers allow)
+  constexpr int TABS = BY_ENTRY ? PER_ROW * ENTRIES : GPC;
+  typedef const __attribute__((address_space(4))) KEntry ScalarEntry;
+  typedef const __attribute__((address_space(4))) v4i ScalarPair;
   KEntry ke[TABS];
   auto load_table = [&](int kt) {
     if constexpr (!BY_ENTRY) {
 #pragma unroll
       for (int g = 0; g < GPC; ++g) ke[g] = p.ktab[(kt * CHUNKS + chunk0) * GPC + g];
-    } else if constexpr (GATHER == kStageChunks) {
+    } else {
+      const KEntry* at = p.ktab + (kt * CHUNKS + chunk0) * ENTRIES;
+      if constexpr (TABS % 2 != 0) {
+        const auto* one = reinterpret_cast<ScalarEntry*>(reinterpret_cast<uint64_t>(at));
+        ke[0].off = one->off;
+        ke[0].dydx = one->dydx;
+      } else {
+        const auto* two = reinterpret_cast<ScalarPair*>(reinterpret_cast<uint64_t>(at));
 #pragma unroll
-      for (int c = 0; c < PER_ROW; ++c) ke[c] = p.ktab[kt * CHUNKS + chunk0 + c];
+        for (int i = 0; i < TABS / 2; ++i) {
+          const v4i v = two[i];
+          ke[2 * i] = KEntry{v[0], v[1]};
+          ke[2 * i + 1] = KEntry{v[2], v[3]};
+        }
+      }
     }
   };
-  auto load_tile = [&](int kt_want, Regs& r) {      // (unconditional: past the last tile it is loaded again, and not used)
-    const int kt = min(kt_want, last);
+  auto load_tile = [&](int i, Regs& r) {      // tile i of the share (unconditional: past the last one that is loaded again, and not used)
+    const int kt_want = kt_lo + i, kt = min(kt_want, last);
+    if (BY_ENTRY && !TABLE_AHEAD) load_table(kt);
     KEntry now[TABS];
 #pragma unroll
     for (int i = 0; i < TABS; ++i) now[i] = ke[i];
-    load_table(min(kt_want + 1, last));
+    if (!BY_ENTRY || TABLE_AHEAD) load_table(min(kt_want + 1, last));
     if constexpr (!BY_ENTRY) {
       r.tails = 0;
 #pragma unroll
@@ -253,24 +292,30 @@ __global__ __launch_bounds__(kThreads, 2) void igemm_stage_kernel(const ConvPara
 #pragma unroll
           for (int e = 0; e < 8; ++e) r.a[c * 8 + e] = fetch(voff, e * p.h * p.w * EB);
         } else {
-          const KEntry* te = p.ktab + (kt * CHUNKS + chunk0 + c) * 8;
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
-            const uint32_t need = (uint32_t)te[e].dydx;
-            r.a[c * 8 + e] = fetch((a_taps[0] & need) == need ? (uint32_t)(a_at[0] + te[e].off) : kOutOfRange, 0);
+            const uint32_t need = (uint32_t)now[c * 8 + e].dydx;
+            r.a[c * 8 + e] = fetch((a_taps[0] & need) == need ? (uint32_t)(a_at[0] + now[c * 8 + e].off) : kOutOfRange, 0);
           }
         }
       }
     }
+  };
+  // the filters of tile i go straight into LDS; tile i + 1 is asked for when every wavefront has left the place it takes
+  typedef __attribute__((address_space(3))) void lds_void;
+  auto issue_filters = [&](int i, int buf) {
+    const int kt = min(kt_lo + i, last);
 #pragma unroll
     for (int j = 0; j < B_LOADS; ++j) {
-      const int u = wave + 4 * j;
-      if (B_UNITS % 4 == 0 || u < B_UNITS) {
-        constexpr int PER = D::BLOCK_BYTES / 1024;
-        const int nb = u / PER, in = u - nb * PER;
-        r.b[j] = *reinterpret_cast<const v4i*>(wb + ((int64_t)nb * p.k_tiles + kt) * D::BLOCK_BYTES + in * 1024);
-      }
+      // (a wavefront without a unit of its own in the last round repeats the last one: the same bytes to the same place)
+      const int u = min(wave + 4 * j, B_UNITS - 1);
+      constexpr int PER = D::BLOCK_BYTES / 1024;
+      const int nb = u / PER, in = u - nb * PER;
+      const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<unsigned char*>(wb + ((int64_t)nb * p.k_tiles + kt) * D::BLOCK_BYTES), 0, D::BLOCK_BYTES, kBufferWord3);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void*)(s_b + buf * B_BYTES + u * 1024), 16, (uint32_t)(lane * 16), in * 1024, 0, 0);
     }
+    __builtin_amdgcn_sched_barrier(0);       // (ahead of the row loads that follow: the order is counted on below)
   };
 
   // LDS byte offset of (row, chunk) inside one part of a tile
@@ -321,12 +366,6 @@ __global__ __launch_bounds__(kThreads, 2) void igemm_stage_kernel(const ConvPara
           *reinterpret_cast<v4i*>(dst) = v;
         }
       }
-    unsigned char* pb = s_b + buf * B_BYTES + lane * 16;
-#pragma unroll
-    for (int j = 0; j < B_LOADS; ++j) {
-      const int u = wave + 4 * j;
-      if (B_UNITS % 4 == 0 || u < B_UNITS) *reinterpret_cast<v4i*>(pb + u * 1024) = r.b[j];
-    }
   };
 
   floatx16 acc[MI][NI], small[SPLIT ? MI : 1][SPLIT ? NI : 1];
@@ -342,32 +381,45 @@ __global__ __launch_bounds__(kThreads, 2) void igemm_stage_kernel(const ConvPara
         }
   };
 
-  int frag_a[KSTEPS];
+  // (LDS reads by hand: the compiler would have them wait for the filters on their way to the other half)
+  const unsigned lds0 = (unsigned)(unsigned long long)(__attribute__((address_space(3))) unsigned char*)smem;
+  unsigned frag_a[KSTEPS];
 #pragma unroll
-  for (int ks = 0; ks < KSTEPS; ++ks) frag_a[ks] = a_place(wm0 + fp, 2 * ks + fh);
+  for (int ks = 0; ks < KSTEPS; ++ks) frag_a[ks] = lds0 + a_place(wm0 + fp, 2 * ks + fh);
+  const unsigned frag_b = lds0 + 2 * A_BYTES + (wn0 / 32) * D::BLOCK_BYTES + lane * 16;
 
-  auto compute_tile = [&](int buf, auto careful_c) {
+  auto compute_tile = [&](auto buf_c, auto careful_c) {
     constexpr bool CAREFUL = decltype(careful_c)::value;
-    const unsigned char* a = s_a + buf * A_BYTES;
-    const unsigned char* b = s_b + buf * B_BYTES + (wn0 / 32) * D::BLOCK_BYTES + lane * 16;
-#pragma unroll
-    for (int k2 = 0; k2 < KSTEPS; k2 += AHEAD) {      // AHEAD K steps of fragments are read before their products start
+    constexpr int BUF = decltype(buf_c)::value;
+    auto steps_of = [&](auto k2_c) {      // AHEAD K steps of fragments are read before their products start
+      constexpr int k2 = decltype(k2_c)::value;
       v4i xf[AHEAD][MI][PARTS], wf[AHEAD][NI][PARTS];
-#pragma unroll
-      for (int i = 0; i < AHEAD; ++i) {
+      static_for<AHEAD>([&](auto i_c) {
+        constexpr int i = decltype(i_c)::value;
+        static_for<PARTS>([&](auto q_c) {
+          constexpr int q = decltype(q_c)::value;
+          static_for<NI>([&](auto ni_c) {
+            constexpr int ni = decltype(ni_c)::value;
+            wf[i][ni][q] = lds_read16_big<BUF * B_BYTES + ni * D::BLOCK_BYTES + (q * KSTEPS + k2 + i) * 1024>(frag_b);
+          });
+          static_for<MI>([&](auto mi_c) {
+            constexpr int mi = decltype(mi_c)::value;
+            xf[i][mi][q] = lds_read16_big<BUF * A_BYTES + q * PART_A + mi * KSTEPS * 1024>(frag_a[k2 + i]);
+          });
+        });
+      });
+      static_for<AHEAD>([&](auto i_c) {
+        constexpr int i = decltype(i_c)::value;
+        // the step's fragments have landed, those of the next one may be on their way; they pass through, so that nothing
+        // that uses them moves above
+        asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"((AHEAD - 1 - i) * PARTS * (MI + NI)));
 #pragma unroll
         for (int q = 0; q < PARTS; ++q) {
 #pragma unroll
-          for (int ni = 0; ni < NI; ++ni)
-            wf[i][ni][q] = *reinterpret_cast<const v4i*>(b + ni * D::BLOCK_BYTES + (q * KSTEPS + k2 + i) * 1024);
+          for (int ni = 0; ni < NI; ++ni) asm volatile("" : "+v"(wf[i][ni][q]));
 #pragma unroll
-          for (int mi = 0; mi < MI; ++mi)
-            xf[i][mi][q] = *reinterpret_cast<const v4i*>(a + q * PART_A + mi * KSTEPS * 1024 + frag_a[k2 + i]);
+          for (int mi = 0; mi < MI; ++mi) asm volatile("" : "+v"(xf[i][mi][q]));
         }
-      }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int i = 0; i < AHEAD; ++i) {
         auto each = [&](auto fn) {
 #pragma unroll
           for (int mi = 0; mi < MI; ++mi)
@@ -398,8 +450,9 @@ __global__ __launch_bounds__(kThreads, 2) void igemm_stage_kernel(const ConvPara
           each([&](int mi, int ni) { H::mma(small[mi][ni], wf[i][ni][2], xf[i][mi][0]); });
           each([&](int mi, int ni) { H::mma(small[mi][ni], wf[i][ni][0], xf[i][mi][2]); });
         }
-      }
-    }
+      });
+    };
+    static_for<KSTEPS / AHEAD>([&](auto k_c) { steps_of(std::integral_constant<int, decltype(k_c)::value * AHEAD>{}); });
   };
 
   // ---- zero fill of the dropped rows this workgroup owns (Alg. 2, mask == 0 branch), behind the first K tile: the stores
@@ -423,10 +476,10 @@ __global__ __launch_bounds__(kThreads, 2) void igemm_stage_kernel(const ConvPara
     };
     const int cols = min(BN, p.c_out - n0);
     if constexpr (!NCHW) {      // lanes side by side on the 16-byte groups of a row
-      constexpr int CPR = BN / V, RPI = kThreads / CPR, ZB = 8;
-      const int c = (t % CPR) * V;
+      constexpr int CPR = BN / V, RPI = kThreads * KG / CPR, ZB = 8;
+      const int c = (t_all % CPR) * V;
       if (c >= cols) return;
-      for (int r0 = lo + t / CPR; r0 < hi; r0 += ZB * RPI) {
+      for (int r0 = lo + t_all / CPR; r0 < hi; r0 += ZB * RPI) {
         unsigned mk[ZB];
 #pragma unroll
         for (int u = 0; u < ZB; ++u) mk[u] = mask_of(min(r0 + u * RPI, hi - 1));
@@ -455,7 +508,7 @@ __global__ __launch_bounds__(kThreads, 2) void igemm_stage_kernel(const ConvPara
           if (r >= hi || mk[u] != 0) continue;
           const int n = fast_div(r, p.div_howo_mul, p.div_howo_shift);
           const int64_t at = n * p.ys_n + (r - n * p.ho_wo) + (int64_t)n0 * p.ys_c;
-          for (int c = wave; c < cols; c += 4) fill_one(at + (int64_t)c * p.ys_c);
+          for (int c = wave + 4 * group; c < cols; c += 4 * KG) fill_one(at + (int64_t)c * p.ys_c);
         }
       }
     }
@@ -463,27 +516,79 @@ __global__ __launch_bounds__(kThreads, 2) void igemm_stage_kernel(const ConvPara
 
   // ---- K loop: two tiles ahead in registers, one ahead in LDS ------------------------------------------------------------
   auto contract = [&](auto careful_c) {
+    constexpr std::integral_constant<int, 0> even;
+    constexpr std::integral_constant<int, 1> odd;
     Regs r0, r1;
-    load_table(0);
+    // (a wavefront's loads return in order: when at most A_LOADS, those of a later tile's rows, are on their way, the
+    // filters asked for before them have landed)
+    auto arrive = [&]() {
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(A_LOADS) : "memory");      // (and this wavefront's stores to LDS are done)
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    load_table(min(kt_lo, last));
+    issue_filters(0, 0);
     load_tile(0, r0);
     load_tile(1, r1);
     store_tile(0, r0, careful_c);
-    __syncthreads();
+    arrive();
     // (two tiles per turn and no way out in the middle: the accumulators and the register slots keep their places)
 #pragma unroll 1
-    for (int kt = 0; kt + 1 < p.k_tiles; kt += 2) {
+    for (int kt = 0; kt + 1 < steps; kt += 2) {
+      issue_filters(kt + 1, 1);
       load_tile(kt + 2, r0);
-      compute_tile(0, careful_c);
+      __builtin_amdgcn_sched_barrier(0);
+      if (KG == 1 || kt < n_kt) compute_tile(even, careful_c);
       if (!decltype(careful_c)::value && kt == 0 && p.zero_fill) fill_zeros();
       store_tile(1, r1, careful_c);
-      __syncthreads();
+      arrive();
+      issue_filters(kt + 2, 0);
       load_tile(kt + 3, r1);
-      compute_tile(1, careful_c);
+      __builtin_amdgcn_sched_barrier(0);
+      if (KG == 1 || kt + 1 < n_kt) compute_tile(odd, careful_c);
       store_tile(0, r0, careful_c);
+      arrive();
+    }
+    if ((steps & 1) && (KG == 1 || steps - 1 < n_kt)) compute_tile(even, careful_c);
+    if (!decltype(careful_c)::value && steps == 1 && p.zero_fill) fill_zeros();
+    wait_vmcnt<0>();                         // (no filters are on their way into LDS any more)
+    if constexpr (SPLIT) {
+#pragma unroll
+      for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[mi][ni][v] += small[mi][ni][v];
+    }
+    if constexpr (KG > 1) {
+      __syncthreads();                       // every wavefront has left its tiles: their place takes the sums
+      constexpr int SLOT = 4 * MI * NI * 4 * 64;
+      static_assert((KG - 1) * SLOT * 16 <= KG * RING, "the sums lie where the tiles were");
+      v4f* part = reinterpret_cast<v4f*>(smem_all) + wave * (MI * NI * 4 * 64) + lane;
+      auto each = [&](auto fn) {
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+          for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) fn(acc[mi][ni], (mi * NI + ni) * 4 + q, 4 * q);
+      };
+      if (group > 0)
+        each([&](floatx16& a, int at, int v) { part[(group - 1) * SLOT + at * 64] = v4f{a[v], a[v + 1], a[v + 2], a[v + 3]}; });
+      __syncthreads();
+      if (group == 0) {
+#pragma unroll
+        for (int g = 0; g < KG - 1; ++g)
+          each([&](floatx16& a, int at, int v) {
+            const v4f s = part[g * SLOT + at * 64];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a[v + e] += s[e];
+          });
+      }
       __syncthreads();
     }
-    if (p.k_tiles & 1) compute_tile(0, careful_c);
-    if (!decltype(careful_c)::value && p.k_tiles == 1 && p.zero_fill) fill_zeros();
   };
   clear();
   contract(std::false_type{});
@@ -494,11 +599,8 @@ __global__ __launch_bounds__(kThreads, 2) void igemm_stage_kernel(const ConvPara
 #pragma unroll
       for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          if constexpr (SPLIT) acc[mi][ni][v] += small[mi][ni][v];
-          odd |= acc[mi][ni][v] != acc[mi][ni][v];
-        }
-    if (__syncthreads_or(odd)) {
+        for (int v = 0; v < 16; ++v) odd |= acc[mi][ni][v] != acc[mi][ni][v];
+    if (__syncthreads_or(odd && group == 0)) {
       clear();
       contract(std::true_type{});
     }
@@ -506,6 +608,7 @@ __global__ __launch_bounds__(kThreads, 2) void igemm_stage_kernel(const ConvPara
   __syncthreads();
 
   // ---- epilogue --------------------------------------------------------------------------------------------------------------
+  if (KG > 1 && group > 0) return;
 #pragma unroll
   for (int mi = 0; mi < MI; ++mi) {
     const int rr = s_rows[wm0 + mi * 32 + fp];
@@ -522,10 +625,10 @@ __global__ __launch_bounds__(kThreads, 2) void igemm_stage_kernel(const ConvPara
   }
 }
 
-template <int DT, int BM, int BN, int WAVES_M, int WAVES_N, int GATHER, bool NCHW>
+template <int DT, int BM, int BN, int WAVES_M, int WAVES_N, int GATHER, bool NCHW, int KG = 1>
 hipError_t igemm_stage_launch(const ConvParams& p, hipStream_t stream) {
-  constexpr size_t lds = stage_lds_bytes<DT, BM, BN>();
-  auto kern = igemm_stage_kernel<DT, BM, BN, WAVES_M, WAVES_N, GATHER, NCHW>;
+  constexpr size_t lds = stage_lds_bytes<DT, BM, BN>(KG);
+  auto kern = igemm_stage_kernel<DT, BM, BN, WAVES_M, WAVES_N, GATHER, NCHW, KG>;
   static std::atomic<bool> attr_set{false};
   if (lds > 64 * 1024 && !attr_set) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -533,12 +636,12 @@ hipError_t igemm_stage_launch(const ConvParams& p, hipStream_t stream) {
     attr_set = true;
   }
   const int nwg = p.m_tiles * p.n_tiles;
-  hipLaunchKernelGGL(kern, dim3(((nwg + 7) / 8) * 8), dim3(kThreads), lds, stream, p);
+  hipLaunchKernelGGL(kern, dim3(((nwg + 7) / 8) * 8), dim3(kThreads * KG), lds, stream, p);
   return hipGetLastError();
 }
 
-// the kernel of tile bm x bn for a dtype and a gather, or null (igemm_stage.hip)
-LaunchFn stage_kernel(int dtype, int gather, bool nchw, int bm, int bn);
+// the kernel of tile bm x bn with K in `groups` shares for a dtype and a gather, or null (igemm_stage.hip)
+LaunchFn stage_kernel(int dtype, int gather, bool nchw, int bm, int bn, int groups);
 // filters into the order of the kernel's tiles, and the gather's table (igemm_stage.hip)
 hipError_t stage_pack(int dtype, int gather, const void* w, void* wp, KEntry* tab, int c_out, int blocks, int c_in, int kh, int kw,
                       int dil_h, int dil_w, int k_tiles, bool nchw, int h, int w_cols, hipStream_t stream);

@@ -1039,7 +1039,7 @@ static bool tap_is_automatic(const sc_conv_desc& d, const Geometry& g, const Ban
 
 using namespace sc;
 
-// tile of the register-staged kernel; groups of wavefronts that share K (direct form); asked for by the environment
+// tile of the register-staged and of the direct float kernel; groups of wavefronts that share K; asked for by the environment
 struct StageTile { int bm, bn, groups; bool asked; };
 
 struct sc_plan {
@@ -1329,7 +1329,7 @@ static bool stage_is_direct(const sc_conv_desc& d, const Geometry& g) {
 static LaunchFn stage_launcher(const sc_conv_desc& d, const Geometry& g, StageTile t) {
   if (stage_is_direct(d, g))
     return split_kernel(t.bm, t.bn, t.groups, d.c_in % StageDims<kF32>::K_TILE == 0, d.c_out % 16 == 0 ? 1 : 2);
-  return t.groups != 1 ? nullptr : stage_kernel(d.dtype == SC_BF16 ? kBF16 : d.dtype == SC_F16 ? kF16 : kF32, g.stage_gather, d.layout == SC_NCHW, t.bm, t.bn);
+  return stage_kernel(d.dtype == SC_BF16 ? kBF16 : d.dtype == SC_F16 ? kF16 : kF32, g.stage_gather, d.layout == SC_NCHW, t.bm, t.bn, t.groups);
 }
 // Its tile for a run of `rows` rows.  SPARSE_CONV_STAGE_TILE=<bm>x<bn>[x<groups>] overrides (tuning and tests), 0x0 switches the
 // kernel off.
@@ -1372,14 +1372,30 @@ static StageTile stage_tile_for(const sc_conv_desc& d, const Geometry& g, int64_
     }
     return best;
   }
-  // Through registers: 64 rows keep most workgroups in flight (us, 64 x 64 / 128 x 64: 128 -> 128 @28 channels first in float
-  // 46 / 59; 51 -> 51 @56 in bf16 44 / 50; 410 -> 410 @7 27 / 39).  Two channel tiles' worth of 16-bit channels in one
-  // workgroup save half of the gathers where that still covers the compute units (128 -> 128 @28 channels first in bf16
-  // 27.5 against 32.6).
-  if (d.c_out <= 32) return {128, 32, 1, false};
-  if (kt <= 2 && (rows + 127) / 128 * ((d.c_out + 63) / 64) >= device_cus()) return {128, 64, 1, false};
-  if (d.dtype != SC_F32 && d.c_out > 64 && (d.c_out % 128 == 0 || d.c_out % 128 > 64) &&
-      (rows + 63) / 64 * ((d.c_out + 127) / 128) >= device_cus() * 3 / 4) return {64, 128, 1, false};
+  // Through registers (us a sparse run, s = 0.5 where not said).  64 rows keep most workgroups in flight: 64 x 64 / 128 x 64
+  // 45 / 53 for 32 x 128 -> 128 @28 channels first in float, 40 / 42 for 64 x 51 -> 51 @56 in bf16 at s = 0.3, 28 / 36 for
+  // 64 x 410 -> 410 @7.  Where 128 channels in a workgroup still cover the compute units once, half of the gathers are saved and
+  // a second group of wavefronts hides one's transfers behind the other's products, 64 x 64 / 64 x 128 in two groups: 45 / 39
+  // for the first layer, 30 / 23 in bf16; not for the groups of ragged pixels, which are few loads: 32 x 102 -> 102 @28 in
+  // float 33.4 / 34.3, in fp16 14.2 / 16.3.  Beyond one round two groups lose (their LDS leaves one workgroup on a compute
+  // unit): 64 x 102 -> 102 @28 in fp16 at s = 0.3 28.5 / 43, 26.4 for 64 x 128 in one group.
+  // Two groups of 64 x 64 / one where they are at most one round: 4 x 128 -> 128 @28 channels first in float 26.7 / 29.9,
+  // 16 x 256 -> 256 @14 46 / 54, 410 -> 410 @7 24 / 28, 8 x 205 -> 205 @14 in fp16 15.2 / 17.2; two rounds: 20 x 37 -> 77
+  // @30 24.5 / 17.6; short K: 33 -> 30 @56 in bf16 (five tiles) 10.5 / 10.0.  Tiles of 32 channels keep a wavefront to a row
+  // block of its own and pay from a round of workgroups on: 64 x 64 / 128 x 32 for 16 x 33 -> 30 @56 in bf16 13.0 / 14.7.
+  const int cus = device_cus();
+  auto wgs_of = [&](int bm, int bn) { return ((rows + bm - 1) / bm) * ((d.c_out + bn - 1) / bn); };
+  if (groups <= 1) {
+    if (d.c_out <= 32 && wgs_of(128, 32) >= cus) return {128, 32, 1, false};
+    if (kt <= 2 && wgs_of(128, 64) >= cus) return {128, 64, 1, false};
+  }
+  const bool wide = d.c_out > 64 && (d.c_out % 128 == 0 || d.c_out % 128 > 64);
+  const int64_t wgs = wgs_of(64, 128);
+  if (wide && wgs >= cus * 3 / 4 && wgs <= cus && g.stage_gather >= kStageChunks && groups != 1)
+    return {64, 128, 2, false};
+  if (wide && wgs > cus && d.dtype != SC_F32 && groups != 2) return {64, 128, 1, false};
+  if (groups > 0) return {64, 64, groups, false};
+  if (wgs_of(64, 64) <= cus && kt >= (d.dtype == SC_F32 ? 4 : 8)) return {64, 64, 2, false};
   return {64, 64, 1, false};
 }
 // does a run take it?  (not where a tile, a band kernel or another form of the tiled kernel was asked for)
