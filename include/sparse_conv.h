@@ -298,8 +298,8 @@ int32_t sc_last_hip_error(void); /* hipError_t of the last failed HIP call on th
  * With g[r, co] = dy[r, co] where mask[r] == 1 and (no ReLU or y[r, co] > 0), and 0 elsewhere:
  *     db[co] = sum_r g[r, co]      dw[co, k] = sum_r g[r, co] * A[r, k]      dx = transposed convolution of g
  * (A = lowered activations, Sec. 3).  The contraction for dw runs over the kept rows only, like the
- * forward GEMM (Sec. 3.2).  NHWC layers with one group, bf16, fp16 or float (the paper's own arithmetic:
- * a plainer kernel on the 32 x 32 x 2 float MFMA), Cin and Cout multiples of 8; SC_ERR_UNSUPPORTED otherwise.
+ * forward GEMM (Sec. 3.2).  NHWC layers with one group, bf16, fp16 or float (the paper's own arithmetic),
+ * Cin and Cout multiples of 8; SC_ERR_UNSUPPORTED otherwise.
  *   sparse_conv_backward_plan   `fwd` is the layer's forward plan (it supplies the mask and the row list and must
  *                         outlive the backward plan; after sparse_conv_plan_set_mask the backward plan follows);
  *                         `desc` the descriptor the forward plan was made from; w_dev the filters.  workspace_dev:

@@ -1868,7 +1868,8 @@ static sc_status build_row_tables(const sc_conv_desc& d, const Geometry& g, unsi
   int32_t* kept_dev = reinterpret_cast<int32_t*>(ws + g.off_kept);
   int32_t host_vals[4] = {-1, 0, 0, 0};   // kept count, most kept rows in one band, widest slab of a 128-row / 256-row tile
   const bool slab = slab_geometry_ok(d, g);
-  // One launch up to 2^17 rows (where a run of rows cut in two leaves both halves a pixel); beyond that every workgroup's count of the rows in front of it costs more than a pass of its own.  Measured per refresh on a
+  // One launch up to 2^17 rows (where a run of rows cut in two leaves both halves a pixel); beyond that every workgroup's
+  // count of the rows in front of it costs more than a pass of its own.  Measured per refresh on a
   // 56 x 56 map of one image, us of GPU time: 13 in five launches and a copy, 5 in one.
   if (g.m <= kTableMostRows && !(bp.ok && bp.split && g.wo == 1)) {
     TableParams p;

@@ -513,7 +513,7 @@ def main():
         chains["the same, every conv through dense_conv_run"] = chain_time(W.pad_channels(ops, 16), W.base_seed(3), cs, dense=True)
         chains["pruned ResNet18 stack, channels padded to multiples of 8 (56/104/208/416: register-staged tiled kernel)"] = \
             chain_time(W.pad_channels(ops, 8), W.base_seed(3), cs)
-        chains["pruned ResNet18 stack with its own channel counts (51/102/205/410: element gather)"] = \
+        chains["pruned ResNet18 stack with its own channel counts (51/102/205/410: element-aligned groups)"] = \
             chain_time(ops, W.base_seed(3), cs)
     if args.mobilenet:
         cs = max(args.steps // 10, 5)
