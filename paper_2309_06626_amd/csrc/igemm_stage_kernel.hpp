@@ -28,8 +28,8 @@
 // they go runs three ahead, because waiting for a load waits for all that were issued before it, and is read by scalar loads
 // where a wavefront shares its entries.  The filters need no registers: they go from memory to LDS as they lie, a tile ahead.
 // Measured at s = 0.5 (element gather / all through registers / this kernel, us): 32 x 128 -> 128 @28 channels first in float
-// 115 / 45 / 39, in bf16 84 / 27.5 / 23, 32 x 51 -> 64 @28 in bf16 - / 19.6 / 13.8; at s = 0.3 64 x 102 -> 102 @28 in fp16
-// 98 / 27.5 / 26.5, 51 -> 51 @56 110 / 44 / 40, 410 -> 410 @7 186 / 27 / 24.
+// 115 / 45 / 37, in bf16 84 / 27.5 / 21.5, 32 x 51 -> 64 @28 in bf16 - / 19.6 / 13.8; at s = 0.3 64 x 102 -> 102 @28 in fp16
+// 98 / 27.5 / 25.5, 51 -> 51 @56 110 / 44 / 40, 410 -> 410 @7 186 / 27 / 22.5.
 //
 // Workgroup = BM kept rows x BN channels, four wavefronts (or KG groups of four); zero-fill ownership and the order of the
 // epilogue are those of the other tiled kernels.
@@ -178,7 +178,7 @@ __global__ __launch_bounds__(kThreads * KG, 2) void igemm_stage_kernel(const Con
   const int t = t_all - group * kThreads;                        // within the group, like `wave`
   const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int kt_lo = group * p.k_tiles / KG, n_kt = (group + 1) * p.k_tiles / KG - kt_lo;
-  const int steps = (p.k_tiles + KG - 1) / KG;                   // of the longest share: every wavefront passes every barrier
+  const int steps = (p.k_tiles + KG - 1) / KG;                   // of the longest share; a shorter one ends in a tile of zeros
   const int wm0 = (wave / WAVES_N) * WM, wn0 = (wave % WAVES_N) * WN;
   const int fp = lane & 31, fh = lane >> 5;
 
@@ -218,6 +218,11 @@ __global__ __launch_bounds__(kThreads * KG, 2) void igemm_stage_kernel(const Con
   constexpr int A_REGS = BY_ENTRY ? PER_ROW * 8 : ROWS * (8 * EB / 4);
   struct Regs { uint32_t a[A_REGS]; uint32_t tails; };
   constexpr int A_LOADS = BY_ENTRY ? PER_ROW * 8 : ROWS * (8 / V);      // loads of a tile's rows
+  // The loads of a tile go out between the products of an earlier one, where the issue slot is free while the matrix unit works;
+  // all at once a wavefront sits in the issue stage until the address unit has taken them (us, at once / between: 128 -> 128 @28
+  // channels first in float, batch 4 26.3 / 21.9, batch 32 39.1 / 37.1; 16 x 256 -> 256 @14 46 / 39; 410 -> 410 @7 24.2 / 22.5).
+  // Where they are many beside few products their addresses crowd the registers (128 rows by entry in bf16 23 / 41).
+  constexpr bool BETWEEN = A_LOADS <= (GATHER == kStageEntries ? 8 : 16);
   constexpr int GPC = 8 / V;          // 16-byte groups per chunk
   const int last = max(kt_lo + n_kt - 1, 0);
 
@@ -252,54 +257,52 @@ __global__ __launch_bounds__(kThreads * KG, 2) void igemm_stage_kernel(const Con
       }
     }
   };
-  auto load_tile = [&](int i, Regs& r) {      // tile i of the share (unconditional: past the last one that is loaded again, and not used)
+  // Where the loads of tile i of the share go (unconditional: past the last one that is loaded again, and not used); load_one
+  // issues the j-th of them.
+  struct Places { uint32_t at[BY_ENTRY ? PER_ROW * (GATHER == kStageChunks ? 1 : 8) : ROWS * GPC]; };
+  auto aim_tile = [&](int i, Regs& r, Places& pl) {
     const int kt_want = kt_lo + i, kt = min(kt_want, last);
     if (BY_ENTRY && !TABLE_AHEAD) load_table(kt);
     KEntry now[TABS];
 #pragma unroll
     for (int i = 0; i < TABS; ++i) now[i] = ke[i];
     if (!BY_ENTRY || TABLE_AHEAD) load_table(min(kt_want + 1, last));
-    if constexpr (!BY_ENTRY) {
-      r.tails = 0;
+    if constexpr (!BY_ENTRY) r.tails = 0;
 #pragma unroll
-      for (int g = 0; g < GPC; ++g) {
-        const uint32_t need = (uint32_t)now[g].dydx & ~kStageTail;
-        if constexpr (GATHER == kStageRaggedGroups) r.tails |= ((uint32_t)now[g].dydx >> 31) << g;
+    for (int g = 0; g < TABS; ++g) {
+      uint32_t need = (uint32_t)now[g].dydx & ~(BY_ENTRY ? 0u : kStageTail);
+      if (KG > 1 && i >= n_kt) need = kStageNoTap;
+      if constexpr (GATHER == kStageRaggedGroups) r.tails |= ((uint32_t)now[g].dydx >> 31) << g;
 #pragma unroll
-        for (int j = 0; j < ROWS; ++j) {
-          const bool ok = (a_taps[j] & need) == need;
-          v4i v;
-          if constexpr (GATHER == kStageGroups) {
-            v = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rx, ok ? (uint32_t)(a_at[j] + now[g].off) : kOutOfRange, 0, 0));
-          } else {
-            const unsigned char* src = ok ? xb + (int64_t)(a_at[j] + now[g].off) : static_cast<const unsigned char*>(p.zeros);
-            __builtin_memcpy(&v, src, 16);          // element-aligned
-          }
-#pragma unroll
-          for (int i = 0; i < 4; ++i) r.a[(j * GPC + g) * 4 + i] = (uint32_t)v[i];
-        }
-      }
-    } else {
-#pragma unroll
-      for (int c = 0; c < PER_ROW; ++c) {
-        auto fetch = [&](uint32_t voff, int soff) -> uint32_t {
-          if constexpr (EB == 4) return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rx, voff, soff, 0);
-          else return (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rx, voff, soff, 0);
-        };
-        if constexpr (GATHER == kStageChunks) {
-          const uint32_t need = (uint32_t)now[c].dydx;
-          const uint32_t voff = (a_taps[0] & need) == need ? (uint32_t)(a_at[0] + now[c].off) : kOutOfRange;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) r.a[c * 8 + e] = fetch(voff, e * p.h * p.w * EB);
-        } else {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const uint32_t need = (uint32_t)now[c * 8 + e].dydx;
-            r.a[c * 8 + e] = fetch((a_taps[0] & need) == need ? (uint32_t)(a_at[0] + now[c * 8 + e].off) : kOutOfRange, 0);
-          }
-        }
-      }
+      for (int j = 0; j < ROWS; ++j) pl.at[j * TABS + g] = (a_taps[j] & need) == need ? (uint32_t)(a_at[j] + now[g].off) : kOutOfRange;
     }
+  };
+  auto load_one = [&](int j, Regs& r, const Places& pl) {
+    if constexpr (!BY_ENTRY) {
+      v4i v;
+      if constexpr (GATHER == kStageGroups) {
+        v = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rx, pl.at[j], 0, 0));
+      } else {
+        const unsigned char* src = pl.at[j] != kOutOfRange ? xb + (int64_t)(int32_t)pl.at[j] : static_cast<const unsigned char*>(p.zeros);
+        __builtin_memcpy(&v, src, 16);          // element-aligned
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) r.a[j * 4 + i] = (uint32_t)v[i];
+    } else {
+      const uint32_t voff = pl.at[GATHER == kStageChunks ? j / 8 : j];
+      const int soff = GATHER == kStageChunks ? (j % 8) * p.h * p.w * EB : 0;
+      if constexpr (EB == 4) r.a[j] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rx, voff, soff, 0);
+      else r.a[j] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rx, voff, soff, 0);
+    }
+  };
+  auto load_all = [&](Regs& r, const Places& pl) {
+#pragma unroll
+    for (int j = 0; j < A_LOADS; ++j) load_one(j, r, pl);
+  };
+  auto load_tile = [&](int i, Regs& r) {
+    Places pl;
+    aim_tile(i, r, pl);
+    load_all(r, pl);
   };
   // the filters of tile i go straight into LDS; tile i + 1 is asked for when every wavefront has left the place it takes
   typedef __attribute__((address_space(3))) void lds_void;
@@ -312,7 +315,7 @@ __global__ __launch_bounds__(kThreads * KG, 2) void igemm_stage_kernel(const Con
       constexpr int PER = D::BLOCK_BYTES / 1024;
       const int nb = u / PER, in = u - nb * PER;
       const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
-          const_cast<unsigned char*>(wb + ((int64_t)nb * p.k_tiles + kt) * D::BLOCK_BYTES), 0, D::BLOCK_BYTES, kBufferWord3);
+          const_cast<unsigned char*>(wb + ((int64_t)nb * p.k_tiles + kt) * D::BLOCK_BYTES), 0, KG > 1 && i >= n_kt ? 0 : D::BLOCK_BYTES, kBufferWord3);
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void*)(s_b + buf * B_BYTES + u * 1024), 16, (uint32_t)(lane * 16), in * 1024, 0, 0);
     }
     __builtin_amdgcn_sched_barrier(0);       // (ahead of the row loads that follow: the order is counted on below)
@@ -388,7 +391,8 @@ __global__ __launch_bounds__(kThreads * KG, 2) void igemm_stage_kernel(const Con
   for (int ks = 0; ks < KSTEPS; ++ks) frag_a[ks] = lds0 + a_place(wm0 + fp, 2 * ks + fh);
   const unsigned frag_b = lds0 + 2 * A_BYTES + (wn0 / 32) * D::BLOCK_BYTES + lane * 16;
 
-  auto compute_tile = [&](auto buf_c, auto careful_c) {
+  // (r, pl: the loads of a later tile, issued between the products)
+  auto compute_tile = [&](auto buf_c, auto careful_c, Regs* r, const Places* pl) {
     constexpr bool CAREFUL = decltype(careful_c)::value;
     constexpr int BUF = decltype(buf_c)::value;
     auto steps_of = [&](auto k2_c) {      // AHEAD K steps of fragments are read before their products start
@@ -420,11 +424,22 @@ __global__ __launch_bounds__(kThreads * KG, 2) void igemm_stage_kernel(const Con
 #pragma unroll
           for (int mi = 0; mi < MI; ++mi) asm volatile("" : "+v"(xf[i][mi][q]));
         }
+        constexpr int ROUNDS = (SPLIT && !CAREFUL ? 6 : 1) * MI * NI, ALL = KSTEPS * ROUNDS;
+        int done = (k2 + i) * ROUNDS;
         auto each = [&](auto fn) {
 #pragma unroll
           for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-            for (int ni = 0; ni < NI; ++ni) fn(mi, ni);
+            for (int ni = 0; ni < NI; ++ni) {
+              fn(mi, ni);
+              if (r) {
+#pragma unroll
+                for (int j = 0; j < A_LOADS; ++j)
+                  if (j * ALL / A_LOADS == done) load_one(j, *r, *pl);
+                __builtin_amdgcn_sched_barrier(0x6);
+              }
+              ++done;
+            }
         };
         if constexpr (!SPLIT) {
           each([&](int mi, int ni) { E::mma(acc[mi][ni], wf[i][ni][0], xf[i][mi][0]); });
@@ -519,6 +534,7 @@ __global__ __launch_bounds__(kThreads * KG, 2) void igemm_stage_kernel(const Con
     constexpr std::integral_constant<int, 0> even;
     constexpr std::integral_constant<int, 1> odd;
     Regs r0, r1;
+    Places pl;
     // (a wavefront's loads return in order: when at most A_LOADS, those of a later tile's rows, are on their way, the
     // filters asked for before them have landed)
     auto arrive = [&]() {
@@ -538,20 +554,22 @@ __global__ __launch_bounds__(kThreads * KG, 2) void igemm_stage_kernel(const Con
 #pragma unroll 1
     for (int kt = 0; kt + 1 < steps; kt += 2) {
       issue_filters(kt + 1, 1);
-      load_tile(kt + 2, r0);
+      aim_tile(kt + 2, r0, pl);
+      if constexpr (!BETWEEN) load_all(r0, pl);
       __builtin_amdgcn_sched_barrier(0);
-      if (KG == 1 || kt < n_kt) compute_tile(even, careful_c);
+      compute_tile(even, careful_c, BETWEEN ? &r0 : nullptr, &pl);
       if (!decltype(careful_c)::value && kt == 0 && p.zero_fill) fill_zeros();
       store_tile(1, r1, careful_c);
       arrive();
       issue_filters(kt + 2, 0);
-      load_tile(kt + 3, r1);
+      aim_tile(kt + 3, r1, pl);
+      if constexpr (!BETWEEN) load_all(r1, pl);
       __builtin_amdgcn_sched_barrier(0);
-      if (KG == 1 || kt + 1 < n_kt) compute_tile(odd, careful_c);
+      compute_tile(odd, careful_c, BETWEEN ? &r1 : nullptr, &pl);
       store_tile(0, r0, careful_c);
       arrive();
     }
-    if ((steps & 1) && (KG == 1 || steps - 1 < n_kt)) compute_tile(even, careful_c);
+    if (steps & 1) compute_tile(even, careful_c, (Regs*)nullptr, (const Places*)nullptr);
     if (!decltype(careful_c)::value && steps == 1 && p.zero_fill) fill_zeros();
     wait_vmcnt<0>();                         // (no filters are on their way into LDS any more)
     if constexpr (SPLIT) {
