@@ -1373,16 +1373,16 @@ static StageTile stage_tile_for(const sc_conv_desc& d, const Geometry& g, int64_
     return best;
   }
   // Through registers (us a sparse run, s = 0.5 where not said).  64 rows keep most workgroups in flight: 64 x 64 / 128 x 64
-  // 45 / 53 for 32 x 128 -> 128 @28 channels first in float, 40 / 42 for 64 x 51 -> 51 @56 in bf16 at s = 0.3, 28 / 36 for
+  // 40 / 48 for 32 x 128 -> 128 @28 channels first in float, 40 / 42 for 64 x 51 -> 51 @56 in bf16 at s = 0.3, 27 / 38 for
   // 64 x 410 -> 410 @7.  Where 128 channels in a workgroup still cover the compute units once, half of the gathers are saved and
-  // a second group of wavefronts hides one's transfers behind the other's products, 64 x 64 / 64 x 128 in two groups: 45 / 39
-  // for the first layer, 30 / 23 in bf16; not for the groups of ragged pixels, which are few loads: 32 x 102 -> 102 @28 in
+  // a second group of wavefronts hides one's transfers behind the other's products, 64 x 64 / 64 x 128 in two groups: 40 / 37
+  // for the first layer, 29 / 21 in bf16; not for the groups of ragged pixels, which are few loads: 32 x 102 -> 102 @28 in
   // float 33.4 / 34.3, in fp16 14.2 / 16.3.  Beyond one round two groups lose (their LDS leaves one workgroup on a compute
-  // unit): 64 x 102 -> 102 @28 in fp16 at s = 0.3 28.5 / 43, 26.4 for 64 x 128 in one group.
-  // Two groups of 64 x 64 / one where they are at most one round: 4 x 128 -> 128 @28 channels first in float 26.7 / 29.9,
-  // 16 x 256 -> 256 @14 46 / 54, 410 -> 410 @7 24 / 28, 8 x 205 -> 205 @14 in fp16 15.2 / 17.2; two rounds: 20 x 37 -> 77
-  // @30 24.5 / 17.6; short K: 33 -> 30 @56 in bf16 (five tiles) 10.5 / 10.0.  Tiles of 32 channels keep a wavefront to a row
-  // block of its own and pay from a round of workgroups on: 64 x 64 / 128 x 32 for 16 x 33 -> 30 @56 in bf16 13.0 / 14.7.
+  // unit): 64 x 102 -> 102 @28 in fp16 at s = 0.3 28.1 / 40, 25.7 for 64 x 128 in one group.
+  // Two groups of 64 x 64 / one where they are at most one round: 4 x 128 -> 128 @28 channels first in float 21.8 / 26.6,
+  // 16 x 256 -> 256 @14 39 / 49, 410 -> 410 @7 22.4 / 27.2, 8 x 205 -> 205 @14 in fp16 14.2 / 17.2; two rounds: 20 x 37 -> 77
+  // @30 24.5 / 17.6; short K: 33 -> 30 @56 in bf16 (five tiles) no difference.  Tiles of 32 channels keep a wavefront to a row
+  // block of its own and pay from a round of workgroups on: 64 x 64 / 128 x 32 for 16 x 33 -> 30 @56 in bf16 13.6 / 16.0.
   const int cus = device_cus();
   auto wgs_of = [&](int bm, int bn) { return ((rows + bm - 1) / bm) * ((d.c_out + bn - 1) / bn); };
   if (groups <= 1) {
