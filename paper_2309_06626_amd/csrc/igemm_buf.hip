@@ -42,7 +42,8 @@ static LaunchFn pick_splitk(int bm, int bn) {
 // Measured (us, s = 0.5, 64 x 64 with one group / two): 64 x 512 -> 512 @7 24.4 / 20.3 (split K of 128 x 128, the choice
 // before: 22.0), 64 x 256 -> 512 @7 13.8 / 12.1, 2 x 256 -> 256 @40 13.6 / 11.8, 30 x 384 -> 384 @13 19.3 / 16.8 (20.7); with more
 // workgroups than compute units 17.1 / 22.7 (64 x 256 -> 256 @14).  64 x 128 and 128 x 64 with two groups: up to 12 % faster
-// alone than one group of 64 x 64, no faster behind other layers (filters cold), left out.
+// alone than one group of 64 x 64, no faster behind other layers (filters cold), left out.  Chosen by the model in the place of a
+// split of K only (see model_pick).
 template <int DT>
 static LaunchFn pick_groups(int bm, int bn) {
   if (bm == 64 && bn == 64) return igemm_buf_launch<DT, 64, 64, 2, 2, 3, false, 2>;

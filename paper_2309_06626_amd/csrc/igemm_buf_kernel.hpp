@@ -50,7 +50,9 @@ __device__ __forceinline__ v4i load16_device_scope(const void* src) {
 // KG > 1: the K tiles are divided among KG groups of wavefronts inside the workgroup, each with a ring of its own; the first
 // group adds the others' sums out of LDS, in order.  For long K walks of few workgroups: a compute unit with one workgroup
 // of four wavefronts takes operands in at little more than half the rate it reaches with twice the wavefronts (see the
-// quantities of the cost model), and unlike SPLITK nothing crosses the memory system.
+// quantities of the cost model), and unlike SPLITK nothing crosses the memory system.  It stands in for a split of K into
+// p.splits = KG or 2 KG shares and adds the same products in the same order: a group with two shares keeps a sum for each,
+// and the sums of all shares are added in share order from zero, so the results are those of the split launch bit for bit.
 template <int DT, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, bool SPLITK = false, int KG = 1>
 __global__ __launch_bounds__(WAVES_M * WAVES_N * 64 * KG) void igemm_buf_kernel(const ConvParams p) {
   using E = Elem<DT>;
@@ -92,7 +94,10 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64 * KG) void igemm_buf_kernel(
   const int kt_lo = SPLITK ? (int)((int64_t)split * p.k_tiles / splits) : KG > 1 ? group * p.k_tiles / KG : 0;
   const int kt_hi = SPLITK ? (int)((int64_t)(split + 1) * p.k_tiles / splits) : KG > 1 ? (group + 1) * p.k_tiles / KG : p.k_tiles;
   const int n_kt = kt_hi - kt_lo;
-  const int n_steps = KG > 1 ? (p.k_tiles + KG - 1) / KG : n_kt;     // of the longest share: every wavefront passes every barrier
+  const int n_steps = KG > 1 ? (p.k_tiles + KG - 1) / KG : n_kt;     // of the longest walk: every wavefront passes every barrier
+  // a group's two shares are whole turns of the ring (the launcher checks it): the sums change hands between two loops, not
+  // inside one (a test for the tile in the loop cost 5 us of 19)
+  const bool two_shares = KG > 1 && p.splits == 2 * KG;
 
   const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6) - group * (NT / 64);      // within the group
   const int wm0 = (wave / WAVES_N) * WM, wn0 = (wave % WAVES_N) * WN;
@@ -234,6 +239,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64 * KG) void igemm_buf_kernel(
     for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.0f;
+  floatx16 first[KG > 1 ? MI : 1][KG > 1 ? NI : 1];      // (the sums of a group's first share of two)
 
   const unsigned lds0 = (unsigned)(unsigned long long)(__attribute__((address_space(3))) unsigned char*)smem;
   unsigned frag_a[4], frag_b[4];   // LDS address of this lane's fragment of K step ks in ring slot 0
@@ -292,14 +298,14 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64 * KG) void igemm_buf_kernel(
   // 128 x 64 and 128 x 128 tiles, 3-5 % slower on the tiles with one MFMA per step, which keep the plain order)
   constexpr bool INTERLEAVE = MI * NI >= 2;
   int issued = 0;
-  auto k_tile = [&](auto stage_c, int kt) {
+  auto k_tile = [&](auto stage_c, int kt) __attribute__((always_inline)) {
     constexpr int ST = decltype(stage_c)::value;
     using Refill = std::integral_constant<int, (ST + STAGES - 1) % STAGES>;
     if (kt + STAGES - 2 < n_kt) wait_vmcnt<(STAGES - 2) * LPT>();
     else wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();   // landed for every wavefront; and all have left tile kt-1
     asm volatile("" ::: "memory");
-    if (KG > 1 && kt >= n_kt) return;      // (a shorter share: the barrier only)
+    if (KG > 1 && kt >= n_kt) return;      // (a shorter walk: the barrier only)
     const bool more = issued < n_kt;
     if constexpr (!INTERLEAVE) {
       if (more) issue_tile(Refill{});
@@ -328,42 +334,67 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64 * KG) void igemm_buf_kernel(
   if constexpr (STAGES >= 3) if (1 < n_kt) { issue_tile(std::integral_constant<int, 1>{}); ++issued; }
   if constexpr (STAGES >= 4) if (2 < n_kt) { issue_tile(std::integral_constant<int, 2>{}); ++issued; }
   static_assert(STAGES <= 4, "ring of at most four tiles");
-  for (int kt = 0; kt < n_steps; kt += STAGES) {
-    k_tile(std::integral_constant<int, 0>{}, kt);
-    if (kt + 1 < n_steps) k_tile(std::integral_constant<int, 1 % STAGES>{}, kt + 1);
-    if constexpr (STAGES >= 3) if (kt + 2 < n_steps) k_tile(std::integral_constant<int, 2 % STAGES>{}, kt + 2);
-    if constexpr (STAGES >= 4) if (kt + 3 < n_steps) k_tile(std::integral_constant<int, 3 % STAGES>{}, kt + 3);
+  auto turns = [&](int from, int to) __attribute__((always_inline)) {
+    for (int kt = from; kt < to; kt += STAGES) {
+      k_tile(std::integral_constant<int, 0>{}, kt);
+      if (kt + 1 < to) k_tile(std::integral_constant<int, 1 % STAGES>{}, kt + 1);
+      if constexpr (STAGES >= 3) if (kt + 2 < to) k_tile(std::integral_constant<int, 2 % STAGES>{}, kt + 2);
+      if constexpr (STAGES >= 4) if (kt + 3 < to) k_tile(std::integral_constant<int, 3 % STAGES>{}, kt + 3);
+    }
+  };
+  if constexpr (KG > 1) {
+    const int n_first = two_shares ? n_steps / 2 : 0;
+    turns(0, n_first);
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          first[mi][ni][v] = acc[mi][ni][v];
+          acc[mi][ni][v] = 0.0f;
+        }
+    turns(n_first, n_steps);
+  } else {
+    turns(0, n_steps);
   }
 
   if constexpr (KG > 1) {
     __syncthreads();                                   // every wavefront has left the rings
-    v4f* part = reinterpret_cast<v4f*>(smem_all) + (wave * (MI * NI * 4)) * 64 + lane;
     constexpr int SLOT = (NT / 64) * MI * NI * 4 * 64;
-    static_assert((KG - 1) * SLOT * 16 <= KG * STAGES * STAGE_BYTES, "the sums lie where the rings were");
-    if (group > 0) {
+    static_assert((KG - 1) * 2 * SLOT * 16 <= KG * STAGES * STAGE_BYTES, "the sums lie where the rings were");
+    v4f* part = reinterpret_cast<v4f*>(smem_all) + (wave * (MI * NI * 4)) * 64 + lane;      // [share of the other groups][SLOT]
+    auto each = [&](auto fn) {
 #pragma unroll
       for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
         for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
-          for (int q = 0; q < 4; ++q)
-            part[(group - 1) * SLOT + ((mi * NI + ni) * 4 + q) * 64] =
-                v4f{acc[mi][ni][4 * q], acc[mi][ni][4 * q + 1], acc[mi][ni][4 * q + 2], acc[mi][ni][4 * q + 3]};
+          for (int q = 0; q < 4; ++q) fn(mi, ni, ((mi * NI + ni) * 4 + q) * 64, 4 * q);
+    };
+    const int shares = two_shares ? 2 : 1;             // of a group
+    if (group > 0) {
+      v4f* mine = part + (group - 1) * shares * SLOT;
+      if (two_shares) {
+        each([&](int mi, int ni, int at, int v) {
+          mine[at] = v4f{first[mi][ni][v], first[mi][ni][v + 1], first[mi][ni][v + 2], first[mi][ni][v + 3]};
+        });
+        mine += SLOT;
+      }
+      each([&](int mi, int ni, int at, int v) { mine[at] = v4f{acc[mi][ni][v], acc[mi][ni][v + 1], acc[mi][ni][v + 2], acc[mi][ni][v + 3]}; });
     }
     __syncthreads();
     if (group == 0) {
+      each([&](int mi, int ni, int, int v) {           // (from zero, as the split launch adds)
 #pragma unroll
-      for (int g = 0; g < KG - 1; ++g)
+        for (int e = 0; e < 4; ++e) acc[mi][ni][v + e] = (0.0f + first[mi][ni][v + e]) + acc[mi][ni][v + e];
+      });
+      for (int s = 0; s < (KG - 1) * shares; ++s)
+        each([&](int mi, int ni, int at, int v) {
+          const v4f o = part[s * SLOT + at];
 #pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-          for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              const v4f v = part[g * SLOT + ((mi * NI + ni) * 4 + q) * 64];
-#pragma unroll
-              for (int e = 0; e < 4; ++e) acc[mi][ni][4 * q + e] += v[e];
-            }
+          for (int e = 0; e < 4; ++e) acc[mi][ni][v + e] += o[e];
+        });
     }
   }
 

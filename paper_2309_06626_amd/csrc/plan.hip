@@ -1055,7 +1055,9 @@ struct sc_plan {
   int64_t kept;
   const KernelEntry* table;
   int table_count;
-  struct Pick { int ti, splits; bool masked; int groups = 1; bool asked = false; };      // (groups of wavefronts that share K inside a workgroup; asked for by the environment)
+  // grouped: tile whose launch with two groups of wavefronts, sharing K inside the workgroup, stands in for the split into
+  // `splits` shares where group_candidates allows it (-1: none); asked: by the environment
+  struct Pick { int ti, splits; bool masked; int grouped = -1; bool asked = false; };
   Pick pick[2];                    // tiled launch of the sparse / dense run when nothing is forced: tile, K splits, and
                                    // (sparse run) whether every row is contracted and the mask decides at the store
   bool prefer_tiled[2];            // measured by sparse_conv_plan_tune: the tiled launch beat the band / row-panel kernel
@@ -1178,7 +1180,8 @@ static sc_plan::Pick model_pick(const sc_plan* pl, int which, int64_t rows) {
   int fbm = 0, fbn = 0, fgr = 0;
   if (const char* env = std::getenv("SPARSE_CONV_TILE_GROUPS"); env && std::sscanf(env, "%dx%dx%d", &fbm, &fbn, &fgr) == 3) {
     const int i = find(fbm, fbn);
-    if (pl->table[i].bm == fbm && pl->table[i].bn == fbn && (fgr == 1 || (fgr == 2 && buf_applies(pl, pl->table[i]) && buf_groups_kernel(d.dtype == SC_BF16 ? kBF16 : kF16, fbm, fbn)))) { best = {i, 1, false, fgr}; best.asked = fgr > 1; return best; }
+    const bool grouped = fgr == 2 && buf_applies(pl, pl->table[i]) && buf_groups_kernel(d.dtype == SC_BF16 ? kBF16 : kF16, fbm, fbn);
+    if (pl->table[i].bm == fbm && pl->table[i].bn == fbn && (fgr == 1 || grouped)) return {i, grouped ? 2 : 1, false, grouped ? i : -1, grouped};
   }
   double best_us = 1e300;
   const bool can_mask = which == 0 && rows < g.m && rows > 0;
@@ -1191,22 +1194,27 @@ static sc_plan::Pick model_pick(const sc_plan* pl, int which, int64_t rows) {
       const double t = predict_us(pl, ke, rows, sp, which == 0 && rows < g.m);
       if (t < best_us) { best_us = t; best = {i, sp, false}; }
     }
-    if (group_candidates(pl, ke, rows) > 1) {
-      const double t = predict_us(pl, ke, rows, 1, which == 0 && rows < g.m, 2);
-      if (t < best_us) { best_us = t; best = {i, 1, false, 2}; }
-    }
     if (can_mask && pl->masked_store != 1) {       // every row contracted, the mask decides at the store: the dense launch plus a mask byte per row
       const double t = predict_us(pl, ke, g.m, 1, false) + 0.1;
       if (t < best_us) { best_us = t; best = {i, 1, true}; }
     }
   }
+  // Two groups of wavefronts only where they add what the best launch adds in its order, i.e. in the place of a split into two
+  // or (where the four shares are whole turns of the ring of three tiles) four: one order of additions whichever of the two
+  // runs.  64 x 512 -> 512 @7 in bf16 at s = 0.5: four shares of 128 x 128 20.0 us, two groups 18.9.
+  if (!best.masked && (best.splits == 2 || (best.splits == 4 && g.k_tiles % 12 == 0)))
+    for (int i = 0; i < pl->table_count; ++i) {
+      if (group_candidates(pl, pl->table[i], rows) < 2) continue;
+      const double t = predict_us(pl, pl->table[i], rows, 1, which == 0 && rows < g.m, 2);
+      if (t < best_us) { best_us = t; best.grouped = i; }
+    }
   return best;
 }
 
 // Split K?  Layers deep in a network have few rows and a long K: large output tiles cannot fill
 // 256 CUs, and with small tiles every workgroup walks the whole K, one L2 round trip after the other.
 // Dividing K among workgroups shortens that walk and still gives every CU work.
-struct TilePick { int ti, splits; bool masked; int groups = 1; };
+struct TilePick { int ti, splits; bool masked; int shares = 0; };      // (shares of K added by two groups of wavefronts; 0: none)
 
 // Row-panel kernel: short K (pointwise layers), several 64-channel tiles, enough rows to fill the
 // CUs with 128-row panels.  There the tiled kernels are bound by the instructions every
@@ -1419,10 +1427,12 @@ static TilePick pick_tile(const sc_plan* pl, int which, int64_t rows) {
   tp.ti = pl->pick[which].ti;
   tp.splits = pl->split_k == 1 ? 1 : std::min(pl->pick[which].splits, most_splits(pl, pl->table[tp.ti], rows));
   tp.masked = pl->masked_store == 2 ? which == 0 : pl->masked_store == 1 ? false : pl->pick[which].masked;
-  if (pl->pick[which].groups > 1 && !tp.masked) tp.groups = pl->pick[which].asked ? 2 : group_candidates(pl, pl->table[tp.ti], rows);
+  const sc_plan::Pick& pick = pl->pick[which];
+  if (pick.grouped >= 0 && !tp.masked && (pick.asked || group_candidates(pl, pl->table[pick.grouped], rows) > 1))
+    tp = {pick.grouped, 1, false, pick.splits};
   if (pl->split_k >= 2 && pl->tile_splitk >= 0) {      // on request: that many splits of the 64 x 128 tile
     const int want = std::min(pl->split_k, most_splits(pl, pl->table[pl->tile_splitk], rows));
-    if (want >= 2) { tp.ti = pl->tile_splitk; tp.splits = want; tp.masked = false; }
+    if (want >= 2) tp = {pl->tile_splitk, want, false};
   }
   return tp;
 }
@@ -1781,8 +1791,10 @@ static sc_status launch_conv(const sc_plan* pl, bool dense, const void* x, const
       fn = sk;
     }
   }
-  if (tp.groups > 1 && fn_is_buf && splits == 1 && !panel && !masked && !p.stream_wgs)
+  if (tp.shares > 0 && fn_is_buf && splits == 1 && !panel && !masked && !p.stream_wgs) {
     fn = buf_groups_kernel(d.dtype == SC_BF16 ? kBF16 : kF16, ke.bm, ke.bn);
+    p.splits = tp.shares;
+  }
   if (splits > 1) {
     p.splits = splits;
     p.partial = reinterpret_cast<float*>(pl->ws + g.off_partial);
@@ -2267,8 +2279,8 @@ sc_status sparse_conv_plan_tune(sc_plan* plan, const void* x_dev, const float* b
         cands[n] = {{i, sp, false}, predict_us(plan, ke, rows, sp, which == 0 && rows < plan->geo.m)};
         best_pred = std::min(best_pred, cands[n++].predicted);
       }
-      if (group_candidates(plan, ke, rows) > 1) {
-        cands[n] = {{i, 1, false, 2}, predict_us(plan, ke, rows, 1, which == 0 && rows < plan->geo.m, 2)};
+      if (most >= 2 && group_candidates(plan, ke, rows) > 1) {
+        cands[n] = {{i, 2, false, i}, predict_us(plan, ke, rows, 1, which == 0 && rows < plan->geo.m, 2)};
         best_pred = std::min(best_pred, cands[n++].predicted);
       }
       if (can_mask && plan->masked_store != 1) {

@@ -203,3 +203,31 @@ def test_groups_of_wavefronts_share_k(case, dtype, monkeypatch):
     check_residual(spec.with_(relu=False), 1651, True, want_kernel=("tile_lds_direct",))
     if spec.sparsity > 0:
         check_compact_output(spec, 1652)
+
+
+@pytest.mark.parametrize("dtype,shape", [
+    ("bf16", dict(n=64, cin=512, h=7, w=7, cout=512)),                  # in the place of a split into four
+    ("f16", dict(n=30, cin=384, h=13, w=13, cout=384)),
+    ("bf16", dict(n=2, cin=256, h=40, w=40, cout=256)),
+    ("bf16", dict(n=12, cin=320, h=14, w=14, cout=448, k=5, p=2)),
+    ("f16", dict(n=64, cin=256, h=14, w=14, cout=512, s=2)),
+])
+def test_automatic_groups_add_in_the_order_of_the_split_they_replace(dtype, shape):
+    """Results do not depend on whether two groups of wavefronts or the split-K launch contracts a layer: the same bits."""
+    spec = spec_of(dtype=dtype, sp=0.5, **shape)
+    ci = W.make_conv_inputs(spec, 1660)
+    layer = R.ConvLayer(spec, ci.w, ci.bias, ci.mask)
+    x = R.to_device(ci.x, dtype)
+    got = []
+    for stream_k in (0, 8):                                            # (any such request keeps the groups out)
+        B.sparse_conv_plan_set_option(layer.plan, B.SC_OPT_STREAM_K, stream_k)
+        got.append((B.sparse_conv_plan_kernel(layer.plan, 0), B.sparse_conv_plan_tiles(layer.plan, 0), R.bits_of(layer.sparse(x))))
+    if got[1][0] == "tile_stream_k":                                   # (no split here: no groups either)
+        B.sparse_conv_plan_set_option(layer.plan, B.SC_OPT_STREAM_K, 1)
+        got[1] = (B.sparse_conv_plan_kernel(layer.plan, 0), B.sparse_conv_plan_tiles(layer.plan, 0), R.bits_of(layer.sparse(x)))
+        assert got[0][:2] == got[1][:2]
+    elif got[0][0] == "tile_lds_direct":
+        assert got[1][0] == "tile_split_k"
+    assert np.array_equal(got[0][2], got[1][2])
+    if shape["cin"] == 512:
+        assert got[0][0] == "tile_lds_direct" and got[0][1][:2] == (64, 64)
