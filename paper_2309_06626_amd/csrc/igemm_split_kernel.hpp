@@ -334,14 +334,14 @@ __global__ __launch_bounds__(2 * BM * KS, 2) void igemm_split_kernel(const ConvP
     }
   };
   contract(std::false_type{});
-  bool odd = false;
+  float odd = 0.0f;
 #pragma unroll
   for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) odd |= acc[ni][v] != acc[ni][v];
+    for (int v = 0; v < 16; ++v) odd = not_finite(acc[ni][v], odd);
   if (t == 0) *s_flag = 0;
   __syncthreads();
-  if (odd) *s_flag = 1;
+  if (odd != odd) *s_flag = 1;
   __syncthreads();
   if (*s_flag) {
     __syncthreads();

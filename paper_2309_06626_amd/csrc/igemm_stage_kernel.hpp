@@ -8,8 +8,9 @@
 //     |x w|, less than the rounding of one float addition; the products themselves are exact in the matrix unit, x1w1
 //     and the five small ones go to accumulators of their own, and one MFMA adds sixteen of them, so fewer roundings
 //     happen than with the float MFMA (two per addition step).  A value that is not finite makes its remainder
-//     not-a-number and with it the sums it enters: a workgroup that finds one contracts its tile again with the float
-//     MFMA on the unsplit values (`careful` pass), which gives the infinities of the plain sum.
+//     not-a-number and with it the sums it enters, and a product of first parts may be infinite where that of the values
+//     is not: a workgroup whose sums are not all finite contracts its tile again with the float MFMA on the unsplit values
+//     (`careful` pass), which gives the infinities of the plain sum and no others.
 //   * NHWC channel counts that are no multiple of the 16-byte group (a pruned network run as it is): a group is an
 //     element-aligned 16-byte load inside one pixel.  The last group of a pixel is the one that ENDS at its last
 //     channel; the entries it repeats meet zero filter entries, and the careful pass clears them.
@@ -67,6 +68,8 @@ template <int DT, int BM, int BN> constexpr size_t stage_lds_bytes(int groups) {
   return 2 * (size_t)((BM + BN) / 32) * StageDims<DT>::BLOCK_BYTES * groups + (BM + BN) * 4;
 }
 
+// not-a-number once one of the values that passed through is infinite or not a number, else zero (an instruction a value)
+__device__ __forceinline__ float not_finite(float v, float before) { return __builtin_fmaf(v, 0.0f, before); }
 // (the two float halves of a packed pair of bf16, exactly)
 __device__ __forceinline__ float bf16_lo(uint32_t v) { return __builtin_bit_cast(float, v << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t v) { return __builtin_bit_cast(float, v & 0xffff0000u); }
@@ -92,9 +95,10 @@ __device__ __forceinline__ void split3(const float (&f)[8], v4i& p1, v4i& p2, v4
     p3[i] = (int)upper_halves(l[0], l[1]);
   }
 }
-// the float a triple of parts stands for (a value that is not finite has itself as the first part)
+// the float a triple of parts stands for (a value that is not finite has itself as the first part); the later parts first: of
+// the largest floats the first two add up to infinity
 __device__ __forceinline__ float join3(float a, float b, float c) {
-  return (__builtin_bit_cast(uint32_t, a) & 0x7f800000u) == 0x7f800000u ? a : (a + b) + c;
+  return (__builtin_bit_cast(uint32_t, a) & 0x7f800000u) == 0x7f800000u ? a : a + (b + c);
 }
 
 // Bias, activation, shortcut and store of a lane's 16 channels c0 .. c0 + 15 of output row rr, for any layout: 16-byte
@@ -612,13 +616,17 @@ __global__ __launch_bounds__(kThreads * KG, 2) void igemm_stage_kernel(const Con
   contract(std::false_type{});
   if constexpr (SPLIT || GATHER == kStageRaggedGroups) {
     bool odd = false;
+    float mark = 0.0f;
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
       for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) odd |= acc[mi][ni][v] != acc[mi][ni][v];
-    if (__syncthreads_or(odd && group == 0)) {
+        for (int v = 0; v < 16; ++v) {
+          if constexpr (SPLIT) mark = not_finite(acc[mi][ni][v], mark);
+          else odd |= acc[mi][ni][v] != acc[mi][ni][v];
+        }
+    if (__syncthreads_or((odd || mark != mark) && group == 0)) {
       clear();
       contract(std::true_type{});
     }

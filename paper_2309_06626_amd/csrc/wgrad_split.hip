@@ -10,7 +10,7 @@
 // on different halves of the banks.  A lane decodes one row a step and hands it round.
 // The sums of the four wavefronts meet in LDS and are added in order; partial sums per split, added in split order by the
 // reduction: results do not depend on scheduling.
-// A wavefront whose sums hold a value that is not a number contracts its rows again with the float MFMA on the unsplit
+// A wavefront whose sums are not all finite contracts its rows again with the float MFMA on the unsplit
 // values, which gives the infinities of the plain sum.
 //
 // What bounds it: the vector instructions that split and decode (about 300 per 24 MFMAs of a wavefront's step) next to the
@@ -186,7 +186,7 @@ __global__ __launch_bounds__(256, 2) void wgrad_split_kernel(const WgradSplitPar
     }
   };
   contract(std::false_type{});
-  bool odd = false;
+  float odd = 0.0f;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -194,9 +194,9 @@ __global__ __launch_bounds__(256, 2) void wgrad_split_kernel(const WgradSplitPar
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         acc[i][j][v] += small[i][j][v];
-        odd |= acc[i][j][v] != acc[i][j][v];
+        odd = not_finite(acc[i][j][v], odd);
       }
-  if (__ballot(odd)) contract(std::true_type{});
+  if (__ballot(odd != odd)) contract(std::true_type{});
 
   // ---- the four wavefronts' sums: [wavefront][block][16 bytes of a lane], block b of the tile added by wavefront b ------------
   __syncthreads();

@@ -101,6 +101,71 @@ def test_values_that_are_not_finite(dtype, cin, layout, where):
         assert torch.allclose(a[fin], b[fin], rtol=tol, atol=tol * float(b[fin].abs().max().clamp(max=100)))
 
 
+# The kernel that goes straight into LDS, groups and ragged groups through registers, channels first; K in one and in two shares.
+FLOAT_FORMS = [(32, 40, "nhwc", "64x32"), (32, 40, "nhwc", "64x64x2"), (20, 33, "nhwc", "64x64"), (13, 40, "nhwc", "64x64x2"), (8, 40, "nchw", "64x64")]
+
+
+def float_form(form, monkeypatch, where=None, **kw):
+    cin, cout, layout, tile = form
+    monkeypatch.setenv("SPARSE_CONV_STAGE_TILE", tile)
+    return spec_of(1, cin, 9, 10, cout, dtype="f32", layout=layout, relu=False, bias=False, sp=0.2, **kw)
+
+
+# largest finite products whose leading parts multiply to infinity: a first part rounds up to 2^64
+NEAR_THE_TOP = [2.0 ** 64 * (1 - 2.0 ** -24), 2.0 ** 64 * (1 - 2.0 ** -10)]
+
+
+@pytest.mark.parametrize("value", NEAR_THE_TOP)
+@pytest.mark.parametrize("form", FLOAT_FORMS)
+def test_finite_products_of_values_that_round_up(form, value, monkeypatch):
+    """x * w just below the largest float, one product a sum; and such a product beside one of the other sign."""
+    spec = float_form(form, monkeypatch, k=1, p=0)
+    ci = W.make_conv_inputs(spec, 1670)
+    v = np.float32(value)
+    x, w = np.zeros_like(ci.x), np.zeros_like(ci.w)
+    ch = (slice(None), slice(None), slice(None)) if spec.layout == "nhwc" else ()
+    x[(*ch, 2) if ch else (slice(None), 2)] = v
+    x[(*ch, 7) if ch else (slice(None), 7)] = v
+    wv = np.moveaxis(w, 3 if spec.layout == "nhwc" else 1, 0)          # [Cin, Cout, ...]
+    wv[2] = v
+    wv[7, ::2] = -v * np.float32(0.5)
+    layer = R.ConvLayer(spec, w, ci.bias, ci.mask)
+    assert B.sparse_conv_plan_kernel(layer.plan, 0) == "tile_staged"
+    y = rows_view(spec, R.to_host_f32(layer.sparse(R.to_device(x, "f32"))))[ci.mask == 1]
+    top = float(v) * float(v)
+    want = np.where(np.arange(spec.c_out) % 2 == 0, 0.5 * top, top)
+    assert np.all(np.abs(y - want) <= 2.0 ** -22 * top)
+
+
+@pytest.mark.parametrize("value", NEAR_THE_TOP)
+def test_float_filter_gradient_of_values_that_round_up(value):
+    """One product just below the largest float in a filter entry's sum."""
+    spec, x, dy, kept, layer, bwd = filter_gradient_case(1691)
+    x[:], dy[:] = 0.0, 0.0
+    row = int(np.flatnonzero(kept)[40])
+    n, oy, ox = row // 81, row % 81 // 9, row % 9
+    x[n, oy, ox, 5], dy[n, oy, ox, 3] = value, -value
+    got, want = filter_gradients(spec, x, dy, kept, bwd)
+    assert np.isfinite(got).all() and np.all(np.abs(got - want) <= 2.0 ** -22 * value * value)
+
+
+def filter_gradient_case(seed):
+    spec = W.ConvSpec("wg", n=2, c_in=16, h=9, w=9, c_out=24, dtype="f32", sparsity=0.3, relu=False)
+    ci = W.make_conv_inputs(spec, seed)
+    dy = np.random.default_rng(seed).standard_normal(spec.y_shape()).astype(np.float32)
+    layer = R.ConvLayer(spec, ci.w, ci.bias, ci.mask)
+    return spec, ci.x.copy(), dy, ci.mask == 1, layer, B.sparse_conv_backward_plan(layer.plan, layer.w)
+
+
+def filter_gradients(spec, x, dy, kept, bwd):
+    dw = torch.empty(spec.w_shape(), dtype=torch.float32, device="cuda:0")
+    B.sparse_conv_backward_run(bwd, R.to_device(x, "f32"), None, R.to_device(dy, "f32"), dw=dw)
+    a = np.pad(x.astype(np.float64), ((0, 0), (1, 1), (1, 1), (0, 0)))
+    a = np.stack([a[:, i:i + spec.h, j:j + spec.w] for i in range(3) for j in range(3)], 3).reshape(spec.m, -1)
+    g = dy.astype(np.float64).reshape(spec.m, -1)
+    return dw.cpu().numpy().astype(np.float64), (g[kept].T @ a[kept]).reshape(spec.w_shape())
+
+
 def test_plan_refresh_reaches_the_staged_filters_and_tile():
     spec = spec_of(2, 40, 12, 12, 48, dtype="f32", sp=0.5)
     a, b = W.make_conv_inputs(spec, 1590), W.make_conv_inputs(spec, 1591)
