@@ -302,10 +302,12 @@ __global__ __launch_bounds__(2 * BM * KS, 2) void igemm_split_kernel(const ConvP
       if (i + 1 < steps) k_tile(std::integral_constant<int, 1>{}, kt_lo + i + 1, careful_c);
     }
     __syncthreads();
+    if constexpr (!decltype(careful_c)::value) {
 #pragma unroll
-    for (int ni = 0; ni < NI; ++ni)
+      for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[ni][v] += small[ni][v];
+        for (int v = 0; v < 16; ++v) acc[ni][v] = (acc[ni][v] + small[ni][v]) * kSumScale;
+    }
     if constexpr (KS > 1) {
       v4f* part = reinterpret_cast<v4f*>(smem_all) + wave * (NI * 4 * 64) + lane;
       constexpr int SLOT = WAVES * NI * 4 * 64;

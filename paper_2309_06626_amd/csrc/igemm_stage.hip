@@ -57,25 +57,19 @@ struct StageOrder {
   }
 };
 
-// eight filter entries in three parts, K steps of a part apart
+// Eight filter entries in three parts, K steps of a part apart.  An entry that is not finite, or becomes so by the scaling, is
+// stored as its two halves with a second part that is not a number, so that every sum it enters asks for the careful pass.
 __device__ __forceinline__ void store_filter_parts(const float (&e)[8], v4i* __restrict__ dst) {
   using D = StageDims<kF32>;
   uint16_t parts[3][8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    const float f = e[i];
-    const uint32_t bits = __builtin_bit_cast(uint32_t, f);
-    const bool finite = (bits & 0x7f800000u) != 0x7f800000u;
-    float a = (float)(__bf16)f;
-    // a finite value that would round to infinity is cut instead; one that is not finite is its own first part and
-    // its second one is not a number, so that every sum it enters asks for the careful pass
-    if (finite && (__builtin_bit_cast(uint32_t, a) & 0x7f800000u) == 0x7f800000u) a = __builtin_bit_cast(float, bits & 0xffff0000u);
-    const float r = f - a;
-    const float b = finite ? (float)(__bf16)r : __builtin_nanf("");
-    const float c = finite ? r - b : 0.0f;
-    parts[0][i] = (uint16_t)(__builtin_bit_cast(uint32_t, a) >> 16);
-    parts[1][i] = (uint16_t)(__builtin_bit_cast(uint32_t, b) >> 16);
-    parts[2][i] = (uint16_t)(__builtin_bit_cast(uint32_t, c) >> 16);
+    const uint32_t bits = __builtin_bit_cast(uint32_t, e[i]);
+    const float v = e[i] * kPartScale, a = (float)(__bf16)v, r = v - a, b = (float)(__bf16)r, c = r - b;
+    const bool fits = (__builtin_bit_cast(uint32_t, a) & 0x7f800000u) != 0x7f800000u;
+    parts[0][i] = (uint16_t)((fits ? __builtin_bit_cast(uint32_t, a) : bits) >> 16);
+    parts[1][i] = fits ? (uint16_t)(__builtin_bit_cast(uint32_t, b) >> 16) : (uint16_t)0x7fc0;
+    parts[2][i] = fits ? (uint16_t)(__builtin_bit_cast(uint32_t, c) >> 16) : (uint16_t)bits;
   }
 #pragma unroll
   for (int q = 0; q < 3; ++q) {

@@ -2,15 +2,18 @@
 //
 // Serves the layers whose rows cannot be transferred as they lie in memory:
 //   * float operands.  The float MFMA runs at a sixteenth of the 16-bit rate, so a float tile is staged as three bf16
-//     parts: x = x1 + x2 + x3 with x1 = bf16(x), x2 = bf16(x - x1), x3 = x - x1 - x2.  The split is exact (24 significand
-//     bits in three times 8, the remainders are representable), and of the nine products of a pair of parts the six
-//     largest are contracted: x1w1, x1w2, x2w1, x2w2, x1w3, x3w1.  What is left out (x2w3, x3w2, x3w3) is below 2^-25 of
-//     |x w|, less than the rounding of one float addition; the products themselves are exact in the matrix unit, x1w1
-//     and the five small ones go to accumulators of their own, and one MFMA adds sixteen of them, so fewer roundings
-//     happen than with the float MFMA (two per addition step).  A value that is not finite makes its remainder
-//     not-a-number and with it the sums it enters, and a product of first parts may be infinite where that of the values
-//     is not: a workgroup whose sums are not all finite contracts its tile again with the float MFMA on the unsplit values
-//     (`careful` pass), which gives the infinities of the plain sum and no others.
+//     parts of the value times 2^24: x1 = bf16(2^24 x), x2 = bf16(2^24 x - x1), x3 = 2^24 x - x1 - x2, both rounded to
+//     nearest.  The split is exact for every float, subnormal ones included: the 24 significand bits go into three times
+//     eight, |x2| <= 2^-8 |2^24 x|, |x3| <= 2^-17 |2^24 x|, and the last bit of the smallest float is 2^-125 after the
+//     scaling, inside the range of a normal bf16 (unscaled, later parts of operands below 2^-110 would fall out of it).
+//     Of the nine products of a pair of parts the six largest are contracted: x1w1, x1w2, x2w1, x2w2, x1w3, x3w1.  What is
+//     left out (x2w3, x3w2, x3w3) is at most 2^-24 (1 + 2^-10) of |x w|, about the half unit of one rounding, and of no
+//     common sign.  The products themselves are exact in the matrix unit, x1w1 and the five small ones go to accumulators
+//     of their own, and one MFMA adds sixteen of them, so fewer roundings happen than with the float MFMA (two per addition
+//     step).  The sums are scaled back by 2^-48.  A value that is not finite makes its remainder not-a-number and with it
+//     the sums it enters; operands from 2^104 on, and sums from 2^80 on, become infinite by the scaling: a workgroup whose
+//     sums are not all finite contracts its tile again with the float MFMA on the unsplit values (`careful` pass), which
+//     gives the infinities of the plain sum and no others.
 //   * NHWC channel counts that are no multiple of the 16-byte group (a pruned network run as it is): a group is an
 //     element-aligned 16-byte load inside one pixel.  The last group of a pixel is the one that ENDS at its last
 //     channel; the entries it repeats meet zero filter entries, and the careful pass clears them.
@@ -70,35 +73,36 @@ template <int DT, int BM, int BN> constexpr size_t stage_lds_bytes(int groups) {
 
 // not-a-number once one of the values that passed through is infinite or not a number, else zero (an instruction a value)
 __device__ __forceinline__ float not_finite(float v, float before) { return __builtin_fmaf(v, 0.0f, before); }
+constexpr float kPartScale = 0x1p24f, kSumScale = 0x1p-48f;      // of the parts of a value, and back for their products
 // (the two float halves of a packed pair of bf16, exactly)
 __device__ __forceinline__ float bf16_lo(uint32_t v) { return __builtin_bit_cast(float, v << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t v) { return __builtin_bit_cast(float, v & 0xffff0000u); }
 // upper halves of two registers side by side
 __device__ __forceinline__ uint32_t upper_halves(uint32_t lo, uint32_t hi) { return __builtin_amdgcn_perm(hi, lo, 0x07060302u); }
-// Eight floats -> three parts of eight bf16.  The first part rounds to nearest (half away from zero: one integer addition;
-// it leaves remainders of either sign, so that the products left out have no common sign), the second one truncates; both
-// remainders are exact, and the last one has at most eight significand bits.
+// two floats, rounded to nearest, side by side
+__device__ __forceinline__ uint32_t bf16_pair(float lo, float hi) {
+  typedef float f2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 h2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{lo, hi}), h2));
+}
+// Eight floats -> three parts of eight bf16.  Both remainders are exact, and the last one has at most eight significand bits.
 __device__ __forceinline__ void split3(const float (&f)[8], v4i& p1, v4i& p2, v4i& p3) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    uint32_t h[2], m[2], l[2];
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const float v = f[2 * i + e];
-      h[e] = __builtin_bit_cast(uint32_t, v) + 0x8000u;
-      const float r = v - __builtin_bit_cast(float, h[e] & 0xffff0000u);
-      m[e] = __builtin_bit_cast(uint32_t, r);
-      l[e] = __builtin_bit_cast(uint32_t, r - __builtin_bit_cast(float, m[e] & 0xffff0000u));
-    }
-    p1[i] = (int)upper_halves(h[0], h[1]);
-    p2[i] = (int)upper_halves(m[0], m[1]);
-    p3[i] = (int)upper_halves(l[0], l[1]);
+    const float v0 = f[2 * i] * kPartScale, v1 = f[2 * i + 1] * kPartScale;
+    const uint32_t h = bf16_pair(v0, v1);
+    const float r0 = v0 - bf16_lo(h), r1 = v1 - bf16_hi(h);
+    const uint32_t m = bf16_pair(r0, r1);
+    p1[i] = (int)h;
+    p2[i] = (int)m;
+    p3[i] = (int)upper_halves(__builtin_bit_cast(uint32_t, r0 - bf16_lo(m)), __builtin_bit_cast(uint32_t, r1 - bf16_hi(m)));
   }
 }
-// the float a triple of parts stands for (a value that is not finite has itself as the first part); the later parts first: of
-// the largest floats the first two add up to infinity
+// the float a triple of packed filter parts stands for (igemm_stage.hip: where the second part is not a number, the others
+// hold the two halves of the value itself)
 __device__ __forceinline__ float join3(float a, float b, float c) {
-  return (__builtin_bit_cast(uint32_t, a) & 0x7f800000u) == 0x7f800000u ? a : a + (b + c);
+  if (b != b) return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, a) | (__builtin_bit_cast(uint32_t, c) >> 16));
+  return ((a + b) + c) * (1.0f / kPartScale);
 }
 
 // Bias, activation, shortcut and store of a lane's 16 channels c0 .. c0 + 15 of output row rr, for any layout: 16-byte
@@ -576,13 +580,13 @@ __global__ __launch_bounds__(kThreads * KG, 2) void igemm_stage_kernel(const Con
     if (steps & 1) compute_tile(even, careful_c, (Regs*)nullptr, (const Places*)nullptr);
     if (!decltype(careful_c)::value && steps == 1 && p.zero_fill) fill_zeros();
     wait_vmcnt<0>();                         // (no filters are on their way into LDS any more)
-    if constexpr (SPLIT) {
+    if constexpr (SPLIT && !decltype(careful_c)::value) {
 #pragma unroll
       for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
         for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) acc[mi][ni][v] += small[mi][ni][v];
+          for (int v = 0; v < 16; ++v) acc[mi][ni][v] = (acc[mi][ni][v] + small[mi][ni][v]) * kSumScale;
     }
     if constexpr (KG > 1) {
       __syncthreads();                       // every wavefront has left its tiles: their place takes the sums

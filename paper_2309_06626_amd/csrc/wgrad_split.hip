@@ -193,7 +193,7 @@ __global__ __launch_bounds__(256, 2) void wgrad_split_kernel(const WgradSplitPar
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        acc[i][j][v] += small[i][j][v];
+        acc[i][j][v] = (acc[i][j][v] + small[i][j][v]) * kSumScale;
         odd = not_finite(acc[i][j][v], odd);
       }
   if (__ballot(odd != odd)) contract(std::true_type{});

@@ -137,6 +137,25 @@ def test_finite_products_of_values_that_round_up(form, value, monkeypatch):
     assert np.all(np.abs(y - want) <= 2.0 ** -22 * top)
 
 
+@pytest.mark.parametrize("sx,sw", [(2.0 ** -118, 1.0), (1.0, 2.0 ** -118), (2.0 ** -124, 1.0), (1.0, 2.0 ** -124), (2.0 ** -126, 2.0 ** 100),
+                                   (2.0 ** 100, 2.0 ** -126), (2.0 ** -60, 2.0 ** -50), (2.0 ** 60, 2.0 ** 50), (2.0 ** -110, 2.0 ** 100)])
+@pytest.mark.parametrize("form", FLOAT_FORMS)
+def test_small_and_large_operands_keep_all_their_bits(form, sx, sw, monkeypatch):
+    spec = float_form(form, monkeypatch)
+    ci = W.make_conv_inputs(spec, 1680)
+    ci.x, ci.w = ci.x * np.float32(sx), ci.w * np.float32(sw)
+    layer = check_layer(ci)
+    assert B.sparse_conv_plan_kernel(layer.plan, 0) == "tile_staged"
+
+
+@pytest.mark.parametrize("sx,sg", [(2.0 ** -118, 1.0), (1.0, 2.0 ** -118), (2.0 ** -124, 2.0 ** 100), (2.0 ** 100, 2.0 ** -126), (2.0 ** 60, 2.0 ** 50)])
+def test_float_filter_gradient_keeps_small_and_large_operands(sx, sg):
+    spec, x, dy, kept, layer, bwd = filter_gradient_case(1690)
+    x, dy = x * np.float32(sx), dy * np.float32(sg)
+    got, want = filter_gradients(spec, x, dy, kept, bwd)
+    assert np.linalg.norm(got - want) <= 2e-6 * np.linalg.norm(want)
+
+
 @pytest.mark.parametrize("value", NEAR_THE_TOP)
 def test_float_filter_gradient_of_values_that_round_up(value):
     """One product just below the largest float in a filter entry's sum."""
