@@ -1409,9 +1409,9 @@ static StageTile stage_tile_for(const sc_conv_desc& d, const Geometry& g, int64_
 // does a run take it?  (not where a tile, a band kernel or another form of the tiled kernel was asked for)
 // (float layers that a band kernel serves keep it while they are small: 16 -> 16 @16, one image, 6.4 against 7.1 us;
 // 16 -> 16 @56, four images, 6.9 against 7.3; with 2.3e8 multiply-adds in all rows 10.4 and 11.4 against 9.5 and 10.8; one
-// line for the sparse and the dense run, see above)
-static bool use_stage(const sc_plan* pl, int which) {
-  if (!pl->stage_pick[which].asked && pl->band.ok && (double)pl->geo.m * pl->geo.k * pl->desc.c_out < 8e7) return false;
+// line for the sparse and the dense run, see above; plain: no compact operand and no shortcut sum, which those bands do not have)
+static bool use_stage(const sc_plan* pl, int which, bool plain = true) {
+  if (plain && !pl->stage_pick[which].asked && pl->band.ok && (double)pl->geo.m * pl->geo.k * pl->desc.c_out < 8e7) return false;
   return pl->stage_pick[which].bm > 0 && pl->forced[which] == -1 && pl->gather_pipeline == 0 &&
          !(pl->masked_store == 2 && which == 0) && !pl->prefer_tiled[which];
 }
@@ -1520,9 +1520,10 @@ static sc_status launch_conv(const sc_plan* pl, bool dense, const void* x, const
   // (of the band and row-panel kernels only the alternating-group band kernel has a shortcut path: any other
   // fused launch takes a tiled kernel)
   const sc_plan::Slab slab = x_compact ? sc_plan::Slab{0, 1} : slab_pick(pl, which, rows);
+  const bool staged = use_stage(pl, which, !x_compact && !y_compact && !residual);
   const bool use_band = band.ok && !x_compact && !y_compact && (!residual || ((band.pp || band.tap) && !band.stream)) &&
                         (pl->forced[which] == kForceBand || (pl->forced[which] == -1 && !band.stream && !pl->prefer_tiled[which])) &&
-                        !(slab.bm && pl->slab >= 2) && !use_stage(pl, which);
+                        !(slab.bm && pl->slab >= 2) && !staged;
   if (use_band) {
     const BandPlan& b = band;
     BandParams q;
@@ -1653,7 +1654,7 @@ static sc_status launch_conv(const sc_plan* pl, bool dense, const void* x, const
     SC_HIP(fn(p, stream));
     return SC_OK;
   }
-  if (use_stage(pl, which)) {
+  if (staged) {
     ConvParams p;
     std::memset(&p, 0, sizeof(p));
     const StageTile tile = pl->stage_pick[which];
@@ -2418,9 +2419,9 @@ sc_status sparse_conv_plan_tiles(const sc_plan* plan, int32_t which, int32_t* ti
 }
 
 // name of the tiled kernel a launch of this plan takes when no band or row-panel kernel applies
-static const char* tiled_kernel_name(const sc_plan* plan, int32_t which) {
+static const char* tiled_kernel_name(const sc_plan* plan, int32_t which, bool plain) {
   const Geometry& g = plan->geo;
-  if (use_stage(plan, which)) return "tile_staged";
+  if (use_stage(plan, which, plain)) return "tile_staged";
   const TilePick tp = pick_tile(plan, which, which ? g.m : plan->kept);
   if (tp.masked) return "tile_masked_store";
   if (tp.splits > 1) return "tile_split_k";
@@ -2440,7 +2441,7 @@ const char* sparse_conv_plan_kernel(const sc_plan* plan, int32_t which) {
   const Geometry& g = plan->geo;
   if (slab_pick(plan, which, which ? g.m : plan->kept).bm) return "tile_slab";
   if (use_panel(plan, which, which ? g.m : plan->kept)) return "tile_row_panel";
-  return tiled_kernel_name(plan, which);
+  return tiled_kernel_name(plan, which, true);
 }
 
 const char* sparse_conv_plan_fused_kernel(const sc_plan* plan, int32_t which) {
@@ -2451,7 +2452,7 @@ const char* sparse_conv_plan_fused_kernel(const sc_plan* plan, int32_t which) {
       !(plan->slab >= 2 && slab_pick(plan, which, which ? plan->geo.m : plan->kept).bm))
     return band.tap ? "band_tap" : "band_alternating";
   if (slab_pick(plan, which, which ? plan->geo.m : plan->kept).bm) return "tile_slab";
-  return tiled_kernel_name(plan, which);
+  return tiled_kernel_name(plan, which, false);
 }
 
 sc_status sparse_conv_plan_set_tiles(sc_plan* plan, int32_t which, int32_t tile_m, int32_t tile_n) {

@@ -9,7 +9,7 @@ from oracle import oracle
 from paper_2309_06626_amd import binding as B
 from paper_2309_06626_amd import runtime as R
 from parity import check_layer, rows_view
-from test_gpu_compact import check_compact_output
+from test_gpu_compact import check_compact_output, run_compact_out
 from test_gpu_parity import spec_of
 from test_gpu_residual import check as check_residual
 
@@ -268,6 +268,23 @@ def test_small_float_bands_share_the_window(case, mask_mode):
     for out_mode in (B.SC_OUT_ZERO_FILL, B.SC_OUT_SCATTER_ONLY):
         layer = check_layer(W.make_conv_inputs(spec, 1640), tiles=(-1, 0), out_mode=out_mode)
         assert B.sparse_conv_plan_kernel(layer.plan, 0) == "band"
+
+
+def test_small_float_layers_without_a_band_form_run_staged(monkeypatch):
+    """Small float layers keep the band kernel; their fused and compact runs, which it does not have, take the staged one."""
+    spec = spec_of(2, 16, 12, 11, 16, dtype="f32", relu=False)
+    layer, ci = check_compact_output(spec, 1645)
+    assert B.sparse_conv_plan_kernel(layer.plan, 0) == "band"
+    assert B.sparse_conv_plan_fused_kernel(layer.plan, 0) == B.sparse_conv_plan_fused_kernel(layer.plan, 1) == "tile_staged"
+    check_residual(spec, 1646, True)
+    check_residual(spec, 1647, False, y_compact=True)
+    x = R.to_device(ci.x, "f32")
+    _, bits = run_compact_out(layer, x)
+    same = []
+    for tile in ("64x32", "64x32x2", "64x32x4"):                       # (results depend on the shares of K, not on the tile)
+        monkeypatch.setenv("SPARSE_CONV_STAGE_TILE", tile)
+        same.append(np.array_equal(run_compact_out(R.ConvLayer(spec, ci.w, ci.bias, ci.mask), x)[1], bits))
+    assert any(same)
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
