@@ -1412,8 +1412,9 @@ static StageTile stage_tile_for(const sc_conv_desc& d, const Geometry& g, int64_
 // line for the sparse and the dense run, see above; plain: no compact operand and no shortcut sum, which those bands do not have)
 static bool use_stage(const sc_plan* pl, int which, bool plain = true) {
   if (plain && !pl->stage_pick[which].asked && pl->band.ok && (double)pl->geo.m * pl->geo.k * pl->desc.c_out < 8e7) return false;
-  return pl->stage_pick[which].bm > 0 && pl->forced[which] == -1 && pl->gather_pipeline == 0 &&
-         !(pl->masked_store == 2 && which == 0) && !pl->prefer_tiled[which];
+  // (options that name a form of the other kernels count only where that form applies)
+  return pl->stage_pick[which].bm > 0 && pl->forced[which] == -1 && (pl->gather_pipeline == 0 || !pl->geo.vec_gather) &&
+         !(pl->masked_store == 2 && which == 0 && plain && pl->desc.layout == SC_NHWC) && !pl->prefer_tiled[which];
 }
 static TilePick pick_tile(const sc_plan* pl, int which, int64_t rows) {
   TilePick tp;

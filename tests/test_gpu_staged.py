@@ -270,6 +270,16 @@ def test_small_float_bands_share_the_window(case, mask_mode):
         assert B.sparse_conv_plan_kernel(layer.plan, 0) == "band"
 
 
+@pytest.mark.parametrize("dtype,cin,layout", [("f32", 13, "nhwc"), ("bf16", 21, "nhwc"), ("f16", 16, "nchw"), ("f32", 16, "nchw")])
+def test_layers_ignore_options_of_other_kernels(dtype, cin, layout):
+    """The gather pipeline of 16-byte groups, and masked stores of NHWC runs, leave the other layers where they are."""
+    spec = spec_of(1, cin, 9, 9, 24, dtype=dtype, layout=layout)
+    options = [(B.SC_OPT_GATHER_PIPELINE, 1), (B.SC_OPT_GATHER_PIPELINE, 2)] + ([(B.SC_OPT_MASKED_STORE, 2)] if layout == "nchw" else [])
+    for option, value in options:
+        layer = check_layer(W.make_conv_inputs(spec, 1648), options={option: value})
+        assert B.sparse_conv_plan_kernel(layer.plan, 0) == B.sparse_conv_plan_kernel(layer.plan, 1) == "tile_staged"
+
+
 def test_small_float_layers_without_a_band_form_run_staged(monkeypatch):
     """Small float layers keep the band kernel; their fused and compact runs, which it does not have, take the staged one."""
     spec = spec_of(2, 16, 12, 11, 16, dtype="f32", relu=False)
