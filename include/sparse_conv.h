@@ -22,7 +22,10 @@
  *   library never allocates, frees or keeps device memory of its own.  Derived data (row
  *   index list, packed filters, gather table) lives in the caller's workspace, which must
  *   stay alive and untouched for as long as the plan is used.  The plan object itself is
- *   host memory owned by the library until sparse_conv_plan_destroy.
+ *   host memory owned by the library until sparse_conv_plan_destroy.  The first sparse_conv_plan
+ *   or sparse_conv_plan_set_mask of a process also makes one allocation of pinned host memory (66 560
+ *   bytes, into which kernels write the counts that these calls return), held until the process ends;
+ *   where it cannot be had, or more than 32 such calls are under way at once, the counts are copied.
  *   `hip_stream` is a hipStream_t passed as void* (NULL = the default stream).
  *
  * Errors
@@ -254,7 +257,9 @@ sc_status sparse_conv_plan_tune(sc_plan* plan, const void* x_dev, const float* b
  *                                                wavefronts share its K tiles (float NHWC); 0x0 = other kernels;
  *                                                automatic otherwise
  *   SPARSE_CONV_TILE_GROUPS=<rows>x<couts>x<1|2> tile of the automatic tiled launch of 16-bit layers and how many
- *                                                groups of wavefronts share its K tiles; automatic otherwise */
+ *                                                groups of wavefronts share its K tiles; automatic otherwise
+ *   SPARSE_CONV_HOST_SLOTS=0                     counts of a plan's row tables are copied from the device (read by
+ *                                                sparse_conv_plan_set_mask too) */
 
 /* Tuning hook: SC_OPT_GATHER_PIPELINE selects how the tiled gather kernel moves its K tiles:
  * 0 = automatic, 1 = global -> registers -> LDS, 2 = global -> LDS directly (NHWC with 16-byte

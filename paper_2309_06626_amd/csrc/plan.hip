@@ -437,9 +437,10 @@ __global__ __launch_bounds__(kTableThreads) void row_tables_kernel(const TablePa
   }
 }
 
-// Host memory that kernels write their few words for the host into: kHostSlots slots in one allocation, made on first use and
-// held until the process ends.  A call holds a slot from its launch to its synchronisation; one that finds none free (or no
-// such memory) copies from the device instead.
+// Host memory that kernels write their few words for the host into: kHostSlots slots in one allocation, made on first use
+// (in a way that a capture in another thread is not disturbed by) and held until the process ends.  A call holds a slot from its
+// launch to its synchronisation; one that finds none free (or no such memory), or whose stream is being captured, copies from
+// the device instead.  SPARSE_CONV_HOST_SLOTS=0: always (tests).
 constexpr int kTableSpanWgs = kTableMostRows / (128 * 256);
 constexpr int kHostSlots = 32, kHostSlotWords = kTableMostWgs * 4 + kTableSpanWgs * 2;
 struct HostSlots {
@@ -447,13 +448,20 @@ struct HostSlots {
   int32_t* base = nullptr;
   bool tried = false;
   uint32_t used = 0;
-  int32_t* take() {
+  int32_t* take(hipStream_t stream) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &status) != hipSuccess) { (void)hipGetLastError(); return nullptr; }
+    if (status != hipStreamCaptureStatusNone) return nullptr;      // (the call is refused at its synchronisation)
+    if (const char* env = std::getenv("SPARSE_CONV_HOST_SLOTS"); env && env[0] == '0') return nullptr;
     std::lock_guard<std::mutex> hold(lock);
     if (!tried) {
       tried = true;
       void* mem = nullptr;
+      hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+      const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
       if (hipHostMalloc(&mem, sizeof(int32_t) * kHostSlots * kHostSlotWords, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess) base = static_cast<int32_t*>(mem);
       else (void)hipGetLastError();
+      if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
     }
     if (!base) return nullptr;
     for (int i = 0; i < kHostSlots; ++i)
@@ -1902,7 +1910,7 @@ static sc_status build_row_tables(const sc_conv_desc& d, const Geometry& g, unsi
     magic_div((uint32_t)(g.ho * g.wo), &p.howo_mul, &p.howo_shift);
     magic_div((uint32_t)g.wo, &p.wo_mul, &p.wo_shift);
     magic_div((uint32_t)p.bh, &p.bh_mul, &p.bh_shift);
-    int32_t* slot = g_host_slots.take();
+    int32_t* slot = g_host_slots.take(stream);
     p.result = slot ? slot : counts;
     const int span_wgs = (int)((g.m + 128 * 256 - 1) / (128 * 256));
     int32_t copied[kHostSlotWords];

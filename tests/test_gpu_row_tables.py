@@ -1,5 +1,7 @@
 """The one-launch row tables of a plan (row list, mask copy, band tables, slab spans) at the edges of its segments, against the
 compaction of the oracle and, through the kernels that read the band tables, against the layer's oracle."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -64,3 +66,54 @@ def test_slab_spans(n, h, w):
     spec = W.ConvSpec("t", n=n, c_in=64, h=h, w=w, c_out=128, sparsity=0.6)
     layer = check_layer(W.make_conv_inputs(spec, 23), sample_rows=400, options={B.SC_OPT_SLAB: 2})
     assert B.sparse_conv_plan_kernel(layer.plan, 0) == "tile_slab"
+
+
+@pytest.mark.parametrize("case", [
+    dict(n=3, c_in=8, h=97, w=211, c_out=8, kh=1, kw=1, pad_h=0, pad_w=0),           # rows alone
+    dict(n=9, c_in=32, h=57, w=41, c_out=32, pad_h=1, pad_w=1),                       # band tables
+    dict(n=2, c_in=64, h=14, w=14, c_out=128, slab=True),                             # spans of one workgroup
+    dict(n=11, c_in=64, h=40, w=41, c_out=128, slab=True),                            # and of a second launch, behind the counts
+])
+def test_counts_copied_from_the_device_equal_those_in_host_memory(case, monkeypatch):
+    """The path of a call that has no slot of host memory: the same plan, the same bits."""
+    case = dict(case)
+    options = {B.SC_OPT_SLAB: 2} if case.pop("slab", False) else {}
+    spec = W.ConvSpec("t", sparsity=0.6, **case)
+    ci, other = W.make_conv_inputs(spec, 29), W.make_conv_inputs(spec, 30)
+    x, got = R.to_device(ci.x, spec.dtype), []
+    for slots in ("1", "0"):
+        monkeypatch.setenv("SPARSE_CONV_HOST_SLOTS", slots)
+        layer = check_layer(ci, sample_rows=300, options=options)
+        B.sparse_conv_plan_set_mask(layer.plan, torch.from_numpy(other.mask).cuda())
+        want = oracle.compact_rows(row_mask(spec, other.mask))
+        assert np.array_equal(B.plan_row_idx(layer.plan).cpu().numpy(), want)
+        got.append((B.sparse_conv_plan_kernel(layer.plan, 0), B.sparse_conv_plan_tiles(layer.plan, 0), R.bits_of(layer.sparse(x)).tobytes()))
+    assert got[0] == got[1]
+
+
+def test_refreshes_of_several_threads_at_once():
+    """Plans refreshed by eight threads on streams of their own: every call finds its own counts."""
+    def work(i):
+        try:
+            rng = np.random.default_rng(40 + i)
+            spec = W.ConvSpec("t", n=1 + i, c_in=32, h=21 + i, w=30, c_out=32, pad_h=1, pad_w=1, sparsity=0.5)
+            ci = W.make_conv_inputs(spec, 41 + i)
+            with torch.cuda.stream(torch.cuda.Stream()):
+                layer = R.ConvLayer(spec, ci.w, ci.bias, ci.mask, check_count=False)
+                for _ in range(40):
+                    m = (rng.random(spec.mask_len) < rng.random()).astype(np.uint8)
+                    B.sparse_conv_plan_set_mask(layer.plan, torch.from_numpy(m).cuda())
+                    want = oracle.compact_rows(row_mask(spec, m))
+                    assert B.sparse_conv_plan_info(layer.plan)["kept"] == want.size
+                    if want.size:
+                        assert np.array_equal(B.plan_row_idx(layer.plan).cpu().numpy(), want)
+        except BaseException as e:              # noqa: BLE001 -- reported below, in the test's own thread
+            failed.append(e)
+
+    failed = []
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(8)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failed, failed[0]
