@@ -14,7 +14,7 @@
  *     activation (Alg. 2, post-process);  bias and ReLU act on kept rows only;
  *   - zero padding, cross-correlation, Ho = floor((H + 2*pad - dil*(kh-1) - 1)/stride) + 1;
  *   - SC_NHWC: x[N,H,W,Cin], w[Cout,kh,kw,Cin], y[N,Ho,Wo,Cout]   (fast path)
- *     SC_NCHW: x[N,Cin,H,W], w[Cout,Cin,kh,kw], y[N,Cout,Ho,Wo]   (element-wise gather path)
+ *     SC_NCHW: x[N,Cin,H,W], w[Cout,Cin,kh,kw], y[N,Cout,Ho,Wo]   (one load per window entry)
  *   - x, w and y share one element type; bias is always float; accumulation is float.
  *
  * Memory and ownership
@@ -236,8 +236,11 @@ sc_status sparse_conv_plan_set_tiles(sc_plan* plan, int32_t which, int32_t tile_
  * many times and holds the masked convolution of x when the call returns.  Candidates are timed as captured graphs
  * of back-to-back launches on a stream the call creates and destroys (with two events; default priority), so that
  * layers of a few microseconds are not measured at the host's launch rate; `hip_stream` is synchronised first and
- * last; no device memory is allocated.  Choices forced with
- * sparse_conv_plan_set_tiles stay as they are; sparse_conv_plan_set_mask returns the sparse run to the model's choice.
+ * last; no device memory is allocated.  Layers of "tile_staged" (float ones, channel counts off the 16-byte group, SC_NCHW):
+ * its tiles and shares of K, the band kernel and the other tiles are timed with the sparse run, and the dense run takes the
+ * fastest form of the kernel chosen with the same shares, so that both runs add a row's products in the same order.  Choices
+ * forced with sparse_conv_plan_set_tiles (of these layers: for either run) or by the environment stay as they are;
+ * sparse_conv_plan_set_mask returns the sparse run (of these layers: both runs) to the model's choice.
  */
 sc_status sparse_conv_plan_tune(sc_plan* plan, const void* x_dev, const float* bias_dev, void* y_dev, void* hip_stream);
 
@@ -254,8 +257,8 @@ sc_status sparse_conv_plan_tune(sc_plan* plan, const void* x_dev, const float* b
  *   SPARSE_CONV_STAGE_TILE=<rows>x<couts>[x<groups>]
  *                                                tile of the kernel reported as "tile_staged" (float layers, channel
  *                                                counts off the 16-byte group, SC_NCHW) and how many groups of
- *                                                wavefronts share its K tiles (float NHWC); 0x0 = other kernels;
- *                                                automatic otherwise
+ *                                                wavefronts share its K tiles (1 or 2; float NHWC with 16-byte groups
+ *                                                in and out also 4); 0x0 = other kernels; automatic otherwise
  *   SPARSE_CONV_TILE_GROUPS=<rows>x<couts>x<1|2> tile of the automatic tiled launch of 16-bit layers and how many
  *                                                groups of wavefronts share its K tiles; automatic otherwise
  *   SPARSE_CONV_HOST_SLOTS=0                     counts of a plan's row tables are copied from the device (read by

@@ -1082,6 +1082,7 @@ struct sc_plan {
   // slab form of the tiled kernel (deep 3x3 layers)
   struct Slab { int bm, splits; };
   StageTile stage_pick[2];         // tile of the register-staged kernel for the sparse / dense run (bm == 0: another kernel)
+  int stage_tuned;                 // sparse_conv_plan_tune measured that kernel fastest (1) or slower than another (-1); 0: not timed
   bool slab_ok;                    // the layer's geometry admits it
   int slab;                        // 0 = automatic, 1 = never, 2 = wherever it applies, 128 / 256 = with tiles of that many rows
   int slab_span[2][2];             // [sparse, dense run][128-row, 256-row tiles]: virtual rows of the widest tile's slab
@@ -1419,7 +1420,8 @@ static StageTile stage_tile_for(const sc_conv_desc& d, const Geometry& g, int64_
 // 16 -> 16 @56, four images, 6.9 against 7.3; with 2.3e8 multiply-adds in all rows 10.4 and 11.4 against 9.5 and 10.8; one
 // line for the sparse and the dense run, see above; plain: no compact operand and no shortcut sum, which those bands do not have)
 static bool use_stage(const sc_plan* pl, int which, bool plain = true) {
-  if (plain && !pl->stage_pick[which].asked && pl->band.ok && (double)pl->geo.m * pl->geo.k * pl->desc.c_out < 8e7) return false;
+  if (plain && pl->stage_tuned < 0) return false;
+  if (plain && !pl->stage_tuned && !pl->stage_pick[which].asked && pl->band.ok && (double)pl->geo.m * pl->geo.k * pl->desc.c_out < 8e7) return false;
   // (options that name a form of the other kernels count only where that form applies)
   return pl->stage_pick[which].bm > 0 && pl->forced[which] == -1 && (pl->gather_pipeline == 0 || !pl->geo.vec_gather) &&
          !(pl->masked_store == 2 && which == 0 && plain && pl->desc.layout == SC_NHWC) && !pl->prefer_tiled[which];
@@ -2076,6 +2078,7 @@ sc_status sparse_conv_plan(const sc_conv_desc* desc, const uint8_t* mask_dev, co
   pl->pick[1] = model_pick(pl, 1, g.m);
   pl->band = bp;
   pl->band_dense = plan_band(d, g, g.m);
+  pl->stage_tuned = 0;
   pl->stage_pick[0] = stage_tile_for(d, g, pl->kept);
   pl->stage_pick[1] = stage_tile_for(d, g, g.m, pl->stage_pick[0].bm ? pl->stage_pick[0].groups : 0);
   pl->slab = 0;
@@ -2109,6 +2112,8 @@ sc_status sparse_conv_plan_set_mask(sc_plan* plan, const uint8_t* mask_dev, void
   plan->band = bp;
   plan->pick[0] = model_pick(plan, 0, plan->kept);      // (a measured choice belonged to the previous mask's row count)
   plan->prefer_tiled[0] = false;
+  if (plan->stage_tuned) plan->prefer_tiled[1] = false;      // (both runs were chosen together)
+  plan->stage_tuned = 0;
   plan->stage_pick[0] = stage_tile_for(d, g, plan->kept);
   plan->stage_pick[1] = stage_tile_for(d, g, g.m, plan->stage_pick[0].bm ? plan->stage_pick[0].groups : 0);
   plan->slab_span[0][0] = slab_span[0]; plan->slab_span[0][1] = slab_span[1];
@@ -2255,27 +2260,11 @@ sc_status sparse_conv_plan_tune(sc_plan* plan, const void* x_dev, const float* b
     return best;
   };
   sc_status result = SC_OK;
-  for (int which = 0; which < 2 && result == SC_OK; ++which) {
+  // every tile x split (and the masked-store variant) of the tiled kernels that the model prices within 1.6 x of its best:
+  // the first that beats best_us by 1.5 % and all after it that beat the last
+  auto try_tiled = [&](int which, sc_plan::Pick* best_pick, double* best_us) -> bool {
     const bool dense = which == 1;
     const int64_t rows = dense ? plan->geo.m : plan->kept;
-    if (plan->forced[which] != -1 || rows == 0) continue;
-    plan->pick[which] = model_pick(plan, which, rows);
-    plan->prefer_tiled[which] = false;
-    if (time_us(dense, 100, 4) < 0.0) { result = SC_ERR_HIP; break; }     // clocks up before anything is compared
-    sc_plan::Pick best_pick = plan->pick[which];
-    bool best_tiled = false;
-    double best_us = time_us(dense, 40, 3);
-    if (best_us < 0.0) { result = SC_ERR_HIP; break; }
-    if (!plan->geo.vec_gather || plan->geo.rowseg) {                   // one tile shape serves these gathers
-      const BandPlan& rb = dense ? plan->band_dense : plan->band;
-      if (rb.ok && rb.rowband) {                                       // band kernel of the small-channel layers or that tile
-        plan->prefer_tiled[which] = true;
-        const double us = time_us(dense, 40, 3);
-        if (!(us > 0.0 && us < 0.985 * best_us)) plan->prefer_tiled[which] = false;
-      }
-      continue;
-    }
-    // candidates: every tile x split (and the masked-store variant) the model prices within 1.6 x of its best
     struct Cand { sc_plan::Pick pick; double predicted; };
     Cand cands[128];
     int n = 0;
@@ -2298,13 +2287,95 @@ sc_status sparse_conv_plan_tune(sc_plan* plan, const void* x_dev, const float* b
         best_pred = std::min(best_pred, cands[n++].predicted);
       }
     }
+    bool found = false;
     for (int c = 0; c < n; ++c) {
       if (cands[c].predicted > 1.6 * best_pred) continue;
       plan->pick[which] = cands[c].pick;
       plan->prefer_tiled[which] = true;
       const double us = time_us(dense, 40, 3);
-      if (us > 0.0 && us < 0.985 * best_us) { best_us = us; best_pick = cands[c].pick; best_tiled = true; }
+      if (us > 0.0 && us < 0.985 * *best_us) { *best_us = us; *best_pick = cands[c].pick; found = true; }
     }
+    return found;
+  };
+  // Layers of the staged kernel: its tiles and shares of K, the band kernel and the tiled ones.  The sparse run decides (where
+  // no row is kept the dense one), and the other run takes the fastest form of the same kernel with the same shares, so that
+  // both go on adding a row's products in one order.
+  const int lead = plan->kept > 0 ? 0 : 1;
+  const bool staged = plan->stage_pick[lead].bm > 0 && !plan->stage_pick[lead].asked && plan->forced[0] == -1 && plan->forced[1] == -1 &&
+                      (plan->gather_pipeline == 0 || !plan->geo.vec_gather) && plan->masked_store != 2;
+  if (staged) {
+    const sc_conv_desc& d = plan->desc;
+    plan->prefer_tiled[0] = plan->prefer_tiled[1] = false;
+    plan->stage_tuned = 0;
+    for (int which = 0; which < 2; ++which) plan->pick[which] = model_pick(plan, which, which ? plan->geo.m : plan->kept);
+    const bool band_first = !use_stage(plan, lead);
+    auto try_staged = [&](int which, int groups, StageTile* best, double* best_us) {
+      for (const int bm : {64, 128})
+        for (const int bn : {32, 64, 128}) {
+          const StageTile t = {bm, bn, groups, false};
+          if ((bn > 32 && d.c_out <= bn / 2) || !stage_launcher(d, plan->geo, t)) continue;
+          plan->stage_pick[which] = t;
+          double us = time_us(which == 1, 10, 1);      // (a look first: what takes 1.6 x as long is no serious candidate)
+          if (us > 1.6 * *best_us) continue;
+          us = time_us(which == 1, 40, 3);
+          if (us > 0.0 && us < *best_us) { *best_us = us; *best = t; }
+        }
+    };
+    if (time_us(lead == 1, 100, 4) < 0.0) result = SC_ERR_HIP;                // clocks up before anything is compared
+    plan->stage_tuned = 1;
+    StageTile tile = plan->stage_pick[lead];
+    double staged_us = result == SC_OK ? time_us(lead == 1, 40, 3) : -1.0;
+    if (staged_us < 0.0) result = SC_ERR_HIP;
+    for (int groups = 1; groups <= 4 && result == SC_OK; groups *= 2) try_staged(lead, groups, &tile, &staged_us);
+    plan->stage_pick[lead] = tile;
+    double best_us = staged_us;
+    if (result == SC_OK && plan->geo.vec_gather) {
+      const bool bands = plan->band.ok && !plan->band.stream && plan->band_dense.ok && !plan->band_dense.stream;
+      plan->stage_tuned = -1;
+      const double band_us = bands ? time_us(lead == 1, 40, 3) : -1.0;
+      bool band_wins = band_us > 0.0 && band_us < (band_first ? best_us / 0.985 : 0.985 * best_us);
+      if (band_wins) best_us = band_us;
+      sc_plan::Pick pick[2] = {plan->pick[0], plan->pick[1]};
+      const bool tiled_wins = try_tiled(lead, &pick[lead], &best_us);
+      plan->pick[lead] = pick[lead];
+      plan->prefer_tiled[lead] = tiled_wins;
+      plan->stage_tuned = tiled_wins || band_wins ? -1 : 1;
+      if (tiled_wins && lead == 0) {
+        double us = 1e300;
+        (void)try_tiled(1, &pick[1], &us);
+        plan->pick[1] = pick[1];
+        plan->prefer_tiled[1] = true;
+      }
+    }
+    if (result == SC_OK && lead == 0 && plan->stage_tuned > 0) {
+      StageTile other = plan->stage_pick[1] = stage_tile_for(d, plan->geo, plan->geo.m, tile.groups);
+      double us = time_us(true, 40, 3);
+      if (us < 0.0) result = SC_ERR_HIP;
+      else try_staged(1, tile.groups, &other, &us);
+      plan->stage_pick[1] = other;
+    }
+  }
+  for (int which = 0; which < 2 && result == SC_OK && !staged; ++which) {
+    const bool dense = which == 1;
+    const int64_t rows = dense ? plan->geo.m : plan->kept;
+    if (plan->forced[which] != -1 || rows == 0) continue;
+    plan->pick[which] = model_pick(plan, which, rows);
+    plan->prefer_tiled[which] = false;
+    if (time_us(dense, 100, 4) < 0.0) { result = SC_ERR_HIP; break; }     // clocks up before anything is compared
+    sc_plan::Pick best_pick = plan->pick[which];
+    bool best_tiled = false;
+    double best_us = time_us(dense, 40, 3);
+    if (best_us < 0.0) { result = SC_ERR_HIP; break; }
+    if (!plan->geo.vec_gather || plan->geo.rowseg) {                   // one tile shape serves these gathers
+      const BandPlan& rb = dense ? plan->band_dense : plan->band;
+      if (rb.ok && rb.rowband) {                                       // band kernel of the small-channel layers or that tile
+        plan->prefer_tiled[which] = true;
+        const double us = time_us(dense, 40, 3);
+        if (!(us > 0.0 && us < 0.985 * best_us)) plan->prefer_tiled[which] = false;
+      }
+      continue;
+    }
+    best_tiled = try_tiled(which, &best_pick, &best_us);
     plan->pick[which] = best_pick;
     plan->prefer_tiled[which] = best_tiled;
     // the slab form of the tiled kernel (deep 3x3 layers): both tile heights, the K splits around one workgroup per
@@ -2334,7 +2405,7 @@ sc_status sparse_conv_plan_tune(sc_plan* plan, const void* x_dev, const float* b
   }
   // A sparse run must not lose to the dense run of its own plan: where it still does, try the dense run's tile with
   // every row contracted and the mask applied at the store.
-  if (result == SC_OK && plan->forced[0] == -1 && plan->forced[1] == -1 && plan->kept > 0 && plan->kept < plan->geo.m &&
+  if (result == SC_OK && !staged && plan->forced[0] == -1 && plan->forced[1] == -1 && plan->kept > 0 && plan->kept < plan->geo.m &&
       plan->masked_store != 1 && plan->geo.vec_gather && !plan->geo.rowseg && plan->desc.layout == SC_NHWC) {
     const double us_sparse = time_us(false, 40, 3), us_dense = time_us(true, 40, 3);
     // (where the dense run takes a band or row-panel kernel, the tile is the one the dense run would take as a tiled launch)

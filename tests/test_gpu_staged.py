@@ -185,6 +185,35 @@ def filter_gradients(spec, x, dy, kept, bwd):
     return dw.cpu().numpy().astype(np.float64), (g[kept].T @ a[kept]).reshape(spec.w_shape())
 
 
+@pytest.mark.parametrize("dtype,layout,case", [
+    ("f32", "nhwc", dict(n=16, cin=64, h=12, w=12, cout=192)),          # staged, in one, two or four shares
+    ("f32", "nhwc", dict(n=4, cin=16, h=56, w=56, cout=16)),            # around the line between band and staged
+    ("f32", "nhwc", dict(n=2, cin=24, h=14, w=14, cout=35, k=1, p=0)),  # output rows off the 16-byte group
+    ("f16", "nhwc", dict(n=8, cin=51, h=14, w=14, cout=102)),
+    ("f32", "nchw", dict(n=2, cin=64, h=14, w=14, cout=64)),
+])
+def test_tuned_staged_layers(dtype, layout, case):
+    """Whatever sparse_conv_plan_tune picks: the oracle's results, kept rows with the bits of the dense run, and the model's
+    choice again after a new mask."""
+    spec = spec_of(dtype=dtype, layout=layout, sp=0.5, **case)
+    ci = W.make_conv_inputs(spec, 1595)
+    layer = R.ConvLayer(spec, ci.w, ci.bias, ci.mask)
+    x, y, d = R.to_device(ci.x, dtype), layer.new_output(), layer.new_output()
+    state = lambda: [(B.sparse_conv_plan_kernel(layer.plan, i), B.sparse_conv_plan_tiles(layer.plan, i)) for i in (0, 1)]
+    model = state()
+    B.sparse_conv_plan_tune(layer.plan, x, layer.bias, y)
+    assert state()[0][0] == state()[1][0] or "tile_masked_store" in state()[0][0]
+    B.dense_conv_run(layer.plan, x, layer.bias, d)
+    torch.cuda.synchronize()
+    kept = ci.mask == 1
+    got, ref = rows_view(spec, R.to_host_f32(y)), rows_view(spec, oracle.masked_conv2d(spec, ci.x, ci.w, ci.bias, ci.mask))
+    assert np.linalg.norm(got - ref) <= {"f32": 1e-5, "f16": 4e-3}[dtype] * np.linalg.norm(ref)
+    assert np.array_equal(rows_view(spec, R.bits_of(y))[kept], rows_view(spec, R.bits_of(d))[kept])
+    assert (rows_view(spec, R.bits_of(y))[~kept] == 0).all()
+    B.sparse_conv_plan_set_mask(layer.plan, torch.from_numpy(ci.mask).cuda())
+    assert state() == model
+
+
 def test_plan_refresh_reaches_the_staged_filters_and_tile():
     spec = spec_of(2, 40, 12, 12, 48, dtype="f32", sp=0.5)
     a, b = W.make_conv_inputs(spec, 1590), W.make_conv_inputs(spec, 1591)
