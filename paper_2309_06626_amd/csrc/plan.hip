@@ -1350,9 +1350,9 @@ static LaunchFn stage_launcher(const sc_conv_desc& d, const Geometry& g, StageTi
 }
 // Its tile for a run of `rows` rows.  SPARSE_CONV_STAGE_TILE=<bm>x<bn>[x<groups>] overrides (tuning and tests), 0x0 switches the
 // kernel off.
-// `groups` > 0 fixes the number of groups: the dense run takes that of the sparse one, so that both add a row's products in
-// the same order and a kept row carries the same bits in either.
-static StageTile stage_tile_for(const sc_conv_desc& d, const Geometry& g, int64_t rows, int groups = 0) {
+// `groups` > 0 fixes the number of groups: both runs of a plan take the same, so that they add a row's products in the same order
+// and a kept row carries the same bits in either (stage_tiles_for).  price: of the direct form, its predicted time.
+static StageTile stage_tile_for(const sc_conv_desc& d, const Geometry& g, int64_t rows, int groups = 0, double* price = nullptr) {
   StageTile none = {0, 0, 1, false};
   if (g.stage_gather < 0 || rows == 0) return none;
   int fbm = 0, fbn = 0, fgr = 1;
@@ -1387,6 +1387,7 @@ static StageTile stage_tile_for(const sc_conv_desc& d, const Geometry& g, int64_
       const double us = full * round_us(resident) + (rest ? round_us((rest + cus - 1) / cus) : 0.0);
       if (us < best_us) { best_us = us; best = sh.t; }
     }
+    if (price) *price = best_us;
     return best;
   }
   // Through registers (us a sparse run, s = 0.5 where not said).  64 rows keep most workgroups in flight: 64 x 64 / 128 x 64
@@ -1398,7 +1399,8 @@ static StageTile stage_tile_for(const sc_conv_desc& d, const Geometry& g, int64_
   // unit): 64 x 102 -> 102 @28 in fp16 at s = 0.3 28.1 / 40, 25.7 for 64 x 128 in one group.
   // Two groups of 64 x 64 / one where they are at most one round: 4 x 128 -> 128 @28 channels first in float 21.8 / 26.6,
   // 16 x 256 -> 256 @14 39 / 49, 410 -> 410 @7 22.4 / 27.2, 8 x 205 -> 205 @14 in fp16 14.2 / 17.2; two rounds: 20 x 37 -> 77
-  // @30 24.5 / 17.6; short K: 33 -> 30 @56 in bf16 (five tiles) no difference.  Tiles of 32 channels keep a wavefront to a row
+  // @30 24.5 / 17.6; short K: 33 -> 30 @56 in bf16 (five tiles) no difference; at one to three tiles the dense run, which takes the
+  // sparse run's groups in several rounds, loses up to half (16 x 3 -> 256 @28 in float 25.0 with two groups, 12.1 with one).  Tiles of 32 channels keep a wavefront to a row
   // block of its own and pay from a round of workgroups on: 64 x 64 / 128 x 32 for 16 x 33 -> 30 @56 in bf16 13.6 / 16.0.
   const int cus = device_cus();
   auto wgs_of = [&](int bm, int bn) { return ((rows + bm - 1) / bm) * ((d.c_out + bn - 1) / bn); };
@@ -1408,23 +1410,52 @@ static StageTile stage_tile_for(const sc_conv_desc& d, const Geometry& g, int64_
   }
   const bool wide = d.c_out > 64 && (d.c_out % 128 == 0 || d.c_out % 128 > 64);
   const int64_t wgs = wgs_of(64, 128);
-  if (wide && wgs >= cus * 3 / 4 && wgs <= cus && g.stage_gather >= kStageChunks && groups != 1)
+  if (wide && wgs >= cus * 3 / 4 && wgs <= cus && g.stage_gather >= kStageChunks && (groups == 0 ? kt >= 4 : groups == 2))
     return {64, 128, 2, false};
   if (wide && wgs > cus && d.dtype != SC_F32 && groups != 2) return {64, 128, 1, false};
   if (groups > 0) return {64, 64, groups, false};
   if (wgs_of(64, 64) <= cus && kt >= (d.dtype == SC_F32 ? 4 : 8)) return {64, 64, 2, false};
   return {64, 64, 1, false};
 }
+// The tiles of both runs.
+static void stage_tiles_for(const sc_conv_desc& d, const Geometry& g, int64_t kept, StageTile (&out)[2]) {
+  out[0] = stage_tile_for(d, g, kept);
+  if (out[0].bm && !out[0].asked && stage_is_direct(d, g)) {
+    // the number of groups that is best for both, the sparse run counting three times: by itself it would cut a short walk in four
+    // where the dense one then takes several rounds (4 x 96 -> 256 @28 pointwise, sparse / dense: 7.3 / 11.2 us)
+    double own[2], best = 1e300;
+    StageTile t[2];
+    (void)stage_tile_for(d, g, kept, 0, &own[0]);
+    (void)stage_tile_for(d, g, g.m, 0, &own[1]);
+    for (int groups = 1; groups <= 4; groups *= 2) {
+      double us[2];
+      t[0] = stage_tile_for(d, g, kept, groups, &us[0]);
+      t[1] = stage_tile_for(d, g, g.m, groups, &us[1]);
+      const double cost = 3.0 * us[0] / own[0] + us[1] / own[1];
+      if (t[0].bm && t[1].bm && cost < best) { best = cost; out[0] = t[0]; out[1] = t[1]; }
+    }
+    return;
+  }
+  out[1] = stage_tile_for(d, g, g.m, out[0].bm ? out[0].groups : 0);
+}
+enum LaunchForm { kPlainRun, kCompactRun, kFusedRun };      // dense operands; a compact one; with a shortcut sum
+// Layers that stay with the other kernels though the staged one could run them (one line for the sparse and the dense run, see
+// above; us, another kernel / staged).
+static bool leave_to_others(const sc_plan* pl, LaunchForm form) {
+  const sc_conv_desc& d = pl->desc;
+  const Geometry& g = pl->geo;
+  // Float layers that a band kernel serves, while they are small (there are no such bands for the other forms): 16 -> 16 @16, one
+  // image, 6.4 / 7.1; 16 -> 16 @56, four images, 6.9 / 7.3; with 2.3e8 multiply-adds in all rows 10.4 and 11.4 / 9.5 and 10.8.
+  if (form == kPlainRun && pl->band.ok && (double)g.m * g.k * d.c_out < 8e7) return true;
+  return false;
+}
 // does a run take it?  (not where a tile, a band kernel or another form of the tiled kernel was asked for)
-// (float layers that a band kernel serves keep it while they are small: 16 -> 16 @16, one image, 6.4 against 7.1 us;
-// 16 -> 16 @56, four images, 6.9 against 7.3; with 2.3e8 multiply-adds in all rows 10.4 and 11.4 against 9.5 and 10.8; one
-// line for the sparse and the dense run, see above; plain: no compact operand and no shortcut sum, which those bands do not have)
-static bool use_stage(const sc_plan* pl, int which, bool plain = true) {
-  if (plain && pl->stage_tuned < 0) return false;
-  if (plain && !pl->stage_tuned && !pl->stage_pick[which].asked && pl->band.ok && (double)pl->geo.m * pl->geo.k * pl->desc.c_out < 8e7) return false;
+static bool use_stage(const sc_plan* pl, int which, LaunchForm form = kPlainRun) {
+  if (form == kPlainRun && pl->stage_tuned < 0) return false;
+  if (pl->stage_tuned <= 0 && !pl->stage_pick[which].asked && leave_to_others(pl, form)) return false;
   // (options that name a form of the other kernels count only where that form applies)
   return pl->stage_pick[which].bm > 0 && pl->forced[which] == -1 && (pl->gather_pipeline == 0 || !pl->geo.vec_gather) &&
-         !(pl->masked_store == 2 && which == 0 && plain && pl->desc.layout == SC_NHWC) && !pl->prefer_tiled[which];
+         !(pl->masked_store == 2 && which == 0 && form == kPlainRun && pl->desc.layout == SC_NHWC) && !pl->prefer_tiled[which];
 }
 static TilePick pick_tile(const sc_plan* pl, int which, int64_t rows) {
   TilePick tp;
@@ -1531,7 +1562,7 @@ static sc_status launch_conv(const sc_plan* pl, bool dense, const void* x, const
   // (of the band and row-panel kernels only the alternating-group band kernel has a shortcut path: any other
   // fused launch takes a tiled kernel)
   const sc_plan::Slab slab = x_compact ? sc_plan::Slab{0, 1} : slab_pick(pl, which, rows);
-  const bool staged = use_stage(pl, which, !x_compact && !y_compact && !residual);
+  const bool staged = use_stage(pl, which, residual ? kFusedRun : x_compact || y_compact ? kCompactRun : kPlainRun);
   const bool use_band = band.ok && !x_compact && !y_compact && (!residual || ((band.pp || band.tap) && !band.stream)) &&
                         (pl->forced[which] == kForceBand || (pl->forced[which] == -1 && !band.stream && !pl->prefer_tiled[which])) &&
                         !(slab.bm && pl->slab >= 2) && !staged;
@@ -2079,8 +2110,7 @@ sc_status sparse_conv_plan(const sc_conv_desc* desc, const uint8_t* mask_dev, co
   pl->band = bp;
   pl->band_dense = plan_band(d, g, g.m);
   pl->stage_tuned = 0;
-  pl->stage_pick[0] = stage_tile_for(d, g, pl->kept);
-  pl->stage_pick[1] = stage_tile_for(d, g, g.m, pl->stage_pick[0].bm ? pl->stage_pick[0].groups : 0);
+  stage_tiles_for(d, g, pl->kept, pl->stage_pick);
   pl->slab = 0;
   pl->slab_ok = slab_geometry_ok(d, g) && slab_kernel(d.dtype == SC_BF16 ? kBF16 : kF16, 128, false);
   pl->slab_span[0][0] = slab_span[0]; pl->slab_span[0][1] = slab_span[1];
@@ -2114,8 +2144,7 @@ sc_status sparse_conv_plan_set_mask(sc_plan* plan, const uint8_t* mask_dev, void
   plan->prefer_tiled[0] = false;
   if (plan->stage_tuned) plan->prefer_tiled[1] = false;      // (both runs were chosen together)
   plan->stage_tuned = 0;
-  plan->stage_pick[0] = stage_tile_for(d, g, plan->kept);
-  plan->stage_pick[1] = stage_tile_for(d, g, g.m, plan->stage_pick[0].bm ? plan->stage_pick[0].groups : 0);
+  stage_tiles_for(d, g, plan->kept, plan->stage_pick);
   plan->slab_span[0][0] = slab_span[0]; plan->slab_span[0][1] = slab_span[1];
   plan->slab_auto[0] = sc_plan::Slab{0, 1};
   return SC_OK;
@@ -2499,9 +2528,9 @@ sc_status sparse_conv_plan_tiles(const sc_plan* plan, int32_t which, int32_t* ti
 }
 
 // name of the tiled kernel a launch of this plan takes when no band or row-panel kernel applies
-static const char* tiled_kernel_name(const sc_plan* plan, int32_t which, bool plain) {
+static const char* tiled_kernel_name(const sc_plan* plan, int32_t which, LaunchForm form) {
   const Geometry& g = plan->geo;
-  if (use_stage(plan, which, plain)) return "tile_staged";
+  if (use_stage(plan, which, form)) return "tile_staged";
   const TilePick tp = pick_tile(plan, which, which ? g.m : plan->kept);
   if (tp.masked) return "tile_masked_store";
   if (tp.splits > 1) return "tile_split_k";
@@ -2521,7 +2550,7 @@ const char* sparse_conv_plan_kernel(const sc_plan* plan, int32_t which) {
   const Geometry& g = plan->geo;
   if (slab_pick(plan, which, which ? g.m : plan->kept).bm) return "tile_slab";
   if (use_panel(plan, which, which ? g.m : plan->kept)) return "tile_row_panel";
-  return tiled_kernel_name(plan, which, true);
+  return tiled_kernel_name(plan, which, kPlainRun);
 }
 
 const char* sparse_conv_plan_fused_kernel(const sc_plan* plan, int32_t which) {
@@ -2532,7 +2561,7 @@ const char* sparse_conv_plan_fused_kernel(const sc_plan* plan, int32_t which) {
       !(plan->slab >= 2 && slab_pick(plan, which, which ? plan->geo.m : plan->kept).bm))
     return band.tap ? "band_tap" : "band_alternating";
   if (slab_pick(plan, which, which ? plan->geo.m : plan->kept).bm) return "tile_slab";
-  return tiled_kernel_name(plan, which, false);
+  return tiled_kernel_name(plan, which, kFusedRun);
 }
 
 sc_status sparse_conv_plan_set_tiles(sc_plan* plan, int32_t which, int32_t tile_m, int32_t tile_n) {

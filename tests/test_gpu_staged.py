@@ -309,6 +309,27 @@ def test_layers_ignore_options_of_other_kernels(dtype, cin, layout):
         assert B.sparse_conv_plan_kernel(layer.plan, 0) == B.sparse_conv_plan_kernel(layer.plan, 1) == "tile_staged"
 
 
+@pytest.mark.parametrize("case", [
+    dict(n=4, cin=256, h=28, w=28, cout=256, k=1, p=0, dtype="f32"),                     # straight into LDS
+    dict(n=16, cin=8, h=28, w=28, cout=256, k=1, p=0, dtype="f32", layout="nchw"),       # through registers, one K tile
+    dict(n=1, cin=13, h=30, w=20, cout=160, k=3, dtype="bf16"),
+])
+def test_groups_of_both_runs(case):
+    """The shares of K are chosen for the sparse and the dense run together: the same bits, and no dense run of several rounds of
+    workgroups that fill a compute unit each."""
+    spec = spec_of(sp=0.5, relu=False, **case)
+    layer = check_layer(W.make_conv_inputs(spec, 1649), sample_rows=300)
+    assert B.sparse_conv_plan_kernel(layer.plan, 0) == B.sparse_conv_plan_kernel(layer.plan, 1) == "tile_staged"
+    ci = W.make_conv_inputs(spec, 1649)
+    x, y, d = R.to_device(ci.x, spec.dtype), layer.new_output(), layer.new_output()
+    layer.sparse(x, y)
+    B.dense_conv_run(layer.plan, x, layer.bias, d)
+    assert np.array_equal(rows_view(spec, R.bits_of(y))[ci.mask == 1], rows_view(spec, R.bits_of(d))[ci.mask == 1])
+    if spec.c_in == 256:                               # four shares of 64 x 32 tiles took the dense run 12.7 us in two rounds, 9.0 now
+        bm, bn, wgs = B.sparse_conv_plan_tiles(layer.plan, 1)
+        assert wgs <= 256 or (bm, bn) != (64, 32)
+
+
 def test_small_float_layers_without_a_band_form_run_staged(monkeypatch):
     """Small float layers keep the band kernel; their fused and compact runs, which it does not have, take the staged one."""
     spec = spec_of(2, 16, 12, 11, 16, dtype="f32", relu=False)
