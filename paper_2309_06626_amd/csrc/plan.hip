@@ -1436,6 +1436,14 @@ static void stage_tiles_for(const sc_conv_desc& d, const Geometry& g, int64_t ke
     }
     return;
   }
+  // Through registers, one or two K tiles before many outputs: the stores are what counts, and the element gather, of which more
+  // workgroups share a compute unit, is as fast or faster where it stores 16-byte groups: 32 x 13 -> 256 @56 pointwise
+  // 35.7 / 37.8 us in bf16, 52 / 61 in float; 16 x 51 -> 256 @28 in bf16 8.2 / 9.1; fewer outputs 8.9 / 7.4 (half of the rows).
+  if (out[0].bm && !out[0].asked && d.layout == SC_NHWC && g.vec_out && g.stage_k_tiles <= (d.dtype == SC_F32 ? 2 : 1) &&
+      kept * d.c_out >= (int64_t)5 << 19) {
+    out[0] = out[1] = {0, 0, 1, false};
+    return;
+  }
   out[1] = stage_tile_for(d, g, g.m, out[0].bm ? out[0].groups : 0);
 }
 enum LaunchForm { kPlainRun, kCompactRun, kFusedRun };      // dense operands; a compact one; with a shortcut sum
@@ -1447,7 +1455,12 @@ static bool leave_to_others(const sc_plan* pl, LaunchForm form) {
   // Float layers that a band kernel serves, while they are small (there are no such bands for the other forms): 16 -> 16 @16, one
   // image, 6.4 / 7.1; 16 -> 16 @56, four images, 6.9 / 7.3; with 2.3e8 multiply-adds in all rows 10.4 and 11.4 / 9.5 and 10.8.
   if (form == kPlainRun && pl->band.ok && (double)g.m * g.k * d.c_out < 8e7) return true;
-  return false;
+  // Float layers with a short K and few outputs: the launch is most of the time, and the tiles that contract every row and mask at
+  // the store save the row list's round trip (fused launches do not have that form).  Half of the rows, plain / compact output, by K
+  // tiles of 32 entries, pointwise @28: 16 x 32 -> 64 (1) 4.7 / 6.1, 4.05 / 4.4; 64 -> 64 (2) 5.4 / 6.1, 4.75 / 5.05; 128 -> 64 (4)
+  // 6.9 / 7.2, 6.3 / 6.2; 160 -> 64 (5) 7.7 / 7.3; more outputs: 16 x 32 -> 256 (1) 9.4 / 10.1, 96 -> 256 (3) 12.1 / 11.6, 32 x 32 -> 64
+  // @56 (1) 16.2 / 13.8.
+  return form != kFusedRun && stage_is_direct(d, g) && g.stage_k_tiles <= 4 && (double)g.m * d.c_out * g.stage_k_tiles < 4e6;
 }
 // does a run take it?  (not where a tile, a band kernel or another form of the tiled kernel was asked for)
 static bool use_stage(const sc_plan* pl, int which, LaunchForm form = kPlainRun) {

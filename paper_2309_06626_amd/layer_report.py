@@ -321,6 +321,39 @@ def mask_generator_times(steps):
     return rows
 
 
+def run_cases(names, passes, timed):
+    """The calls of perf/cases.py, whole passes through the public entry points: each over three states in turn (inputs, plans
+    and buffers of three seeds), eager, `passes` of them between two synchronisations; us a pass, median of seven such blocks.
+    timed=False: the passes alone, the target of a rocprofv3 run."""
+    import time
+
+    import torch
+
+    import perf.cases as C
+
+    rows = []
+    for case in C.listed():
+        if names and case["name"] not in names:
+            continue
+        states = [C.prepare(case, seed) for seed in range(3 if timed else 1)]
+        blocks = []
+        for block in range(9 if timed else 1):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            for i in range(passes):
+                C.run(states[i % len(states)])
+            torch.cuda.synchronize()
+            blocks.append((time.perf_counter() - t0) / passes * 1e6)
+        us = sorted(blocks[2:])[3] if timed else float("nan")          # (the first two blocks warm up)
+        work = C.work(case)
+        rows.append({"case": case["name"], "us": us, **work})
+        if timed:
+            print(f"| {case['name']} | {us:.1f} | {work['bytes'] / us / 1e3:.0f} | {work['flops'] / us / 1e6:.1f} |", flush=True)
+        del states
+        torch.cuda.empty_cache()
+    return rows
+
+
 def oracle_times(want):
     """The CPU oracle (test infrastructure, timed here as the baseline the benchmark description asks for) on every layer
     of the wanted configurations with synthetic inputs of each layer's own shape: all host cores, and one thread (a child
@@ -383,6 +416,8 @@ def main():
                     help="NAME[:BMxBN][:splitN][:slabBM][:dense][:cold][:time][:backward[:dx]] -- only launch that layer of config 2 (s = 0.5), 3, 4 or 5 --steps times "
                          "(sparse run, or the dense run), optionally with a forced tile of the tiled kernel, N splits of K, the slab kernel with BM-row tiles, "
                          "optionally rotating through buffer copies larger than the memory-side cache: the target of a rocprofv3 run")
+    ap.add_argument("--cases", action="store_true", help="only time the calls of perf/cases.py, --steps passes at a time")
+    ap.add_argument("--profile-case", default="", help="only run --steps passes of that call of perf/cases.py: the target of a rocprofv3 run")
     args = ap.parse_args()
 
     import torch
@@ -396,6 +431,15 @@ def main():
     if os.environ.get("SPARSE_CONV_LIBRARY"):
         B.LIB_PATH = os.environ["SPARSE_CONV_LIBRARY"]
     B.lib()
+    if args.profile_case:
+        run_cases({args.profile_case}, args.steps, timed=False)
+        print(f"{args.profile_case}: {args.steps} passes")
+        return
+    if args.cases:
+        print("| call | us a pass | GB/s | TFLOP/s |")
+        print("|---|---|---|---|")
+        run_cases(set(), args.steps, timed=True)
+        return
     if args.profile_layer:
         from paper_2309_06626_amd import runtime as R
         from paper_2309_06626_amd.metrics import buffer_sets_for_cold_runs

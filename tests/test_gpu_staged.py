@@ -330,6 +330,26 @@ def test_groups_of_both_runs(case):
         assert wgs <= 256 or (bm, bn) != (64, 32)
 
 
+@pytest.mark.parametrize("cin,k", [(32, 1), (8, 1), (128, 1), (4, 3)])
+def test_short_float_walks_stay_with_the_float_tiles(cin, k):
+    """Plain and compact runs of small float layers of at most four K tiles; fused ones, and a fifth tile, are staged."""
+    spec = spec_of(2, cin, 19, 13, 48, k=k, p=k // 2, dtype="f32", relu=False)
+    layer = check_layer(W.make_conv_inputs(spec, 1651))
+    assert "staged" not in B.sparse_conv_plan_kernel(layer.plan, 0) and "staged" not in B.sparse_conv_plan_kernel(layer.plan, 1)
+    assert B.sparse_conv_plan_fused_kernel(layer.plan, 0) == "tile_staged"
+    check_compact_output(spec, 1652)
+    check_residual(spec, 1653, True, want_kernel=("tile_staged",))
+    longer = check_layer(W.make_conv_inputs(spec.with_(c_in=160), 1654))
+    assert B.sparse_conv_plan_kernel(longer.plan, 0) == "tile_staged"
+
+
+@pytest.mark.parametrize("dtype,sp,kernel", [("bf16", 0.1, "tile_elements"), ("f32", 0.1, "tile_elements"), ("bf16", 0.5, "tile_staged"), ("f32", 0.5, "tile_staged")])
+def test_many_outputs_behind_one_ragged_k_tile(dtype, sp, kernel):
+    spec = spec_of(4, 13, 56, 56, 256, k=1, p=0, dtype=dtype, sp=sp)
+    layer = check_layer(W.make_conv_inputs(spec, 1655), sample_rows=300)
+    assert B.sparse_conv_plan_kernel(layer.plan, 0) == B.sparse_conv_plan_kernel(layer.plan, 1) == kernel
+
+
 def test_small_float_layers_without_a_band_form_run_staged(monkeypatch):
     """Small float layers keep the band kernel; their fused and compact runs, which it does not have, take the staged one."""
     spec = spec_of(2, 16, 12, 11, 16, dtype="f32", relu=False)
