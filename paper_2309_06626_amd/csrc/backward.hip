@@ -774,8 +774,8 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* __restri
   }
 }
 
-// Both reductions of the float path in one launch (4.7 + 5.8 us apart, 6.2 us together at 51 splits of 64 x 576): the first `dw_blocks` workgroups are wgrad_reduce_kernel's, the others
-// colsum_final_kernel's (either may be none).
+// Both reductions of the float path in one launch (4.7 + 5.8 us apart, 6.2 us together at 56 splits of 64 x 576): the first
+// `dw_blocks` workgroups are wgrad_reduce_kernel's, the others colsum_final_kernel's (either may be none).
 __global__ __launch_bounds__(256) void float_reduce_kernel(const float* __restrict__ partial, int splits, int64_t count,
                                                            float* __restrict__ dw, int dw_blocks, const float* __restrict__ sums,
                                                            int slabs, int c, float* __restrict__ db) {
