@@ -61,10 +61,10 @@ def test_shortcut_and_compact_rows(dtype, cin, layout):
 
 @pytest.mark.parametrize("sx,sw", [(2.0 ** -60, 2.0 ** -50), (2.0 ** 60, 2.0 ** 50), (2.0 ** -110, 2.0 ** 100)])
 def test_float_parts_at_the_ends_of_the_range(sx, sw):
-    spec = spec_of(1, 24, 10, 10, 32, dtype="f32", bias=False)
+    spec = spec_of(1, 24, 10, 10, 36, dtype="f32", bias=False)          # (no band kernel: output channels off the 16-channel group)
     ci = W.make_conv_inputs(spec, 1560)
     ci.x, ci.w = ci.x * np.float32(sx), ci.w * np.float32(sw)
-    check_layer(ci)
+    assert B.sparse_conv_plan_kernel(check_layer(ci).plan, 0) == "tile_staged"
 
 
 VALUES = [np.inf, -np.inf, np.nan, 3.4e38, -3.4028235e38]
@@ -215,9 +215,10 @@ def test_tuned_staged_layers(dtype, layout, case):
 
 
 def test_plan_refresh_reaches_the_staged_filters_and_tile():
-    spec = spec_of(2, 40, 12, 12, 48, dtype="f32", sp=0.5)
+    spec = spec_of(2, 40, 12, 12, 44, dtype="f32", sp=0.5)
     a, b = W.make_conv_inputs(spec, 1590), W.make_conv_inputs(spec, 1591)
     layer = R.ConvLayer(spec, a.w, b.bias, a.mask)
+    assert B.sparse_conv_plan_kernel(layer.plan, 0) == "tile_staged"
     layer.sparse(R.to_device(a.x, "f32"))
     B.sparse_conv_plan_set_filters(layer.plan, R.to_device(b.w, "f32"))
     B.sparse_conv_plan_set_mask(layer.plan, torch.from_numpy(b.mask).cuda())
@@ -261,10 +262,13 @@ def test_float_filter_gradient_of_values_that_are_not_finite(value):
     assert torch.allclose(got[fin], want[fin], rtol=1e-4, atol=1e-4)
 
 
-@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("dtype,staged", [("f32", False), ("f32", True), ("bf16", False), ("f16", False)])
 @pytest.mark.parametrize("cin,cout,k", [(8, 40, 3), (64, 264, 1), (72, 16, 5)])
-def test_refreshed_filters_equal_those_of_a_new_plan(cin, cout, k, dtype):
-    """Forward and input gradient after set_filters (one launch each, the rotation folded in): the bits of fresh plans."""
+def test_refreshed_filters_equal_those_of_a_new_plan(cin, cout, k, dtype, staged, monkeypatch):
+    """Forward and input gradient after set_filters (one launch each, the rotation folded in): the bits of fresh plans.
+    staged: these layers are small enough for other kernels, so the float parts have to be asked for."""
+    if staged:
+        monkeypatch.setenv("SPARSE_CONV_STAGE_TILE", "64x32")
     spec = spec_of(2, cin, 9, 11, cout, k=k, p=k // 2, dtype=dtype, relu=False)
     a, b = W.make_conv_inputs(spec, 1630), W.make_conv_inputs(spec, 1631)
     x, dy = R.to_device(b.x, dtype), torch.randn(spec.y_shape(), device="cuda:0").to(B.TORCH_DTYPE[dtype])
@@ -272,6 +276,7 @@ def test_refreshed_filters_equal_those_of_a_new_plan(cin, cout, k, dtype):
     for first in (a.w, b.w):
         layer = R.ConvLayer(spec, first, b.bias, b.mask)
         bwd = B.sparse_conv_backward_plan(layer.plan, layer.w)
+        assert not staged or B.sparse_conv_plan_kernel(layer.plan, 0) == "tile_staged"
         if first is a.w:
             w = R.to_device(b.w, dtype)
             B.sparse_conv_plan_set_filters(layer.plan, w)
