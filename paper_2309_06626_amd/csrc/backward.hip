@@ -101,11 +101,10 @@ __global__ __launch_bounds__(256) void grad_map_kernel(const T* __restrict__ y, 
 }
 // Second pass: a workgroup owns four channels; 64 lanes per channel each add every 64th slab, then the 64
 // sub-sums are added in lane order.
-__global__ __launch_bounds__(256) void colsum_final_kernel(const float* __restrict__ partial, int slabs, int c,
-                                                           float* __restrict__ out) {
-  __shared__ float s_sub[64][5];
+__device__ __forceinline__ void colsum_final(float (*s_sub)[5], int block, const float* __restrict__ partial, int slabs, int c,
+                                             float* __restrict__ out) {
   const int e = threadIdx.x & 3, sl = threadIdx.x >> 2;
-  const int col = blockIdx.x * 4 + e;
+  const int col = block * 4 + e;
   float acc = 0.0f;
   if (col < c)
     for (int s = sl; s < slabs; s += 64) acc += partial[(int64_t)s * c + col];
@@ -116,6 +115,11 @@ __global__ __launch_bounds__(256) void colsum_final_kernel(const float* __restri
     for (int l = 0; l < 64; ++l) tot += s_sub[l][threadIdx.x];
     out[col] = tot;
   }
+}
+__global__ __launch_bounds__(256) void colsum_final_kernel(const float* __restrict__ partial, int slabs, int c,
+                                                           float* __restrict__ out) {
+  __shared__ float s_sub[64][5];
+  colsum_final(s_sub, blockIdx.x, partial, slabs, c, out);
 }
 
 // ---- filters for the input gradient: w'[ci][kh-1-ky][kw-1-kx][co] = w[co][ky][kx][ci] ---------------------------
@@ -750,11 +754,10 @@ static hipError_t wgrad2_launch(Wgrad2Params p, hipStream_t stream) {
 // dw[i] = sum over the splits of partial[s][i].  A workgroup owns 64 consecutive elements (16 groups of
 // four); 16 lanes per group each add every 16th split (independent 16-byte loads in flight), then the 16
 // sub-sums are added in lane order: the order of additions is fixed.  (Cout * K is a multiple of 64.)
-__global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* __restrict__ partial, int splits, int64_t count,
-                                                           float* __restrict__ dw) {
-  __shared__ v4f s_sub[16][17];
+__device__ __forceinline__ void wgrad_reduce(v4f (*s_sub)[17], int block, const float* __restrict__ partial, int splits, int64_t count,
+                                             float* __restrict__ dw) {
   const int e = threadIdx.x & 15, sl = threadIdx.x >> 4;
-  const int64_t i = ((int64_t)blockIdx.x * 16 + e) * 4;
+  const int64_t i = ((int64_t)block * 16 + e) * 4;
   v4f acc = {0.0f, 0.0f, 0.0f, 0.0f};
   if (i < count)
     for (int s = sl; s < splits; s += 16) {
@@ -774,48 +777,20 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* __restri
   }
 }
 
+__global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* __restrict__ partial, int splits, int64_t count,
+                                                           float* __restrict__ dw) {
+  __shared__ v4f s_sub[16][17];
+  wgrad_reduce(s_sub, blockIdx.x, partial, splits, count, dw);
+}
+
 // Both reductions of the float path in one launch (4.7 + 5.8 us apart, 6.2 us together at 56 splits of 64 x 576): the first
-// `dw_blocks` workgroups are wgrad_reduce_kernel's, the others colsum_final_kernel's (either may be none).
+// `dw_blocks` workgroups add the row splits, the others the column sums (either may be none).
 __global__ __launch_bounds__(256) void float_reduce_kernel(const float* __restrict__ partial, int splits, int64_t count,
                                                            float* __restrict__ dw, int dw_blocks, const float* __restrict__ sums,
                                                            int slabs, int c, float* __restrict__ db) {
   __shared__ __align__(16) unsigned char s_mem[sizeof(v4f) * 16 * 17];
-  if ((int)blockIdx.x < dw_blocks) {
-    v4f (*s_sub)[17] = reinterpret_cast<v4f (*)[17]>(s_mem);
-    const int e = threadIdx.x & 15, sl = threadIdx.x >> 4;
-    const int64_t i = ((int64_t)blockIdx.x * 16 + e) * 4;
-    v4f acc = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (i < count)
-      for (int s = sl; s < splits; s += 16) {
-        const v4f v = *reinterpret_cast<const v4f*>(partial + (int64_t)s * count + i);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[j] += v[j];
-      }
-    s_sub[sl][e] = acc;
-    __syncthreads();
-    if (threadIdx.x < 16 && i < count) {
-      v4f tot = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-      for (int l = 0; l < 16; ++l)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) tot[j] += s_sub[l][threadIdx.x][j];
-      *reinterpret_cast<v4f*>(dw + i) = tot;
-    }
-  } else {
-    float (*s_sub)[5] = reinterpret_cast<float (*)[5]>(s_mem);
-    const int e = threadIdx.x & 3, sl = threadIdx.x >> 2;
-    const int col = ((int)blockIdx.x - dw_blocks) * 4 + e;
-    float acc = 0.0f;
-    if (col < c)
-      for (int s = sl; s < slabs; s += 64) acc += sums[(int64_t)s * c + col];
-    s_sub[sl][e] = acc;
-    __syncthreads();
-    if (threadIdx.x < 4 && col < c) {
-      float tot = 0.0f;
-      for (int l = 0; l < 64; ++l) tot += s_sub[l][threadIdx.x];
-      db[col] = tot;
-    }
-  }
+  if ((int)blockIdx.x < dw_blocks) wgrad_reduce(reinterpret_cast<v4f (*)[17]>(s_mem), blockIdx.x, partial, splits, count, dw);
+  else colsum_final(reinterpret_cast<float (*)[5]>(s_mem), (int)blockIdx.x - dw_blocks, sums, slabs, c, db);
 }
 
 // The same for the partial results of wgrad2_kernel: per split Cout * K filter-gradient sums, then Cout bias-gradient
