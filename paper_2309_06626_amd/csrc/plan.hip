@@ -2370,6 +2370,7 @@ sc_status sparse_conv_plan_tune(sc_plan* plan, const void* x_dev, const float* b
     if (staged_us < 0.0) result = SC_ERR_HIP;
     for (int groups = 1; groups <= 4 && result == SC_OK; groups *= 2) try_staged(lead, groups, &tile, &staged_us);
     plan->stage_pick[lead] = tile;
+    if (lead == 0) plan->stage_pick[1] = stage_tile_for(d, plan->geo, plan->geo.m, tile.groups);
     double best_us = staged_us;
     if (result == SC_OK && plan->geo.vec_gather) {
       const bool bands = plan->band.ok && !plan->band.stream && plan->band_dense.ok && !plan->band_dense.stream;
@@ -2390,7 +2391,7 @@ sc_status sparse_conv_plan_tune(sc_plan* plan, const void* x_dev, const float* b
       }
     }
     if (result == SC_OK && lead == 0 && plan->stage_tuned > 0) {
-      StageTile other = plan->stage_pick[1] = stage_tile_for(d, plan->geo, plan->geo.m, tile.groups);
+      StageTile other = plan->stage_pick[1];
       double us = time_us(true, 40, 3);
       if (us < 0.0) result = SC_ERR_HIP;
       else try_staged(1, tile.groups, &other, &us);
