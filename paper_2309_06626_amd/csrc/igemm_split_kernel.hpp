@@ -10,10 +10,10 @@
 // What bounds it: a wavefront's own chain, splitting, then multiplying.  Six MFMAs per pair of blocks are 0.35 us a K tile of
 // 128 x 64 at the matrix pipes' rate; it costs 0.53 us with two workgroups on a compute unit, and a workgroup alone takes
 // 0.69 us a tile, one wait after the other, which is what the groups that share K are for.  On 64 -> 64 @56 at batch 32 the matrix
-// pipes and the vector issue are busy 31 % of the time each, LDS 11 %, and 392 workgroups are one and a half per compute unit
-// (profiles/float_and_ragged_layers_counters.md).  Measured at s = 0.5 (float MFMA before / this kernel, us; batch 32): 64 -> 64 @56
-// 58 / 31 (119 TFLOP/s of float arithmetic), 128 -> 128 @28 55 / 31, 256 -> 256 @14 61 / 38, batch 16 384 -> 384 @12 88 / 32, one
-// image of 128 -> 128 @28 32 / 15.  Error of the first against 64 bits: 3.0e-7 before, 1.0e-7 now.
+// pipes and the vector issue are busy 31 % of the time each, LDS 11 % (counters), and 392 workgroups are one and a half per compute
+// unit.  Measured at s = 0.5 (float MFMA before / this kernel, us; batch 32): 64 -> 64 @56 58 / 31 (119 TFLOP/s of float
+// arithmetic), 128 -> 128 @28 55 / 31, 256 -> 256 @14 61 / 38, batch 16 384 -> 384 @12 88 / 32, one image of 128 -> 128 @28
+// 32 / 15.  Error of the first against 64 bits: 3.0e-7 before, 1.0e-7 now.
 //
 // Two tiles in LDS a group: 56 KB and four wavefronts for 128 x 64, 44 for 128 x 32, 40 KB and two for 64 x 64, 28 for 64 x 32, so
 // that two to five workgroups of one group share a compute unit and fill each other's waits.

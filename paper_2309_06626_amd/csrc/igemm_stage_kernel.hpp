@@ -29,10 +29,10 @@
 // What bounds it: no unit alone.  The rows of a K tile pass LDS twice (written by the threads that fetched them, read by the
 // wavefronts), and the phases of a workgroup (addresses, products, split and stores) are one after the other; the address units
 // are the busiest, 49 % of the time channels first in float (one load per entry), 57 % with the element-aligned groups of
-// 102 channels, next to 26 and 14 % of the matrix pipes, 20 % of the vector issue and 14 and 19 % of LDS
-// (profiles/float_and_ragged_layers_counters.md).  Row loads run two tiles ahead in registers; the table that says where
-// they go runs three ahead, because waiting for a load waits for all that were issued before it, and is read by scalar loads
-// where a wavefront shares its entries.  The filters need no registers: they go from memory to LDS as they lie, a tile ahead.
+// 102 channels, next to 26 and 14 % of the matrix pipes, 20 % of the vector issue and 14 and 19 % of LDS (counters).  Row loads
+// run two tiles ahead in registers; the table that says where they go runs three ahead, because waiting for a load waits for
+// all that were issued before it, and is read by scalar loads where a wavefront shares its entries.  The filters need no
+// registers: they go from memory to LDS as they lie, a tile ahead.
 // Measured at s = 0.5 (element gather / all through registers / this kernel, us): 32 x 128 -> 128 @28 channels first in float
 // 115 / 45 / 37, in bf16 84 / 27.5 / 21.5, 32 x 51 -> 64 @28 in bf16 - / 19.6 / 13.8; at s = 0.3 64 x 102 -> 102 @28 in fp16
 // 98 / 27.5 / 25.5, 51 -> 51 @56 110 / 44 / 40, 410 -> 410 @7 186 / 27 / 22.5.

@@ -14,9 +14,9 @@
 // values, which gives the infinities of the plain sum.
 //
 // What bounds it: the vector instructions that split and decode (about 300 per 24 MFMAs of a wavefront's step; the vector issue is
-// busy 59 % of the time, the matrix pipes 29 %, LDS 21 %: profiles/float_and_ragged_layers_counters.md) next to the matrix
-// work, with two wavefronts per SIMD.  16 x 64 -> 64 @56 at s = 0.5 (25 088 rows to contract): 72 us on the float
-// MFMA (wgrad_f32_kernel, which stays for windows past the validity bits and tensors past 2 GiB), 20 us here.
+// busy 59 % of the time, the matrix pipes 29 %, LDS 21 %: counters) next to the matrix work, with two wavefronts per SIMD.
+// 16 x 64 -> 64 @56 at s = 0.5 (25 088 rows to contract): 72 us on the float MFMA (wgrad_f32_kernel, which stays for windows past
+// the validity bits and tensors past 2 GiB), 20 us here.
 #include "wgrad_split.hpp"
 
 #include "igemm_stage_kernel.hpp"
