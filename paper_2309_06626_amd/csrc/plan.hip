@@ -1400,8 +1400,9 @@ static StageTile stage_tile_for(const sc_conv_desc& d, const Geometry& g, int64_
   // Two groups of 64 x 64 / one where they are at most one round: 4 x 128 -> 128 @28 channels first in float 21.8 / 26.6,
   // 16 x 256 -> 256 @14 39 / 49, 410 -> 410 @7 22.4 / 27.2, 8 x 205 -> 205 @14 in fp16 14.2 / 17.2; two rounds: 20 x 37 -> 77
   // @30 24.5 / 17.6; short K: 33 -> 30 @56 in bf16 (five tiles) no difference; at one to three tiles the dense run, which takes the
-  // sparse run's groups in several rounds, loses up to half (16 x 3 -> 256 @28 in float 25.0 with two groups, 12.1 with one).  Tiles of 32 channels keep a wavefront to a row
-  // block of its own and pay from a round of workgroups on: 64 x 64 / 128 x 32 for 16 x 33 -> 30 @56 in bf16 13.6 / 16.0.
+  // sparse run's groups in several rounds, loses up to half (16 x 3 -> 256 @28 in float 25.0 with two groups, 12.1 with one).
+  // Tiles of 32 channels keep a wavefront to a row block of its own and pay from a round of workgroups on: 64 x 64 / 128 x 32 for
+  // 16 x 33 -> 30 @56 in bf16 13.6 / 16.0.
   const int cus = device_cus();
   auto wgs_of = [&](int bm, int bn) { return ((rows + bm - 1) / bm) * ((d.c_out + bn - 1) / bn); };
   if (groups <= 1) {
