@@ -235,13 +235,11 @@ __global__ __launch_bounds__(kThreads) void igemm_panel_kernel(const ConvParams 
     const int n0 = n * BN;
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi) {
-      if (rr[mi] < 0) continue;
 #pragma unroll
       for (int ni = 0; ni < NI; ++ni) {
         const int c0 = n0 + wn0 + ni * 32 + 16 * fh;
         if (c0 >= p.c_out) continue;
-        store_kept_block<DT>(acc[mi][ni], rr[mi], c0, y, p.bias ? s_bias + c0 : nullptr, 0, p.relu, 1, p.c_out,
-                             p.ho_wo, 0, 0, 0);
+        store_block_pairs<DT>(acc[mi][ni], rr[mi], false, c0, y, p.bias ? s_bias + c0 : nullptr, p.relu, p.c_out);
       }
     }
     prev_full = rows_full && n0 + BN <= p.c_out;

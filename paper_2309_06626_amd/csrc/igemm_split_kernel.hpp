@@ -355,13 +355,13 @@ __global__ __launch_bounds__(2 * BM * KS, 2) void igemm_split_kernel(const ConvP
   __syncthreads();
 
   // ---- epilogue --------------------------------------------------------------------------------------------------------------
-  if (group == 0 && out_row >= 0) {
+  if (group == 0) {
 #pragma unroll
     for (int ni = 0; ni < NI; ++ni) {
       const int c0 = n0 + ni * 32 + 16 * fh;
       if (c0 >= p.c_out) continue;
-      store_kept_block_res<kF32>(acc[ni], out_row, c0, y, p.bias ? s_bias + (c0 - n0) : nullptr, 0, p.relu, VEC_OUT, p.c_out, p.ho_wo,
-                                 0, 0, 0, static_cast<const float*>(p.residual), p.residual_relu);
+      store_block_pairs<kF32, VEC_OUT == 1>(acc[ni], out_row, false, c0, y, p.bias ? s_bias + (c0 - n0) : nullptr, p.relu, p.c_out,
+                                            static_cast<const float*>(p.residual), p.residual_relu);
     }
   }
 }
