@@ -7,13 +7,15 @@
 // K, 16-byte groups exchanged like in igemm_dma_kernel) and the filters in the order of the plan's packed parts.  Both
 // arrive through `buffer_load ... lds`: no registers, no LDS stores.
 //
-// What bounds it: a wavefront's own chain, splitting, then multiplying.  Six MFMAs per pair of blocks are 0.35 us a K tile of
-// 128 x 64 at the matrix pipes' rate; it costs 0.53 us with two workgroups on a compute unit, and a workgroup alone takes
-// 0.69 us a tile, one wait after the other, which is what the groups that share K are for.  On 64 -> 64 @56 at batch 32 the matrix
-// pipes and the vector issue are busy 31 % of the time each, LDS 11 % (counters), and 392 workgroups are one and a half per compute
-// unit.  Measured at s = 0.5 (float MFMA before / this kernel, us; batch 32): 64 -> 64 @56 58 / 31 (119 TFLOP/s of float
-// arithmetic), 128 -> 128 @28 55 / 31, 256 -> 256 @14 61 / 38, batch 16 384 -> 384 @12 88 / 32, one image of 128 -> 128 @28
-// 32 / 15.  Error of the first against 64 bits: 3.0e-7 before, 1.0e-7 now.
+// What bounds it: the issue slots of a wavefront.  A K tile of 128 x 64 is 24 MFMAs (768 cycles), and about 110 instructions that
+// split, 16 LDS reads and 7 transfers at 5, 8 and 40 cycles; one after the other they took 1 950 cycles (0.885 us for a workgroup
+// alone), now 1 300 (0.57): the split of the next step and the transfers lie behind the MFMAs of this one, across the barrier, the
+// places of a tap's rows are worked out once a tap, and what was left of the loop's own bookkeeping (700 cycles without any work) went
+// with its branches.  Deeper rings of tiles (three, four) change nothing: no transfer is waited for.  Two workgroups on a compute unit
+// still take 1.15 us a pair of tiles, LDS and the address unit (1 300 and 900 cycles) beside 1 540 of products.
+// Measured at s = 0.5 (float MFMA / split one after the other / this kernel, us; batch 32):  64 -> 64 @56 58 / 31 / 28 (132 TFLOP/s of
+// float arithmetic), 128 -> 128 @28 55 / 28.5 / 25.8, 256 -> 256 @14 61 / 38 / 31, batch 16 384 -> 384 @12 88 / 32 / 29.8, one image of
+// 128 -> 128 @28 32 / 15 / 12.7, 96 -> 256 @28 pointwise - / 14.5 / 13.0.  The same bits as before.
 //
 // Two tiles in LDS a group: 56 KB and four wavefronts for 128 x 64, 44 for 128 x 32, 40 KB and two for 64 x 64, 28 for 64 x 32, so
 // that two to five workgroups of one group share a compute unit and fill each other's waits.
@@ -119,58 +121,72 @@ __global__ __launch_bounds__(2 * BM * KS, 2) void igemm_split_kernel(const ConvP
 
   const int step_x = p.dil_w * p.xs_w * 4, step_y = p.dil_h * p.xs_h * 4;
   int s_ci, s_ky, s_kx, s_off, s_kt;      // scalar walk over the window (TAPS), next K tile to issue
-  uint32_t s_bits;
+  uint32_t a_voff[A_LOADS];               // where the rows of that tile lie (TAPS: up to s_ci channels into the tap)
+  const int w_step = p.k_tiles * D::BLOCK_BYTES;
+  int s_w;                                // and its filters
+  auto aim = [&](int off, uint32_t need) {
+#pragma unroll
+    for (int j = 0; j < A_LOADS; ++j) a_voff[j] = (a_taps[j] & need) == need ? (uint32_t)(a_at[j] + off) : kOutOfRange;     // out of range: zeros
+  };
   auto rewind = [&]() {
     s_kt = kt_lo;
+    s_w = ((n0 / 32) * p.k_tiles + kt_lo) * D::BLOCK_BYTES;     // packed filters: [32 channels][K tile]
     if constexpr (TAPS) {
       const int tap = kt_lo * 32 / p.c_in;
       s_ci = kt_lo * 32 - tap * p.c_in;
       s_ky = tap / p.kw;
       s_kx = tap - s_ky * p.kw;
-      s_off = s_ci * 4 + s_kx * step_x + s_ky * step_y;
-      s_bits = (1u << s_ky) | (1u << (8 + s_kx));
+      s_off = s_kx * step_x + s_ky * step_y;
+      aim(s_off, (1u << s_ky) | (1u << (8 + s_kx)));
     } else {
       ke = p.ktab[min(s_kt, p.k_tiles - 1) * 8 + lc];
     }
   };
   rewind();
-  const int w_tile0 = (n0 / 32) * p.k_tiles;                  // packed filters: [32 channels][K tile]
-  auto issue_tile = [&](int stage) {
-    unsigned char* sa = smem + stage * STAGE_BYTES + wave * 8 * kRowBytes;
-    const uint32_t need = TAPS ? s_bits : (uint32_t)ke.dydx;
-    const int off = TAPS ? s_off : ke.off;
-#pragma unroll
-    for (int j = 0; j < A_LOADS; ++j) {
-      const uint32_t voff = (a_taps[j] & need) == need ? (uint32_t)(a_at[j] + off) : kOutOfRange;     // out of range: zeros
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void*)(sa + j * RPR * kRowBytes), 16, voff, 0, 0, 0);
-    }
-    unsigned char* sb = smem + stage * STAGE_BYTES + A_BYTES;
-#pragma unroll
-    for (int j = 0; j < B_LOADS; ++j) {
+  // Transfer number l of the next tile into slot `stage`: its filters, then its rows.  Past the end of a share the next one's
+  // tile, past the end of the walk the last filters and rows of the last window row arrive; nothing uses them.
+  constexpr int LOADS = A_LOADS + B_LOADS;
+  auto fetch_filters = [&](unsigned char* dst, int at) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void*)dst, 16, (uint32_t)(lane * 16), at, 0, 0);
+  };
+  auto fetch_rows = [&](unsigned char* dst, uint32_t at) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void*)dst, 16, at, TAPS ? s_ci * 4 : 0, 0, 0);
+  };
+  auto issue_one = [&](int stage, auto l_c) {
+    constexpr int l = decltype(l_c)::value;
+    if constexpr (l < B_LOADS) {
       // (a wavefront without a unit of its own in the last round repeats the last one: the same bytes to the same place)
-      const int u = min(wave + WAVES * j, B_UNITS - 1);
+      const int u = min(wave + WAVES * l, B_UNITS - 1);
       constexpr int PER = D::BLOCK_BYTES / 1024;
       const int nb = u / PER, in = u - nb * PER;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void*)(sb + u * 1024), 16, (uint32_t)(lane * 16),
-                                               (w_tile0 + nb * p.k_tiles + s_kt) * D::BLOCK_BYTES + in * 1024, 0, 0);
+      fetch_filters(smem + stage * STAGE_BYTES + A_BYTES + u * 1024, s_w + nb * w_step + in * 1024);
+    } else {
+      constexpr int j = l - B_LOADS;
+      if constexpr (!TAPS && j == 0) aim(ke.off, (uint32_t)ke.dydx);
+      fetch_rows(smem + stage * STAGE_BYTES + (wave * 8 + j * RPR) * kRowBytes, a_voff[j]);
     }
-    ++s_kt;
+  };
+  auto walk_on = [&]() {
+    if (++s_kt < p.k_tiles) s_w += D::BLOCK_BYTES;
     if constexpr (TAPS) {
       s_ci += 32;
-      s_off += 128;
       if (s_ci == p.c_in) {
         s_ci = 0;
-        s_off += step_x - p.c_in * 4;
+        s_off += step_x;
         if (++s_kx == p.kw) {
           s_kx = 0;
-          ++s_ky;
-          s_off += step_y - p.kw * step_x;
+          s_ky = min(s_ky + 1, p.kh - 1);
+          s_off = s_ky * step_y;
         }
-        s_bits = (1u << s_ky) | (1u << (8 + s_kx));
+        aim(s_off, (1u << s_ky) | (1u << (8 + s_kx)));
       }
     } else {
       ke = p.ktab[min(s_kt, p.k_tiles - 1) * 8 + lc];         // (used by the next call, a tile later)
     }
+  };
+  auto issue_tile = [&](int stage) {
+    static_for<LOADS>([&](auto l_c) { issue_one(stage, l_c); });
+    walk_on();
   };
 
   floatx16 acc[NI], small[NI];
@@ -191,65 +207,76 @@ __global__ __launch_bounds__(2 * BM * KS, 2) void igemm_split_kernel(const ConvP
       frag_a[ks][g] = lds0 + (unsigned)((wm0 + fp) * kRowBytes + (((4 * ks + 2 * fh + g) ^ (((wm0 + fp) >> 1) & 7)) << 4));
   const unsigned frag_b = lds0 + (unsigned)(A_BYTES + lane * 16);
 
-  struct Frags { v4i x[2]; v4i w[NI][3]; };
-  auto read_x = [&](auto stage_c, int ks, Frags& f) {
-    constexpr int SO = decltype(stage_c)::value * STAGE_BYTES;
-    f.x[0] = lds_read16_big<SO>(frag_a[ks][0]);
-    f.x[1] = lds_read16_big<SO>(frag_a[ks][1]);
+  struct Filters { v4i q[NI][3]; };
+  struct Parts { v4i q[3]; };
+  auto read_step = [&](auto stage_c, auto ks_c, v4i (&x)[2], Filters& f) {
+    constexpr int ST = decltype(stage_c)::value * STAGE_BYTES, ks = decltype(ks_c)::value;
+    x[0] = lds_read16_big<ST>(frag_a[ks][0]);
+    x[1] = lds_read16_big<ST>(frag_a[ks][1]);
+    static_for<NI>([&](auto ni_c) {
+      constexpr int at = ST + ks * 1024 + decltype(ni_c)::value * D::BLOCK_BYTES;
+      f.q[decltype(ni_c)::value][0] = lds_read16_big<at>(frag_b);
+      f.q[decltype(ni_c)::value][1] = lds_read16_big<at + 2048>(frag_b);
+      f.q[decltype(ni_c)::value][2] = lds_read16_big<at + 4096>(frag_b);
+    });
   };
-  auto read_w = [&](auto stage_c, auto ks_c, Frags& f) {
-    constexpr int SO = decltype(stage_c)::value * STAGE_BYTES + decltype(ks_c)::value * 1024;
-    auto block = [&](auto ni_c) {
-      constexpr int ni = decltype(ni_c)::value;
-      if constexpr (ni < NI) {
-        f.w[ni][0] = lds_read16_big<SO + ni * D::BLOCK_BYTES>(frag_b);
-        f.w[ni][1] = lds_read16_big<SO + ni * D::BLOCK_BYTES + 2048>(frag_b);
-        f.w[ni][2] = lds_read16_big<SO + ni * D::BLOCK_BYTES + 4096>(frag_b);
-      }
+  // the rows' fragments (behind them the filters' may still be on their way), or all of them, have landed; they pass through,
+  // so nothing that uses them moves above
+  auto rows_landed = [&](v4i (&x)[2]) { asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(x[0]), "+v"(x[1]) : "n"(3 * NI)); };
+  auto all_landed = [&](Filters& f) {
+    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f.q[0][0]), "+v"(f.q[0][1]), "+v"(f.q[0][2]));
+    if constexpr (NI == 2) asm volatile("" : "+v"(f.q[NI - 1][0]), "+v"(f.q[NI - 1][1]), "+v"(f.q[NI - 1][2]));
+  };
+  // product number i of a K step
+  auto product = [&](auto i_c, const Filters& f, const Parts& x) {
+    constexpr int i = decltype(i_c)::value / NI, ni = decltype(i_c)::value % NI;
+    constexpr int WQ[6] = {0, 1, 0, 1, 2, 0}, XQ[6] = {0, 0, 1, 1, 0, 2};
+    Elem<kBF16>::mma(i == 0 ? acc[ni] : small[ni], f.q[ni][WQ[i]], x.q[XQ[i]]);
+  };
+  // The products of one K step and, behind them, the split of the next step's rows and the transfers of the next tile: four to
+  // six vector instructions behind every MFMA, where the issue slot is free while the matrix unit works (a fifth costs nothing, an
+  // eighth 12 cycles), dealt out so that none waits for the one before it (8 cycles instead of 5).
+  constexpr int NP = 6 * NI, HEAD = NI == 2 ? 3 : 1, PIECES = 9;
+  auto products = [&](const Filters& f, const Parts& x, v4i (&nx)[2], Parts& np, auto transfer) {
+    float v[8], part[8];
+    int pk[3][4];
+    auto scale = [&](int e) { v[e] = __builtin_bit_cast(v4f, nx[e >> 2])[e & 3] * kPartScale; asm volatile("" : "+v"(v[e])); };
+    auto pack = [&](int third, int i) {
+      pk[third][i] = third == 2 ? (int)upper_halves(__builtin_bit_cast(uint32_t, v[2 * i]), __builtin_bit_cast(uint32_t, v[2 * i + 1]))
+                                : (int)bf16_pair(v[2 * i], v[2 * i + 1]);
+      asm volatile("" : "+v"(pk[third][i]));      // (not sunk to where the parts are used)
+      np.q[third][i] = pk[third][i];
     };
-    block(std::integral_constant<int, 0>{});
-    block(std::integral_constant<int, 1>{});
-  };
-  // at most N LDS reads still on their way; the fragments pass through, so nothing that uses them moves above
-  auto landed = [&](auto n_c, Frags& f) {
-    constexpr int N = decltype(n_c)::value;
-    asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(f.x[0]), "+v"(f.x[1]) : "n"(N));
-#pragma unroll
-    for (int ni = 0; ni < NI; ++ni) asm volatile("" : "+v"(f.w[ni][0]), "+v"(f.w[ni][1]), "+v"(f.w[ni][2]));
-  };
-  auto contract_step = [&](const Frags& f, auto careful_c) {
-    constexpr bool CAREFUL = decltype(careful_c)::value;
-    float x[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) x[e] = __builtin_bit_cast(v4f, f.x[e >> 2])[e & 3];
-    if constexpr (CAREFUL) {
-#pragma unroll
-      for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          auto part = [&](int q) {
-            const uint32_t v = (uint32_t)f.w[ni][q][e >> 1];
-            return (e & 1) ? bf16_hi(v) : bf16_lo(v);
-          };
-          acc[ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(join3(part(0), part(1), part(2)), x[e], acc[ni], 0, 0, 0);
-        }
-    } else {
-      using H = Elem<kBF16>;
-      v4i p1, p2, p3;
-      split3(x, p1, p2, p3);
-#pragma unroll
-      for (int ni = 0; ni < NI; ++ni) H::mma(acc[ni], f.w[ni][0], p1);
-#pragma unroll
-      for (int ni = 0; ni < NI; ++ni) H::mma(small[ni], f.w[ni][1], p1);
-#pragma unroll
-      for (int ni = 0; ni < NI; ++ni) H::mma(small[ni], f.w[ni][0], p2);
-#pragma unroll
-      for (int ni = 0; ni < NI; ++ni) H::mma(small[ni], f.w[ni][1], p2);
-#pragma unroll
-      for (int ni = 0; ni < NI; ++ni) H::mma(small[ni], f.w[ni][2], p1);
-#pragma unroll
-      for (int ni = 0; ni < NI; ++ni) H::mma(small[ni], f.w[ni][0], p3);
-    }
+    auto widen = [&](int third, int e) {
+      part[e] = e & 1 ? bf16_hi((uint32_t)pk[third][e >> 1]) : bf16_lo((uint32_t)pk[third][e >> 1]);
+      asm volatile("" : "+v"(part[e]));
+    };
+    auto rest = [&](int e) { v[e] -= part[e]; asm volatile("" : "+v"(v[e])); };
+    auto piece = [&](auto c_c) {
+      constexpr int c = decltype(c_c)::value;
+      if constexpr (c == 0) for (int e = 0; e < 6; ++e) scale(e);
+      if constexpr (c == 1) { scale(6); scale(7); for (int i = 0; i < 4; ++i) pack(0, i); }
+      if constexpr (c == 2) for (int e = 0; e < 6; ++e) widen(0, e);
+      if constexpr (c == 3) { widen(0, 6); widen(0, 7); for (int e = 0; e < 4; ++e) rest(e); }
+      if constexpr (c == 4) { for (int e = 4; e < 8; ++e) rest(e); pack(1, 0); pack(1, 1); }
+      if constexpr (c == 5) { pack(1, 2); pack(1, 3); for (int e = 0; e < 4; ++e) widen(1, e); }
+      if constexpr (c == 6) { for (int e = 4; e < 8; ++e) widen(1, e); rest(0); rest(1); }
+      if constexpr (c == 7) for (int e = 2; e < 8; ++e) rest(e);
+      if constexpr (c == 8) for (int i = 0; i < 4; ++i) pack(2, i);
+    };
+    static_for<NP>([&](auto i_c) {
+      constexpr int i = decltype(i_c)::value;
+      product(i_c, f, x);
+      __builtin_amdgcn_sched_barrier(0);
+      constexpr int l0 = i * LOADS / NP, l1 = (i + 1) * LOADS / NP;
+      static_for<l1 - l0>([&](auto l_c) { transfer(std::integral_constant<int, l0 + decltype(l_c)::value>{}); });
+      if constexpr (i == HEAD - 1) rows_landed(nx);
+      if constexpr (i >= HEAD) {
+        constexpr int c0 = (i - HEAD) * PIECES / (NP - HEAD), c1 = (i - HEAD + 1) * PIECES / (NP - HEAD);
+        static_for<c1 - c0>([&](auto c_c) { piece(std::integral_constant<int, c0 + decltype(c_c)::value>{}); });
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
   };
 
   auto fill_zeros = [&]() {
@@ -275,33 +302,94 @@ __global__ __launch_bounds__(2 * BM * KS, 2) void igemm_split_kernel(const ConvP
     }
   };
 
-  auto k_tile = [&](auto stage_c, int kt, auto careful_c) {      // kt: of this group's share
-    constexpr int ST = decltype(stage_c)::value;
+  using Zero = std::integral_constant<int, 0>;
+  using One = std::integral_constant<int, 1>;
+  const int n_kt = kt_hi - kt_lo;
+  auto arrive = [&]() {
     wait_vmcnt<0>();
-    __builtin_amdgcn_s_barrier();        // the tile has landed for every wavefront, and all have left the one before
+    __builtin_amdgcn_s_barrier();        // the tile has landed for every wavefront, and all have read the one before
     asm volatile("" ::: "memory");
-    if (kt + 1 < kt_hi) issue_tile(ST ^ 1);
-    if (KS > 1 && kt >= kt_hi) return;
-    Frags f0, f1;
-    read_x(stage_c, 0, f0);
-    read_w(stage_c, std::integral_constant<int, 0>{}, f0);
-    read_x(stage_c, 1, f1);
-    read_w(stage_c, std::integral_constant<int, 1>{}, f1);
-    landed(std::integral_constant<int, 2 + 3 * NI>{}, f0);
-    contract_step(f0, careful_c);
-    landed(std::integral_constant<int, 0>{}, f1);
-    contract_step(f1, careful_c);
+    __builtin_amdgcn_sched_barrier(0);
   };
-  auto contract = [&](auto careful_c) {
-    clear();
-    if (kt_lo < kt_hi) issue_tile(0);
-    for (int i = 0; i < steps; i += 2) {
-      k_tile(std::integral_constant<int, 0>{}, kt_lo + i, careful_c);
-      if constexpr (!decltype(careful_c)::value) {
-        if (i == 0 && p.zero_fill) fill_zeros();        // (these stores drain under the K loop)
-      }
-      if (i + 1 < steps) k_tile(std::integral_constant<int, 1>{}, kt_lo + i + 1, careful_c);
+  auto pipeline = [&]() {
+    Filters w0, w1;
+    Parts p0, p1;
+    v4i x[2];
+    issue_tile(0);
+    arrive();
+    issue_tile(1);
+    read_step(Zero{}, Zero{}, x, w0);
+    rows_landed(x);
+    {
+      float v[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = __builtin_bit_cast(v4f, x[e >> 2])[e & 3];
+      split3(v, p0.q[0], p0.q[1], p0.q[2]);
     }
+    all_landed(w0);
+    // tile i of the share, in slot S; the first half of the next one is read, and split, behind its second half
+    auto tile = [&](auto stage_c, int i) {
+      constexpr int S = decltype(stage_c)::value;
+      if (KS > 1 && i >= n_kt) {
+        arrive();
+        return;
+      }
+      read_step(stage_c, One{}, x, w1);
+      products(w0, p0, x, p1, [](auto) {});
+      all_landed(w1);
+      arrive();
+      // (behind the last tile this reads what lies there, and nothing uses it)
+      read_step(std::integral_constant<int, S ^ 1>{}, Zero{}, x, w0);
+      products(w1, p1, x, p0, [&](auto l_c) { issue_one(S, l_c); });
+      walk_on();
+      all_landed(w0);
+    };
+    tile(Zero{}, 0);
+    if (p.zero_fill) fill_zeros();        // (these stores drain under the K loop)
+    int i = 1;
+#pragma unroll 1
+    for (; i + 1 < steps; i += 2) {
+      tile(One{}, i);
+      tile(Zero{}, i + 1);
+    }
+    if (i < steps) tile(One{}, i);
+    wait_vmcnt<0>();
+  };
+  // the same sums on the float MFMA
+  auto careful_tile = [&](auto stage_c, int i) {
+    wait_vmcnt<0>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    issue_tile(decltype(stage_c)::value ^ 1);
+    if (KS > 1 && i >= n_kt) return;
+    static_for<2>([&](auto ks_c) {
+      v4i x[2];
+      Filters f;
+      read_step(stage_c, ks_c, x, f);
+      rows_landed(x);
+      all_landed(f);
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          auto part = [&](int q) {
+            const uint32_t v = (uint32_t)f.q[ni][q][e >> 1];
+            return (e & 1) ? bf16_hi(v) : bf16_lo(v);
+          };
+          acc[ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(join3(part(0), part(1), part(2)), __builtin_bit_cast(v4f, x[e >> 2])[e & 3], acc[ni], 0, 0, 0);
+        }
+    });
+  };
+  auto careful_walk = [&]() {
+    issue_tile(0);
+#pragma unroll 1
+    for (int i = 0; i < steps; i += 2) {
+      careful_tile(Zero{}, i);
+      if (i + 1 < steps) careful_tile(One{}, i + 1);
+    }
+    wait_vmcnt<0>();
+  };
+  auto finish = [&](auto careful_c) {          // the sums of the groups together
     __syncthreads();
     if constexpr (!decltype(careful_c)::value) {
 #pragma unroll
@@ -336,7 +424,9 @@ __global__ __launch_bounds__(2 * BM * KS, 2) void igemm_split_kernel(const ConvP
       __syncthreads();
     }
   };
-  contract(std::false_type{});
+  clear();
+  pipeline();
+  finish(std::false_type{});
   float odd = 0.0f;
 #pragma unroll
   for (int ni = 0; ni < NI; ++ni)
@@ -349,7 +439,9 @@ __global__ __launch_bounds__(2 * BM * KS, 2) void igemm_split_kernel(const ConvP
   if (*s_flag) {
     __syncthreads();
     rewind();
-    contract(std::true_type{});
+    clear();
+    careful_walk();
+    finish(std::true_type{});
   }
   for (int i = t; i < BN; i += NTALL) s_bias[i] = i == t ? bias_v : p.bias && n0 + i < p.c_out ? p.bias[n0 + i] : 0.0f;
   __syncthreads();

@@ -1363,12 +1363,12 @@ static StageTile stage_tile_for(const sc_conv_desc& d, const Geometry& g, int64_
     // Priced like the other tiled launches, with quantities measured on this kernel (us, MI355X): what a K tile costs a
     // compute unit with enough workgroups on it, what it costs a workgroup alone, and a round of workgroups beyond its K
     // loop.  Sparse runs at s = 0.5, chosen tile / 128 x 64 in one group / the float-MFMA kernel:  32 x 64 -> 64 @56
-    // 33 / 33 / 60;  128 -> 128 @28 31 / 38 / 55;  256 -> 256 @14 38 / 62 / 61;  16 x 384 -> 384 @12 32 / 87 / 88;
-    // 1 x 128 -> 128 @28 15 / 34 / 32 (batch 32 where not said; where few workgroups walk a long K, groups share it).
+    // 28 / 28 / 60;  128 -> 128 @28 25.8 / 28 / 55;  256 -> 256 @14 31 / 47 / 61;  16 x 384 -> 384 @12 29.9 / 67 / 88;
+    // 1 x 128 -> 128 @28 12.7 / 24.9 / 32 (batch 32 where not said; where few workgroups walk a long K, groups share it).
     struct Shape { StageTile t; double per_tile, alone; int waves; };
-    static const Shape shapes[] = {{{128, 64, 1, false}, 0.53, 0.69, 4}, {{128, 64, 2, false}, 0.53, 0.71, 8}, {{128, 32, 1, false}, 0.35, 0.50, 4},
-                                   {{128, 32, 2, false}, 0.35, 0.70, 8}, {{64, 64, 2, false}, 0.29, 0.70, 4},  {{64, 32, 1, false}, 0.21, 0.48, 2},
-                                   {{64, 32, 2, false}, 0.205, 0.48, 4}, {{64, 32, 4, false}, 0.205, 0.50, 8}};
+    static const Shape shapes[] = {{{128, 64, 1, false}, 0.57, 0.62, 4}, {{128, 64, 2, false}, 0.57, 0.97, 8},  {{128, 32, 1, false}, 0.32, 0.50, 4},
+                                   {{128, 32, 2, false}, 0.33, 0.76, 8}, {{64, 64, 1, false}, 0.27, 0.53, 2},   {{64, 64, 2, false}, 0.30, 0.72, 4},
+                                   {{64, 32, 1, false}, 0.185, 0.47, 2}, {{64, 32, 2, false}, 0.19, 0.585, 4}, {{64, 32, 4, false}, 0.19, 0.955, 8}};
     const int cus = device_cus();
     StageTile best = none;
     double best_us = 1e300;
@@ -1380,7 +1380,7 @@ static StageTile stage_tile_for(const sc_conv_desc& d, const Geometry& g, int64_
       const int steps = (kt + sh.t.groups - 1) / sh.t.groups;
       auto round_us = [&](int64_t on_cu) {
         double step = std::max(sh.alone, (double)on_cu * sh.t.groups * sh.per_tile);
-        if (sh.waves == 2 && on_cu >= 2) step = std::max(step, 0.95);       // (their wavefronts share two of the four SIMDs)
+        if (sh.waves == 2 && on_cu >= 2) step = std::max(step, 0.80);       // (their wavefronts share two of the four SIMDs)
         return 4.0 + steps * step;
       };
       const int64_t full = wgs / ((int64_t)cus * resident), rest = wgs - full * cus * resident;

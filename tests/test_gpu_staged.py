@@ -27,6 +27,15 @@ CASES = [
 ]
 
 
+@pytest.mark.parametrize("tile", ["128x64", "128x64x2", "128x32", "128x32x2", "64x64", "64x64x2", "64x32", "64x32x2", "64x32x4"])
+@pytest.mark.parametrize("cin,k", [(32, 1), (64, 1), (96, 1), (4, 3), (32, 3), (64, 3), (40, 3), (32, 2)])
+def test_float_walks(cin, k, tile, monkeypatch):
+    """One to eighteen K tiles, odd and even, tiles within a tap and across taps; shares that differ by a tile or hold none; the
+    step past the end of a walk, whose operands nothing may use."""
+    monkeypatch.setenv("SPARSE_CONV_STAGE_TILE", tile)
+    check_layer(W.make_conv_inputs(spec_of(n=2, cin=cin, h=11, w=9, cout=84, k=k, p=k // 2, dtype="f32", sp=0.35), 1571))
+
+
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
 @pytest.mark.parametrize("layout", ["nhwc", "nchw"])
 @pytest.mark.parametrize("case", range(len(CASES)))
