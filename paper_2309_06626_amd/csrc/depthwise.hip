@@ -1,8 +1,9 @@
 // Masked depthwise convolution (groups == Cin == Cout, NHWC): every channel is filtered by its own
 // kh x kw window and the mask removes output pixels exactly as for ordinary layers (Sec. 3: a dropped
 // pixel is dropped in all channels; Alg. 2: its output is zero).  There is no contraction over channels,
-// so nothing here is GEMM-shaped.  Three kernels: a general one (below), an LDS-tiled one for 3x3 windows
-// (float), and its two-term-dot-product form for the 16-bit types.
+// so nothing here is GEMM-shaped.  Four kernels: a general one (below), an LDS-tiled one for 3x3 windows
+// (float), its two-term-dot-product form for the 16-bit types with a compact operand, and one for the 16-bit types whose
+// lanes walk down the columns of dense operands.
 //
 // General kernel:
 //   lane      = one output pixel x one 16-byte group of channels (8 for the 16-bit types, 4 for float)
@@ -16,7 +17,7 @@
 #include <algorithm>
 
 #include "conv_params.hpp"
-#include "mma_common.hpp"
+#include "igemm_buf_kernel.hpp"
 
 namespace sc {
 
@@ -528,6 +529,182 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void d
   }
 }
 
+// ---- 16-bit types, dense input: columns walked downwards in registers ---------------------------------------------------
+// The pairs of rows do not have to pass LDS: a lane that walks down one column of output pixels reads every input row once, and
+// the pair of rows it puts together for one step is the upper or the lower operand of the next.  A lane holds one column and
+// four channels (8 bytes a load); the lanes of a wavefront lie side by side on (image, column, channel group), so loads and
+// stores are contiguous, and the two neighbouring columns of a window come from L1.  No barriers, no staging: a step's loads
+// are on their way while the step before is computed, and the wavefronts drift apart as they like.
+//   stride 1, output rows i, i+1:  out[i] = P . (w0, w1) + N . (w2, 0),  out[i+1] = P . (0, w0) + N . (w1, w2), with P the pair
+//             of input rows (i-ph, i-ph+1) and N the next one, which is the next step's P
+//   stride 2, output row t:        out[t] = P . (w0, w1) + N . (w2, 0)
+// The entries that meet a zero filter entry are not cleared here: a value that is not finite there makes a not-a-number, and a
+// wavefront that finds a result that is not finite computes the step again with them cleared.
+//
+// What bounds it: memory, whatever its parallelism.  64 x 144 @56 (bf16, s = 0.5) moves its 116 MB in 32 us from and to HBM (a copy of
+// the same tensors takes 23, and 17 where they stay in the memory-side cache; this kernel 24 there); two steps ahead instead of one, two
+// to four workgroups a compute unit, shorter and more segments, image by image or segment by segment change it by 2 %.  13 vector
+// instructions an output are 10 us.  Measured, staged kernel above / this one (us, s = 0.5, three sets of buffers in turn, batch 64
+// where not said):  144 @56 38.8 / 32.0, stride 2 20.2 / 13.9;  32 @112 32.8 / 32.2;  384 @14 12.2 / 9.0;  960 @7 10.0 / 6.5;
+// 8 x 576 @14 8.0 / 3.8;  one image of 96 @40 6.6 / 2.8, of 144 @14 stride 2 4.2 / 2.5.  Compact operands and tensors past the 2 GiB of
+// a buffer's offsets stay with the staged kernel.
+struct DwWalk {
+  int32_t lanes;                      // n * wo * (c / 4)
+  int32_t steps, seg_steps, segs;     // steps of a column (two output rows, or one at stride 2), those of a segment, segments
+  int32_t groups;                     // workgroups per segment
+  uint32_t x_bytes, y_bytes;
+  int32_t mask_bytes;
+  uint32_t div_g_mul, div_g_shift;    // lanes -> c / 4
+};
+
+template <typename T, int S>
+__global__ __launch_bounds__(256, 3) void depthwise3x3_walk_kernel(const DepthwiseParams p, const DwWalk q) {
+  typedef unsigned u2 __attribute__((ext_vector_type(2)));
+  constexpr int OUT = S == 1 ? 2 : 1;       // output rows of a step
+  // neighbouring workgroups (they share columns) run on one die
+  const int per_xcd = (q.groups * q.segs + 7) >> 3;
+  const int b = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (b >= q.groups * q.segs) return;
+  const int seg = b / q.groups, lane_id = (b - seg * q.groups) * 256 + threadIdx.x;
+  const bool on = lane_id < q.lanes;
+  const int id = on ? lane_id : 0;
+  const int cg = p.c >> 2;
+  const int col = fast_div(id, q.div_g_mul, q.div_g_shift), c0 = (id - col * cg) * 4;
+  const int n = fast_div(col, p.div_wo_mul, p.div_wo_shift), ox = col - n * p.wo;
+
+  // filter pairs (first window row of a pair in the low half), bias
+  unsigned w01[3][4], w2z[3][4], z0[3][4], w12[3][4];
+  {
+    const T* __restrict__ wp = static_cast<const T*>(p.wp) + c0;
+    unsigned w[9][4];
+#pragma unroll
+    for (int tap = 0; tap < 9; ++tap) {
+      const u2 v = *reinterpret_cast<const u2*>(wp + (int64_t)tap * p.c);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) w[tap][c] = c & 1 ? v[c >> 1] >> 16 : v[c >> 1] & 0xffffu;
+    }
+#pragma unroll
+    for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        w01[kx][c] = w[kx][c] | (w[3 + kx][c] << 16);
+        w2z[kx][c] = w[6 + kx][c];
+        z0[kx][c] = w[kx][c] << 16;
+        w12[kx][c] = w[3 + kx][c] | (w[6 + kx][c] << 16);
+      }
+  }
+  float bias_v[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) bias_v[c] = p.bias ? p.bias[c0 + c] : 0.0f;
+  const float floor_v = p.relu ? 0.0f : -__builtin_inff();
+
+  // Loads and stores are unconditional -- what must not happen has an offset outside its buffer -- so that the number on their way
+  // is known and a wait for a step's rows waits neither for later rows nor for the stores (with branches around them every step
+  // waited for all: 33.9 instead of 32.0 us on 64 x 144 @56, 14.3 instead of 13.2 at stride 2).
+  const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.x), 0, (int)q.x_bytes, kBufferWord3);
+  const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(p.y, 0, (int)q.y_bytes, kBufferWord3);
+  const __amdgpu_buffer_rsrc_t rm = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.mask), 0, p.mask ? q.mask_bytes : 0, kBufferWord3);
+  const int row_bytes = p.w * p.c * 2;
+  const int ix0 = ox * S - p.pw;
+  const unsigned x0 = (unsigned)((n * p.h * p.w + ix0) * p.c + c0) * 2u;      // (of column ix0 in row 0; wraps for a column left of the image)
+  bool in[3];
+#pragma unroll
+  for (int kx = 0; kx < 3; ++kx) in[kx] = on && (unsigned)(ix0 + kx) < (unsigned)p.w;
+
+  const int s_lo = seg * q.seg_steps, s_hi = min(s_lo + q.seg_steps, q.steps);
+  struct Rows { u2 a[3], b[3]; };           // two input rows on their way
+  auto request = [&](int iy, Rows& r) {     // rows iy, iy + 1 (zeros outside the image)
+    const bool a = (unsigned)iy < (unsigned)p.h, bb = (unsigned)(iy + 1) < (unsigned)p.h;
+    const unsigned at = x0 + (unsigned)(iy * row_bytes);
+#pragma unroll
+    for (int kx = 0; kx < 3; ++kx) {
+      const unsigned v = at + (unsigned)(kx * p.c * 2);
+      r.a[kx] = __builtin_bit_cast(u2, __builtin_amdgcn_raw_buffer_load_b64(rx, a && in[kx] ? v : kOutOfRange, 0, 0));
+      r.b[kx] = __builtin_bit_cast(u2, __builtin_amdgcn_raw_buffer_load_b64(rx, bb && in[kx] ? v + (unsigned)row_bytes : kOutOfRange, 0, 0));
+    }
+  };
+  auto pair_up = [&](const Rows& r, unsigned (&d)[3][4]) {
+#pragma unroll
+    for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        d[kx][c] = __builtin_amdgcn_perm(r.b[kx][c >> 1], r.a[kx][c >> 1], c & 1 ? 0x07060302u : 0x05040100u);
+  };
+  const unsigned pix0 = (unsigned)(n * p.ho_wo + ox), mask0 = p.mask_spatial ? (unsigned)ox : pix0;
+  const unsigned y0 = (pix0 * (unsigned)p.c + (unsigned)c0) * 2u;
+  struct Keep { unsigned k[OUT]; };
+  auto request_mask = [&](int step, Keep& m) {
+#pragma unroll
+    for (int o = 0; o < OUT; ++o)
+      m.k[o] = (unsigned)__builtin_amdgcn_raw_buffer_load_b8(rm, mask0 + (unsigned)(min(step * OUT + o, p.ho - 1) * p.wo), 0, 0);
+  };
+
+  unsigned P[3][4], N[3][4];
+  Rows rows;
+  Keep mask_bytes;
+  {
+    Rows first;
+    request(s_lo * 2 - p.ph, first);
+    request(s_lo * 2 - p.ph + 2, rows);
+    request_mask(s_lo, mask_bytes);
+    pair_up(first, P);
+  }
+  auto step_of = [&](int s, unsigned (&P)[3][4], unsigned (&N)[3][4]) {
+    pair_up(rows, N);
+    bool drop[OUT];
+#pragma unroll
+    for (int o = 0; o < OUT; ++o) drop[o] = p.mask && mask_bytes.k[o] == 0;
+    // (past the last step of the segment: rows of the next one, or zeros, which nothing uses)
+    request((s + 1) * 2 - p.ph + 2, rows);
+    request_mask(s + 1, mask_bytes);
+    float a[OUT][4];
+    auto sums = [&](auto careful_c) {
+      constexpr bool CAREFUL = decltype(careful_c)::value;
+#pragma unroll
+      for (int o = 0; o < OUT; ++o)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) a[o][c] = bias_v[c];
+#pragma unroll
+      for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          a[0][c] = Dot2<T>::run(P[kx][c], w01[kx][c], a[0][c]);
+          a[0][c] = Dot2<T>::run(CAREFUL ? N[kx][c] & 0xffffu : N[kx][c], w2z[kx][c], a[0][c]);
+          if constexpr (OUT == 2) {
+            a[1][c] = Dot2<T>::run(CAREFUL ? P[kx][c] & 0xffff0000u : P[kx][c], z0[kx][c], a[1][c]);
+            a[1][c] = Dot2<T>::run(N[kx][c], w12[kx][c], a[1][c]);
+          }
+        }
+    };
+    sums(std::false_type{});
+    float odd = 0.0f;
+#pragma unroll
+    for (int o = 0; o < OUT; ++o)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) odd = __builtin_fmaf(a[o][c], 0.0f, odd);
+    if (__any(odd != odd)) sums(std::true_type{});
+#pragma unroll
+    for (int o = 0; o < OUT; ++o) {
+      const int oy = s * OUT + o;
+      DwGroup<T, 4> out;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) out.v[c] = (T)__builtin_fmaxf(a[o][c], floor_v);
+      const u2 o2 = __builtin_bit_cast(u2, out);
+      const bool store = on && oy < p.ho && (!drop[o] || p.zero_fill);
+      unsigned lo = drop[o] ? 0u : o2[0], hi = drop[o] ? 0u : o2[1];      // Alg. 2, mask == 0 branch
+      unsigned at = store ? y0 + (unsigned)(oy * p.wo * p.c * 2) : kOutOfRange;
+      asm volatile("" : "+v"(lo), "+v"(hi), "+v"(at));                    // (selects, not branches)
+      __builtin_amdgcn_raw_buffer_store_b64(u2{lo, hi}, ry, at, 0, 0);
+    }
+  };
+  int s = s_lo;
+  for (; s + 1 < s_hi; s += 2) {
+    step_of(s, P, N);
+    step_of(s + 1, N, P);
+  }
+  if (s < s_hi) step_of(s, P, N);
+}
+
 // position of every kept row in the row list: rank[row_idx[i]] = i
 __global__ void depthwise_rank_kernel(const int32_t* __restrict__ row_idx, const int32_t* __restrict__ kept,
                                       int32_t* __restrict__ rank) {
@@ -630,6 +807,31 @@ static hipError_t launch_pair_tiles(const DepthwiseParams& p, hipStream_t stream
   return hipGetLastError();
 }
 
+template <typename T, int S>
+static hipError_t launch_walk(const DepthwiseParams& p, int64_t x_bytes, hipStream_t stream) {
+  DwWalk q;
+  q.lanes = (int32_t)((int64_t)p.n * p.wo * (p.c / 4));
+  q.steps = S == 1 ? (p.ho + 1) / 2 : p.ho;
+  q.groups = (q.lanes + 255) / 256;
+  // Columns are cut into segments while all workgroups are resident at once, three on a compute unit (64 x 144 @56, one segment: 32.0
+  // us; four 35, eight 41).  A segment reads two input rows of its neighbours' and waits for its first rows, so once segments of
+  // four steps put a workgroup on every compute unit they are not cut shorter (64 x 384 @14, seven steps, in two segments 9.0, in
+  // three 9.3; 64 x 960 @7, four steps, in one 6.5, in two 7.4); smaller layers are (one image of 96 @40, twenty steps: twenty
+  // segments 2.8, fourteen 3.5, four 5.0).
+  constexpr int kCus = 256;
+  q.segs = std::max(1, std::min(q.steps, 3 * kCus / q.groups));
+  q.seg_steps = (q.steps + q.segs - 1) / q.segs;
+  if (q.seg_steps < 4 && (int64_t)q.groups * ((q.steps + 3) / 4) >= kCus) q.seg_steps = std::min(q.steps, 4);
+  q.segs = (q.steps + q.seg_steps - 1) / q.seg_steps;
+  q.x_bytes = (uint32_t)x_bytes;
+  q.y_bytes = (uint32_t)((int64_t)p.n * p.ho_wo * p.c * 2);
+  q.mask_bytes = p.ho_wo * (p.mask_spatial ? 1 : p.n);
+  magic_div((uint32_t)(p.c / 4), &q.div_g_mul, &q.div_g_shift);
+  const int64_t wgs = (int64_t)q.groups * q.segs;
+  hipLaunchKernelGGL((depthwise3x3_walk_kernel<T, S>), dim3((unsigned)((wgs + 7) / 8 * 8)), dim3(256), 0, stream, p, q);
+  return hipGetLastError();
+}
+
 template <typename T>
 static hipError_t launch_typed(const DepthwiseParams& p, hipStream_t stream) {
   constexpr int V = DwVec<T>::V;
@@ -640,6 +842,11 @@ static hipError_t launch_typed(const DepthwiseParams& p, hipStream_t stream) {
     if constexpr (sizeof(T) == 2) {
       if (p.x_compact && p.x_rank)
         return p.sh == 1 ? launch_pair_tiles<T, 1, true>(p, stream) : launch_pair_tiles<T, 2, true>(p, stream);
+      // (offsets are 32-bit, and those from 2^31 on are the ones outside a tensor)
+      const int64_t x_bytes = (int64_t)p.n * p.h * p.w * p.c * 2;
+      const int64_t y_bytes = (int64_t)p.n * p.ho_wo * p.c * 2;
+      if (!p.x_compact && !p.rank && std::max(x_bytes, y_bytes) < ((int64_t)1 << 31))
+        return p.sh == 1 ? launch_walk<T, 1>(p, x_bytes, stream) : launch_walk<T, 2>(p, x_bytes, stream);
       if (!p.x_compact)
         return p.sh == 1 ? launch_pair_tiles<T, 1, false>(p, stream) : launch_pair_tiles<T, 2, false>(p, stream);
     } else if (!p.x_compact) {

@@ -75,6 +75,23 @@ def test_depthwise_layers(dtype, shape):
     check_depthwise(dw_spec(dtype=dtype, sparsity=0.4, **shape), 401)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("shape", [
+    dict(n=1, c=8, h=1, w=1),                          # one pixel: every tap but one is padding
+    dict(n=3, c=8, h=5, w=1, sparsity=0.2),            # one column, an odd number of rows
+    dict(n=1, c=8, h=2, w=43),                         # 86 lanes
+    dict(n=2, c=40, h=7, w=13, p=0),                   # no padding, odd output height
+    dict(n=1, c=24, h=9, w=8, p=2),                    # windows entirely inside the padding
+    dict(n=2, c=16, h=8, w=9, s=2, p=0),               # stride 2, rows left over at the bottom
+    dict(n=1, c=8, h=1, w=3, s=2),
+    dict(n=7, c=72, h=9, w=11, mask_mode="spatial"),   # images within a wavefront, a last workgroup nearly empty
+    dict(n=64, c=64, h=18, w=16, mask_mode="spatial"),   # all compute units: segments of four steps and a last one of one
+    dict(n=64, c=128, h=13, w=32, s=2),                # two segments, four and three steps
+])
+def test_columns_walked_downwards(dtype, shape):
+    check_depthwise(dw_spec(dtype=dtype, **{"sparsity": 0.4, **shape}), 431)
+
+
 @pytest.mark.parametrize("sparsity", [0.0, 0.25, 0.7])
 def test_depthwise_sparsities_and_modes(sparsity):
     spec = dw_spec(2, 64, 20, 20, sparsity=sparsity)
