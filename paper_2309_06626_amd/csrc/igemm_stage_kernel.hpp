@@ -27,14 +27,14 @@
 // filters are packed in the same order at plan time, so their transfer is a plain copy.
 //
 // What bounds it: no unit alone.  The rows of a K tile pass LDS twice (written by the threads that fetched them, read by the
-// wavefronts), and the phases of a workgroup (addresses, products, split and stores) are one after the other; the address units
+// wavefronts); the split and the stores of the next tile go out behind the products of this one where that pays; the address units
 // are the busiest, 49 % of the time channels first in float (one load per entry), 57 % with the element-aligned groups of
 // 102 channels, next to 26 and 14 % of the matrix pipes, 20 % of the vector issue and 14 and 19 % of LDS (counters).  Row loads
 // run two tiles ahead in registers; the table that says where they go runs three ahead, because waiting for a load waits for
 // all that were issued before it, and is read by scalar loads where a wavefront shares its entries.  The filters need no
 // registers: they go from memory to LDS as they lie, a tile ahead.
 // Measured at s = 0.5 (element gather / all through registers / this kernel, us): 32 x 128 -> 128 @28 channels first in float
-// 115 / 45 / 37, in bf16 84 / 27.5 / 21.5, 32 x 51 -> 64 @28 in bf16 - / 19.6 / 13.8; at s = 0.3 64 x 102 -> 102 @28 in fp16
+// 115 / 45 / 35.4, in bf16 84 / 27.5 / 20.9, 32 x 51 -> 64 @28 in bf16 - / 19.6 / 13.8; at s = 0.3 64 x 102 -> 102 @28 in fp16
 // 98 / 27.5 / 25.5, 51 -> 51 @56 110 / 44 / 40, 410 -> 410 @7 186 / 27 / 22.5.
 //
 // Workgroup = BM kept rows x BN channels, four wavefronts (or KG groups of four); zero-fill ownership and the order of the
@@ -381,6 +381,49 @@ __global__ __launch_bounds__(kThreads * KG, 2) void igemm_stage_kernel(const Con
       }
   };
 
+  // The same in pieces that go between the products of the tile before (the place was left at the last barrier): a float chunk in ten
+  // of four to six vector instructions, none of which waits for the one before it, the last one with the stores; a 16-bit chunk in one.
+  constexpr int CHUNK_PIECES = SPLIT ? 10 : 1, PIECES = ROWS * PER_ROW * CHUNK_PIECES;
+  struct Split { float v[8], part[8]; uint32_t pk[3][4]; };
+  auto store_piece = [&](int buf, const Regs& r, Split& sp, int piece) {
+    const int chunk = piece / CHUNK_PIECES, j = chunk / PER_ROW, c = chunk % PER_ROW, step = piece % CHUNK_PIECES;
+    unsigned char* dst = s_a + buf * A_BYTES + a_place(row0 + ROW_STEP * j, chunk0 + c);
+    if constexpr (!SPLIT) {
+      v4i v;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if constexpr (BY_ENTRY) v[i] = (int)((r.a[c * 8 + 2 * i] & 0xffffu) | (r.a[c * 8 + 2 * i + 1] << 16));
+        else v[i] = (int)r.a[j * 4 + i];
+      }
+      *reinterpret_cast<v4i*>(dst) = v;
+    } else {
+      auto scale = [&](int e) { sp.v[e] = __builtin_bit_cast(float, r.a[chunk * 8 + e]) * kPartScale; asm volatile("" : "+v"(sp.v[e])); };
+      auto pack = [&](int q, int i) {
+        sp.pk[q][i] = q == 2 ? upper_halves(__builtin_bit_cast(uint32_t, sp.v[2 * i]), __builtin_bit_cast(uint32_t, sp.v[2 * i + 1])) : bf16_pair(sp.v[2 * i], sp.v[2 * i + 1]);
+        asm volatile("" : "+v"(sp.pk[q][i]));      // (not sunk to the stores)
+      };
+      auto widen = [&](int q, int e) {
+        sp.part[e] = e & 1 ? bf16_hi(sp.pk[q][e >> 1]) : bf16_lo(sp.pk[q][e >> 1]);
+        asm volatile("" : "+v"(sp.part[e]));
+      };
+      auto rest = [&](int e) { sp.v[e] -= sp.part[e]; asm volatile("" : "+v"(sp.v[e])); };
+      if (step == 0) for (int e = 0; e < 6; ++e) scale(e);
+      if (step == 1) { scale(6); scale(7); for (int i = 0; i < 4; ++i) pack(0, i); }
+      if (step == 2) for (int e = 0; e < 6; ++e) widen(0, e);
+      if (step == 3) { widen(0, 6); widen(0, 7); for (int e = 0; e < 4; ++e) rest(e); }
+      if (step == 4) { for (int e = 4; e < 8; ++e) rest(e); pack(1, 0); pack(1, 1); }
+      if (step == 5) { pack(1, 2); pack(1, 3); for (int e = 0; e < 4; ++e) widen(1, e); }
+      if (step == 6) { for (int e = 4; e < 8; ++e) widen(1, e); rest(0); rest(1); }
+      if (step == 7) for (int e = 2; e < 8; ++e) rest(e);
+      if (step == 8) for (int i = 0; i < 4; ++i) pack(2, i);
+      if (step == 9) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+          *reinterpret_cast<v4i*>(dst + q * PART_A) = v4i{(int)sp.pk[q][0], (int)sp.pk[q][1], (int)sp.pk[q][2], (int)sp.pk[q][3]};
+      }
+    }
+  };
+
   floatx16 acc[MI][NI], small[SPLIT ? MI : 1][SPLIT ? NI : 1];
   auto clear = [&]() {
 #pragma unroll
@@ -401,8 +444,9 @@ __global__ __launch_bounds__(kThreads * KG, 2) void igemm_stage_kernel(const Con
   for (int ks = 0; ks < KSTEPS; ++ks) frag_a[ks] = lds0 + a_place(wm0 + fp, 2 * ks + fh);
   const unsigned frag_b = lds0 + 2 * A_BYTES + (wn0 / 32) * D::BLOCK_BYTES + lane * 16;
 
-  // (r, pl: the loads of a later tile, issued between the products)
-  auto compute_tile = [&](auto buf_c, auto careful_c, Regs* r, const Places* pl) {
+  // (r, pl: the loads of a later tile, issued between the products; st: the next tile, stored between them)
+  auto compute_tile = [&](auto buf_c, auto careful_c, Regs* r, const Places* pl, const Regs* st) {
+    Split sp;
     constexpr bool CAREFUL = decltype(careful_c)::value;
     constexpr int BUF = decltype(buf_c)::value;
     auto steps_of = [&](auto k2_c) {      // AHEAD K steps of fragments are read before their products start
@@ -434,7 +478,7 @@ __global__ __launch_bounds__(kThreads * KG, 2) void igemm_stage_kernel(const Con
 #pragma unroll
           for (int mi = 0; mi < MI; ++mi) asm volatile("" : "+v"(xf[i][mi][q]));
         }
-        constexpr int ROUNDS = (SPLIT && !CAREFUL ? 6 : 1) * MI * NI, ALL = KSTEPS * ROUNDS;
+        constexpr int ROUNDS = (SPLIT && !CAREFUL ? 6 : 1) * MI * NI, ALL = KSTEPS * ROUNDS, FIRST = ALL / 4;
         int done = (k2 + i) * ROUNDS;
         auto each = [&](auto fn) {
 #pragma unroll
@@ -446,6 +490,14 @@ __global__ __launch_bounds__(kThreads * KG, 2) void igemm_stage_kernel(const Con
 #pragma unroll
                 for (int j = 0; j < A_LOADS; ++j)
                   if (j * ALL / A_LOADS == done) load_one(j, *r, *pl);
+              }
+              if (!CAREFUL && st) {
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < PIECES; ++i)
+                  if (FIRST + i * (ALL - FIRST) / PIECES == done) store_piece(BUF ^ 1, *st, sp, i);
+                __builtin_amdgcn_sched_barrier(0);
+              } else if (r) {
                 __builtin_amdgcn_sched_barrier(0x6);
               }
               ++done;
@@ -541,6 +593,11 @@ __global__ __launch_bounds__(kThreads * KG, 2) void igemm_stage_kernel(const Con
 
   // ---- K loop: two tiles ahead in registers, one ahead in LDS ------------------------------------------------------------
   auto contract = [&](auto careful_c) {
+    // The next tile's split and stores behind the products of this one, or after them (us, after / behind: 32 x 128 -> 128 @28 channels
+    // first in float 36.9 / 35.4, in bf16 21.3 / 20.9;  16 x 256 -> 256 @14 38.8 / 36.9;  32 x 102 -> 102 @28 NHWC in float 33.3 / 31.2).
+    // The few stores of 16-bit groups gain nothing (64 x 102 -> 102 @28 in fp16 26.5 / 26.6), and a table entry for every load leaves
+    // no registers for it (16 x 3 -> 64 @56 channels first in float 9.8 / 10.1).
+    constexpr bool BEHIND = !decltype(careful_c)::value && (GATHER == kStageChunks || (SPLIT && GATHER != kStageEntries));
     constexpr std::integral_constant<int, 0> even;
     constexpr std::integral_constant<int, 1> odd;
     Regs r0, r1;
@@ -567,19 +624,19 @@ __global__ __launch_bounds__(kThreads * KG, 2) void igemm_stage_kernel(const Con
       aim_tile(kt + 2, r0, pl);
       if constexpr (!BETWEEN) load_all(r0, pl);
       __builtin_amdgcn_sched_barrier(0);
-      compute_tile(even, careful_c, BETWEEN ? &r0 : nullptr, &pl);
+      compute_tile(even, careful_c, BETWEEN ? &r0 : nullptr, &pl, BEHIND ? &r1 : nullptr);
       if (!decltype(careful_c)::value && kt == 0 && p.zero_fill) fill_zeros();
-      store_tile(1, r1, careful_c);
+      if constexpr (!BEHIND) store_tile(1, r1, careful_c);
       arrive();
       issue_filters(kt + 2, 0);
       aim_tile(kt + 3, r1, pl);
       if constexpr (!BETWEEN) load_all(r1, pl);
       __builtin_amdgcn_sched_barrier(0);
-      compute_tile(odd, careful_c, BETWEEN ? &r1 : nullptr, &pl);
-      store_tile(0, r0, careful_c);
+      compute_tile(odd, careful_c, BETWEEN ? &r1 : nullptr, &pl, BEHIND ? &r0 : nullptr);
+      if constexpr (!BEHIND) store_tile(0, r0, careful_c);
       arrive();
     }
-    if (steps & 1) compute_tile(even, careful_c, (Regs*)nullptr, (const Places*)nullptr);
+    if (steps & 1) compute_tile(even, careful_c, (Regs*)nullptr, (const Places*)nullptr, (const Regs*)nullptr);
     if (!decltype(careful_c)::value && steps == 1 && p.zero_fill) fill_zeros();
     wait_vmcnt<0>();                         // (no filters are on their way into LDS any more)
     if constexpr (SPLIT && !decltype(careful_c)::value) {
