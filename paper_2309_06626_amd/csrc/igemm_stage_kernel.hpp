@@ -596,8 +596,10 @@ __global__ __launch_bounds__(kThreads * KG, 2) void igemm_stage_kernel(const Con
     // The next tile's split and stores behind the products of this one, or after them (us, after / behind: 32 x 128 -> 128 @28 channels
     // first in float 36.9 / 35.4, in bf16 21.3 / 20.9;  16 x 256 -> 256 @14 38.8 / 36.9;  32 x 102 -> 102 @28 NHWC in float 33.3 / 31.2).
     // The few stores of 16-bit groups gain nothing (64 x 102 -> 102 @28 in fp16 26.5 / 26.6), and a table entry for every load leaves
-    // no registers for it (16 x 3 -> 64 @56 channels first in float 9.8 / 10.1).
-    constexpr bool BEHIND = !decltype(careful_c)::value && (GATHER == kStageChunks || (SPLIT && GATHER != kStageEntries));
+    // no registers for it (16 x 3 -> 64 @56 channels first in float 9.8 / 10.1).  Nor have the 128-row tiles of 16-bit chunks, whose loads
+    // go out at once: both register slots would lie in scratch memory (32 x 32 -> 32 @56 in bf16 19.0 / 38.5, pointwise 64 -> 256 @28
+    // 15.1 / 20.2; dense runs up to four times as long).
+    constexpr bool BEHIND = !decltype(careful_c)::value && BETWEEN && (GATHER == kStageChunks || (SPLIT && GATHER != kStageEntries));
     constexpr std::integral_constant<int, 0> even;
     constexpr std::integral_constant<int, 1> odd;
     Regs r0, r1;
