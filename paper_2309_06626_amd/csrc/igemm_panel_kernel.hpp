@@ -29,8 +29,12 @@ inline size_t igemm_panel_lds_bytes(int k_tiles, int c_out) {
   return (size_t)k_tiles * (BM + 2 * BN) * kRowBytes + BM * sizeof(int32_t) + (size_t)((c_out + 63) / 64) * 64 * sizeof(float);
 }
 
+// Four wavefronts a SIMD, which one K tile's LDS leaves room for: 110 registers.  Left to itself the compiler takes 140 for the
+// paired stores, and a workgroup less fits a compute unit (us, three / four; batch 64, bf16, s = 0.5): 32 -> 192 @56 24.8 / 20.3 (dense
+// 26.3 / 24.7, compact rows 16.6 / 12.8), 24 -> 144 @56 22.3 / 19.2, batch 32 of 64 -> 256 @56 dense 19.8 / 15.7; and 96 -> 576 @56, of
+// whose two K tiles two workgroups fit, 69.6 / 67.3 (compact rows 50.8 / 46.0).
 template <int DT, int BM, int BN, int WAVES_M, int WAVES_N>
-__global__ __launch_bounds__(kThreads) void igemm_panel_kernel(const ConvParams p) {
+__global__ __launch_bounds__(kThreads, 4) void igemm_panel_kernel(const ConvParams p) {
   using E = Elem<DT>;
   using T = typename E::T;
   constexpr int V = E::V;

@@ -57,3 +57,9 @@ def test_no_kernel_works_in_scratch_memory(kernels):
         plain = re.match(r"_ZN2sc\d+(\w+?_kernel)", name)
         allowed = SPILLS.get(plain.group(1), 0) if plain else 0
         assert k[".private_segment_fixed_size"] <= allowed, (name, k[".private_segment_fixed_size"])
+
+
+def test_four_row_panel_wavefronts_fit_a_simd(kernels):
+    """A row panel of one K tile leaves LDS for four workgroups of four wavefronts; the 512 registers of a SIMD have to as well."""
+    panels = [k[".vgpr_count"] for n, k in kernels.items() if "igemm_panel_kernel" in n]
+    assert len(panels) == 2 and max(panels) <= 128
