@@ -510,28 +510,37 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64 * KG) void igemm_buf_kernel(
   }
 
   // ---- epilogue ----------------------------------------------------------------------------------------
-  // The high tiles serve the layers of many rows, where the stores of a short K count (384 -> 112 channels, 69 264 kept rows:
-  // 23.6 -> 22.4 us paired); in the small tiles the exchange between lanes only adds to the chain of a workgroup
-  // (64 x 64, two K tiles 4.1 -> 4.2 us, eighteen 10.0 -> 10.2).
+  // Pairs of lanes where a row of 112 channels or more ends in half a block of 32 channels, which half of the lanes store alone (us, lane
+  // by lane / paired; compact rows, half of maps of 28 x 28: 64 x 384 -> 112 8.45 / 8.05, -> 208 12.6 / 12.1, -> 240 13.15 / 12.4; 128 x 192 ->
+  // 112 11.3 / 10.9; -> 80 12.9 / 13.1).  Whole blocks lose by the exchange (-> 96 7.8 / 7.9, 128 x 576 -> 96 15.4 / 15.8, 64 x 960 -> 160 17.6 /
+  // 18.0, -> 128 no difference), and so do the narrower and lower tiles (384 -> 48 10.85 / 11.1, 192 -> 32 7.2 / 7.3; 64 x 64, two K tiles
+  // 4.1 / 4.2).
   if (KG > 1 && group > 0) return;
-  constexpr bool paired = BM >= 128;
+  const bool paired = BM >= 128 && BN == 128 && (p.c_out & 16) != 0 && p.c_out >= 112;
 #pragma unroll
   for (int mi = 0; mi < MI; ++mi) {
     const int rr = s_rows[wm0 + mi * 32 + fp];
     const bool dropped = rr < -1 && p.masked_store == 1;      // masked stores that write the zeros too
-    if (!paired && rr < 0 && !dropped) continue;
+    if (paired) {
+      if constexpr (BM >= 128 && BN == 128) {
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni) {
+          const int c0 = n0 + wn0 + ni * 32 + 16 * fh;
+          if (c0 >= p.c_out) continue;
+          store_block_pairs<DT>(acc[mi][ni], dropped ? -2 - rr : rr, dropped, c0, y, p.bias ? s_bias + (c0 - n0) : nullptr, p.relu,
+                                p.c_out, static_cast<const T*>(p.residual), p.residual_relu);
+        }
+      }
+      continue;
+    }
+    if (rr < 0 && !dropped) continue;
 #pragma unroll
     for (int ni = 0; ni < NI; ++ni) {
       const int c0 = n0 + wn0 + ni * 32 + 16 * fh;
       if (c0 >= p.c_out) continue;
-      if constexpr (paired) {
-        store_block_pairs<DT>(acc[mi][ni], dropped ? -2 - rr : rr, dropped, c0, y, p.bias ? s_bias + (c0 - n0) : nullptr, p.relu,
-                              p.c_out, static_cast<const T*>(p.residual), p.residual_relu);
-      } else {
-        if (rr < 0) { store_zero_block<DT>(-2 - rr, c0, y, 1, p.c_out, p.ho_wo, 0, 0, 0); continue; }
-        store_kept_block_res<DT>(acc[mi][ni], rr, c0, y, p.bias ? s_bias + (c0 - n0) : nullptr, 0, p.relu, 1, p.c_out,
-                                 p.ho_wo, 0, 0, 0, static_cast<const T*>(p.residual), p.residual_relu);
-      }
+      if (rr < 0) { store_zero_block<DT>(-2 - rr, c0, y, 1, p.c_out, p.ho_wo, 0, 0, 0); continue; }
+      store_kept_block_res<DT>(acc[mi][ni], rr, c0, y, p.bias ? s_bias + (c0 - n0) : nullptr, 0, p.relu, 1, p.c_out,
+                               p.ho_wo, 0, 0, 0, static_cast<const T*>(p.residual), p.residual_relu);
     }
   }
 }

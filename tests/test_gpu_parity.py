@@ -9,7 +9,7 @@ import workloads as W
 from oracle import oracle
 from paper_2309_06626_amd import binding as B
 from paper_2309_06626_amd import runtime as R
-from parity import TOL, assert_close, check_layer, compare_network, rows_view
+from parity import TOL, assert_close, check_layer, compare_network, row_mask, rows_view
 
 pytestmark = pytest.mark.gpu
 
@@ -67,6 +67,32 @@ def test_every_tile_shape(tile, dtype):
     spec = spec_of(8, 32, 19, 19, 160, dtype=dtype, sp=0.5)
     layer = check_layer(W.make_conv_inputs(spec, 31), tiles=tile)
     assert B.sparse_conv_plan_tiles(layer.plan, 0)[:2] == tile
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("tile", [(128, 128), (256, 128)])
+@pytest.mark.parametrize("cout", [80, 96, 112, 128, 240, 272])
+def test_stores_of_whole_and_half_channel_blocks(cout, tile, dtype):
+    """The last channel block of a row whole or half, in one and in three channel tiles: row list, masked store, shortcut; the
+    compact rows carry the bits of the dense layout."""
+    spec = spec_of(2, 64, 13, 12, cout, k=1, p=0, dtype=dtype, sp=0.4)
+    ci = W.make_conv_inputs(spec, 41)
+    for masked in (1, 2):
+        layer = check_layer(ci, tiles=tile, options={B.SC_OPT_MASKED_STORE: masked, B.SC_OPT_ROW_PANEL: 1})
+        assert B.sparse_conv_plan_tiles(layer.plan, 0)[:2] == tile
+    x, y = R.to_device(ci.x, dtype), layer.new_output(fill_nan=True)
+    layer.sparse(x, y)
+    kept = torch.from_numpy(row_mask(spec, ci.mask)).cuda() == 1
+    rows = torch.full((int(kept.sum()), cout), float("nan"), dtype=y.dtype, device=y.device)
+    B.sparse_conv_run_rows(layer.plan, x, layer.bias, rows, B.SC_ROWS_DENSE, B.SC_ROWS_COMPACT)
+    assert torch.equal(rows, y.view(-1, cout)[kept])
+    res = torch.randn(y.shape, generator=torch.Generator().manual_seed(7)).to(y.dtype).cuda()
+    fused = torch.full_like(y, float("nan"))
+    B.sparse_conv_run_residual(layer.plan, x, layer.bias, res, fused)
+    want = torch.where(kept.view(y.shape[:3] + (1,)), y, torch.zeros_like(y)).float() + res.float()
+    # y was rounded once (eps / 2 of |y|) and the sum once (eps / 2 of at most |y| + |res|, and of what y's rounding added)
+    eps = torch.finfo(y.dtype).eps
+    assert ((fused.float() - want).abs() <= eps * (1 + eps) * (y.float().abs() + res.float().abs()) + 1e-6).all()
 
 
 def test_tile_choice_follows_the_reduced_row_count():
