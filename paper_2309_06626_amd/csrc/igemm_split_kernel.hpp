@@ -209,15 +209,15 @@ __global__ __launch_bounds__(2 * BM * KS, 2) void igemm_split_kernel(const ConvP
 
   struct Filters { v4i q[NI][3]; };
   struct Parts { v4i q[3]; };
-  auto read_step = [&](auto stage_c, auto ks_c, v4i (&x)[2], Filters& f) {
+  auto read_step = [&](auto stage_c, auto ks_c, v4i (&x)[2], Filters& f, unsigned more = 0) {
     constexpr int ST = decltype(stage_c)::value * STAGE_BYTES, ks = decltype(ks_c)::value;
-    x[0] = lds_read16_big<ST>(frag_a[ks][0]);
-    x[1] = lds_read16_big<ST>(frag_a[ks][1]);
+    x[0] = lds_read16_big<ST>(frag_a[ks][0] + more);
+    x[1] = lds_read16_big<ST>(frag_a[ks][1] + more);
     static_for<NI>([&](auto ni_c) {
       constexpr int at = ST + ks * 1024 + decltype(ni_c)::value * D::BLOCK_BYTES;
-      f.q[decltype(ni_c)::value][0] = lds_read16_big<at>(frag_b);
-      f.q[decltype(ni_c)::value][1] = lds_read16_big<at + 2048>(frag_b);
-      f.q[decltype(ni_c)::value][2] = lds_read16_big<at + 4096>(frag_b);
+      f.q[decltype(ni_c)::value][0] = lds_read16_big<at>(frag_b + more);
+      f.q[decltype(ni_c)::value][1] = lds_read16_big<at + 2048>(frag_b + more);
+      f.q[decltype(ni_c)::value][2] = lds_read16_big<at + 4096>(frag_b + more);
     });
   };
   // the rows' fragments (behind them the filters' may still be on their way), or all of them, have landed; they pass through,
@@ -317,7 +317,7 @@ __global__ __launch_bounds__(2 * BM * KS, 2) void igemm_split_kernel(const ConvP
     v4i x[2];
     issue_tile(0);
     arrive();
-    issue_tile(1);
+    if (steps > 1) issue_tile(1);
     read_step(Zero{}, Zero{}, x, w0);
     rows_landed(x);
     {
@@ -327,32 +327,38 @@ __global__ __launch_bounds__(2 * BM * KS, 2) void igemm_split_kernel(const ConvP
       split3(v, p0.q[0], p0.q[1], p0.q[2]);
     }
     all_landed(w0);
-    // tile i of the share, in slot S; the first half of the next one is read, and split, behind its second half
-    auto tile = [&](auto stage_c, int i) {
+    // a tile of the share, in slot S; the first half of the next one is read, and split, behind its second half
+    auto tile = [&](auto stage_c) {
       constexpr int S = decltype(stage_c)::value;
-      if (KS > 1 && i >= n_kt) {
-        arrive();
-        return;
-      }
       read_step(stage_c, One{}, x, w1);
       products(w0, p0, x, p1, [](auto) {});
       all_landed(w1);
       arrive();
-      // (behind the last tile this reads what lies there, and nothing uses it)
+      // (behind the last tile of a share that is shorter than another this reads what lies there, and nothing uses it)
       read_step(std::integral_constant<int, S ^ 1>{}, Zero{}, x, w0);
       products(w1, p1, x, p0, [&](auto l_c) { issue_one(S, l_c); });
       walk_on();
       all_landed(w0);
     };
-    tile(Zero{}, 0);
+    if (steps > 1) tile(Zero{});
     if (p.zero_fill) fill_zeros();        // (these stores drain under the K loop)
     int i = 1;
 #pragma unroll 1
-    for (; i + 1 < steps; i += 2) {
-      tile(One{}, i);
-      tile(Zero{}, i + 1);
+    for (; i + 2 < steps; i += 2) {
+      tile(One{});
+      tile(Zero{});
     }
-    if (i < steps) tile(One{}, i);
+    if (i + 1 < steps) tile(One{});
+    // The last tile: nothing follows that would have to be asked for, waited for or split (us, like the others / so: fused, one image of
+    // 32 -> 64 @28 pointwise 7.30 / 6.94, 64 x 32 -> 32 @28 11.2 / 10.9; plain, one image of 128 -> 128 @28 12.8 / 12.2, dense 32 x 32 -> 256
+    // @56 pointwise 45.9 / 42.8).
+    if (KS == 1 || n_kt == steps) {
+      const unsigned at = (steps & 1) ? 0u : (unsigned)STAGE_BYTES;
+      read_step(Zero{}, One{}, x, w1, at);
+      products(w0, p0, x, p1, [](auto) {});
+      all_landed(w1);
+      static_for<NP>([&](auto i_c) { product(i_c, w1, p1); });
+    }
     wait_vmcnt<0>();
   };
   // the same sums on the float MFMA
