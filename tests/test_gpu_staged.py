@@ -28,12 +28,16 @@ CASES = [
 
 
 @pytest.mark.parametrize("tile", ["128x64", "128x64x2", "128x32", "128x32x2", "64x64", "64x64x2", "64x32", "64x32x2", "64x32x4"])
+@pytest.mark.parametrize("cout", [84, 80])
 @pytest.mark.parametrize("cin,k", [(32, 1), (64, 1), (96, 1), (4, 3), (32, 3), (64, 3), (40, 3), (32, 2)])
-def test_float_walks(cin, k, tile, monkeypatch):
+def test_float_walks(cin, k, cout, tile, monkeypatch):
     """One to eighteen K tiles, odd and even, tiles within a tap and across taps; shares that differ by a tile or hold none; the
-    step past the end of a walk, whose operands nothing may use."""
+    step past the end of a walk, whose operands nothing may use; rows of whole 16-channel blocks and of whole groups only."""
     monkeypatch.setenv("SPARSE_CONV_STAGE_TILE", tile)
-    check_layer(W.make_conv_inputs(spec_of(n=2, cin=cin, h=11, w=9, cout=84, k=k, p=k // 2, dtype="f32", sp=0.35), 1571))
+    layer = check_layer(W.make_conv_inputs(spec_of(n=2, cin=cin, h=11, w=9, cout=cout, k=k, p=k // 2, dtype="f32", sp=0.35), 1571))
+    for which in (0, 1):
+        assert B.sparse_conv_plan_kernel(layer.plan, which) == "tile_staged"
+        assert ["%d" % v for v in B.sparse_conv_plan_tiles(layer.plan, which)[:2]] == tile.split("x")[:2]
 
 
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
