@@ -1360,15 +1360,18 @@ static StageTile stage_tile_for(const sc_conv_desc& d, const Geometry& g, int64_
     return fbm > 0 && stage_launcher(d, g, {fbm, fbn, fgr, true}) ? StageTile{fbm, fbn, fgr, true} : none;
   const int kt = g.stage_k_tiles;
   if (stage_is_direct(d, g)) {
-    // Priced like the other tiled launches, with quantities measured on this kernel (us, MI355X): what a K tile costs a
-    // compute unit with enough workgroups on it, what it costs a workgroup alone, and a round of workgroups beyond its K
-    // loop.  Sparse runs at s = 0.5, chosen tile / 128 x 64 in one group / the float-MFMA kernel:  32 x 64 -> 64 @56
-    // 28 / 28 / 60;  128 -> 128 @28 25.8 / 28 / 55;  256 -> 256 @14 31 / 47 / 61;  16 x 384 -> 384 @12 29.9 / 67 / 88;
-    // 1 x 128 -> 128 @28 12.7 / 24.9 / 32 (batch 32 where not said; where few workgroups walk a long K, groups share it).
-    struct Shape { StageTile t; double per_tile, alone; int waves; };
-    static const Shape shapes[] = {{{128, 64, 1, false}, 0.57, 0.62, 4}, {{128, 64, 2, false}, 0.57, 0.97, 8},  {{128, 32, 1, false}, 0.32, 0.50, 4},
-                                   {{128, 32, 2, false}, 0.33, 0.76, 8}, {{64, 64, 1, false}, 0.27, 0.53, 2},   {{64, 64, 2, false}, 0.30, 0.72, 4},
-                                   {{64, 32, 1, false}, 0.185, 0.47, 2}, {{64, 32, 2, false}, 0.19, 0.585, 4}, {{64, 32, 4, false}, 0.19, 0.955, 8}};
+    // Priced like the other tiled launches (us, MI355X): what a K tile costs a compute unit with enough workgroups on it, what it costs
+    // a workgroup alone, and a round of workgroups beyond its K loop, where the stores and the zero fill of a tile count.  The figures
+    // are fitted to the sparse and dense runs of all nine tiles on 90 layers (1 to 100 K tiles, 8 to 400 channels).  Chosen tile against
+    // the fastest one, geometric mean over 150 layers: sparse runs 1.012, dense 1.020, fused 1.038; with one figure for every tile's round
+    // 1.023, 1.026 and 1.048.  Sparse runs at s = 0.5, chosen tile / 128 x 64 in one group / the float-MFMA kernel:  32 x 64 -> 64 @56
+    // 27.5 / 27.5 / 60;  128 -> 128 @28 25.5 / 28.6 / 55;  256 -> 256 @14 30.8 / 47 / 61;  16 x 384 -> 384 @12 29.2 / 67 / 88;
+    // 1 x 128 -> 128 @28 12.2 / 25 / 32 (batch 32 where not said; where few workgroups walk a long K, groups share it).
+    struct Shape { StageTile t; double per_tile, alone, round; int waves; };
+    static const Shape shapes[] = {
+        {{128, 64, 1, false}, 0.57, 0.57, 5.5, 4},  {{128, 64, 2, false}, 0.46, 0.93, 5.9, 8}, {{128, 32, 1, false}, 0.40, 0.48, 4.7, 4},
+        {{128, 32, 2, false}, 0.33, 0.77, 5.0, 8},  {{64, 64, 1, false}, 0.32, 0.49, 5.6, 2},  {{64, 64, 2, false}, 0.30, 0.63, 5.4, 4},
+        {{64, 32, 1, false}, 0.215, 0.44, 4.5, 2}, {{64, 32, 2, false}, 0.20, 0.53, 4.6, 4}, {{64, 32, 4, false}, 0.19, 0.86, 4.7, 8}};
     const int cus = device_cus();
     StageTile best = none;
     double best_us = 1e300;
@@ -1380,8 +1383,8 @@ static StageTile stage_tile_for(const sc_conv_desc& d, const Geometry& g, int64_
       const int steps = (kt + sh.t.groups - 1) / sh.t.groups;
       auto round_us = [&](int64_t on_cu) {
         double step = std::max(sh.alone, (double)on_cu * sh.t.groups * sh.per_tile);
-        if (sh.waves == 2 && on_cu >= 2) step = std::max(step, 0.80);       // (their wavefronts share two of the four SIMDs)
-        return 4.0 + steps * step;
+        if (sh.waves == 2 && on_cu >= 2) step = std::max(step, 0.81);       // (their wavefronts share two of the four SIMDs)
+        return sh.round + steps * step;
       };
       const int64_t full = wgs / ((int64_t)cus * resident), rest = wgs - full * cus * resident;
       const double us = full * round_us(resident) + (rest ? round_us((rest + cus - 1) / cus) : 0.0);
