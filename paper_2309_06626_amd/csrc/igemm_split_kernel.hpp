@@ -31,9 +31,12 @@ template <int BM, int BN, int KS> constexpr size_t split_lds_bytes() {
 // TAPS: a K tile lies inside one window tap (Cin a multiple of 32): the walk over the window is scalar.  Otherwise each
 // lane finds its 16-byte group in the plan's table.
 // VEC_OUT: 1 = Cout a multiple of 16, 2 = a multiple of four.
+// FUSED: with a shortcut sum.  Its groups of the dropped rows are asked for several passes at a time: one by one, each a round trip to
+// memory, the tiles of few threads had become slower than the two groups that were chosen before (us, one by one / together:
+// 4 x 244 -> 104 @70 pointwise 20.3 / 17.0; 64 x 32 -> 32 @28 10.8 / 9.05; 32 x 32 -> 256 @56 89.6 / 66.4).
 // KS: the K tiles are divided among KS groups of wavefronts, each with LDS tiles of its own; the first group adds the others'
 // sums in order and stores.  For launches with few workgroups, whose time is one K tile's latency after the other.
-template <int BM, int BN, int KS, bool TAPS, int VEC_OUT>
+template <int BM, int BN, int KS, bool TAPS, int VEC_OUT, bool FUSED>
 __global__ __launch_bounds__(2 * BM * KS, 2) void igemm_split_kernel(const ConvParams p) {
   using D = StageDims<kF32>;
   constexpr int NT = 2 * BM;                       // threads of a group: a wavefront per 32 rows
@@ -283,22 +286,30 @@ __global__ __launch_bounds__(2 * BM * KS, 2) void igemm_split_kernel(const ConvP
     const int valid = min(BN, p.c_out - n0) / 4;
     if (zc >= valid) return;
     unsigned char* ybase = reinterpret_cast<unsigned char*>(y) + (int64_t)n0 * 4 + zc * 16;
-    const int64_t res_at = (int64_t)n0 * 4 + zc * 16;
-    const v4i z = {0, 0, 0, 0};
-    auto pass = [&](int r, unsigned keep) {
-      if (r < z_hi && keep == 0) {
-        const int64_t at = (int64_t)r * p.c_out * 4;
-        *reinterpret_cast<v4i*>(ybase + at) = p.residual ? dropped_row_group<kF32>(p.residual, res_at + at, p.residual_relu) : z;
+    auto passes = [&](int r0, const unsigned (&keep)[ZB]) {
+      v4i v[ZB];
+      auto each = [&](auto fn) {
+#pragma unroll
+        for (int u = 0; u < ZB; ++u) {
+          const int r = r0 + u * RPI;
+          if (r < z_hi && keep[u] == 0) fn(v[u], (int64_t)r * p.c_out * 4);
+        }
+      };
+      if constexpr (FUSED) {
+        const unsigned char* res = static_cast<const unsigned char*>(p.residual) + (int64_t)n0 * 4 + zc * 16;
+        each([&](v4i& g, int64_t at) { g = *reinterpret_cast<const v4i*>(res + at); });
+        __builtin_amdgcn_s_waitcnt(0x0f70);      // vmcnt(0), said once: the compiler would have the K loop wait for them
+        each([&](v4i& g, int64_t at) { *reinterpret_cast<v4i*>(ybase + at) = shortcut_alone<kF32>(g, p.residual_relu); });
+      } else {
+        each([&](v4i&, int64_t at) { *reinterpret_cast<v4i*>(ybase + at) = v4i{0, 0, 0, 0}; });
       }
     };
-#pragma unroll
-    for (int u = 0; u < ZB; ++u) pass(z_lo + zr + u * RPI, mk[u]);
+    passes(z_lo + zr, mk);
     for (int r0 = z_lo + zr + ZB * RPI; r0 < z_hi; r0 += ZB * RPI) {
       unsigned m[ZB];
 #pragma unroll
       for (int u = 0; u < ZB; ++u) m[u] = mask_of(min(r0 + u * RPI, z_hi - 1));
-#pragma unroll
-      for (int u = 0; u < ZB; ++u) pass(r0 + u * RPI, m[u]);
+      passes(r0, m);
     }
   };
 
@@ -459,7 +470,7 @@ __global__ __launch_bounds__(2 * BM * KS, 2) void igemm_split_kernel(const ConvP
       const int c0 = n0 + ni * 32 + 16 * fh;
       if (c0 >= p.c_out) continue;
       store_block_pairs<kF32, VEC_OUT == 1>(acc[ni], out_row, false, c0, y, p.bias ? s_bias + (c0 - n0) : nullptr, p.relu, p.c_out,
-                                            static_cast<const float*>(p.residual), p.residual_relu);
+                                            FUSED ? static_cast<const float*>(p.residual) : nullptr, FUSED ? p.residual_relu : 0);
     }
   }
 }
@@ -467,12 +478,13 @@ __global__ __launch_bounds__(2 * BM * KS, 2) void igemm_split_kernel(const ConvP
 template <int BM, int BN, int KS, bool TAPS, int VEC_OUT>
 hipError_t igemm_split_launch(const ConvParams& p, hipStream_t stream) {
   constexpr size_t lds = split_lds_bytes<BM, BN, KS>();
-  auto kern = igemm_split_kernel<BM, BN, KS, TAPS, VEC_OUT>;
-  static std::atomic<bool> attr_set{false};
-  if (lds > 64 * 1024 && !attr_set) {
+  auto kern = p.residual ? igemm_split_kernel<BM, BN, KS, TAPS, VEC_OUT, true> : igemm_split_kernel<BM, BN, KS, TAPS, VEC_OUT, false>;
+  static std::atomic<bool> attr_set[2] = {{false}, {false}};
+  std::atomic<bool>& set = attr_set[p.residual ? 1 : 0];
+  if (lds > 64 * 1024 && !set) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    attr_set = true;
+    set = true;
   }
   const int nwg = p.m_tiles * p.n_tiles;
   hipLaunchKernelGGL(kern, dim3(((nwg + 7) / 8) * 8), dim3(2 * BM * KS), lds, stream, p);

@@ -262,11 +262,9 @@ __device__ __forceinline__ void store_block_pairs(const floatx16& acc, int row, 
 // zeros (Alg. 2, mask == 0 branch), or post(shortcut) when a shortcut tensor is fused into the launch -- the
 // convolution contributes +0.0 there, added in float like everywhere else (so -0.0 of the shortcut becomes +0.0).
 template <int DT>
-__device__ __forceinline__ v4i dropped_row_group(const void* res, int64_t at, int post_relu) {
+__device__ __forceinline__ v4i shortcut_alone(v4i g, int post_relu) {      // post(shortcut)
   using T = typename Elem<DT>::T;
   constexpr int GC = 16 / (int)sizeof(T);
-  if (!res) return v4i{0, 0, 0, 0};
-  const v4i g = *reinterpret_cast<const v4i*>(static_cast<const unsigned char*>(res) + at);
   T e[GC];
   __builtin_memcpy(e, &g, 16);
 #pragma unroll
@@ -278,6 +276,11 @@ __device__ __forceinline__ v4i dropped_row_group(const void* res, int64_t at, in
   v4i out;
   __builtin_memcpy(&out, e, 16);
   return out;
+}
+template <int DT>
+__device__ __forceinline__ v4i dropped_row_group(const void* res, int64_t at, int post_relu) {
+  if (!res) return v4i{0, 0, 0, 0};
+  return shortcut_alone<DT>(*reinterpret_cast<const v4i*>(static_cast<const unsigned char*>(res) + at), post_relu);
 }
 
 }  // namespace sc
