@@ -101,6 +101,10 @@ __global__ __launch_bounds__(256) void depthwise_kernel(const DepthwiseParams p)
   *reinterpret_cast<G*>(y) = out;
 }
 
+// max(f, activation_floor) is the activation.  Without one the floor is not a number, which fmaxf passes over: f stays as it is, also
+// where it is not a number itself (above a floor of -inf it would become -inf).
+__device__ __forceinline__ float activation_floor(int relu) { return relu ? 0.0f : __builtin_nanf(""); }
+
 // 3x3 windows without dilation, stride S in both directions, 16-byte channel groups.  A workgroup owns a
 // tile of TY x TX output pixels of one image and a chunk of CG channel groups.  It stages the input
 // patch of the tile -- ((TY-1)*S+3) x ((TX-1)*S+3) pixels x CG groups, zeros outside the image -- in LDS
@@ -186,7 +190,7 @@ __global__ __launch_bounds__(256) void depthwise3x3_kernel(const DepthwiseParams
   float bias_v[V];
 #pragma unroll
   for (int k = 0; k < V; ++k) bias_v[k] = p.bias ? p.bias[c0 + k] : 0.0f;
-  const float floor_v = p.relu ? 0.0f : -__builtin_inff();      // max(f, floor) is the activation
+  const float floor_v = activation_floor(p.relu);
   T* __restrict__ y = static_cast<T*>(p.y) + c0;
   __syncthreads();
   if (!lane_on) return;
@@ -328,7 +332,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void d
   float bias_v[V];
 #pragma unroll
   for (int k = 0; k < V; ++k) bias_v[k] = p.bias ? p.bias[c0 + k] : 0.0f;
-  const float floor_v = p.relu ? 0.0f : -__builtin_inff();
+  const float floor_v = activation_floor(p.relu);
   T* __restrict__ y = static_cast<T*>(p.y) + c0;
 
   // ---- staging: request a tile's patch and mask bytes; later interleave the rows two by two into LDS ------
@@ -596,7 +600,7 @@ __global__ __launch_bounds__(256, 3) void depthwise3x3_walk_kernel(const Depthwi
   float bias_v[4];
 #pragma unroll
   for (int c = 0; c < 4; ++c) bias_v[c] = p.bias ? p.bias[c0 + c] : 0.0f;
-  const float floor_v = p.relu ? 0.0f : -__builtin_inff();
+  const float floor_v = activation_floor(p.relu);
 
   // Loads and stores are unconditional -- what must not happen has an offset outside its buffer -- so that the number on their way
   // is known and a wait for a step's rows waits neither for later rows nor for the stores (with branches around them every step

@@ -226,6 +226,36 @@ def test_a_non_finite_input_value_reaches_only_the_windows_that_contain_it(dtype
     assert np.abs(got[finite] - clean[finite]).max() <= TOL[dtype] * np.abs(clean).max()
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("k", [3, 5])
+@pytest.mark.parametrize("stride", [1, 2])
+def test_values_that_are_not_finite_keep_their_kind_without_an_activation(dtype, k, stride):
+    """Infinities of either sign, and sums that are not a number because an operand is not or because infinities of both signs meet:
+    the same kinds as the oracle's in every kernel (dense operands, compact rows out, compact rows in)."""
+    spec = dw_spec(1, 16, 12, 12, k=k, s=stride, dtype=dtype, sparsity=0.25, relu=False)
+    ci = W.make_conv_inputs(spec, 461)
+    x = ci.x.copy()
+    x[0, 5, 6, :8] = np.inf
+    x[0, 6, 6, 4:] = -np.inf
+    x[0, 1, 1, 3] = np.nan
+    layer = R.ConvLayer(spec, ci.w, ci.bias, ci.mask)
+    kept = row_mask(spec, ci.mask) == 1
+    with np.errstate(invalid="ignore", over="ignore"):
+        ref = rows_view(spec, oracle.masked_depthwise_conv2d(spec, x, ci.w, ci.bias, ci.mask))[kept]
+    kinds = lambda v: np.select([np.isnan(v), np.isposinf(v), np.isneginf(v)], [1, 2, 3], 0)
+    want = kinds(ref)
+    assert {0, 1, 2, 3} == set(want.flat)
+    xd, y = R.to_device(x, dtype), layer.new_output(fill_nan=True)
+    rows = torch.empty((int(kept.sum()), spec.c_out), dtype=y.dtype, device=y.device)
+    layer.sparse(xd, y)
+    assert np.array_equal(kinds(rows_view(spec, R.to_host_f32(y))[kept]), want)
+    B.sparse_conv_run_rows(layer.plan, xd, layer.bias, rows, B.SC_ROWS_DENSE, B.SC_ROWS_COMPACT)
+    assert np.array_equal(kinds(R.to_host_f32(rows)), want)
+    B.sparse_conv_plan_set_input_mask(layer.plan, torch.ones(144, dtype=torch.uint8, device=y.device))
+    B.sparse_conv_run_rows(layer.plan, xd.view(144, 16), layer.bias, rows.fill_(0), B.SC_ROWS_COMPACT, B.SC_ROWS_COMPACT)
+    assert np.array_equal(kinds(R.to_host_f32(rows)), want)
+
+
 # ---------------------------------------------------------------------------------------------------------
 # compact input under the producer's mask (sparse_conv_plan_set_input_mask)
 # ---------------------------------------------------------------------------------------------------------
