@@ -597,9 +597,10 @@ __global__ __launch_bounds__(256, 3) void depthwise3x3_walk_kernel(const Depthwi
         w12[kx][c] = w[3 + kx][c] | (w[6 + kx][c] << 16);
       }
   }
+  // (plus zero: from -0 on, an entry below zero that meets a zero filter entry would keep a sum of zeros at -0)
   float bias_v[4];
 #pragma unroll
-  for (int c = 0; c < 4; ++c) bias_v[c] = p.bias ? p.bias[c0 + c] : 0.0f;
+  for (int c = 0; c < 4; ++c) bias_v[c] = p.bias ? p.bias[c0 + c] + 0.0f : 0.0f;
   const float floor_v = activation_floor(p.relu);
 
   // Loads and stores are unconditional -- what must not happen has an offset outside its buffer -- so that the number on their way
