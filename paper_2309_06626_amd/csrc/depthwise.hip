@@ -545,17 +545,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void d
 // The entries that meet a zero filter entry are not cleared here: a value that is not finite there makes a not-a-number, and a
 // wavefront that finds a result that is not finite computes the step again with them cleared.
 //
-// What bounds it: memory, whatever its parallelism.  64 x 144 @56 (bf16, s = 0.5) moves its 116 MB in 32 us from and to HBM (a copy of
-// the same tensors takes 23, and 17 where they stay in the memory-side cache; this kernel 24 there); two steps ahead instead of one, two
-// to four workgroups a compute unit, shorter and more segments, image by image or segment by segment change it by 2 %.  13 vector
-// instructions an output are 10 us.  Measured, staged kernel above / this one (us, s = 0.5, three sets of buffers in turn, batch 64
-// where not said):  144 @56 38.8 / 32.0, stride 2 20.2 / 13.9;  32 @112 32.8 / 32.2;  384 @14 12.2 / 9.0;  960 @7 10.0 / 6.5;
-// 8 x 576 @14 8.0 / 3.8;  one image of 96 @40 6.6 / 2.8, of 144 @14 stride 2 4.2 / 2.5.  Compact operands and tensors past the 2 GiB of
-// a buffer's offsets stay with the staged kernel.
+// What bounds it: memory, as far as cached accesses go.  64 x 144 @56 (bf16, s = 0.5) moves its 116 MB in 32 us from and to HBM (a plain
+// copy of the same tensors takes 23, and 17 where they stay in the memory-side cache; this kernel 24 there; streaming accesses, which
+// reach 6.4 TB/s in a copy, are not tried); two steps ahead instead of one, two to four workgroups a compute unit, image by image or
+// segment by segment change it by 2 %.  13 vector instructions an output are 10 us.  How the columns are shared out counts more: a
+// compute unit with one workgroup more than the others is waited for (launch_walk).
+// Measured, staged kernel above / this one (us, s = 0.5, three sets of buffers in turn, batch 64 where not said):  144 @56 39.1 / 32.3,
+// stride 2 20.2 / 13.0, batch 200 107 / 93;  32 @112 32.9 / 31.4, batch 110 51.8 / 52.5, 160 70.7 / 66.5, 220 95.2 / 92.3;  384 @14 12.3 /
+// 8.0;  960 @7 10.1 / 6.5;  8 x 576 @14 8.5 / 3.8;  one image of 96 @40 6.6 / 2.8.  Compact operands, tensors past the 2 GiB of a
+// buffer's offsets and large maps at stride 2 (launch_typed) stay with the staged kernel.
 struct DwWalk {
   int32_t lanes;                      // n * wo * (c / 4)
-  int32_t steps, seg_steps, segs;     // steps of a column (two output rows, or one at stride 2), those of a segment, segments
-  int32_t groups;                     // workgroups per segment
+  int32_t steps;                      // of a column: two output rows each, or one at stride 2
+  int32_t whole;                      // workgroups (a multiple of eight) that walk whole columns
+  int32_t rest, seg_steps, segs;      // the others' groups of columns, each cut into `segs` segments of `seg_steps` steps
   uint32_t x_bytes, y_bytes;
   int32_t mask_bytes;
   uint32_t div_g_mul, div_g_shift;    // lanes -> c / 4
@@ -566,10 +569,13 @@ __global__ __launch_bounds__(256, 3) void depthwise3x3_walk_kernel(const Depthwi
   typedef unsigned u2 __attribute__((ext_vector_type(2)));
   constexpr int OUT = S == 1 ? 2 : 1;       // output rows of a step
   // neighbouring workgroups (they share columns) run on one die
-  const int per_xcd = (q.groups * q.segs + 7) >> 3;
-  const int b = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if (b >= q.groups * q.segs) return;
-  const int seg = b / q.groups, lane_id = (b - seg * q.groups) * 256 + threadIdx.x;
+  const bool column = (int)blockIdx.x < q.whole;
+  const int wgs = column ? q.whole : q.rest * q.segs, groups = column ? q.whole : q.rest;
+  const int b = (blockIdx.x & 7) * ((wgs + 7) >> 3) + (((int)blockIdx.x - (column ? 0 : q.whole)) >> 3);
+  if (b >= wgs) return;
+  const int seg = b / groups, group = b - seg * groups + (column ? 0 : q.whole);
+  const int s_lo = seg * q.seg_steps, s_hi = column ? q.steps : min(s_lo + q.seg_steps, q.steps);
+  const int lane_id = group * 256 + threadIdx.x;
   const bool on = lane_id < q.lanes;
   const int id = on ? lane_id : 0;
   const int cg = p.c >> 2;
@@ -597,10 +603,9 @@ __global__ __launch_bounds__(256, 3) void depthwise3x3_walk_kernel(const Depthwi
         w12[kx][c] = w[3 + kx][c] | (w[6 + kx][c] << 16);
       }
   }
-  // (plus zero: from -0 on, an entry below zero that meets a zero filter entry would keep a sum of zeros at -0)
   float bias_v[4];
 #pragma unroll
-  for (int c = 0; c < 4; ++c) bias_v[c] = p.bias ? p.bias[c0 + c] + 0.0f : 0.0f;
+  for (int c = 0; c < 4; ++c) bias_v[c] = p.bias ? p.bias[c0 + c] : 0.0f;
   const float floor_v = activation_floor(p.relu);
 
   // Loads and stores are unconditional -- what must not happen has an offset outside its buffer -- so that the number on their way
@@ -616,7 +621,6 @@ __global__ __launch_bounds__(256, 3) void depthwise3x3_walk_kernel(const Depthwi
 #pragma unroll
   for (int kx = 0; kx < 3; ++kx) in[kx] = on && (unsigned)(ix0 + kx) < (unsigned)p.w;
 
-  const int s_lo = seg * q.seg_steps, s_hi = min(s_lo + q.seg_steps, q.steps);
   struct Rows { u2 a[3], b[3]; };           // two input rows on their way
   auto request = [&](int iy, Rows& r) {     // rows iy, iy + 1 (zeros outside the image)
     const bool a = (unsigned)iy < (unsigned)p.h, bb = (unsigned)(iy + 1) < (unsigned)p.h;
@@ -653,6 +657,13 @@ __global__ __launch_bounds__(256, 3) void depthwise3x3_walk_kernel(const Depthwi
     request(s_lo * 2 - p.ph + 2, rows);
     request_mask(s_lo, mask_bytes);
     pair_up(first, P);
+  }
+  // Plus zero: from a bias of -0 on, an entry below zero that meets a zero filter entry would keep a sum of zeros at -0.  (Here, where all
+  // of the first loads are on their way: beside the bias's own loads each would be waited for, 0.3 us.)
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    asm volatile("" : "+v"(bias_v[c]));
+    bias_v[c] += 0.0f;
   }
   auto step_of = [&](int s, unsigned (&P)[3][4], unsigned (&N)[3][4]) {
     pair_up(rows, N);
@@ -807,7 +818,7 @@ static hipError_t launch_pair_tiles(const DepthwiseParams& p, hipStream_t stream
   const size_t lds = (size_t)q.pairs_h * pair_bytes + 256 + 256 * sizeof(int);   // patch, mask bytes, compact rows
   // persistent workgroups: about three per compute unit (LDS and registers allow that many), split over the chunks
   constexpr int per_cu = 3;
-  const int wgs = std::max(1, std::min(q.tiles, (256 * per_cu + chunks - 1) / chunks));
+  const int wgs = std::max(1, std::min(q.tiles, (p.cus * per_cu + chunks - 1) / chunks));
   hipLaunchKernelGGL((depthwise3x3_dot2_kernel<T, S, XC>), dim3((unsigned)wgs, (unsigned)chunks), dim3(256), lds, stream, p, q);
   return hipGetLastError();
 }
@@ -817,23 +828,41 @@ static hipError_t launch_walk(const DepthwiseParams& p, int64_t x_bytes, hipStre
   DwWalk q;
   q.lanes = (int32_t)((int64_t)p.n * p.wo * (p.c / 4));
   q.steps = S == 1 ? (p.ho + 1) / 2 : p.ho;
-  q.groups = (q.lanes + 255) / 256;
-  // Columns are cut into segments while all workgroups are resident at once, three on a compute unit (64 x 144 @56, one segment: 32.0
-  // us; four 35, eight 41).  A segment reads two input rows of its neighbours' and waits for its first rows, so once segments of
-  // four steps put a workgroup on every compute unit they are not cut shorter (64 x 384 @14, seven steps, in two segments 9.0, in
-  // three 9.3; 64 x 960 @7, four steps, in one 6.5, in two 7.4); smaller layers are (one image of 96 @40, twenty steps: twenty
-  // segments 2.8, fourteen 3.5, four 5.0).
-  constexpr int kCus = 256;
-  q.segs = std::max(1, std::min(q.steps, 3 * kCus / q.groups));
-  q.seg_steps = (q.steps + q.segs - 1) / q.segs;
-  if (q.seg_steps < 4 && (int64_t)q.groups * ((q.steps + 3) / 4) >= kCus) q.seg_steps = std::min(q.steps, 4);
-  q.segs = (q.steps + q.seg_steps - 1) / q.seg_steps;
+  // Whole columns for as many groups as fill the compute units evenly, the rest cut so that its segments do; or all of them cut.  Three
+  // times (us) decide, cubed and added: the busiest compute unit's, the longest chain of steps', and that of the bytes at the rate of
+  // memory, of which segments read more at stride 1.  Fitted to 1 150 launches on 75 layers; the cut that is chosen takes 1.01 times the
+  // best one's time.  As many segments as are resident at once, of equal length, and whole columns beyond / this rule: 98 x 144 @56 55.4 /
+  // 48.2, 150 x 144 73.6 / 69.4, 160 x 32 @112 81 / 66.5, 220 x 32 108 / 92.3, 64 x 384 @14 9.1 / 8.0, 100 x 96 @56 42 / 34.
+  constexpr double per_step = S == 1 ? 0.302 : 0.268, per_segment = S == 1 ? 1.52 : 2.86;      // a compute unit: a step, a segment in steps
+  constexpr double chain_step = S == 1 ? 0.377 : 0.267, chain_segment = S == 1 ? 0.31 : 7.8;    // a workgroup alone
+  constexpr double more_rows = S == 1 ? 0.46 : 0.0;                                            // a segment reads, of what it would in a column
+  const int groups = (q.lanes + 255) / 256, unit = std::max(8, p.cus / 8 * 8);
+  const double bytes_us = (double)(x_bytes + (int64_t)p.n * p.ho_wo * p.c * 2) / 4.235e6;
+  double best = 1e300;
+  for (int whole : {0, groups / unit * unit}) {
+    if (whole > 0 && whole == groups) continue;
+    for (int cut : {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 20, 28, 40, 56, 112}) {
+      const int rest = groups - whole, steps = (q.steps + cut - 1) / cut, segs = (q.steps + steps - 1) / steps;
+      if (cut > q.steps) break;
+      const double work = per_step * (whole / unit * (q.steps + per_segment) + (double)(((int64_t)rest * segs + unit - 1) / unit) * (steps + per_segment));
+      const double chain = chain_step * ((whole ? q.steps : steps) + chain_segment);
+      const double bytes = bytes_us * (1.0 + more_rows * ((double)(whole + (int64_t)rest * segs) / groups - 1.0) / (2 * q.steps));
+      const double cost = work * work * work + chain * chain * chain + bytes * bytes * bytes;
+      if (cost < best) {
+        best = cost;
+        q.whole = whole;
+        q.rest = rest;
+        q.seg_steps = steps;
+        q.segs = segs;
+      }
+    }
+  }
   q.x_bytes = (uint32_t)x_bytes;
   q.y_bytes = (uint32_t)((int64_t)p.n * p.ho_wo * p.c * 2);
   q.mask_bytes = p.ho_wo * (p.mask_spatial ? 1 : p.n);
   magic_div((uint32_t)(p.c / 4), &q.div_g_mul, &q.div_g_shift);
-  const int64_t wgs = (int64_t)q.groups * q.segs;
-  hipLaunchKernelGGL((depthwise3x3_walk_kernel<T, S>), dim3((unsigned)((wgs + 7) / 8 * 8)), dim3(256), 0, stream, p, q);
+  const int64_t wgs = q.whole + ((int64_t)q.rest * q.segs + 7) / 8 * 8;
+  hipLaunchKernelGGL((depthwise3x3_walk_kernel<T, S>), dim3((unsigned)wgs), dim3(256), 0, stream, p, q);
   return hipGetLastError();
 }
 
@@ -850,7 +879,11 @@ static hipError_t launch_typed(const DepthwiseParams& p, hipStream_t stream) {
       // (offsets are 32-bit, and those from 2^31 on are the ones outside a tensor)
       const int64_t x_bytes = (int64_t)p.n * p.h * p.w * p.c * 2;
       const int64_t y_bytes = (int64_t)p.n * p.ho_wo * p.c * 2;
-      if (!p.x_compact && !p.rank && std::max(x_bytes, y_bytes) < ((int64_t)1 << 31))
+      // Stride 2 on maps of more than 48 output rows, beyond what the memory-side cache takes of them, stays with the staged kernel (us,
+      // staged / walk, s = 0.5: 100 x 96 @112 64 / 67, 200 x 96 119 / 126, 200 x 32 43 / 46, 64 x 64 30.6 / 30.5; but 32 x 96 @112 23.6 /
+      // 19.4, 64 x 32 15.2 / 12.0, 256 x 144 @56 66 / 63).
+      const bool long_columns = p.sh == 2 && p.ho > 48 && x_bytes + y_bytes > 100000000;
+      if (!p.x_compact && !p.rank && std::max(x_bytes, y_bytes) < ((int64_t)1 << 31) && !long_columns)
         return p.sh == 1 ? launch_walk<T, 1>(p, x_bytes, stream) : launch_walk<T, 2>(p, x_bytes, stream);
       if (!p.x_compact)
         return p.sh == 1 ? launch_pair_tiles<T, 1, false>(p, stream) : launch_pair_tiles<T, 2, false>(p, stream);

@@ -1554,7 +1554,7 @@ static sc_status launch_conv(const sc_plan* pl, bool dense, const void* x, const
     q.items = zero_fill ? g.m : rows;
     q.zero_fill = zero_fill ? 1 : 0;
     q.rank = (compact && y_compact) ? reinterpret_cast<const int32_t*>(pl->ws + g.off_band_rows) : nullptr;
-    q.n = d.n; q.ho = g.ho;
+    q.n = d.n; q.ho = g.ho; q.cus = device_cus();
     q.c = d.c_in; q.h = d.h; q.w = d.w; q.ho_wo = g.ho * g.wo; q.wo = g.wo;
     q.kh = d.kh; q.kw = d.kw; q.sh = d.stride_h; q.sw = d.stride_w; q.ph = d.pad_h; q.pw = d.pad_w;
     q.dil_h = d.dil_h; q.dil_w = d.dil_w;

@@ -87,6 +87,8 @@ def test_depthwise_layers(dtype, shape):
     dict(n=7, c=72, h=9, w=11, mask_mode="spatial"),   # images within a wavefront, a last workgroup nearly empty
     dict(n=64, c=64, h=18, w=16, mask_mode="spatial"),   # all compute units: segments of four steps and a last one of one
     dict(n=64, c=128, h=13, w=32, s=2),                # two segments, four and three steps
+    dict(n=37, c=128, h=9, w=57),                      # 264 groups of columns: whole ones, and eight cut into single steps
+    dict(n=66, c=64, h=9, w=129, s=2, mask_mode="spatial"),   # the same at stride 2, thirteen cut
 ])
 def test_columns_walked_downwards(dtype, shape):
     check_depthwise(dw_spec(dtype=dtype, **{"sparsity": 0.4, **shape}), 431)
