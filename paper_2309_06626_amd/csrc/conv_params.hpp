@@ -88,6 +88,7 @@ struct DepthwiseParams {
   const int32_t* rank;     // [M]: position of a kept row in the row list (compact output); else null
   int32_t n, ho;           // images, output rows
   int32_t cus;             // compute units of the device
+  int32_t kernel;          // 16-bit 3x3 layers with dense operands: 0 automatic, 1 staged, 2 column walk (where it applies)
   int32_t zero_fill;       // dropped pixels of a dense-layout output receive zeros (else they are left alone)
   // compact input of a layer with windows: row of every input pixel in x, -1 for a pixel its producer dropped
   // (such a pixel reads as +0.0); null: a compact input holds the layer's own kept pixels (1x1 windows)

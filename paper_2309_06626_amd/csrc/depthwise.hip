@@ -883,7 +883,7 @@ static hipError_t launch_typed(const DepthwiseParams& p, hipStream_t stream) {
       // staged / walk, s = 0.5: 100 x 96 @112 64 / 67, 200 x 96 119 / 126, 200 x 32 43 / 46, 64 x 64 30.6 / 30.5; but 32 x 96 @112 23.6 /
       // 19.4, 64 x 32 15.2 / 12.0, 256 x 144 @56 66 / 63).
       const bool long_columns = p.sh == 2 && p.ho > 48 && x_bytes + y_bytes > 100000000;
-      if (!p.x_compact && !p.rank && std::max(x_bytes, y_bytes) < ((int64_t)1 << 31) && !long_columns)
+      if (!p.x_compact && !p.rank && std::max(x_bytes, y_bytes) < ((int64_t)1 << 31) && (p.kernel == 0 ? !long_columns : p.kernel == 2))
         return p.sh == 1 ? launch_walk<T, 1>(p, x_bytes, stream) : launch_walk<T, 2>(p, x_bytes, stream);
       if (!p.x_compact)
         return p.sh == 1 ? launch_pair_tiles<T, 1, false>(p, stream) : launch_pair_tiles<T, 2, false>(p, stream);

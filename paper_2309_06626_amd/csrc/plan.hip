@@ -1082,6 +1082,7 @@ struct sc_plan {
   // slab form of the tiled kernel (deep 3x3 layers)
   struct Slab { int bm, splits; };
   StageTile stage_pick[2];         // tile of the register-staged kernel for the sparse / dense run (bm == 0: another kernel)
+  int depthwise_kernel;            // asked for by SPARSE_CONV_DEPTHWISE_KERNEL=staged|walk (tests): 0 none, 1 staged, 2 column walk
   int stage_tuned;                 // sparse_conv_plan_tune measured that kernel fastest (1) or slower than another (-1); 0: not timed
   bool slab_ok;                    // the layer's geometry admits it
   int slab;                        // 0 = automatic, 1 = never, 2 = wherever it applies, 128 / 256 = with tiles of that many rows
@@ -1554,7 +1555,7 @@ static sc_status launch_conv(const sc_plan* pl, bool dense, const void* x, const
     q.items = zero_fill ? g.m : rows;
     q.zero_fill = zero_fill ? 1 : 0;
     q.rank = (compact && y_compact) ? reinterpret_cast<const int32_t*>(pl->ws + g.off_band_rows) : nullptr;
-    q.n = d.n; q.ho = g.ho; q.cus = device_cus();
+    q.n = d.n; q.ho = g.ho; q.cus = device_cus(); q.kernel = pl->depthwise_kernel;
     q.c = d.c_in; q.h = d.h; q.w = d.w; q.ho_wo = g.ho * g.wo; q.wo = g.wo;
     q.kh = d.kh; q.kw = d.kw; q.sh = d.stride_h; q.sw = d.stride_w; q.ph = d.pad_h; q.pw = d.pad_w;
     q.dil_h = d.dil_h; q.dil_w = d.dil_w;
@@ -2112,6 +2113,8 @@ sc_status sparse_conv_plan(const sc_conv_desc* desc, const uint8_t* mask_dev, co
   pl->forced[0] = pl->forced[1] = -1;
   pl->prefer_tiled[0] = pl->prefer_tiled[1] = false;
   pl->tuned = false;
+  const char* depthwise_kernel = std::getenv("SPARSE_CONV_DEPTHWISE_KERNEL");
+  pl->depthwise_kernel = !depthwise_kernel ? 0 : std::strcmp(depthwise_kernel, "staged") == 0 ? 1 : std::strcmp(depthwise_kernel, "walk") == 0 ? 2 : 0;
   pl->gather_pipeline = 0;
   pl->split_k = 0;
   pl->row_panel = 0;

@@ -94,6 +94,29 @@ def test_columns_walked_downwards(dtype, shape):
     check_depthwise(dw_spec(dtype=dtype, **{"sparsity": 0.4, **shape}), 431)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("shape", [
+    dict(n=2, c=32, h=14, w=14),
+    dict(n=1, c=8, h=2, w=43, p=2),
+    dict(n=2, c=40, h=7, w=13, p=0, mask_mode="spatial"),
+    dict(n=1, c=96, h=17, w=11, s=2),
+    dict(n=3, c=296, h=20, w=18, s=2),                 # chunks of channel groups, the last one ragged
+])
+def test_both_kernels_of_dense_operands(dtype, shape, monkeypatch):
+    """The staged kernel, to which dense operands go from 2 GiB on and at stride 2 on large maps, and the column walk: zero fill, untouched
+    dropped pixels, dense runs; the same bits."""
+    spec = dw_spec(dtype=dtype, **{"sparsity": 0.4, **shape})
+    x, bits = R.to_device(W.make_conv_inputs(spec, 433).x, dtype), []
+    for kernel in ("staged", "walk"):
+        monkeypatch.setenv("SPARSE_CONV_DEPTHWISE_KERNEL", kernel)
+        check_depthwise(spec, 433, out_mode=B.SC_OUT_SCATTER_ONLY)
+        layer = check_depthwise(spec, 433)
+        y = layer.new_output(fill_nan=True)
+        layer.sparse(x, y)
+        bits.append(R.bits_of(y))
+    assert np.array_equal(*bits)
+
+
 @pytest.mark.parametrize("sparsity", [0.0, 0.25, 0.7])
 def test_depthwise_sparsities_and_modes(sparsity):
     spec = dw_spec(2, 64, 20, 20, sparsity=sparsity)
