@@ -658,13 +658,6 @@ __global__ __launch_bounds__(256, 3) void depthwise3x3_walk_kernel(const Depthwi
     request_mask(s_lo, mask_bytes);
     pair_up(first, P);
   }
-  // Plus zero: from a bias of -0 on, an entry below zero that meets a zero filter entry would keep a sum of zeros at -0.  (Here, where all
-  // of the first loads are on their way: beside the bias's own loads each would be waited for, 0.3 us.)
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    asm volatile("" : "+v"(bias_v[c]));
-    bias_v[c] += 0.0f;
-  }
   auto step_of = [&](int s, unsigned (&P)[3][4], unsigned (&N)[3][4]) {
     pair_up(rows, N);
     bool drop[OUT];

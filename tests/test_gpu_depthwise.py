@@ -281,21 +281,6 @@ def test_values_that_are_not_finite_keep_their_kind_without_an_activation(dtype,
     assert np.array_equal(kinds(R.to_host_f32(rows)), want)
 
 
-@pytest.mark.parametrize("dtype", ["bf16", "f16"])
-@pytest.mark.parametrize("stride", [1, 2])
-def test_zero_sums_are_positive_whatever_lies_beside_the_window(dtype, stride):
-    """A bias of -0 and products that are all -0: +0 in the dense layout as in compact rows, which another kernel writes."""
-    spec = dw_spec(1, 8, 9, 9, s=stride, dtype=dtype, sparsity=0.25, relu=False)
-    ci = W.make_conv_inputs(spec, 463)
-    x = R.to_device(-np.abs(ci.x) - 1, dtype)
-    layer = R.ConvLayer(spec, np.zeros_like(ci.w), np.full_like(ci.bias, -0.0), ci.mask)
-    y = layer.new_output(fill_nan=True)
-    rows = torch.empty((layer.info["kept"], 8), dtype=y.dtype, device=y.device)
-    layer.sparse(x, y)
-    B.sparse_conv_run_rows(layer.plan, x, layer.bias, rows, B.SC_ROWS_DENSE, B.SC_ROWS_COMPACT)
-    assert not R.bits_of(rows).any() and not R.bits_of(y).any()
-
-
 # ---------------------------------------------------------------------------------------------------------
 # compact input under the producer's mask (sparse_conv_plan_set_input_mask)
 # ---------------------------------------------------------------------------------------------------------
