@@ -352,7 +352,7 @@ __global__ __launch_bounds__(2 * BM * KS, 2) void igemm_split_kernel(const ConvP
       all_landed(w0);
     };
     if (steps > 1) tile(Zero{});
-    if (p.zero_fill) fill_zeros();        // (these stores drain under the K loop)
+    if (p.zero_fill) fill_zeros();        // (under the products of a tile's first half: the next arrive waits for the stores too)
     int i = 1;
 #pragma unroll 1
     for (; i + 2 < steps; i += 2) {

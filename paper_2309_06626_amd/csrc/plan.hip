@@ -1461,11 +1461,12 @@ static bool leave_to_others(const sc_plan* pl, LaunchForm form) {
   // image, 6.4 / 7.1; 16 -> 16 @56, four images, 6.9 / 7.3; with 2.3e8 multiply-adds in all rows 10.4 and 11.4 / 9.5 and 10.8.
   if (form == kPlainRun && pl->band.ok && (double)g.m * g.k * d.c_out < 8e7) return true;
   // Float layers with a short K and few outputs: the launch is most of the time, and the tiles that contract every row and mask at
-  // the store save the row list's round trip (fused launches do not have that form).  Half of the rows, plain / compact output, by K
-  // tiles of 32 entries, pointwise @28: 16 x 32 -> 64 (1) 4.7 / 6.1, 4.05 / 4.4; 64 -> 64 (2) 5.4 / 6.1, 4.75 / 5.05; 128 -> 64 (4)
-  // 6.9 / 7.2, 6.3 / 6.2; 160 -> 64 (5) 7.7 / 7.3; more outputs: 16 x 32 -> 256 (1) 9.4 / 10.1, 96 -> 256 (3) 12.1 / 11.6, 32 x 32 -> 64
-  // @56 (1) 16.2 / 13.8.
-  return form != kFusedRun && stage_is_direct(d, g) && g.stage_k_tiles <= 4 && (double)g.m * d.c_out * g.stage_k_tiles < 4e6;
+  // the store save the row list's round trip (fused launches do not have that form; compact and dense runs, which would gain, add in the
+  // order of the plain one).  Half of the rows, another kernel / staged, plain, compact output and dense, by K tiles of 32 entries,
+  // pointwise @28: 16 x 32 -> 64 (1) 5.1 / 5.9, 4.55 / 4.15, 5.0 / 4.7; 64 -> 64 (2) 5.8 / 6.1, 5.2 / 4.6, 5.7 / 5.2; 32 x 32 -> 32 (1) 5.5 / 5.8, 4.8 / 4.1, 5.3 /
+  // 4.7; 16 x 128 -> 64 (4) 7.3 / 6.6, 6.9 / 5.5, 7.3 / 6.0; more outputs: 32 -> 256 (1) 9.9 / 7.85, 7.4 / 5.6, 11.3 / 7.7, 96 -> 96 (3) 7.4 / 7.2, 6.2 / 5.4, 9.3 /
+  // 6.3.
+  return form != kFusedRun && stage_is_direct(d, g) && g.stage_k_tiles <= 4 && (double)g.m * d.c_out * g.stage_k_tiles < 2.4e6;
 }
 // does a run take it?  (not where a tile, a band kernel or another form of the tiled kernel was asked for)
 static bool use_stage(const sc_plan* pl, int which, LaunchForm form = kPlainRun) {
