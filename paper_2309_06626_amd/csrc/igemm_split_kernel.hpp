@@ -9,13 +9,14 @@
 //
 // What bounds it: the issue slots of a wavefront.  A K tile of 128 x 64 is 24 MFMAs (768 cycles), and about 110 instructions that
 // split, 16 LDS reads and 7 transfers at 5, 8 and 40 cycles; one after the other they took 1 950 cycles (0.885 us for a workgroup
-// alone), now 1 300 (0.57): the split of the next step and the transfers lie behind the MFMAs of this one, across the barrier, the
+// alone), now 1 300 (0.57 to 0.6): the split of the next step and the transfers lie behind the MFMAs of this one, across the barrier, the
 // places of a tap's rows are worked out once a tap, and what was left of the loop's own bookkeeping (700 cycles without any work) went
 // with its branches.  Deeper rings of tiles (three, four) change nothing: no transfer is waited for.  Two workgroups on a compute unit
 // still take 1.15 us a pair of tiles, LDS and the address unit (1 300 and 900 cycles) beside 1 540 of products.
-// Measured at s = 0.5 (float MFMA / split one after the other / this kernel, us; batch 32):  64 -> 64 @56 58 / 31 / 28 (132 TFLOP/s of
-// float arithmetic), 128 -> 128 @28 55 / 28.5 / 25.8, 256 -> 256 @14 61 / 38 / 31, batch 16 384 -> 384 @12 88 / 32 / 29.8, one image of
-// 128 -> 128 @28 32 / 15 / 12.7, 96 -> 256 @28 pointwise - / 14.5 / 13.0.  The same bits as before.
+// On 64 -> 64 @56 at batch 32 (392 workgroups) the matrix pipes are busy 38 % of the time, the address units 39, the vector issue 36, LDS 13.
+// Measured at s = 0.5 (float MFMA / split one after the other, stores in single lanes / this kernel, us; batch 32):  64 -> 64 @56 58 / 32 /
+// 28.5 (130 TFLOP/s of float arithmetic), 128 -> 128 @28 55 / 31 / 25.8, 256 -> 256 @14 61 / 38 / 30.7, batch 16 384 -> 384 @12 88 / 31 / 29.1, one image
+// of 128 -> 128 @28 32 / 14.5 / 12.2, batch 16 96 -> 256 @28 pointwise - / 11.9 / 9.0.  The same bits for the same tile.
 //
 // Two tiles in LDS a group: 56 KB and four wavefronts for 128 x 64, 44 for 128 x 32, 40 KB and two for 64 x 64, 28 for 64 x 32, so
 // that two to five workgroups of one group share a compute unit and fill each other's waits.
