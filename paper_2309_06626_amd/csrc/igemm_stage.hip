@@ -201,6 +201,17 @@ __global__ void repack_kernel(const typename Elem<DT>::T* __restrict__ w, v4i* _
     wp[(int64_t)row * per_row + g] = v;
     return;
   }
+  if constexpr (DT != kF32) {      // for the window kernel: [32 channels][chunk][K step][tap][lane], k_tiles chunks
+    const int idx = (blockIdx.x - row_blocks) * blockDim.x + threadIdx.x;
+    const int lane = idx & 63, unit = idx >> 6, tap = unit % taps, ks = unit / taps & 3, rest = unit / taps >> 2;
+    const int chunk = rest % k_tiles, nb = rest / k_tiles;
+    if (nb >= part_blocks) return;
+    T e[8];
+    group(nb * 32 + channel(lane & 31), tap * c_in + chunk * 64 + ks * 16 + (lane >> 5) * 8, e);
+    v4i v;
+    __builtin_memcpy(&v, e, 16);
+    parts[idx] = v;
+  }
   if constexpr (DT == kF32) {
     const int idx = (blockIdx.x - row_blocks) * blockDim.x + threadIdx.x;
     const int lane = idx & 63, unit = idx >> 6, ks = unit % D::KSTEPS, tile = unit / D::KSTEPS;
@@ -218,7 +229,8 @@ hipError_t repack_filters(int dtype, const void* w, void* wp, void* parts, int c
                           int part_blocks, int k_tiles, bool rotated, hipStream_t stream) {
   const int v = dtype == kF32 ? 4 : 8;
   const int row_blocks = (int)(((int64_t)rows * (k_stride / v) + 255) / 256);
-  const int blocks = row_blocks + (parts ? (int)(((int64_t)part_blocks * k_tiles * StageDims<kF32>::KSTEPS * 64 + 255) / 256) : 0);
+  const int64_t units = (int64_t)part_blocks * k_tiles * (dtype == kF32 ? StageDims<kF32>::KSTEPS : 4 * taps);
+  const int blocks = row_blocks + (parts ? (int)((units * 64 + 255) / 256) : 0);
   auto launch = [&](auto kern, auto* src) {
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, stream, src, (v4i*)wp, (v4i*)parts, c_out, c_in, taps, k_stride, rows, row_blocks,
                        part_blocks, k_tiles);

@@ -24,6 +24,7 @@
 #include "igemm_split_kernel.hpp"
 #include "igemm_stage_kernel.hpp"
 #include "igemm_streamk_kernel.hpp"
+#include "igemm_window_kernel.hpp"
 #include "igemm_panel_kernel.hpp"
 
 namespace sc {
@@ -644,6 +645,8 @@ struct Geometry {
   // gather's order, repeated entries of a pixel's last group, 32-channel blocks of its packed filters
   int32_t stage_gather, stage_k_tiles, stage_tail, stage_blocks;
   size_t off_stage_w, off_stage_tab;
+  bool window;             // the layer may run the window kernel (igemm_window_kernel.hpp): its packed filters at off_window_w
+  size_t off_window_w;
   size_t off_xrank, off_xcounts;   // depthwise layers with windows: rank map of a compact input, its segment counts
 };
 
@@ -761,6 +764,13 @@ static sc_status check_desc(const sc_conv_desc* d, Geometry* g) {
     g->off_stage_w = off;   off = align_up(off + (size_t)g->stage_blocks * g->stage_k_tiles * block_bytes, 256);
     g->off_stage_tab = off; off = align_up(off + (size_t)g->stage_k_tiles * tile * sizeof(KEntry), 256);
   }
+  // Window kernel: 3 x 3 at stride 1, whole chunks of channels, tensors and virtual pixels in 31 bits.
+  g->window = g->vec_gather && g->vec_out && d->dtype != SC_F32 && d->kh == 3 && d->kw == 3 && d->stride_h == 1 && d->stride_w == 1 &&
+              d->dil_h == 1 && d->dil_w == 1 && !depthwise && d->c_in % kWinChunk == 0 && g->x_elems * eb < lim &&
+              (int64_t)d->n * (d->h + 2 * (int64_t)d->pad_h) * (d->w + 2 * (int64_t)d->pad_w) < lim &&
+              (int64_t)((d->c_out + 31) / 32) * 32 * k * eb < lim && (int64_t)g->cout_pad * g->k_stride < lim;
+  g->off_window_w = off;
+  if (g->window) off = align_up(off + (size_t)((d->c_out + 31) / 32) * 32 * k * eb, 256);
   g->total = off;
   return SC_OK;
 }
@@ -1064,8 +1074,8 @@ struct sc_plan {
   const KernelEntry* table;
   int table_count;
   // grouped: tile whose launch with two groups of wavefronts, sharing K inside the workgroup, stands in for the split into
-  // `splits` shares where group_candidates allows it (-1: none); asked: by the environment
-  struct Pick { int ti, splits; bool masked; int grouped = -1; bool asked = false; };
+  // `splits` shares where group_candidates allows it (-1: none); asked: by the environment; us: its predicted time (0: not priced)
+  struct Pick { int ti, splits; bool masked; int grouped = -1; bool asked = false; double us = 0.0; };
   Pick pick[2];                    // tiled launch of the sparse / dense run when nothing is forced: tile, K splits, and
                                    // (sparse run) whether every row is contracted and the mask decides at the store
   bool prefer_tiled[2];            // measured by sparse_conv_plan_tune: the tiled launch beat the band / row-panel kernel
@@ -1086,6 +1096,8 @@ struct sc_plan {
   int stage_tuned;                 // sparse_conv_plan_tune measured that kernel fastest (1) or slower than another (-1); 0: not timed
   bool slab_ok;                    // the layer's geometry admits it
   int slab;                        // 0 = automatic, 1 = never, 2 = wherever it applies, 128 / 256 = with tiles of that many rows
+  struct Window { int bm, bn; bool before_bands; };
+  Window window[2];                // tile of the window kernel for the sparse / dense run (bm == 0: another kernel), and whether a band kernel gives way
   int slab_span[2][2];             // [sparse, dense run][128-row, 256-row tiles]: virtual rows of the widest tile's slab
   Slab slab_auto[2];               // what an automatic launch of the sparse / dense run takes (bm == 0: another kernel)
 };
@@ -1218,6 +1230,7 @@ static sc_plan::Pick model_pick(const sc_plan* pl, int which, int64_t rows) {
       const double t = predict_us(pl, pl->table[i], rows, 1, which == 0 && rows < g.m, 2);
       if (t < best_us) { best_us = t; best.grouped = i; }
     }
+  best.us = best_us;
   return best;
 }
 
@@ -1337,6 +1350,79 @@ static sc_plan::Slab slab_pick(const sc_plan* pl, int which, int64_t rows) {
     if (slab_buffer_bytes(pl->desc, bm, pl->slab_span[which][bm == 256])) return {bm, slab_splits(pl, bm, rows)};
   }
   return none;
+}
+// ---- window kernel ------------------------------------------------------------------------------------------
+// bytes of one of its slabs for tiles of bm rows (0: they do not fit)
+static int window_slab_bytes(const sc_plan* pl, int which, int bm) {
+  const sc_conv_desc& d = pl->desc;
+  int span = pl->slab_span[which][bm == 256];
+  if (pl->kept == pl->geo.m) span = std::max(span, pl->slab_span[1][bm == 256]);      // (such a run goes over the identity map)
+  const int64_t px = (int64_t)span * (d.w + 2 * d.pad_w);
+  if (span <= 0 || px > kWinMostPixels) return 0;
+  return (int)((px * kWinPitch + 8191) / 8192 * 8192);
+}
+// Its tile for the sparse / dense run, where it is expected to be faster than the cheapest tiled launch (bm == 0: it is not).
+// SPARSE_CONV_WINDOW_TILE=<bm>x<bn> overrides, in the place of band kernels too (tuning and tests); 0x0 switches the kernel off.
+static sc_plan::Window window_tile_for(const sc_plan* pl, int which) {
+  const sc_plan::Window none = {0, 0, false};
+  const sc_conv_desc& d = pl->desc;
+  const int64_t rows = which ? pl->geo.m : pl->kept;
+  if (!pl->geo.window || rows == 0 || !window_kernel(kBF16, 64, 64)) return none;
+  const int chunks = d.c_in / kWinChunk;
+  auto fits = [&](int bm, int bn) {
+    const int sb = window_kernel(kBF16, bm, bn) ? window_slab_bytes(pl, which, bm) : 0;
+    return sb > 0 && window_lds_bytes(bm, bn, sb, chunks) <= kLdsLimit;
+  };
+  int fbm = 0, fbn = 0;
+  if (const char* env = std::getenv("SPARSE_CONV_WINDOW_TILE"); env && std::sscanf(env, "%dx%d", &fbm, &fbn) == 2)
+    return fbm > 0 && fits(fbm, fbn) ? sc_plan::Window{fbm, fbn, true} : none;
+  // Band kernels that fetch their input once stay ahead (us, band kernel / this one: 32 x 64 -> 64 @56 10.3 / 16, 1 x 64 -> 64 @56 5.7 / 6.7).
+  // The plain one, to which deep layers of few outputs are left, gives way to this kernel and to the other tiles alike: 10 x 128 -> 16
+  // @11x16 14.8 / 7.3, 4 x 128 -> 16 @10x8 14.5 / 6.8; 58 x 128 -> 16 @31x36, every row kept, 41.9 / 15.8, in other tiles 12.0.
+  const BandPlan& band = which ? pl->band_dense : pl->band;
+  const bool plain_band = band.ok && !band.stream && !band.pp && !band.tap && !band.rowband;
+  if (band.ok && !band.stream && !(plain_band && chunks > 1)) return none;
+  // Priced like the other tiled launches (us, MI355X): a launch and its first round of workgroups, every further round, a chunk of 64
+  // channels in a round, what a chunk takes longer the more compute units it keeps busy, and a megabyte of y.  Fitted to the runs of 170
+  // layers (1 to 8 chunks, 16 to 512 outputs, maps of 7 to 80): standard deviation 4 to 8 %.  The others' price leaves out y and the
+  // round trip of a split walk's sums; with both added it is as good.  On those layers the choice between these tiles and the cheapest
+  // other launch takes 1.004 (sparse) and 1.006 times (dense) the time of the best one, and 1 / 1.34 and 1 / 1.35 of the others' alone.
+  // 256 rows are for runs over every row: a sparse one of so many spans too many pixels.
+  struct Shape { int bm, bn; double us[2][5]; };      // [sparse, dense]: first, further round, chunk, chunk by load, megabyte
+  static const Shape shapes[] = {{256, 128, {{0, 0, 0, 0, 0}, {5.10, 6.0, 4.73, 0.61, 0.245}}},
+                                 {128, 128, {{5.82, 3.34, 2.53, 0.04, 0.339}, {5.25, 3.67, 2.43, 0.49, 0.261}}},
+                                 {128, 64, {{5.72, 3.76, 1.37, 0.23, 0.257}, {5.33, 3.66, 1.28, 0.42, 0.197}}},
+                                 {64, 128, {{5.10, 0.82, 1.35, 0.43, 0.280}, {4.49, 1.16, 1.31, 0.66, 0.224}}},
+                                 {64, 64, {{5.30, 1.32, 0.72, 0.44, 0.219}, {4.84, 1.59, 0.69, 0.55, 0.0}}}};
+  const int cus = device_cus(), form = which || pl->kept == pl->geo.m ? 1 : 0;
+  const sc_plan::Pick& other = pl->pick[which];
+  const double mb = (double)pl->geo.y_elems * 2e-6;
+  const double other_us = form ? -0.75 + 1.017 * other.us + 0.515 * mb + (other.splits > 1 ? 2.4 : 0.0)
+                               : -0.38 + 0.99 * other.us + 0.372 * mb + (other.splits > 1 ? 2.85 : 0.0);
+  sc_plan::Window best = {0, 0, plain_band};
+  // (one chunk: nothing hides its slab; 10 x 64 -> 224 @16 6.35 / 6.6 in tiles that contract every row and mask at the store)
+  double best_us = other.us == 0.0 ? 0.0 : (chunks == 1 ? 0.97 : 1.0) * other_us;
+  for (const Shape& sh : shapes) {
+    if ((sh.bm == 256 && form == 0) || !fits(sh.bm, sh.bn)) continue;
+    const int64_t wgs = ((rows + sh.bm - 1) / sh.bm) * ((d.c_out + sh.bn - 1) / sh.bn);
+    const double load = (double)wgs / cus, rounds = (double)((wgs + cus - 1) / cus);
+    if (rounds > 1.0 && sh.bm == 64) continue;      // (set-up and sums again each round: 36 x 128 -> 432 @26x24 in three 24.0 / 30.0)
+    const double* c = sh.us[form];
+    const double us = c[0] + c[1] * (rounds - 1) + chunks * (c[2] * rounds + c[3] * load) + c[4] * mb;
+    if (us < best_us) { best_us = us; best = {sh.bm, sh.bn, plain_band}; }
+  }
+  return best;
+}
+// (not where a tile or a form of another kernel was asked for or measured faster)
+static bool window_is_free(const sc_plan* pl, int which, int64_t rows) {
+  return rows > 0 && pl->forced[which] == -1 && !pl->prefer_tiled[which] && pl->gather_pipeline == 0 && pl->split_k == 0 &&
+         pl->stream_k < 2 && pl->masked_store != 2 && pl->slab == 0 && pl->row_panel != 2 && !pl->slab_auto[which].bm;
+}
+// does a run of a dense input take the window kernel?
+static bool use_window(const sc_plan* pl, int which, int64_t rows) { return pl->window[which].bm > 0 && window_is_free(pl, which, rows); }
+// is the band kernel that applies left out for it, or for a tile?
+static bool bands_give_way(const sc_plan* pl, int which, int64_t rows) {
+  return pl->window[which].before_bands && window_is_free(pl, which, rows);
 }
 // ---- register-staged kernel ------------------------------------------------------------------------------
 // The direct-to-LDS form serves the float NHWC layers whose rows are whole 16-byte groups.
@@ -1486,7 +1572,9 @@ static TilePick pick_tile(const sc_plan* pl, int which, int64_t rows) {
     return tp;
   }
   tp.ti = pl->pick[which].ti;
-  tp.splits = pl->split_k == 1 ? 1 : std::min(pl->pick[which].splits, most_splits(pl, pl->table[tp.ti], rows));
+  // (a stream-K walk that is asked for where the window kernel would run finds no automatic split in its way)
+  const bool keep_whole = pl->split_k == 1 || (pl->stream_k >= 2 && pl->window[which].bm > 0);
+  tp.splits = keep_whole ? 1 : std::min(pl->pick[which].splits, most_splits(pl, pl->table[tp.ti], rows));
   tp.masked = pl->masked_store == 2 ? which == 0 : pl->masked_store == 1 ? false : pl->pick[which].masked;
   const sc_plan::Pick& pick = pl->pick[which];
   if (pick.grouped >= 0 && !tp.masked && (pick.asked || group_candidates(pl, pl->table[pick.grouped], rows) > 1))
@@ -1584,7 +1672,7 @@ static sc_status launch_conv(const sc_plan* pl, bool dense, const void* x, const
   const bool staged = use_stage(pl, which, residual ? kFusedRun : x_compact || y_compact ? kCompactRun : kPlainRun);
   const bool use_band = band.ok && !x_compact && !y_compact && (!residual || ((band.pp || band.tap) && !band.stream)) &&
                         (pl->forced[which] == kForceBand || (pl->forced[which] == -1 && !band.stream && !pl->prefer_tiled[which])) &&
-                        !(slab.bm && pl->slab >= 2) && !staged;
+                        !(slab.bm && pl->slab >= 2) && !staged && !bands_give_way(pl, which, rows);
   if (use_band) {
     const BandPlan& b = band;
     BandParams q;
@@ -1665,6 +1753,46 @@ static sc_status launch_conv(const sc_plan* pl, bool dense, const void* x, const
     const int cpp = d.c_in / g.vec;
     const int shape = (d.kh == 3 && d.kw == 3 && cpp == 8) ? 1 : (d.kh == 3 && d.kw == 3 && cpp == 4) ? 2 : 0;
     SC_HIP(pl->band_table->fn[shape][b.ni_idx][mi_idx](q, b.lds, stream));
+    return SC_OK;
+  }
+  if (!x_compact && !slab.bm && use_window(pl, which, rows)) {
+    const sc_plan::Window win = pl->window[which];
+    ConvParams p;
+    std::memset(&p, 0, sizeof(p));
+    p.x = x;
+    p.wp = pl->ws + g.off_window_w;
+    p.bias = d.has_bias ? bias : nullptr;
+    p.y = y;
+    p.row_idx = identity ? nullptr : reinterpret_cast<const int32_t*>(pl->ws + g.off_rows);
+    p.mask = pl->ws + g.off_mask;
+    p.rows = (int32_t)rows;
+    p.m_total = (int32_t)g.m;
+    p.h = d.h; p.w = d.w; p.ho_wo = g.ho * g.wo; p.wo = g.wo;
+    magic_div((uint32_t)p.ho_wo, &p.div_howo_mul, &p.div_howo_shift);
+    magic_div((uint32_t)p.wo, &p.div_wo_mul, &p.div_wo_shift);
+    p.ph = d.pad_h; p.pw = d.pad_w;
+    p.c_in = d.c_in; p.c_out = d.c_out;
+    p.relu = d.relu;
+    p.zero_fill = zero_fill ? 1 : 0;
+    p.mask_spatial = d.mask_mode == SC_MASK_SPATIAL;
+    p.y_compact = compact && y_compact ? 1 : 0;
+    p.residual = residual;
+    p.residual_relu = residual_relu ? 1 : 0;
+    p.m_tiles = (int32_t)((rows + win.bm - 1) / win.bm);
+    p.n_tiles = (d.c_out + win.bn - 1) / win.bn;
+    p.x_bytes = (uint32_t)(g.x_elems * eb);
+    p.w_bytes = (uint32_t)((uint64_t)((d.c_out + 31) / 32) * 32 * g.k * eb);
+    p.slab_bytes = window_slab_bytes(pl, which, win.bm);
+    p.slab_hp = d.h + 2 * d.pad_h;
+    p.slab_wp = d.w + 2 * d.pad_w;
+    magic_div((uint32_t)p.slab_hp, &p.div_hp_mul, &p.div_hp_shift);
+    magic_div((uint32_t)p.slab_wp, &p.div_wp_mul, &p.div_wp_shift);
+#ifdef SC_TIMING
+    p.dbg = g_dbg;
+#endif
+    LaunchFn fn = window_kernel(d.dtype == SC_BF16 ? kBF16 : kF16, win.bm, win.bn);
+    if (!fn || !p.slab_bytes) return SC_ERR_UNSUPPORTED;    // cannot happen: the pick checked both
+    SC_HIP(fn(p, stream));
     return SC_OK;
   }
   if (slab.bm) {
@@ -1896,8 +2024,9 @@ static sc_status pack_filters(const sc_conv_desc& d, const Geometry& g, unsigned
   if (by_groups) {
     const bool parts = g.stage_gather == kStageGroups;
     const int blocks32 = (d.c_out + 31) / 32;
-    SC_HIP(repack_filters(dt, w_dev, ws + g.off_wp, parts ? ws + g.off_stage_w : nullptr, d.c_out, d.c_in, d.kh * d.kw, g.k_stride,
-                          tables ? g.cout_pad : blocks32 * 32, tables ? g.stage_blocks : blocks32, g.stage_k_tiles, rotated, stream));
+    SC_HIP(repack_filters(dt, w_dev, ws + g.off_wp, parts ? ws + g.off_stage_w : g.window ? ws + g.off_window_w : nullptr, d.c_out, d.c_in,
+                          d.kh * d.kw, g.k_stride, tables ? g.cout_pad : blocks32 * 32, tables && parts ? g.stage_blocks : blocks32,
+                          parts ? g.stage_k_tiles : d.c_in / kWinChunk, rotated, stream));
   } else {
     int64_t total = (int64_t)g.cout_pad * g.k_stride;
     int grid = (int)((total + 255) / 256);
@@ -1941,7 +2070,7 @@ static sc_status build_row_tables(const sc_conv_desc& d, const Geometry& g, unsi
   int32_t* rows = reinterpret_cast<int32_t*>(ws + g.off_rows);
   int32_t* kept_dev = reinterpret_cast<int32_t*>(ws + g.off_kept);
   int32_t host_vals[4] = {-1, 0, 0, 0};   // kept count, most kept rows in one band, widest slab of a 128-row / 256-row tile
-  const bool slab = slab_geometry_ok(d, g);
+  const bool slab = slab_geometry_ok(d, g) || g.window;
   // One launch up to 2^17 rows (where a run of rows cut in two leaves both halves a pixel); beyond that every workgroup's
   // count of the rows in front of it costs more than a pass of its own.  Measured per refresh on a
   // 56 x 56 map of one image, us of GPU time: 13 in five launches and a copy, 5 in one.
@@ -2135,8 +2264,10 @@ sc_status sparse_conv_plan(const sc_conv_desc* desc, const uint8_t* mask_dev, co
   pl->slab = 0;
   pl->slab_ok = slab_geometry_ok(d, g) && slab_kernel(d.dtype == SC_BF16 ? kBF16 : kF16, 128, false);
   pl->slab_span[0][0] = slab_span[0]; pl->slab_span[0][1] = slab_span[1];
-  pl->slab_span[1][0] = pl->slab_ok ? slab_dense_span(d, g, 128) : 0;
-  pl->slab_span[1][1] = pl->slab_ok ? slab_dense_span(d, g, 256) : 0;
+  pl->slab_span[1][0] = pl->slab_ok || g.window ? slab_dense_span(d, g, 128) : 0;
+  pl->slab_span[1][1] = pl->slab_ok || g.window ? slab_dense_span(d, g, 256) : 0;
+  pl->window[0] = window_tile_for(pl, 0);
+  pl->window[1] = window_tile_for(pl, 1);
   // (automatic launches take the slab form only where sparse_conv_plan_tune measured it faster: the cost model's
   // quantities -- bytes through the L1 path, matrix time -- do not rank it, its K loop is bound by LDS reads)
   pl->slab_auto[0] = pl->slab_auto[1] = sc_plan::Slab{0, 1};
@@ -2168,6 +2299,7 @@ sc_status sparse_conv_plan_set_mask(sc_plan* plan, const uint8_t* mask_dev, void
   stage_tiles_for(d, g, plan->kept, plan->stage_pick);
   plan->slab_span[0][0] = slab_span[0]; plan->slab_span[0][1] = slab_span[1];
   plan->slab_auto[0] = sc_plan::Slab{0, 1};
+  plan->window[0] = window_tile_for(plan, 0);
   return SC_OK;
 }
 
@@ -2511,17 +2643,26 @@ sc_status sparse_conv_plan_tiles(const sc_plan* plan, int32_t which, int32_t* ti
   }
   const BandPlan& band = which ? plan->band_dense : plan->band;
   if (band.ok && (plan->forced[which] == kForceBand || (plan->forced[which] == -1 && !band.stream && !plan->prefer_tiled[which])) &&
-      !(plan->slab >= 2 && slab_pick(plan, which, which ? plan->geo.m : plan->kept).bm) && !use_stage(plan, which)) {
+      !(plan->slab >= 2 && slab_pick(plan, which, which ? plan->geo.m : plan->kept).bm) && !use_stage(plan, which) &&
+      !bands_give_way(plan, which, which ? plan->geo.m : plan->kept)) {
     if (tile_m) *tile_m = -band.bh;     // (rows per run; split bands hold half a run each)
     if (tile_n) *tile_n = 32 * band.ni;
     if (workgroups) *workgroups = band.pp && !band.tap ? band.pp_grid : (int64_t)band.n_bands * band.n_tiles;
     return SC_OK;
   }
   int64_t rows = which ? plan->geo.m : plan->kept;
+  const bool window = use_window(plan, which, rows);
   if (const sc_plan::Slab sl = slab_pick(plan, which, rows); sl.bm) {
     if (tile_m) *tile_m = sl.bm;
     if (tile_n) *tile_n = kSlabBN;
     if (workgroups) *workgroups = ((rows + sl.bm - 1) / sl.bm) * ((plan->desc.c_out + kSlabBN - 1) / kSlabBN) * std::min(sl.splits, plan->desc.c_in / kSlabCh);
+    return SC_OK;
+  }
+  if (window) {
+    const sc_plan::Window win = plan->window[which];
+    if (tile_m) *tile_m = win.bm;
+    if (tile_n) *tile_n = win.bn;
+    if (workgroups) *workgroups = ((rows + win.bm - 1) / win.bm) * ((plan->desc.c_out + win.bn - 1) / win.bn);
     return SC_OK;
   }
   if (use_stage(plan, which)) {
@@ -2553,6 +2694,7 @@ sc_status sparse_conv_plan_tiles(const sc_plan* plan, int32_t which, int32_t* ti
 static const char* tiled_kernel_name(const sc_plan* plan, int32_t which, LaunchForm form) {
   const Geometry& g = plan->geo;
   if (use_stage(plan, which, form)) return "tile_staged";
+  if (use_window(plan, which, which ? g.m : plan->kept)) return "tile_lds_direct";
   const TilePick tp = pick_tile(plan, which, which ? g.m : plan->kept);
   if (tp.masked) return "tile_masked_store";
   if (tp.splits > 1) return "tile_split_k";
@@ -2567,7 +2709,8 @@ const char* sparse_conv_plan_kernel(const sc_plan* plan, int32_t which) {
   if (plan->geo.depthwise) return "depthwise";
   const BandPlan& band = which ? plan->band_dense : plan->band;
   if (band.ok && (plan->forced[which] == kForceBand || (plan->forced[which] == -1 && !band.stream && !plan->prefer_tiled[which])) &&
-      !(plan->slab >= 2 && slab_pick(plan, which, which ? plan->geo.m : plan->kept).bm) && !use_stage(plan, which))
+      !(plan->slab >= 2 && slab_pick(plan, which, which ? plan->geo.m : plan->kept).bm) && !use_stage(plan, which) &&
+      !bands_give_way(plan, which, which ? plan->geo.m : plan->kept))
     return band.rowband ? "band_row_segments" : band.stream ? "band_stream" : band.tap ? "band_tap" : band.pp ? "band_alternating" : "band";
   const Geometry& g = plan->geo;
   if (slab_pick(plan, which, which ? g.m : plan->kept).bm) return "tile_slab";

@@ -1,0 +1,107 @@
+"""Window kernel (3x3 layers at stride 1 with whole chunks of 64 channels: every input pixel of a tile once in LDS, filters straight
+into registers) against the oracle, through the C ABI."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from oracle import oracle
+from paper_2309_06626_amd import binding as B
+from paper_2309_06626_amd import runtime as R
+from parity import check_layer, row_mask
+from test_gpu_compact import check_compact_output
+from test_gpu_parity import spec_of
+from test_gpu_residual import check as check_residual
+
+pytestmark = pytest.mark.gpu
+
+TILES = [(256, 128), (128, 128), (128, 64), (64, 128), (64, 64)]
+SHAPES = {
+    "one_chunk_edge_channels": dict(n=2, cin=64, h=15, w=13, cout=80),             # no second slab; half a block of channels
+    "images_in_a_tile": dict(n=9, cin=128, h=7, w=5, cout=144, sp=0.3),            # maps smaller than a set of lanes
+    "no_padding": dict(n=2, cin=128, h=12, w=10, cout=320, p=0),
+    "padding_2": dict(n=1, cin=192, h=8, w=30, cout=16, p=2, sp=0.0),              # output larger than the input, every row kept
+    "one_row_kept": dict(n=1, cin=64, h=6, w=6, cout=32, sp=0.97),
+    "wide_map": dict(n=1, cin=64, h=4, w=120, cout=64, sp=0.7),                    # a tap row is most of the slab
+}
+
+
+def fits(spec, mask, tile):
+    """Whether the widest slab of a tile fits: at most 512 pixels, and its one or two buffers beside the rest of LDS."""
+    rows = oracle.compact_rows(row_mask(spec, mask))
+    hp, wp = spec.h + 2 * spec.pad_h, spec.w + 2 * spec.pad_w
+    span = 0
+    for r in (rows, np.arange(spec.m)) if rows.size == spec.m else (rows,):
+        vrow = (r // (spec.ho * spec.wo)) * hp + (r % (spec.ho * spec.wo)) // spec.wo
+        bm = max(tile[0], 128)                      # (64-row tiles go by the widest of 128 rows)
+        first, last = vrow[::bm], vrow[np.minimum(np.arange(0, r.size, bm) + bm, r.size) - 1]
+        span = max(span, int((last + 3 - first).max()))
+    slab = -(-span * wp * 144 // 8192) * 8192 * (2 if spec.c_in > 64 else 1)
+    sums = {(256, 128): 0, (128, 128): 4, (128, 64): 4, (64, 128): 2, (64, 64): 2}[tile] * 32768
+    rest = tile[0] * 12 + tile[1] * 4 + 2048 + 128 + (tile[0] + 64) * 4
+    return span * wp <= 512 and max(slab, sums) + rest <= 160 * 1024
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("tile", TILES)
+@pytest.mark.parametrize("shape", list(SHAPES))
+def test_window_kernel_matches_the_oracle(shape, tile, dtype, monkeypatch):
+    monkeypatch.setenv("SPARSE_CONV_WINDOW_TILE", "%dx%d" % tile)
+    spec = spec_of(dtype=dtype, **SHAPES[shape])
+    ci = W.make_conv_inputs(spec, 3000 + len(shape))
+    layer = check_layer(ci)
+    if fits(spec, ci.mask, tile):
+        assert B.sparse_conv_plan_kernel(layer.plan, 0) == "tile_lds_direct" and B.sparse_conv_plan_tiles(layer.plan, 0)[:2] == tile
+
+
+@pytest.mark.parametrize("tile", TILES)
+def test_window_kernel_other_operands(tile, monkeypatch):
+    """Rows left alone, compact rows, shortcut sums, a shared mask; masks with long runs of dropped rows; new masks."""
+    monkeypatch.setenv("SPARSE_CONV_WINDOW_TILE", "%dx%d" % tile)
+    spec = spec_of(3, 128, 10, 9, 96, sp=0.4)
+    check_layer(W.make_conv_inputs(spec, 3100), out_mode=B.SC_OUT_SCATTER_ONLY)
+    check_layer(W.make_conv_inputs(spec.with_(mask_mode="spatial"), 3101))
+    check_compact_output(spec, 3102)
+    for sp in (0.4, 0.0, 0.9):                       # (at 0.9 most dropped rows lie behind the listed ones)
+        check_residual(spec.with_(sparsity=sp, relu=False), 3103, True, want_kernel=("tile_lds_direct", "tile_masked_store", "tile_split_k"))
+    ci = W.make_conv_inputs(spec.with_(sparsity=0.5), 3104)
+    half = np.zeros_like(ci.mask)
+    half[::2] = 1                                    # every other pixel: all rows of a set of lanes in half of the bank groups
+    runs = np.sort(ci.mask)                          # all dropped rows in front
+    for mask in (half, runs, runs[::-1].copy()):
+        check_layer(dataclasses.replace(ci, mask=mask))
+    layer = R.ConvLayer(spec.with_(sparsity=0.5), ci.w, ci.bias, ci.mask)
+    x = R.to_device(ci.x, spec.dtype)
+    for mask in (runs, half):
+        B.sparse_conv_plan_set_mask(layer.plan, torch.from_numpy(mask.astype(np.uint8)).cuda())
+        fresh = R.ConvLayer(spec.with_(sparsity=0.5), ci.w, ci.bias, mask)
+        assert np.array_equal(R.bits_of(layer.sparse(x)), R.bits_of(fresh.sparse(x)))
+
+
+def test_values_outside_a_window_do_not_enter(monkeypatch):
+    """Infinities of a pixel reach the rows whose window holds it and no others, at the borders of images too."""
+    monkeypatch.setenv("SPARSE_CONV_WINDOW_TILE", "64x64")
+    spec = spec_of(2, 64, 9, 8, 32, sp=0.0, relu=False)
+    ci = W.make_conv_inputs(spec, 3200)
+    layer = R.ConvLayer(spec, ci.w, ci.bias, ci.mask)
+    clean = layer.sparse(R.to_device(ci.x, spec.dtype)).clone()
+    for n, y, x in ((0, 8, 7), (1, 0, 0), (0, 4, 0)):
+        bad = ci.x.copy()
+        bad[n, y, x, :] = np.inf
+        got = layer.sparse(R.to_device(bad, spec.dtype))
+        reached = torch.zeros(got.shape[:3], dtype=torch.bool, device=got.device)
+        reached[n, max(y - 1, 0): y + 2, max(x - 1, 0): x + 2] = True
+        assert torch.equal(got[~reached], clean[~reached]) and not torch.isfinite(got[reached].float()).any()
+
+
+def test_refreshed_filters_reach_the_window_kernel(monkeypatch):
+    monkeypatch.setenv("SPARSE_CONV_WINDOW_TILE", "64x128")
+    spec = spec_of(2, 128, 9, 8, 72 + 8, sp=0.3)
+    one, two = W.make_conv_inputs(spec, 3300), W.make_conv_inputs(spec, 3301)
+    layer = R.ConvLayer(spec, one.w, one.bias, one.mask)
+    fresh = R.ConvLayer(spec, two.w, one.bias, one.mask)
+    B.sparse_conv_plan_set_filters(layer.plan, R.to_device(two.w, spec.dtype))
+    x = R.to_device(one.x, spec.dtype)
+    assert np.array_equal(R.bits_of(layer.sparse(x)), R.bits_of(fresh.sparse(x)))
