@@ -207,7 +207,8 @@ __global__ void repack_kernel(const typename Elem<DT>::T* __restrict__ w, v4i* _
     const int chunk = rest % k_tiles, nb = rest / k_tiles;
     if (nb >= part_blocks) return;
     T e[8];
-    group(nb * 32 + channel(lane & 31), tap * c_in + chunk * 64 + ks * 16 + (lane >> 5) * 8, e);
+    const int ci = chunk * 64 + ks * 16 + (lane >> 5) * 8;
+    group(nb * 32 + channel(lane & 31), ci < c_in ? tap * c_in + ci : k, e);      // (zeros behind the last channel)
     v4i v;
     __builtin_memcpy(&v, e, 16);
     parts[idx] = v;

@@ -1,4 +1,4 @@
-// Tiled masked-convolution kernel for 3 x 3 windows at stride 1 (16-bit NHWC, Cin a multiple of 64): every input pixel of a tile
+// Tiled masked-convolution kernel for 3 x 3 windows at stride 1 (16-bit NHWC, Cin and Cout multiples of 8): every input pixel of a tile
 // passes into LDS once, the filters go straight into registers.
 //
 // What bounds the tiled kernels whose K tiles pass a ring in LDS (igemm_buf_kernel), taken apart by leaving one thing out at a time
@@ -62,7 +62,7 @@ __global__ __launch_bounds__(512) void igemm_window_kernel(const ConvParams p) {
   static_assert(EB == 2 && D::WAVES_M * D::WAVES_N * KG == 8, "16-bit operands, eight wavefronts");
 
   extern __shared__ __align__(16) unsigned char smem[];
-  const int chunks = p.c_in / kWinChunk;
+  const int chunks = (p.c_in + kWinChunk - 1) / kWinChunk, last_ci = p.c_in - (chunks - 1) * kWinChunk;      // channels of the last chunk
   const size_t slabs = (size_t)p.slab_bytes * (chunks > 1 ? 2 : 1);
   int32_t* s_rows = reinterpret_cast<int32_t*>(smem + (slabs > D::sums_bytes() ? slabs : D::sums_bytes()));      // [BM] row of y
   int32_t* s_corner = s_rows + BM;                        // [BM] LDS byte of the window's first pixel
@@ -148,18 +148,20 @@ __global__ __launch_bounds__(512) void igemm_window_kernel(const ConvParams p) {
   if (t < 32) s_count[t] = 0;
   if (t < BN) s_bias[t] = bias_v;
   __syncthreads();
-  uint32_t s_voff[kWinRounds];
+  uint32_t s_voff[kWinRounds], in_last = 0;               // (bit j: the group lies inside the last chunk)
 #pragma unroll
   for (int j = 0; j < kWinRounds; ++j) {
     const int g = j * 512 + t, px = g / kWinGroups, in = g - px * kWinGroups;
     const uint32_t at = px < kWinMostPixels ? (uint32_t)s_px[min(px, kWinMostPixels - 1)] : kOutOfRange;
     s_voff[j] = in < kWinGroups - 1 && at != kOutOfRange ? at + in * 16 : kOutOfRange;      // out of range: LDS gets zeros
+    in_last |= (in * 8 < last_ci ? 1u : 0u) << j;
   }
   auto ask_slab = [&](int chunk) {
     unsigned char* dst = smem + (chunk & 1) * p.slab_bytes + wave * 1024;
+    const uint32_t in_chunk = chunk + 1 < chunks ? ~0u : in_last;
 #pragma unroll
     for (int j = 0; j < kWinRounds; ++j) {
-      const uint32_t voff = s_voff[j];      // (a local: as a direct argument the host pass drops the kernel's stub)
+      const uint32_t voff = in_chunk >> j & 1u ? s_voff[j] : kOutOfRange;
       if (j < rounds) __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void*)(dst + j * 8192), 16, voff, chunk * kWinChunk * EB, 0, 0);
     }
   };
@@ -242,6 +244,7 @@ __global__ __launch_bounds__(512) void igemm_window_kernel(const ConvParams p) {
     const unsigned slab_at = (unsigned)((chunk & 1) * p.slab_bytes);
 #pragma unroll 1
     for (int q = 0; q < D::PASSES; ++q, ++pass) {
+      if (chunk + 1 == chunks && (kg + KG * q) * 16 >= last_ci) break;      // (no channels left in the last chunk)
       const int next_at = pass_at(pass + 1);
       const unsigned from = slab_at + (unsigned)(q * KG * 32);
       v4i xa[3][MI];
@@ -361,7 +364,7 @@ __global__ __launch_bounds__(512) void igemm_window_kernel(const ConvParams p) {
     for (int b = 0; b < D::MINE; ++b) {
       const int rr = s_rows[wm0 + ((KG == 1 ? 0 : kg * D::MINE) + b) * 32 + fp];
       if (rr < 0) continue;
-      store_kept_block_res<DT>(sum[b], rr, c0, y, p.bias ? s_bias + (c0 - n0) : nullptr, 0, p.relu, 1, p.c_out, p.ho_wo, 0, 0, 0,
+      store_kept_block_res<DT>(sum[b], rr, c0, y, p.bias ? s_bias + (c0 - n0) : nullptr, 0, p.relu, p.vec_out, p.c_out, p.ho_wo, 0, 0, 0,
                                static_cast<const T*>(p.residual), p.residual_relu);
     }
   }
@@ -369,7 +372,7 @@ __global__ __launch_bounds__(512) void igemm_window_kernel(const ConvParams p) {
 
 template <int DT, int BM, int BN>
 hipError_t igemm_window_launch(const ConvParams& p, hipStream_t stream) {
-  const size_t lds = win_lds_bytes<BM, BN>(p.slab_bytes, p.c_in / kWinChunk);
+  const size_t lds = win_lds_bytes<BM, BN>(p.slab_bytes, (p.c_in + kWinChunk - 1) / kWinChunk);
   auto kern = igemm_window_kernel<DT, BM, BN>;
   static std::atomic<bool> attr_set{false};
   if (!attr_set) {

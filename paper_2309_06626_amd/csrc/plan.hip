@@ -764,13 +764,14 @@ static sc_status check_desc(const sc_conv_desc* d, Geometry* g) {
     g->off_stage_w = off;   off = align_up(off + (size_t)g->stage_blocks * g->stage_k_tiles * block_bytes, 256);
     g->off_stage_tab = off; off = align_up(off + (size_t)g->stage_k_tiles * tile * sizeof(KEntry), 256);
   }
-  // Window kernel: 3 x 3 at stride 1, whole chunks of channels, tensors and virtual pixels in 31 bits.
-  g->window = g->vec_gather && g->vec_out && d->dtype != SC_F32 && d->kh == 3 && d->kw == 3 && d->stride_h == 1 && d->stride_w == 1 &&
-              d->dil_h == 1 && d->dil_w == 1 && !depthwise && d->c_in % kWinChunk == 0 && g->x_elems * eb < lim &&
+  // Window kernel: 3 x 3 at stride 1, whole 16-byte groups, tensors and virtual pixels in 31 bits.  Its packed filters hold whole chunks.
+  const int64_t window_k = (int64_t)9 * ((d->c_in + kWinChunk - 1) / kWinChunk) * kWinChunk;
+  g->window = g->vec_gather && (g->vec_out || g->vec_out8) && d->dtype != SC_F32 && d->kh == 3 && d->kw == 3 && d->stride_h == 1 && d->stride_w == 1 &&
+              d->dil_h == 1 && d->dil_w == 1 && !depthwise && g->x_elems * eb < lim &&
               (int64_t)d->n * (d->h + 2 * (int64_t)d->pad_h) * (d->w + 2 * (int64_t)d->pad_w) < lim &&
-              (int64_t)((d->c_out + 31) / 32) * 32 * k * eb < lim && (int64_t)g->cout_pad * g->k_stride < lim;
+              (int64_t)((d->c_out + 31) / 32) * 32 * window_k * eb < lim && (int64_t)g->cout_pad * g->k_stride < lim;
   g->off_window_w = off;
-  if (g->window) off = align_up(off + (size_t)((d->c_out + 31) / 32) * 32 * k * eb, 256);
+  if (g->window) off = align_up(off + (size_t)((d->c_out + 31) / 32) * 32 * window_k * eb, 256);
   g->total = off;
   return SC_OK;
 }
@@ -1096,8 +1097,9 @@ struct sc_plan {
   int stage_tuned;                 // sparse_conv_plan_tune measured that kernel fastest (1) or slower than another (-1); 0: not timed
   bool slab_ok;                    // the layer's geometry admits it
   int slab;                        // 0 = automatic, 1 = never, 2 = wherever it applies, 128 / 256 = with tiles of that many rows
-  struct Window { int bm, bn; bool before_bands; };
-  Window window[2];                // tile of the window kernel for the sparse / dense run (bm == 0: another kernel), and whether a band kernel gives way
+  struct Window { int bm, bn; bool before_bands, plain_only = false; };
+  Window window[2];                // tile of the window kernel for the sparse / dense run (bm == 0: another kernel), whether a band kernel gives way,
+                                   // and whether only plain runs take it (the others never went to that band kernel)
   int slab_span[2][2];             // [sparse, dense run][128-row, 256-row tiles]: virtual rows of the widest tile's slab
   Slab slab_auto[2];               // what an automatic launch of the sparse / dense run takes (bm == 0: another kernel)
 };
@@ -1368,7 +1370,7 @@ static sc_plan::Window window_tile_for(const sc_plan* pl, int which) {
   const sc_conv_desc& d = pl->desc;
   const int64_t rows = which ? pl->geo.m : pl->kept;
   if (!pl->geo.window || rows == 0 || !window_kernel(kBF16, 64, 64)) return none;
-  const int chunks = d.c_in / kWinChunk;
+  const int chunks = (d.c_in + kWinChunk - 1) / kWinChunk;
   auto fits = [&](int bm, int bn) {
     const int sb = window_kernel(kBF16, bm, bn) ? window_slab_bytes(pl, which, bm) : 0;
     return sb > 0 && window_lds_bytes(bm, bn, sb, chunks) <= kLdsLimit;
@@ -1376,12 +1378,15 @@ static sc_plan::Window window_tile_for(const sc_plan* pl, int which) {
   int fbm = 0, fbn = 0;
   if (const char* env = std::getenv("SPARSE_CONV_WINDOW_TILE"); env && std::sscanf(env, "%dx%d", &fbm, &fbn) == 2)
     return fbm > 0 && fits(fbm, fbn) ? sc_plan::Window{fbm, fbn, true} : none;
-  // Band kernels that fetch their input once stay ahead (us, band kernel / this one: 32 x 64 -> 64 @56 10.3 / 16, 1 x 64 -> 64 @56 5.7 / 6.7).
-  // The plain one, to which deep layers of few outputs are left, gives way to this kernel and to the other tiles alike: 10 x 128 -> 16
-  // @11x16 14.8 / 7.3, 4 x 128 -> 16 @10x8 14.5 / 6.8; 58 x 128 -> 16 @31x36, every row kept, 41.9 / 15.8, in other tiles 12.0.
+  // Band kernels that fetch their input once stay ahead (us, band kernel / this one: 32 x 64 -> 64 @56 10.3 / 16, 1 x 64 -> 64 @56 5.7 /
+  // 6.7, 8 x 32 -> 16 @48 4.4 / 6.5).  The plain one gives way to this kernel and to the other tiles alike from 48 channels on: 3 x 48 ->
+  // 32 @17x22 8.1 / 6.3, 44 x 112 -> 32 @12x10 13.4 / 7.4, 4 x 128 -> 16 @10x8 14.5 / 6.8; 58 x 128 -> 16 @31x36, every row kept, 41.9 / 15.8,
+  // in other tiles 12.0.  With fewer channels it takes 7 and more before many outputs (3 x 32 -> 144 @35 9.6 / 6.7, 1 x 16 -> 240 @20 7.7 /
+  // 6.3), where this kernel is one round of workgroups (6 x 32 -> 368 @52 is not: 15.3 / 16.9).
   const BandPlan& band = which ? pl->band_dense : pl->band;
-  const bool plain_band = band.ok && !band.stream && !band.pp && !band.tap && !band.rowband;
-  if (band.ok && !band.stream && !(plain_band && chunks > 1)) return none;
+  const bool band_runs = band.ok && !band.stream, plain_band = band_runs && !band.pp && !band.tap && !band.rowband && !std::getenv("SPARSE_CONV_BAND_KERNEL");
+  const bool deep = d.c_in >= 48;
+  if (band_runs && !(plain_band && (deep || d.c_out >= 80))) return none;
   // Priced like the other tiled launches (us, MI355X): a launch and its first round of workgroups, every further round, a chunk of 64
   // channels in a round, what a chunk takes longer the more compute units it keeps busy, and a megabyte of y.  Fitted to the runs of 170
   // layers (1 to 8 chunks, 16 to 512 outputs, maps of 7 to 80): standard deviation 4 to 8 %.  The others' price leaves out y and the
@@ -1397,19 +1402,30 @@ static sc_plan::Window window_tile_for(const sc_plan* pl, int which) {
   const int cus = device_cus(), form = which || pl->kept == pl->geo.m ? 1 : 0;
   const sc_plan::Pick& other = pl->pick[which];
   const double mb = (double)pl->geo.y_elems * 2e-6;
-  const double other_us = form ? -0.75 + 1.017 * other.us + 0.515 * mb + (other.splits > 1 ? 2.4 : 0.0)
-                               : -0.38 + 0.99 * other.us + 0.372 * mb + (other.splits > 1 ? 2.85 : 0.0);
-  sc_plan::Window best = {0, 0, plain_band};
-  // (one chunk: nothing hides its slab; 10 x 64 -> 224 @16 6.35 / 6.6 in tiles that contract every row and mask at the store)
-  double best_us = other.us == 0.0 ? 0.0 : (chunks == 1 ? 0.97 : 1.0) * other_us;
+  // The other launch by the model's price of it, y and a split walk's round trip: of the buffer-load kernel, of the direct-to-LDS one
+  // and of the one through registers, whose K tiles cost more than the model has them (direct-to-LDS, 5 x 104 -> 96 @30: 7.9, takes 11).
+  static const double others[3][2][3] = {{{-0.38, 0.99, 0.372}, {-0.75, 1.017, 0.515}},
+                                         {{-2.99, 1.647, 0.209}, {-2.745, 1.621, 0.180}},
+                                         {{-3.73, 1.91, 0.278}, {-3.74, 1.892, 0.381}}};
+  const int family = !pl->geo.vec_out ? 2 : d.c_in % 64 != 0 ? 1 : 0;
+  const double* o = others[family][form];
+  double other_us = o[0] + o[1] * other.us + o[2] * mb + (other.splits > 1 ? 2.6 : 0.0);
+  if (other.us == 0.0) other_us = 0.0;                            // (a launch that was asked for)
+  if (plain_band && !deep) other_us = 7.4;
+  sc_plan::Window best = {0, 0, plain_band && deep};
+  // (what has to be won: one chunk or less leaves this kernel's set-up uncovered, 10 x 64 -> 224 @16 6.35 / 6.6)
+  double best_us = (d.c_in < 48 ? 0.9 : family ? 0.943 : chunks == 1 ? 0.97 : 1.0) * other_us;
   for (const Shape& sh : shapes) {
     if ((sh.bm == 256 && form == 0) || !fits(sh.bm, sh.bn)) continue;
     const int64_t wgs = ((rows + sh.bm - 1) / sh.bm) * ((d.c_out + sh.bn - 1) / sh.bn);
     const double load = (double)wgs / cus, rounds = (double)((wgs + cus - 1) / cus);
     if (rounds > 1.0 && sh.bm == 64) continue;      // (set-up and sums again each round: 36 x 128 -> 432 @26x24 in three 24.0 / 30.0)
     const double* c = sh.us[form];
-    const double us = c[0] + c[1] * (rounds - 1) + chunks * (c[2] * rounds + c[3] * load) + c[4] * mb;
-    if (us < best_us) { best_us = us; best = {sh.bm, sh.bn, plain_band}; }
+    const int kg = sh.bm == 256 ? 1 : sh.bn == 128 ? 2 : 4, last = (d.c_in - (chunks - 1) * kWinChunk + 15) / 16;      // K groups, K steps of the last chunk
+    const double walk = chunks - 1 + (double)((last + kg - 1) / kg * kg) / 4;
+    const double us = c[0] + c[1] * (rounds - 1) + walk * (c[2] * rounds + c[3] * load) + c[4] * mb;
+    if (plain_band && !deep && rounds > 1.0) continue;
+    if (us < best_us) { best_us = us; best = {sh.bm, sh.bn, plain_band, plain_band && !deep}; }
   }
   return best;
 }
@@ -1419,7 +1435,9 @@ static bool window_is_free(const sc_plan* pl, int which, int64_t rows) {
          pl->stream_k < 2 && pl->masked_store != 2 && pl->slab == 0 && pl->row_panel != 2 && !pl->slab_auto[which].bm;
 }
 // does a run of a dense input take the window kernel?
-static bool use_window(const sc_plan* pl, int which, int64_t rows) { return pl->window[which].bm > 0 && window_is_free(pl, which, rows); }
+static bool use_window(const sc_plan* pl, int which, int64_t rows, bool plain = true) {
+  return pl->window[which].bm > 0 && (plain || !pl->window[which].plain_only) && window_is_free(pl, which, rows);
+}
 // is the band kernel that applies left out for it, or for a tile?
 static bool bands_give_way(const sc_plan* pl, int which, int64_t rows) {
   return pl->window[which].before_bands && window_is_free(pl, which, rows);
@@ -1755,7 +1773,7 @@ static sc_status launch_conv(const sc_plan* pl, bool dense, const void* x, const
     SC_HIP(pl->band_table->fn[shape][b.ni_idx][mi_idx](q, b.lds, stream));
     return SC_OK;
   }
-  if (!x_compact && !slab.bm && use_window(pl, which, rows)) {
+  if (!x_compact && !slab.bm && use_window(pl, which, rows, !residual && !y_compact)) {
     const sc_plan::Window win = pl->window[which];
     ConvParams p;
     std::memset(&p, 0, sizeof(p));
@@ -1781,7 +1799,8 @@ static sc_status launch_conv(const sc_plan* pl, bool dense, const void* x, const
     p.m_tiles = (int32_t)((rows + win.bm - 1) / win.bm);
     p.n_tiles = (d.c_out + win.bn - 1) / win.bn;
     p.x_bytes = (uint32_t)(g.x_elems * eb);
-    p.w_bytes = (uint32_t)((uint64_t)((d.c_out + 31) / 32) * 32 * g.k * eb);
+    p.w_bytes = (uint32_t)((uint64_t)((d.c_out + 31) / 32) * 32 * 9 * ((d.c_in + kWinChunk - 1) / kWinChunk) * kWinChunk * eb);
+    p.vec_out = g.vec_out ? 1 : 2;
     p.slab_bytes = window_slab_bytes(pl, which, win.bm);
     p.slab_hp = d.h + 2 * d.pad_h;
     p.slab_wp = d.w + 2 * d.pad_w;
@@ -2026,7 +2045,7 @@ static sc_status pack_filters(const sc_conv_desc& d, const Geometry& g, unsigned
     const int blocks32 = (d.c_out + 31) / 32;
     SC_HIP(repack_filters(dt, w_dev, ws + g.off_wp, parts ? ws + g.off_stage_w : g.window ? ws + g.off_window_w : nullptr, d.c_out, d.c_in,
                           d.kh * d.kw, g.k_stride, tables ? g.cout_pad : blocks32 * 32, tables && parts ? g.stage_blocks : blocks32,
-                          parts ? g.stage_k_tiles : d.c_in / kWinChunk, rotated, stream));
+                          parts ? g.stage_k_tiles : (d.c_in + kWinChunk - 1) / kWinChunk, rotated, stream));
   } else {
     int64_t total = (int64_t)g.cout_pad * g.k_stride;
     int grid = (int)((total + 255) / 256);
@@ -2694,7 +2713,7 @@ sc_status sparse_conv_plan_tiles(const sc_plan* plan, int32_t which, int32_t* ti
 static const char* tiled_kernel_name(const sc_plan* plan, int32_t which, LaunchForm form) {
   const Geometry& g = plan->geo;
   if (use_stage(plan, which, form)) return "tile_staged";
-  if (use_window(plan, which, which ? g.m : plan->kept)) return "tile_lds_direct";
+  if (use_window(plan, which, which ? g.m : plan->kept, form == kPlainRun)) return "tile_lds_direct";
   const TilePick tp = pick_tile(plan, which, which ? g.m : plan->kept);
   if (tp.masked) return "tile_masked_store";
   if (tp.splits > 1) return "tile_split_k";

@@ -1,4 +1,4 @@
-"""Window kernel (3x3 layers at stride 1 with whole chunks of 64 channels: every input pixel of a tile once in LDS, filters straight
+"""Window kernel (3x3 layers at stride 1 whose channels are whole 16-byte groups: every input pixel of a tile once in LDS, filters straight
 into registers) against the oracle, through the C ABI."""
 import dataclasses
 
@@ -24,6 +24,9 @@ SHAPES = {
     "no_padding": dict(n=2, cin=128, h=12, w=10, cout=320, p=0),
     "padding_2": dict(n=1, cin=192, h=8, w=30, cout=16, p=2, sp=0.0),              # output larger than the input, every row kept
     "one_row_kept": dict(n=1, cin=64, h=6, w=6, cout=32, sp=0.97),
+    "last_chunk_of_8": dict(n=2, cin=72, h=9, w=11, cout=24),                       # half a K step behind the first chunk; half a block
+    "last_chunk_of_40": dict(n=3, cin=104, h=10, w=7, cout=104, sp=0.3),
+    "under_a_chunk": dict(n=2, cin=24, h=11, w=12, cout=152, sp=0.2),
     "wide_map": dict(n=1, cin=64, h=4, w=120, cout=64, sp=0.7),                    # a tap row is most of the slab
 }
 
@@ -56,16 +59,17 @@ def test_window_kernel_matches_the_oracle(shape, tile, dtype, monkeypatch):
         assert B.sparse_conv_plan_kernel(layer.plan, 0) == "tile_lds_direct" and B.sparse_conv_plan_tiles(layer.plan, 0)[:2] == tile
 
 
+@pytest.mark.parametrize("cin,cout", [(128, 96), (88, 56)])
 @pytest.mark.parametrize("tile", TILES)
-def test_window_kernel_other_operands(tile, monkeypatch):
+def test_window_kernel_other_operands(tile, cin, cout, monkeypatch):
     """Rows left alone, compact rows, shortcut sums, a shared mask; masks with long runs of dropped rows; new masks."""
     monkeypatch.setenv("SPARSE_CONV_WINDOW_TILE", "%dx%d" % tile)
-    spec = spec_of(3, 128, 10, 9, 96, sp=0.4)
+    spec = spec_of(3, cin, 10, 9, cout, sp=0.4)
     check_layer(W.make_conv_inputs(spec, 3100), out_mode=B.SC_OUT_SCATTER_ONLY)
     check_layer(W.make_conv_inputs(spec.with_(mask_mode="spatial"), 3101))
     check_compact_output(spec, 3102)
     for sp in (0.4, 0.0, 0.9):                       # (at 0.9 most dropped rows lie behind the listed ones)
-        check_residual(spec.with_(sparsity=sp, relu=False), 3103, True, want_kernel=("tile_lds_direct", "tile_masked_store", "tile_split_k"))
+        check_residual(spec.with_(sparsity=sp, relu=False), 3103, True, want_kernel=("tile_lds_direct", "tile_masked_store", "tile_split_k", "tile_registers"))
     ci = W.make_conv_inputs(spec.with_(sparsity=0.5), 3104)
     half = np.zeros_like(ci.mask)
     half[::2] = 1                                    # every other pixel: all rows of a set of lanes in half of the bank groups
@@ -98,7 +102,7 @@ def test_values_outside_a_window_do_not_enter(monkeypatch):
 
 def test_refreshed_filters_reach_the_window_kernel(monkeypatch):
     monkeypatch.setenv("SPARSE_CONV_WINDOW_TILE", "64x128")
-    spec = spec_of(2, 128, 9, 8, 72 + 8, sp=0.3)
+    spec = spec_of(2, 136, 9, 8, 72, sp=0.3)
     one, two = W.make_conv_inputs(spec, 3300), W.make_conv_inputs(spec, 3301)
     layer = R.ConvLayer(spec, one.w, one.bias, one.mask)
     fresh = R.ConvLayer(spec, two.w, one.bias, one.mask)
