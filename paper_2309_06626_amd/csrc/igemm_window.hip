@@ -3,19 +3,19 @@
 
 namespace sc {
 
-template <int DT>
+template <int DT, int KS>
 static LaunchFn pick(int bm, int bn) {
-  if (bm == 256 && bn == 128) return igemm_window_launch<DT, 256, 128>;
-  if (bm == 128 && bn == 128) return igemm_window_launch<DT, 128, 128>;
-  if (bm == 128 && bn == 64) return igemm_window_launch<DT, 128, 64>;
-  if (bm == 64 && bn == 128) return igemm_window_launch<DT, 64, 128>;
-  if (bm == 64 && bn == 64) return igemm_window_launch<DT, 64, 64>;
+  if (bm == 256 && bn == 128) return igemm_window_launch<DT, 256, 128, KS>;
+  if (bm == 128 && bn == 128) return igemm_window_launch<DT, 128, 128, KS>;
+  if (bm == 128 && bn == 64) return igemm_window_launch<DT, 128, 64, KS>;
+  if (bm == 64 && bn == 128) return igemm_window_launch<DT, 64, 128, KS>;
+  if (bm == 64 && bn == 64) return igemm_window_launch<DT, 64, 64, KS>;
   return nullptr;
 }
 
-LaunchFn window_kernel(int dtype, int bm, int bn) {
-  if (dtype == kBF16) return pick<kBF16>(bm, bn);
-  if (dtype == kF16) return pick<kF16>(bm, bn);
+LaunchFn window_kernel(int dtype, int ks, int bm, int bn) {
+  if (dtype == kBF16) return ks == 3 ? pick<kBF16, 3>(bm, bn) : ks == 5 ? pick<kBF16, 5>(bm, bn) : nullptr;
+  if (dtype == kF16) return ks == 3 ? pick<kF16, 3>(bm, bn) : ks == 5 ? pick<kF16, 5>(bm, bn) : nullptr;
   return nullptr;
 }
 

@@ -1,4 +1,4 @@
-// Tiled masked-convolution kernel for 3 x 3 windows at stride 1 (16-bit NHWC, Cin and Cout multiples of 8): every input pixel of a tile
+// Tiled masked-convolution kernel for 3 x 3 and 5 x 5 windows at stride 1 (16-bit NHWC, Cin and Cout multiples of 8): every input pixel of a tile
 // passes into LDS once, the filters go straight into registers.
 //
 // What bounds the tiled kernels whose K tiles pass a ring in LDS (igemm_buf_kernel), taken apart by leaving one thing out at a time
@@ -7,7 +7,7 @@
 // K tile.  Here a K tile costs 22 KB of transfers instead of 32 (a pixel's nine uses share one), half of the LDS writes, and no barrier:
 //   * the slab: for a chunk of 64 channels, the run of virtual zero-padded pixels under the windows of the tile's rows, so that a tap is
 //     one displacement for all of them; the next chunk's slab lands while this one is contracted, and wavefronts meet once a chunk;
-//   * filters, packed in fragment order (stage repack_kernel), nine fragments a wavefront on their way at any time;
+//   * filters, packed in fragment order (repack_kernel), nine fragments a wavefront (five of 25) on their way at any time;
 //   * wavefronts stand side by side over the channels, so that no two load the same filters, and share K where that leaves some over:
 //     a K group takes every KG-th step of 16 channels, and the groups' sums are added through LDS in order at the end.
 // A pixel takes nine 16-byte groups in LDS, of which eight hold channels: reads of sixteen pixels side by side touch every bank once,
@@ -31,7 +31,6 @@ namespace sc {
 constexpr int kWinChunk = 64;                            // channels of a slab
 constexpr int kWinPitch = 2 * kWinChunk + 16;            // bytes of a pixel in LDS: nine 16-byte groups, the last one unused
 constexpr int kWinGroups = kWinPitch / 16;
-constexpr int kWinTaps = 9;
 constexpr int kWinMostPixels = 512;                      // of a slab (a thread decodes each)
 constexpr int kWinRounds = (kWinMostPixels * kWinPitch + 8191) / 8192;      // transfers of the whole workgroup for a slab at most
 
@@ -51,12 +50,14 @@ template <int BM, int BN> size_t win_lds_bytes(int slab_bytes, int chunks) {
   return (slabs > D::sums_bytes() ? slabs : D::sums_bytes()) + D::tail_bytes();
 }
 
-template <int DT, int BM, int BN>
+template <int DT, int BM, int BN, int KS>      // KS x KS windows
 __global__ __launch_bounds__(512) void igemm_window_kernel(const ConvParams p) {
   using E = Elem<DT>;
   using T = typename E::T;
   using D = WinDims<BM, BN>;
   constexpr int EB = sizeof(T), MI = D::MI, KG = D::KG;
+  constexpr int TAPS = KS * KS, AHEAD = KS == 3 ? 9 : 5;      // filter fragments a wavefront has on their way: a whole part of a pass
+  static_assert(TAPS % AHEAD == 0, "whole turns");
   constexpr int CPR = BN * EB / 16, RPI = 512 / CPR;      // 16-byte groups of a row slice, dense rows a pass of the zero fill covers
   constexpr int NZ = WinDims<BM, BN>::ZERO_ROWS / RPI;    // passes that go out before the K loop
   static_assert(EB == 2 && D::WAVES_M * D::WAVES_N * KG == 8, "16-bit operands, eight wavefronts");
@@ -109,19 +110,19 @@ __global__ __launch_bounds__(512) void igemm_window_kernel(const ConvParams p) {
   typedef __attribute__((address_space(3))) void lds_void;
 
   // Filters, packed in the order in which the matrix unit takes them: [32 channels][chunk][K step][tap][lane] of 16 bytes.  A
-  // wavefront of K group kg takes K steps kg, kg + KG, ... of a chunk; nine fragments -- a pass -- are on their way at any time.
+  // wavefront of K group kg takes K steps kg, kg + KG, ... of a chunk, one pass over the taps each; AHEAD fragments are on their way at any time.
   const int n_pass = chunks * D::PASSES;
   const int nb = min((n0 + wn0) >> 5, (p.c_out - 1) >> 5);
   const uint32_t w_lane = (uint32_t)(lane * 16);
   auto pass_at = [&](int pass) {
     const int q = min(pass, n_pass - 1);
-    return ((nb * chunks + q / D::PASSES) * 4 + kg + KG * (q % D::PASSES)) * (kWinTaps * 1024);
+    return ((nb * chunks + q / D::PASSES) * 4 + kg + KG * (q % D::PASSES)) * (TAPS * 1024);
   };
-  v4i bf[kWinTaps];
+  v4i bf[AHEAD];
   {
     const int at = pass_at(0);
 #pragma unroll
-    for (int tap = 0; tap < kWinTaps; ++tap) bf[tap] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rw, w_lane, at + tap * 1024, 0));
+    for (int tap = 0; tap < AHEAD; ++tap) bf[tap] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rw, w_lane, at + tap * 1024, 0));
   }
 
   const int zc = t % CPR, zr = t / CPR;
@@ -135,7 +136,7 @@ __global__ __launch_bounds__(512) void igemm_window_kernel(const ConvParams p) {
     return (n * hp + oy) * wp + rem - oy * p.wo;
   };
   const int v_lo = corner(r_first);
-  const int slab_px = min(corner(r_last) + 2 * wp + 3 - v_lo, kWinMostPixels);
+  const int slab_px = min(corner(r_last) + (KS - 1) * wp + KS - v_lo, kWinMostPixels);
   const int rounds = min((slab_px * kWinPitch + 8191) >> 13, p.slab_bytes >> 13);
   {
     const int v = v_lo + t;
@@ -245,35 +246,36 @@ __global__ __launch_bounds__(512) void igemm_window_kernel(const ConvParams p) {
 #pragma unroll 1
     for (int q = 0; q < D::PASSES; ++q, ++pass) {
       if (chunk + 1 == chunks && (kg + KG * q) * 16 >= last_ci) break;      // (no channels left in the last chunk)
-      const int next_at = pass_at(pass + 1);
+      const int this_at = pass_at(pass), next_at = pass_at(pass + 1);
       const unsigned from = slab_at + (unsigned)(q * KG * 32);
       v4i xa[3][MI];
       auto read = [&](int tap, int mi) {
-        xa[tap % 3][mi] = lds_read16_at<0>(a_base[mi] + from + (unsigned)((tap / 3) * tap_row + (tap % 3) * kWinPitch));
+        xa[tap % 3][mi] = lds_read16_at<0>(a_base[mi] + from + (unsigned)((tap / KS) * tap_row + (tap % KS) * kWinPitch));
       };
 #pragma unroll
       for (int tap = 0; tap < 2; ++tap)
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi) read(tap, mi);
 #pragma unroll
-      for (int tap = 0; tap < kWinTaps; ++tap) {      // a fragment of the tap two ahead is asked for behind every product
-        if (tap + 1 < kWinTaps) wait_frags<MI>(xa[tap % 3]);
+      for (int tap = 0; tap < TAPS; ++tap) {      // a fragment of the tap two ahead is asked for behind every product
+        if (tap + 1 < TAPS) wait_frags<MI>(xa[tap % 3]);
         else wait_frags<0>(xa[tap % 3]);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi) {
-          E::mma(acc[mi], bf[tap], xa[tap % 3][mi]);
+          E::mma(acc[mi], bf[tap % AHEAD], xa[tap % 3][mi]);
           __builtin_amdgcn_sched_barrier(0);
-          if (tap + 2 < kWinTaps) read(tap + 2, mi);
+          if (tap + 2 < TAPS) read(tap + 2, mi);
           __builtin_amdgcn_sched_barrier(0);
         }
-        bf[tap] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rw, w_lane, next_at + tap * 1024, 0));
+        const int next = tap + AHEAD < TAPS ? this_at + (tap + AHEAD) * 1024 : next_at + (tap + AHEAD - TAPS) * 1024;
+        bf[tap % AHEAD] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rw, w_lane, next, 0));
       }
     }
     if (chunk + 1 < chunks) {
-      // the next slab has landed when at most the filters asked for since are on their way, nine at least
+      // the next slab has landed when at most the filters asked for since are on their way, a pass at least
       __builtin_amdgcn_sched_barrier(0);
-      wait_vmcnt<kWinTaps>();
+      wait_vmcnt<AHEAD>();
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
       __builtin_amdgcn_sched_barrier(0);
@@ -370,10 +372,12 @@ __global__ __launch_bounds__(512) void igemm_window_kernel(const ConvParams p) {
   }
 }
 
-template <int DT, int BM, int BN>
+template <int DT, int BM, int BN, int KS>
 hipError_t igemm_window_launch(const ConvParams& p, hipStream_t stream) {
-  const size_t lds = win_lds_bytes<BM, BN>(p.slab_bytes, (p.c_in + kWinChunk - 1) / kWinChunk);
-  auto kern = igemm_window_kernel<DT, BM, BN>;
+  // (p.splits: at most one workgroup a compute unit, so that none waits beside an idle one: 64 x 512 -> 512 @7 15.0 / 13.9)
+  size_t lds = win_lds_bytes<BM, BN>(p.slab_bytes, (p.c_in + kWinChunk - 1) / kWinChunk);
+  if (p.splits == 1 && lds < 81 * 1024) lds = 81 * 1024;
+  auto kern = igemm_window_kernel<DT, BM, BN, KS>;
   static std::atomic<bool> attr_set{false};
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
@@ -385,8 +389,8 @@ hipError_t igemm_window_launch(const ConvParams& p, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// the window kernel of tile bm x bn for a 16-bit dtype, or null; LDS it needs
-LaunchFn window_kernel(int dtype, int bm, int bn);
+// the window kernel of tile bm x bn for a 16-bit dtype and ks x ks windows, or null; LDS it needs
+LaunchFn window_kernel(int dtype, int ks, int bm, int bn);
 size_t window_lds_bytes(int bm, int bn, int slab_bytes, int chunks);
 
 }  // namespace sc

@@ -99,34 +99,30 @@ __global__ __launch_bounds__(256) void mask_scatter_kernel(const uint8_t* __rest
   if (seg == nseg - 1 && lane == 0) {
     kept_out[0] = base;
     kept_out[1] = 0;      // the per-band maximum, raised by band_rows_kernel
-    kept_out[2] = 0;      // the widest slab of a 128-row / 256-row tile, raised by slab_span_kernel
-    kept_out[3] = 0;
+    kept_out[2] = 0;      // the widest slab of a 64-row / 128-row / 256-row tile, raised by slab_span_kernel
+    kept_out[3] = kept_out[4] = 0;
   }
 }
 
-// Slab kernel (igemm_slab_kernel.hpp): virtual rows between the window corner of the first and of the last kept row of
-// every tile of 128 and of 256 kept rows, plus the window height; the maximum over the tiles sizes the LDS slab.  per_wg:
-// each workgroup leaves its own two maxima (one workgroup covers the tiles of 32 768 rows), else all raise the same two.
+// Slab and window kernels: virtual rows between the window corner of the first and of the last kept row of every tile of 64, 128 and
+// 256 kept rows, plus the window height; the maximum over the tiles sizes the LDS slab.
 __global__ __launch_bounds__(256) void slab_span_kernel(const int32_t* __restrict__ row_idx, const int32_t* __restrict__ kept_dev,
-                                                        int ho_wo, int wo, int hp, int kh, int32_t* __restrict__ span_out, int per_wg) {
-  __shared__ int s_span[2];
-  if (threadIdx.x < 2) s_span[threadIdx.x] = 0;
+                                                        int ho_wo, int wo, int hp, int kh, int32_t* __restrict__ span_out) {
+  __shared__ int s_span[3];
+  if (threadIdx.x < 3) s_span[threadIdx.x] = 0;
   __syncthreads();
   const int kept = kept_dev[0];
   const int tile = blockIdx.x * 256 + threadIdx.x;
   auto vrow = [&](int r) { return (r / ho_wo) * hp + (r % ho_wo) / wo; };
-  for (int b = 0; b < 2; ++b) {
-    const int bm = 128 << b;
+  for (int b = 0; b < 3; ++b) {
+    const int bm = 64 << b;
     const int64_t m0 = (int64_t)tile * bm;
     if (m0 >= kept) continue;
     const int last = (int)min((int64_t)kept, m0 + bm) - 1;
     atomicMax(&s_span[b], vrow(row_idx[last]) + kh - vrow(row_idx[m0]));
   }
   __syncthreads();
-  if (threadIdx.x < 2) {
-    if (per_wg) span_out[blockIdx.x * 2 + threadIdx.x] = s_span[threadIdx.x];
-    else atomicMax(span_out + threadIdx.x, s_span[threadIdx.x]);
-  }
+  if (threadIdx.x < 3) atomicMax(span_out + threadIdx.x, s_span[threadIdx.x]);
 }
 
 // The inverse map for a compact tensor: rank[r] = position of row r among the kept rows, -1 for a dropped
@@ -296,9 +292,12 @@ struct TableParams {
 };
 
 __global__ __launch_bounds__(kTableThreads) void row_tables_kernel(const TableParams p) {
-  __shared__ unsigned long long s_bits[kTableRows / 64];    // which rows of the segment are kept
-  __shared__ int s_before[kTableRows / 64];                 // kept rows of the segment in front of each word
-  __shared__ int s_wave[4], s_red[3];
+  constexpr int WORDS = kTableRows / 64;
+  __shared__ unsigned long long s_bits[2 * WORDS];          // which rows of the segment, and (for spans) of the one behind it, are kept
+  __shared__ int s_before[2 * WORDS];                       // kept rows in front of each word, counted from the segment's first
+  __shared__ int s_wave[4], s_next[4], s_red[3], s_span[3];
+  constexpr int TILES = 2 * kTableRows / 64 + 2;
+  __shared__ int s_tile[2][TILES];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int r0 = blockIdx.x * kTableRows;
   const int ho_wo = p.ho * p.wo;
@@ -311,6 +310,14 @@ __global__ __launch_bounds__(kTableThreads) void row_tables_kernel(const TablePa
     const int q = p.period ? r - fast_div(r, p.howo_mul, p.howo_shift) * p.period : r;
     v[it] = r < p.m ? p.mask[q] : (uint8_t)0;
     if (r < p.mask_len) p.copy[r] = v[it];
+  }
+  unsigned char next[4] = {0, 0, 0, 0};
+  if (p.slab_hp) {
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+      const int r = r0 + kTableRows + wave * 256 + it * 64 + lane;
+      if (r < p.m) next[it] = p.mask[p.period ? r - fast_div(r, p.howo_mul, p.howo_shift) * p.period : r];
+    }
   }
   auto band_at = [&](int r, int* band, int* first, int* end) {      // rows [first, end) of the band that row r lies in
     const int img = fast_div(r, p.howo_mul, p.howo_shift), pix = r - img * ho_wo;
@@ -354,7 +361,8 @@ __global__ __launch_bounds__(kTableThreads) void row_tables_kernel(const TablePa
     const int img = fast_div(r, p.howo_mul, p.howo_shift), rem = r - img * p.period;
     return (img ? img * kept_in(0, p.period) : 0) + kept_in(0, rem);
   };
-  if (t < 3) s_red[t] = 0;
+  if (t < 3) s_red[t] = s_span[t] = 0;
+  if (t < 2 * TILES) s_tile[t / TILES][t % TILES] = -1;
   __syncthreads();
   if (r0 > 0) {
     const int to_start = wave_sum(kept_before(start)), to_r0 = wave_sum(start == r0 ? 0 : kept_before(r0));
@@ -371,6 +379,16 @@ __global__ __launch_bounds__(kTableThreads) void row_tables_kernel(const TablePa
     own += __popcll(bits);
   }
   if (lane == 0) s_wave[wave] = own;
+  if (p.slab_hp) {
+    int behind = 0;
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+      const unsigned long long bits = __ballot(next[it] != 0);
+      if (lane == 0) { s_bits[WORDS + wave * 4 + it] = bits; s_before[WORDS + wave * 4 + it] = behind; }
+      behind += __popcll(bits);
+    }
+    if (lane == 0) s_next[wave] = behind;
+  }
   __syncthreads();
   int before_wave = 0, total = 0;
   for (int w = 0; w < 4; ++w) {
@@ -378,6 +396,11 @@ __global__ __launch_bounds__(kTableThreads) void row_tables_kernel(const TablePa
     total += s_wave[w];
   }
   if (lane < 4) s_before[wave * 4 + lane] += before_wave;
+  if (p.slab_hp && lane < 4) {
+    int more = total;
+    for (int w = 0; w < wave; ++w) more += s_next[w];
+    s_before[WORDS + wave * 4 + lane] += more;
+  }
   const int start_rank = s_red[0], base = s_red[1];
   __syncthreads();
   auto rank_at = [&](int r) {                  // kept rows in front of row r, a row of the segment or `start`
@@ -385,6 +408,24 @@ __global__ __launch_bounds__(kTableThreads) void row_tables_kernel(const TablePa
     const int q = r - r0;
     return base + s_before[q >> 6] + (int)__popcll(s_bits[q >> 6] & ((1ull << (q & 63)) - 1ull));
   };
+  // For spans: the virtual rows of the first and the last row of every 64 kept ones that lie in this segment or the next.
+  const int in_sight = p.slab_hp ? s_before[2 * WORDS - 1] + (int)__popcll(s_bits[2 * WORDS - 1]) : 0;
+  const bool all_seen = r0 + 2 * kTableRows >= p.m;
+  auto mark = [&](int r, int rank) {
+    const bool first = (rank & 63) == 0, last = (rank & 63) == 63 || (all_seen && rank == base + in_sight - 1);
+    if (!first && !last) return;
+    const int img = fast_div(r, p.howo_mul, p.howo_shift);
+    const int vrow = img * p.slab_hp + fast_div(r - img * ho_wo, p.wo_mul, p.wo_shift);
+    if (first) s_tile[0][(rank >> 6) - (base >> 6)] = vrow;
+    if (last) s_tile[1][(rank >> 6) - (base >> 6)] = vrow;
+  };
+  if (p.slab_hp) {
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+      const int w = WORDS + wave * 4 + it;
+      if (next[it] != 0) mark(r0 + w * 64 + lane, base + s_before[w] + (int)__popcll(s_bits[w] & ((1ull << lane) - 1ull)));
+    }
+  }
   int fullest = 0;
 #pragma unroll
   for (int it = 0; it < 4; ++it) {
@@ -393,6 +434,7 @@ __global__ __launch_bounds__(kTableThreads) void row_tables_kernel(const TablePa
     const bool keep = v[it] != 0;
     const int rank = rank_at(r);
     if (keep) p.row_idx[rank] = r;
+    if (p.slab_hp && keep) mark(r, rank);
     if (p.n_bands) {
       int band, first, end;
       band_at(r, &band, &first, &end);
@@ -407,32 +449,30 @@ __global__ __launch_bounds__(kTableThreads) void row_tables_kernel(const TablePa
   if (lane == 0) atomicMax(&s_red[2], fullest);
   const bool last = blockIdx.x == gridDim.x - 1;
   const int kept = base + total;
-  __syncthreads();                             // (also: this workgroup's row list is in memory for its own readers)
-  int span[2] = {0, 0};
-  if (p.slab_hp && gridDim.x == 1) {
-    auto vrow = [&](int r) {
-      const int img = fast_div(r, p.howo_mul, p.howo_shift);
-      return img * p.slab_hp + fast_div(r - img * ho_wo, p.wo_mul, p.wo_shift);
-    };
-    for (int b = 0; b < 2; ++b)
-      for (int m0 = t * (128 << b); m0 < kept; m0 += kTableThreads * (128 << b))
-        span[b] = max(span[b], vrow(p.row_idx[min(kept, m0 + (128 << b)) - 1]) + p.slab_kh - vrow(p.row_idx[m0]));
-    if (t < 2) s_wave[t] = 0;
+  __syncthreads();
+  if (p.slab_hp) {
+    // The tiles of 64, 128 and 256 rows whose first row lies in this segment.  One whose last row is out of sight is more than a
+    // segment of rows long: too wide for any slab.
+    const int tile = (base >> 6) + t, n_last = (base + in_sight - 1) >> 6;
+    if (t < TILES && tile * 64 >= base && tile * 64 < kept) {
+      for (int b = 0; b < 3 && (tile & ((1 << b) - 1)) == 0; ++b) {
+        int end = t + (1 << b) - 1;
+        if (all_seen) end = min(end, n_last - (base >> 6));
+        const int v1 = end < TILES ? s_tile[1][end] : -1;
+        atomicMax(&s_span[b], v1 < 0 ? 0xffff : min(v1 + p.slab_kh - s_tile[0][t], 0xffff));
+      }
+    }
     __syncthreads();
-    for (int b = 0; b < 2; ++b) atomicMax(&s_wave[b], span[b]);
-    __syncthreads();
-    span[0] = s_wave[0];
-    span[1] = s_wave[1];
   }
   if (t == 0) {
     int32_t* out = p.result + blockIdx.x * 4;
     out[0] = total;
     out[1] = s_red[2];
-    out[2] = span[0];
-    out[3] = span[1];
+    out[2] = s_span[0];                        // (tiles of 64 rows)
+    out[3] = s_span[1] | s_span[2] << 16;      // (of 128 and 256)
     if (last) {
       p.kept_out[0] = kept;
-      p.kept_out[1] = p.kept_out[2] = p.kept_out[3] = 0;
+      p.kept_out[1] = p.kept_out[2] = p.kept_out[3] = p.kept_out[4] = 0;
       if (p.n_bands) p.band_i0[p.n_bands] = kept;
     }
   }
@@ -442,8 +482,7 @@ __global__ __launch_bounds__(kTableThreads) void row_tables_kernel(const TablePa
 // (in a way that a capture in another thread is not disturbed by) and held until the process ends.  A call holds a slot from its
 // launch to its synchronisation; one that finds none free (or no such memory), or whose stream is being captured, copies from
 // the device instead.  SPARSE_CONV_HOST_SLOTS=0: always (tests).
-constexpr int kTableSpanWgs = kTableMostRows / (128 * 256);
-constexpr int kHostSlots = 32, kHostSlotWords = kTableMostWgs * 4 + kTableSpanWgs * 2;
+constexpr int kHostSlots = 32, kHostSlotWords = kTableMostWgs * 4;
 struct HostSlots {
   std::mutex lock;
   int32_t* base = nullptr;
@@ -764,9 +803,9 @@ static sc_status check_desc(const sc_conv_desc* d, Geometry* g) {
     g->off_stage_w = off;   off = align_up(off + (size_t)g->stage_blocks * g->stage_k_tiles * block_bytes, 256);
     g->off_stage_tab = off; off = align_up(off + (size_t)g->stage_k_tiles * tile * sizeof(KEntry), 256);
   }
-  // Window kernel: 3 x 3 at stride 1, whole 16-byte groups, tensors and virtual pixels in 31 bits.  Its packed filters hold whole chunks.
-  const int64_t window_k = (int64_t)9 * ((d->c_in + kWinChunk - 1) / kWinChunk) * kWinChunk;
-  g->window = g->vec_gather && (g->vec_out || g->vec_out8) && d->dtype != SC_F32 && d->kh == 3 && d->kw == 3 && d->stride_h == 1 && d->stride_w == 1 &&
+  // Window kernel: 3 x 3 or 5 x 5 at stride 1, whole 16-byte groups, tensors and virtual pixels in 31 bits.  Its packed filters hold whole chunks.
+  const int64_t window_k = (int64_t)d->kh * d->kw * ((d->c_in + kWinChunk - 1) / kWinChunk) * kWinChunk;
+  g->window = g->vec_gather && (g->vec_out || g->vec_out8) && d->dtype != SC_F32 && (d->kh == 3 || d->kh == 5) && d->kw == d->kh && d->stride_h == 1 && d->stride_w == 1 &&
               d->dil_h == 1 && d->dil_w == 1 && !depthwise && g->x_elems * eb < lim &&
               (int64_t)d->n * (d->h + 2 * (int64_t)d->pad_h) * (d->w + 2 * (int64_t)d->pad_w) < lim &&
               (int64_t)((d->c_out + 31) / 32) * 32 * window_k * eb < lim && (int64_t)g->cout_pad * g->k_stride < lim;
@@ -1100,7 +1139,7 @@ struct sc_plan {
   struct Window { int bm, bn; bool before_bands, plain_only = false; };
   Window window[2];                // tile of the window kernel for the sparse / dense run (bm == 0: another kernel), whether a band kernel gives way,
                                    // and whether only plain runs take it (the others never went to that band kernel)
-  int slab_span[2][2];             // [sparse, dense run][128-row, 256-row tiles]: virtual rows of the widest tile's slab
+  int slab_span[2][3];             // [sparse, dense run][64-row, 128-row, 256-row tiles]: virtual rows of the widest tile's slab
   Slab slab_auto[2];               // what an automatic launch of the sparse / dense run takes (bm == 0: another kernel)
 };
 constexpr int kForceBand = -2;
@@ -1308,6 +1347,7 @@ static int stream_k_workgroups(const sc_plan* pl, const KernelEntry& ke, int64_t
 
 // ---- slab form of the tiled kernel --------------------------------------------------------------------
 // 3x3 windows, stride 1, no dilation, 16-bit NHWC, input channels in chunks of 32, tensors below 2 GiB.
+static int span_of(int bm) { return bm == 256 ? 2 : bm == 128 ? 1 : 0; }      // index of a tile's span
 static bool slab_geometry_ok(const sc_conv_desc& d, const Geometry& g) {
   if (g.depthwise || g.rowseg || d.dtype == SC_F32 || d.layout != SC_NHWC || !g.vec_out) return false;
   if (d.kh != 3 || d.kw != 3 || d.stride_h != 1 || d.stride_w != 1 || d.dil_h != 1 || d.dil_w != 1) return false;
@@ -1349,7 +1389,7 @@ static sc_plan::Slab slab_pick(const sc_plan* pl, int which, int64_t rows) {
   }
   for (int bm = 256; bm >= 128; bm >>= 1) {
     if (pl->slab >= 128 && pl->slab != bm) continue;
-    if (slab_buffer_bytes(pl->desc, bm, pl->slab_span[which][bm == 256])) return {bm, slab_splits(pl, bm, rows)};
+    if (slab_buffer_bytes(pl->desc, bm, pl->slab_span[which][span_of(bm)])) return {bm, slab_splits(pl, bm, rows)};
   }
   return none;
 }
@@ -1357,8 +1397,8 @@ static sc_plan::Slab slab_pick(const sc_plan* pl, int which, int64_t rows) {
 // bytes of one of its slabs for tiles of bm rows (0: they do not fit)
 static int window_slab_bytes(const sc_plan* pl, int which, int bm) {
   const sc_conv_desc& d = pl->desc;
-  int span = pl->slab_span[which][bm == 256];
-  if (pl->kept == pl->geo.m) span = std::max(span, pl->slab_span[1][bm == 256]);      // (such a run goes over the identity map)
+  int span = pl->slab_span[which][span_of(bm)];
+  if (pl->kept == pl->geo.m) span = std::max(span, pl->slab_span[1][span_of(bm)]);      // (such a run goes over the identity map)
   const int64_t px = (int64_t)span * (d.w + 2 * d.pad_w);
   if (span <= 0 || px > kWinMostPixels) return 0;
   return (int)((px * kWinPitch + 8191) / 8192 * 8192);
@@ -1369,10 +1409,10 @@ static sc_plan::Window window_tile_for(const sc_plan* pl, int which) {
   const sc_plan::Window none = {0, 0, false};
   const sc_conv_desc& d = pl->desc;
   const int64_t rows = which ? pl->geo.m : pl->kept;
-  if (!pl->geo.window || rows == 0 || !window_kernel(kBF16, 64, 64)) return none;
+  if (!pl->geo.window || rows == 0 || !window_kernel(kBF16, d.kh, 64, 64)) return none;
   const int chunks = (d.c_in + kWinChunk - 1) / kWinChunk;
   auto fits = [&](int bm, int bn) {
-    const int sb = window_kernel(kBF16, bm, bn) ? window_slab_bytes(pl, which, bm) : 0;
+    const int sb = window_kernel(kBF16, d.kh, bm, bn) ? window_slab_bytes(pl, which, bm) : 0;
     return sb > 0 && window_lds_bytes(bm, bn, sb, chunks) <= kLdsLimit;
   };
   int fbm = 0, fbn = 0;
@@ -1422,7 +1462,7 @@ static sc_plan::Window window_tile_for(const sc_plan* pl, int which) {
     if (rounds > 1.0 && sh.bm == 64) continue;      // (set-up and sums again each round: 36 x 128 -> 432 @26x24 in three 24.0 / 30.0)
     const double* c = sh.us[form];
     const int kg = sh.bm == 256 ? 1 : sh.bn == 128 ? 2 : 4, last = (d.c_in - (chunks - 1) * kWinChunk + 15) / 16;      // K groups, K steps of the last chunk
-    const double walk = chunks - 1 + (double)((last + kg - 1) / kg * kg) / 4;
+    const double walk = (chunks - 1 + (double)((last + kg - 1) / kg * kg) / 4) * (d.kh * d.kw / 9.0);      // (in chunks of a 3 x 3 window)
     const double us = c[0] + c[1] * (rounds - 1) + walk * (c[2] * rounds + c[3] * load) + c[4] * mb;
     if (plain_band && !deep && rounds > 1.0) continue;
     if (us < best_us) { best_us = us; best = {sh.bm, sh.bn, plain_band, plain_band && !deep}; }
@@ -1798,8 +1838,9 @@ static sc_status launch_conv(const sc_plan* pl, bool dense, const void* x, const
     p.residual_relu = residual_relu ? 1 : 0;
     p.m_tiles = (int32_t)((rows + win.bm - 1) / win.bm);
     p.n_tiles = (d.c_out + win.bn - 1) / win.bn;
+    p.splits = p.m_tiles * p.n_tiles <= device_cus() ? 1 : 0;
     p.x_bytes = (uint32_t)(g.x_elems * eb);
-    p.w_bytes = (uint32_t)((uint64_t)((d.c_out + 31) / 32) * 32 * 9 * ((d.c_in + kWinChunk - 1) / kWinChunk) * kWinChunk * eb);
+    p.w_bytes = (uint32_t)((uint64_t)((d.c_out + 31) / 32) * 32 * d.kh * d.kw * ((d.c_in + kWinChunk - 1) / kWinChunk) * kWinChunk * eb);
     p.vec_out = g.vec_out ? 1 : 2;
     p.slab_bytes = window_slab_bytes(pl, which, win.bm);
     p.slab_hp = d.h + 2 * d.pad_h;
@@ -1809,7 +1850,7 @@ static sc_status launch_conv(const sc_plan* pl, bool dense, const void* x, const
 #ifdef SC_TIMING
     p.dbg = g_dbg;
 #endif
-    LaunchFn fn = window_kernel(d.dtype == SC_BF16 ? kBF16 : kF16, win.bm, win.bn);
+    LaunchFn fn = window_kernel(d.dtype == SC_BF16 ? kBF16 : kF16, d.kh, win.bm, win.bn);
     if (!fn || !p.slab_bytes) return SC_ERR_UNSUPPORTED;    // cannot happen: the pick checked both
     SC_HIP(fn(p, stream));
     return SC_OK;
@@ -1844,8 +1885,8 @@ static sc_status launch_conv(const sc_plan* pl, bool dense, const void* x, const
     p.x_bytes = (uint32_t)((uint64_t)d.n * d.h * d.w * d.c_in * eb);
     p.w_bytes = (uint32_t)((uint64_t)g.cout_pad * g.k_stride * eb);
     // (a mask that keeps every row runs over the identity map: its tiles are those of the dense run)
-    p.slab_bytes = slab_buffer_bytes(d, slab.bm, std::max(pl->slab_span[which][slab.bm == 256],
-                                                          identity ? pl->slab_span[1][slab.bm == 256] : 0));
+    p.slab_bytes = slab_buffer_bytes(d, slab.bm, std::max(pl->slab_span[which][span_of(slab.bm)],
+                                                          identity ? pl->slab_span[1][span_of(slab.bm)] : 0));
     p.slab_hp = d.h + 2 * d.pad_h;
     p.slab_wp = d.w + 2 * d.pad_w;
     magic_div((uint32_t)p.slab_hp, &p.div_hp_mul, &p.div_hp_shift);
@@ -2088,7 +2129,7 @@ static sc_status build_row_tables(const sc_conv_desc& d, const Geometry& g, unsi
   int32_t* counts = reinterpret_cast<int32_t*>(ws + g.off_counts);
   int32_t* rows = reinterpret_cast<int32_t*>(ws + g.off_rows);
   int32_t* kept_dev = reinterpret_cast<int32_t*>(ws + g.off_kept);
-  int32_t host_vals[4] = {-1, 0, 0, 0};   // kept count, most kept rows in one band, widest slab of a 128-row / 256-row tile
+  int32_t host_vals[5] = {-1, 0, 0, 0, 0};   // kept count, most kept rows in one band, widest slab of a 64-row / 128-row / 256-row tile
   const bool slab = slab_geometry_ok(d, g) || g.window;
   // One launch up to 2^17 rows (where a run of rows cut in two leaves both halves a pixel); beyond that every workgroup's
   // count of the rows in front of it costs more than a pass of its own.  Measured per refresh on a
@@ -2106,25 +2147,19 @@ static sc_status build_row_tables(const sc_conv_desc& d, const Geometry& g, unsi
     p.m = (int32_t)g.m; p.period = period; p.mask_len = (int32_t)g.mask_len;
     p.ho = g.ho; p.wo = g.wo; p.bh = 1;
     if (bp.ok) { p.n_bands = bp.n_bands; p.bands_per_image = bp.bands_per_image; p.bh = bp.bh; p.split = bp.split; }
-    if (slab && wgs == 1) { p.slab_hp = d.h + 2 * d.pad_h; p.slab_kh = d.kh; }
+    if (slab) { p.slab_hp = d.h + 2 * d.pad_h; p.slab_kh = d.kh; }
     magic_div((uint32_t)(g.ho * g.wo), &p.howo_mul, &p.howo_shift);
     magic_div((uint32_t)g.wo, &p.wo_mul, &p.wo_shift);
     magic_div((uint32_t)p.bh, &p.bh_mul, &p.bh_shift);
     int32_t* slot = g_host_slots.take(stream);
     p.result = slot ? slot : counts;
-    const int span_wgs = (int)((g.m + 128 * 256 - 1) / (128 * 256));
     int32_t copied[kHostSlotWords];
     const sc_status s = [&]() -> sc_status {
       hipLaunchKernelGGL(row_tables_kernel, dim3(wgs), dim3(kTableThreads), 0, stream, p);
       SC_HIP(hipGetLastError());
       if (g.depthwise)
         SC_HIP(depthwise_rank(rows, kept_dev, reinterpret_cast<int32_t*>(ws + g.off_band_rows), g.m, stream));
-      if (slab && wgs > 1) {
-        hipLaunchKernelGGL(slab_span_kernel, dim3(span_wgs), dim3(256), 0, stream, rows, kept_dev, g.ho * g.wo, g.wo, d.h + 2 * d.pad_h,
-                           d.kh, p.result + 4 * wgs, 1);
-        SC_HIP(hipGetLastError());
-      }
-      if (!slot) SC_HIP(hipMemcpyAsync(copied, counts, sizeof(int32_t) * (4 * wgs + 2 * span_wgs), hipMemcpyDeviceToHost, stream));
+      if (!slot) SC_HIP(hipMemcpyAsync(copied, counts, sizeof(int32_t) * 4 * wgs, hipMemcpyDeviceToHost, stream));
       SC_HIP(hipStreamSynchronize(stream));
       return SC_OK;
     }();
@@ -2137,11 +2172,10 @@ static sc_status build_row_tables(const sc_conv_desc& d, const Geometry& g, unsi
     for (int i = 0; i < wgs; ++i) {
       kept += res[4 * i];
       fullest = std::max(fullest, (int)res[4 * i + 1]);
-      if (wgs == 1) { host_vals[2] = res[2]; host_vals[3] = res[3]; }
+      host_vals[2] = std::max(host_vals[2], (int)res[4 * i + 2]);
+      host_vals[3] = std::max(host_vals[3], (int)((uint32_t)res[4 * i + 3] & 0xffffu));
+      host_vals[4] = std::max(host_vals[4], (int)((uint32_t)res[4 * i + 3] >> 16));
     }
-    if (slab && wgs > 1)
-      for (int i = 0; i < span_wgs; ++i)
-        for (int b = 0; b < 2; ++b) host_vals[2 + b] = std::max(host_vals[2 + b], (int)res[4 * wgs + 2 * i + b]);
     if (slot) g_host_slots.give_back(slot);
     host_vals[0] = kept;
     host_vals[1] = fullest;
@@ -2170,18 +2204,17 @@ static sc_status build_row_tables(const sc_conv_desc& d, const Geometry& g, unsi
     }
 
     if (slab) {
-      hipLaunchKernelGGL(slab_span_kernel, dim3((unsigned)((g.m + 127) / 128 + 255) / 256), dim3(256), 0, stream, rows, kept_dev,
-                         g.ho * g.wo, g.wo, d.h + 2 * d.pad_h, d.kh, kept_dev + 2, 0);
+      hipLaunchKernelGGL(slab_span_kernel, dim3((unsigned)((g.m + 63) / 64 + 255) / 256), dim3(256), 0, stream, rows, kept_dev,
+                         g.ho * g.wo, g.wo, d.h + 2 * d.pad_h, d.kh, kept_dev + 2);
       SC_HIP(hipGetLastError());
     }
 
-    SC_HIP(hipMemcpyAsync(host_vals, kept_dev, 4 * sizeof(int32_t), hipMemcpyDeviceToHost, stream));
+    SC_HIP(hipMemcpyAsync(host_vals, kept_dev, sizeof(host_vals), hipMemcpyDeviceToHost, stream));
     SC_HIP(hipStreamSynchronize(stream));
   }
   *kept_out = host_vals[0];
   bp.max_kept = host_vals[1];
-  slab_span_out[0] = host_vals[2];
-  slab_span_out[1] = host_vals[3];
+  for (int b = 0; b < 3; ++b) slab_span_out[b] = host_vals[2 + b];
 
   if (d.sparsity >= 0.0f) {
     // Sec. 3.2: rows in the GEMM = output_size - sparsity * output_size (rounded half up).  The descriptor carries
@@ -2246,7 +2279,7 @@ sc_status sparse_conv_plan(const sc_conv_desc* desc, const uint8_t* mask_dev, co
   int32_t kept_host = 0;
   s = pack_filters(d, g, ws, w_dev, true, false, stream);
   if (s != SC_OK) return s;
-  int32_t slab_span[2] = {0, 0};
+  int32_t slab_span[3] = {0, 0, 0};
   s = build_row_tables(d, g, ws, mask_dev, stream, &bp, &kept_host, slab_span);   // synchronises the stream
   if (s != SC_OK) return s;
 
@@ -2282,9 +2315,10 @@ sc_status sparse_conv_plan(const sc_conv_desc* desc, const uint8_t* mask_dev, co
   stage_tiles_for(d, g, pl->kept, pl->stage_pick);
   pl->slab = 0;
   pl->slab_ok = slab_geometry_ok(d, g) && slab_kernel(d.dtype == SC_BF16 ? kBF16 : kF16, 128, false);
-  pl->slab_span[0][0] = slab_span[0]; pl->slab_span[0][1] = slab_span[1];
-  pl->slab_span[1][0] = pl->slab_ok || g.window ? slab_dense_span(d, g, 128) : 0;
-  pl->slab_span[1][1] = pl->slab_ok || g.window ? slab_dense_span(d, g, 256) : 0;
+  for (int b = 0; b < 3; ++b) {
+    pl->slab_span[0][b] = slab_span[b];
+    pl->slab_span[1][b] = pl->slab_ok || g.window ? slab_dense_span(d, g, 64 << b) : 0;
+  }
   pl->window[0] = window_tile_for(pl, 0);
   pl->window[1] = window_tile_for(pl, 1);
   // (automatic launches take the slab form only where sparse_conv_plan_tune measured it faster: the cost model's
@@ -2306,7 +2340,7 @@ sc_status sparse_conv_plan_set_mask(sc_plan* plan, const uint8_t* mask_dev, void
   const Geometry& g = plan->geo;
   BandPlan bp = plan->band;
   int32_t kept_host = 0;
-  int32_t slab_span[2] = {0, 0};
+  int32_t slab_span[3] = {0, 0, 0};
   sc_status s = build_row_tables(d, g, plan->ws, mask_dev, static_cast<hipStream_t>(hip_stream), &bp, &kept_host, slab_span);
   if (s != SC_OK) return s;
   plan->kept = kept_host;
@@ -2316,7 +2350,7 @@ sc_status sparse_conv_plan_set_mask(sc_plan* plan, const uint8_t* mask_dev, void
   if (plan->stage_tuned) plan->prefer_tiled[1] = false;      // (both runs were chosen together)
   plan->stage_tuned = 0;
   stage_tiles_for(d, g, plan->kept, plan->stage_pick);
-  plan->slab_span[0][0] = slab_span[0]; plan->slab_span[0][1] = slab_span[1];
+  for (int b = 0; b < 3; ++b) plan->slab_span[0][b] = slab_span[b];
   plan->slab_auto[0] = sc_plan::Slab{0, 1};
   plan->window[0] = window_tile_for(plan, 0);
   return SC_OK;
@@ -2587,7 +2621,7 @@ sc_status sparse_conv_plan_tune(sc_plan* plan, const void* x_dev, const float* b
     if (plan->slab_ok && plan->slab == 0 && plan->split_k == 0 && !(bsel.ok && !bsel.stream && !best_tiled)) {
       sc_plan::Slab best_slab = {0, 1};
       for (int bm = 256; bm >= 128; bm >>= 1) {
-        if (!slab_buffer_bytes(plan->desc, bm, plan->slab_span[which][bm == 256])) continue;
+        if (!slab_buffer_bytes(plan->desc, bm, plan->slab_span[which][span_of(bm)])) continue;
         const int around = slab_splits(plan, bm, rows);
         int tried[4] = {0, 0, 0, 0}, n_tried = 0;
         for (int sp : {around, around - 1, around + 1, 1}) {

@@ -1,4 +1,4 @@
-"""Window kernel (3x3 layers at stride 1 whose channels are whole 16-byte groups: every input pixel of a tile once in LDS, filters straight
+"""Window kernel (3x3 and 5x5 layers at stride 1 whose channels are whole 16-byte groups: every input pixel of a tile once in LDS, filters straight
 into registers) against the oracle, through the C ABI."""
 import dataclasses
 
@@ -27,6 +27,8 @@ SHAPES = {
     "last_chunk_of_8": dict(n=2, cin=72, h=9, w=11, cout=24),                       # half a K step behind the first chunk; half a block
     "last_chunk_of_40": dict(n=3, cin=104, h=10, w=7, cout=104, sp=0.3),
     "under_a_chunk": dict(n=2, cin=24, h=11, w=12, cout=152, sp=0.2),
+    "window_5x5": dict(n=3, cin=80, h=9, w=11, cout=72, k=5, p=2),
+    "window_5x5_no_padding": dict(n=2, cin=136, h=12, w=9, cout=96, k=5, p=0, sp=0.3),
     "wide_map": dict(n=1, cin=64, h=4, w=120, cout=64, sp=0.7),                    # a tap row is most of the slab
 }
 
@@ -38,9 +40,9 @@ def fits(spec, mask, tile):
     span = 0
     for r in (rows, np.arange(spec.m)) if rows.size == spec.m else (rows,):
         vrow = (r // (spec.ho * spec.wo)) * hp + (r % (spec.ho * spec.wo)) // spec.wo
-        bm = max(tile[0], 128)                      # (64-row tiles go by the widest of 128 rows)
+        bm = tile[0]
         first, last = vrow[::bm], vrow[np.minimum(np.arange(0, r.size, bm) + bm, r.size) - 1]
-        span = max(span, int((last + 3 - first).max()))
+        span = max(span, int((last + spec.kh - first).max()))
     slab = -(-span * wp * 144 // 8192) * 8192 * (2 if spec.c_in > 64 else 1)
     sums = {(256, 128): 0, (128, 128): 4, (128, 64): 4, (64, 128): 2, (64, 64): 2}[tile] * 32768
     rest = tile[0] * 12 + tile[1] * 4 + 2048 + 128 + (tile[0] + 64) * 4
