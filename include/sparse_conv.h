@@ -261,6 +261,9 @@ sc_status sparse_conv_plan_tune(sc_plan* plan, const void* x_dev, const float* b
  *                                                in and out also 4); 0x0 = other kernels; automatic otherwise
  *   SPARSE_CONV_TILE_GROUPS=<rows>x<couts>x<1|2> tile of the automatic tiled launch of 16-bit layers and how many
  *                                                groups of wavefronts share its K tiles; automatic otherwise
+ *   SPARSE_CONV_WINDOW_TILE=<rows>x<couts>       tile of the kernel of 16-bit NHWC layers with 3x3 and 5x5 windows at
+ *                                                stride 1 that keeps its input in LDS for all taps, also where a band
+ *                                                kernel would run; 0x0 = other kernels; automatic otherwise
  *   SPARSE_CONV_DEPTHWISE_KERNEL=staged|walk     kernel of 16-bit depthwise layers with 3x3 windows and dense operands
  *                                                (walk: where tensors are below 2 GiB); automatic otherwise
  *   SPARSE_CONV_HOST_SLOTS=0                     counts of a plan's row tables are copied from the device (read by
