@@ -203,7 +203,9 @@ __global__ void repack_kernel(const typename Elem<DT>::T* __restrict__ w, v4i* _
   }
   if constexpr (DT != kF32) {      // for the window kernel: [32 channels][chunk][K step][tap][lane], k_tiles chunks
     const int idx = (blockIdx.x - row_blocks) * blockDim.x + threadIdx.x;
-    const int lane = idx & 63, unit = idx >> 6, tap = unit % taps, ks = unit / taps & 3, rest = unit / taps >> 2;
+    // (the four wavefronts of a workgroup take the four K steps of a tap, so that the 128 bytes of a chunk are read by one compute unit;
+    // with taps side by side instead they came from L2 four times: 512 -> 512 3x3 7.8 -> 6.4 us a launch, 128 -> 128 the same)
+    const int lane = idx & 63, unit = idx >> 6, ks = unit & 3, part = unit >> 2, tap = part % taps, rest = part / taps;
     const int chunk = rest % k_tiles, nb = rest / k_tiles;
     if (nb >= part_blocks) return;
     T e[8];
@@ -211,7 +213,7 @@ __global__ void repack_kernel(const typename Elem<DT>::T* __restrict__ w, v4i* _
     group(nb * 32 + channel(lane & 31), ci < c_in ? tap * c_in + ci : k, e);      // (zeros behind the last channel)
     v4i v;
     __builtin_memcpy(&v, e, 16);
-    parts[idx] = v;
+    parts[((rest * 4 + ks) * taps + tap) * 64 + lane] = v;
   }
   if constexpr (DT == kF32) {
     const int idx = (blockIdx.x - row_blocks) * blockDim.x + threadIdx.x;
