@@ -1630,9 +1630,7 @@ static TilePick pick_tile(const sc_plan* pl, int which, int64_t rows) {
     return tp;
   }
   tp.ti = pl->pick[which].ti;
-  // (a stream-K walk that is asked for where the window kernel would run finds no automatic split in its way)
-  const bool keep_whole = pl->split_k == 1 || (pl->stream_k >= 2 && pl->window[which].bm > 0);
-  tp.splits = keep_whole ? 1 : std::min(pl->pick[which].splits, most_splits(pl, pl->table[tp.ti], rows));
+  tp.splits = pl->split_k == 1 ? 1 : std::min(pl->pick[which].splits, most_splits(pl, pl->table[tp.ti], rows));
   tp.masked = pl->masked_store == 2 ? which == 0 : pl->masked_store == 1 ? false : pl->pick[which].masked;
   const sc_plan::Pick& pick = pl->pick[which];
   if (pick.grouped >= 0 && !tp.masked && (pick.asked || group_candidates(pl, pl->table[pick.grouped], rows) > 1))

@@ -95,6 +95,20 @@ def test_stream_k_full_size_deep_layers_sampled_rows():
         torch.cuda.empty_cache()
 
 
+def test_stream_k_request_means_the_same_whichever_kernel_is_automatic(monkeypatch):
+    """A layer that is split automatically keeps its split under a stream-K request, also where another kernel would run without one."""
+    spec = spec_of(64, 512, 7, 7, 512, dtype="bf16", sp=0.5)
+    ci = W.make_conv_inputs(spec, 1325)
+    x, got = R.to_device(ci.x, spec.dtype), []
+    for window in (None, "0x0"):
+        if window:
+            monkeypatch.setenv("SPARSE_CONV_WINDOW_TILE", window)
+        layer = R.ConvLayer(spec, ci.w, ci.bias, ci.mask)
+        B.sparse_conv_plan_set_option(layer.plan, B.SC_OPT_STREAM_K, 8)
+        got.append((B.sparse_conv_plan_kernel(layer.plan, 0), B.sparse_conv_plan_tiles(layer.plan, 0), R.bits_of(layer.sparse(x)).tobytes()))
+    assert got[0][0] == "tile_split_k" and got[0] == got[1]
+
+
 @pytest.mark.parametrize("post_relu", [False, True])
 def test_stream_k_with_a_fused_shortcut(post_relu):
     spec = spec_of(2, 256, 10, 10, 256, dtype="bf16", sp=0.5, relu=False)
