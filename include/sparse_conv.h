@@ -215,8 +215,9 @@ sc_status sparse_conv_plan_tiles(const sc_plan* plan, int32_t which, int32_t* ti
                                  int64_t* workgroups);
 
 /* Name of the kernel the sparse (which = 0) or dense (which = 1) launch uses: "band",
- * "band_alternating", "band_tap", "band_stream", "band_row_segments", "tile_row_panel", "tile_slab", "tile_split_k", "tile_masked_store", "tile_stream_k", "tile_lds_direct",
- * "tile_registers", "tile_staged", "tile_row_segments", "tile_elements" or "depthwise".
+ * "band_alternating", "band_tap", "band_stream", "band_row_segments", "tile_row_panel", "tile_window", "tile_slab",
+ * "tile_split_k", "tile_masked_store", "tile_stream_k", "tile_lds_direct", "tile_registers", "tile_staged",
+ * "tile_row_segments", "tile_elements" or "depthwise".
  * A static string; NULL for a NULL plan or an unknown `which`. */
 const char* sparse_conv_plan_kernel(const sc_plan* plan, int32_t which);
 /* The same for a launch fused with a shortcut sum (sparse_conv_run_residual / dense_conv_run_residual with dense
@@ -261,9 +262,10 @@ sc_status sparse_conv_plan_tune(sc_plan* plan, const void* x_dev, const float* b
  *                                                in and out also 4); 0x0 = other kernels; automatic otherwise
  *   SPARSE_CONV_TILE_GROUPS=<rows>x<couts>x<1|2> tile of the automatic tiled launch of 16-bit layers and how many
  *                                                groups of wavefronts share its K tiles; automatic otherwise
- *   SPARSE_CONV_WINDOW_TILE=<rows>x<couts>       tile of the kernel of 16-bit NHWC layers with 3x3 and 5x5 windows at
- *                                                stride 1 that keeps its input in LDS for all taps, also where a band
- *                                                kernel would run; 0x0 = other kernels; automatic otherwise
+ *   SPARSE_CONV_WINDOW_TILE=<rows>x<couts>       tile of the kernel reported as "tile_window" (16-bit NHWC layers with
+ *                                                3x3 and 5x5 windows at stride 1; keeps its input in LDS for all
+ *                                                taps), also where a band kernel would run; 0x0 = other kernels;
+ *                                                automatic otherwise
  *   SPARSE_CONV_DEPTHWISE_KERNEL=staged|walk     kernel of 16-bit depthwise layers with 3x3 windows and dense operands
  *                                                (walk: where tensors are below 2 GiB); automatic otherwise
  *   SPARSE_CONV_HOST_SLOTS=0                     counts of a plan's row tables are copied from the device (read by

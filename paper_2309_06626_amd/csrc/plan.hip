@@ -2745,7 +2745,7 @@ sc_status sparse_conv_plan_tiles(const sc_plan* plan, int32_t which, int32_t* ti
 static const char* tiled_kernel_name(const sc_plan* plan, int32_t which, LaunchForm form) {
   const Geometry& g = plan->geo;
   if (use_stage(plan, which, form)) return "tile_staged";
-  if (use_window(plan, which, which ? g.m : plan->kept, form == kPlainRun)) return "tile_lds_direct";
+  if (use_window(plan, which, which ? g.m : plan->kept, form == kPlainRun)) return "tile_window";
   const TilePick tp = pick_tile(plan, which, which ? g.m : plan->kept);
   if (tp.masked) return "tile_masked_store";
   if (tp.splits > 1) return "tile_split_k";

@@ -167,4 +167,4 @@ def test_tuned_choice_on_a_layer_the_slab_kernel_serves():
         ref, absum = oracle.masked_conv2d_rows(spec, ci.x, ci.w, ci.bias, mask, rows, want_absum=True)
         sel = np.ones_like(kept) if dense else kept
         assert_close(rows_view(spec, R.to_host_f32(out))[rows][sel], ref[sel], absum[sel], TOL[spec.dtype], f"tuned, dense={dense}")
-    assert B.sparse_conv_plan_kernel(layer.plan, 1) in ("tile_slab", "tile_lds_direct", "tile_split_k")
+    assert B.sparse_conv_plan_kernel(layer.plan, 1) in ("tile_slab", "tile_window", "tile_lds_direct", "tile_split_k")

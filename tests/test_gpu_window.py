@@ -29,6 +29,7 @@ SHAPES = {
     "under_a_chunk": dict(n=2, cin=24, h=11, w=12, cout=152, sp=0.2),
     "window_5x5": dict(n=3, cin=80, h=9, w=11, cout=72, k=5, p=2),
     "window_5x5_no_padding": dict(n=2, cin=136, h=12, w=9, cout=96, k=5, p=0, sp=0.3),
+    "wide_map_most_kept": dict(n=2, cin=64, h=9, w=60, cout=64, sp=0.3),            # five to seven rows of 62 pixels
     "wide_map": dict(n=1, cin=64, h=4, w=120, cout=64, sp=0.7),                    # a tap row is most of the slab
 }
 
@@ -49,6 +50,15 @@ def fits(spec, mask, tile):
     return span * wp <= 512 and max(slab, sums) + rest <= 160 * 1024
 
 
+def assert_window(layer, spec, mask, tile):
+    """Wherever the tile's slabs fit, the sparse and dense runs are the window kernel's in that tile; elsewhere none is."""
+    for which, m in ((0, mask), (1, np.ones_like(mask))):
+        took = B.sparse_conv_plan_kernel(layer.plan, which) == "tile_window"
+        assert took == fits(spec, m, tile)
+        assert not took or B.sparse_conv_plan_tiles(layer.plan, which)[:2] == tile
+    return layer
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("tile", TILES)
 @pytest.mark.parametrize("shape", list(SHAPES))
@@ -56,9 +66,8 @@ def test_window_kernel_matches_the_oracle(shape, tile, dtype, monkeypatch):
     monkeypatch.setenv("SPARSE_CONV_WINDOW_TILE", "%dx%d" % tile)
     spec = spec_of(dtype=dtype, **SHAPES[shape])
     ci = W.make_conv_inputs(spec, 3000 + len(shape))
-    layer = check_layer(ci)
-    if fits(spec, ci.mask, tile):
-        assert B.sparse_conv_plan_kernel(layer.plan, 0) == "tile_lds_direct" and B.sparse_conv_plan_tiles(layer.plan, 0)[:2] == tile
+    assert_window(check_layer(ci), spec, ci.mask, tile)
+    assert tile[0] > 64 or fits(spec, np.ones_like(ci.mask), tile)      # (something does run)
 
 
 @pytest.mark.parametrize("cin,cout", [(128, 96), (88, 56)])
@@ -67,23 +76,27 @@ def test_window_kernel_other_operands(tile, cin, cout, monkeypatch):
     """Rows left alone, compact rows, shortcut sums, a shared mask; masks with long runs of dropped rows; new masks."""
     monkeypatch.setenv("SPARSE_CONV_WINDOW_TILE", "%dx%d" % tile)
     spec = spec_of(3, cin, 10, 9, cout, sp=0.4)
-    check_layer(W.make_conv_inputs(spec, 3100), out_mode=B.SC_OUT_SCATTER_ONLY)
-    check_layer(W.make_conv_inputs(spec.with_(mask_mode="spatial"), 3101))
-    check_compact_output(spec, 3102)
+    for seed, sp, out_mode in ((3100, spec, B.SC_OUT_SCATTER_ONLY), (3101, spec.with_(mask_mode="spatial"), B.SC_OUT_ZERO_FILL)):
+        ci = W.make_conv_inputs(sp, seed)
+        assert_window(check_layer(ci, out_mode=out_mode), sp, ci.mask, tile)
+    assert_window(check_compact_output(spec, 3102)[0], spec, W.make_conv_inputs(spec, 3102).mask, tile)
     for sp in (0.4, 0.0, 0.9):                       # (at 0.9 most dropped rows lie behind the listed ones)
-        check_residual(spec.with_(sparsity=sp, relu=False), 3103, True, want_kernel=("tile_lds_direct", "tile_masked_store", "tile_split_k", "tile_registers"))
-    ci = W.make_conv_inputs(spec.with_(sparsity=0.5), 3104)
+        s = spec.with_(sparsity=sp, relu=False)
+        assert_window(check_residual(s, 3103, True), s, W.make_conv_inputs(s, 3103).mask, tile)
+    s = spec.with_(sparsity=0.5)
+    ci = W.make_conv_inputs(s, 3104)
     half = np.zeros_like(ci.mask)
     half[::2] = 1                                    # every other pixel: all rows of a set of lanes in half of the bank groups
     runs = np.sort(ci.mask)                          # all dropped rows in front
     for mask in (half, runs, runs[::-1].copy()):
-        check_layer(dataclasses.replace(ci, mask=mask))
-    layer = R.ConvLayer(spec.with_(sparsity=0.5), ci.w, ci.bias, ci.mask)
+        assert_window(check_layer(dataclasses.replace(ci, mask=mask)), s, mask, tile)
+    layer = R.ConvLayer(s, ci.w, ci.bias, ci.mask)
     x = R.to_device(ci.x, spec.dtype)
     for mask in (runs, half):
         B.sparse_conv_plan_set_mask(layer.plan, torch.from_numpy(mask.astype(np.uint8)).cuda())
-        fresh = R.ConvLayer(spec.with_(sparsity=0.5), ci.w, ci.bias, mask)
-        assert np.array_equal(R.bits_of(layer.sparse(x)), R.bits_of(fresh.sparse(x)))
+        fresh = R.ConvLayer(s, ci.w, ci.bias, mask)
+        assert np.array_equal(R.bits_of(layer.sparse(x)), R.bits_of(assert_window(fresh, s, mask, tile).sparse(x)))
+        assert_window(layer, s, mask, tile)
 
 
 def test_values_outside_a_window_do_not_enter(monkeypatch):
@@ -91,7 +104,8 @@ def test_values_outside_a_window_do_not_enter(monkeypatch):
     monkeypatch.setenv("SPARSE_CONV_WINDOW_TILE", "64x64")
     spec = spec_of(2, 64, 9, 8, 32, sp=0.0, relu=False)
     ci = W.make_conv_inputs(spec, 3200)
-    layer = R.ConvLayer(spec, ci.w, ci.bias, ci.mask)
+    layer = assert_window(R.ConvLayer(spec, ci.w, ci.bias, ci.mask), spec, ci.mask, (64, 64))
+    assert B.sparse_conv_plan_kernel(layer.plan, 0) == "tile_window"
     clean = layer.sparse(R.to_device(ci.x, spec.dtype)).clone()
     for n, y, x in ((0, 8, 7), (1, 0, 0), (0, 4, 0)):
         bad = ci.x.copy()
@@ -106,7 +120,8 @@ def test_refreshed_filters_reach_the_window_kernel(monkeypatch):
     monkeypatch.setenv("SPARSE_CONV_WINDOW_TILE", "64x128")
     spec = spec_of(2, 136, 9, 8, 72, sp=0.3)
     one, two = W.make_conv_inputs(spec, 3300), W.make_conv_inputs(spec, 3301)
-    layer = R.ConvLayer(spec, one.w, one.bias, one.mask)
+    layer = assert_window(R.ConvLayer(spec, one.w, one.bias, one.mask), spec, one.mask, (64, 128))
+    assert B.sparse_conv_plan_kernel(layer.plan, 0) == "tile_window"
     fresh = R.ConvLayer(spec, two.w, one.bias, one.mask)
     B.sparse_conv_plan_set_filters(layer.plan, R.to_device(two.w, spec.dtype))
     x = R.to_device(one.x, spec.dtype)
