@@ -221,7 +221,7 @@ sc_status sparse_conv_plan_tiles(const sc_plan* plan, int32_t which, int32_t* ti
  * A static string; NULL for a NULL plan or an unknown `which`. */
 const char* sparse_conv_plan_kernel(const sc_plan* plan, int32_t which);
 /* The same for a launch fused with a shortcut sum (sparse_conv_run_residual / dense_conv_run_residual with dense
- * operands): "band_alternating" or one of the "tile_..." names; NULL also for depthwise plans (no fused form). */
+ * operands): "band_alternating", "band_tap" or one of the "tile_..." names; NULL also for depthwise plans (no fused form). */
 const char* sparse_conv_plan_fused_kernel(const sc_plan* plan, int32_t which);
 
 /* Tuning hook: force the kernel of later runs.  (0,0) restores the automatic choice; tile_m > 0

@@ -2774,7 +2774,8 @@ const char* sparse_conv_plan_fused_kernel(const sc_plan* plan, int32_t which) {
   const BandPlan& band = which ? plan->band_dense : plan->band;
   if (band.ok && (band.pp || band.tap) && !band.stream &&
       (plan->forced[which] == kForceBand || (plan->forced[which] == -1 && !plan->prefer_tiled[which])) &&
-      !(plan->slab >= 2 && slab_pick(plan, which, which ? plan->geo.m : plan->kept).bm))
+      !(plan->slab >= 2 && slab_pick(plan, which, which ? plan->geo.m : plan->kept).bm) &&
+      !bands_give_way(plan, which, which ? plan->geo.m : plan->kept))
     return band.tap ? "band_tap" : "band_alternating";
   if (slab_pick(plan, which, which ? plan->geo.m : plan->kept).bm) return "tile_slab";
   return tiled_kernel_name(plan, which, kFusedRun);

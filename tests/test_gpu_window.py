@@ -51,10 +51,10 @@ def fits(spec, mask, tile):
 
 
 def assert_window(layer, spec, mask, tile):
-    """Wherever the tile's slabs fit, the sparse and dense runs are the window kernel's in that tile; elsewhere none is."""
+    """Wherever the tile's slabs fit, the plain and the fused sparse and dense runs are the window kernel's in that tile; elsewhere none is."""
     for which, m in ((0, mask), (1, np.ones_like(mask))):
         took = B.sparse_conv_plan_kernel(layer.plan, which) == "tile_window"
-        assert took == fits(spec, m, tile)
+        assert took == (B.sparse_conv_plan_fused_kernel(layer.plan, which) == "tile_window") == fits(spec, m, tile)
         assert not took or B.sparse_conv_plan_tiles(layer.plan, which)[:2] == tile
     return layer
 
