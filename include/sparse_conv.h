@@ -23,7 +23,7 @@
  *   index list, packed filters, gather table) lives in the caller's workspace, which must
  *   stay alive and untouched for as long as the plan is used.  The plan object itself is
  *   host memory owned by the library until sparse_conv_plan_destroy.  The first sparse_conv_plan
- *   or sparse_conv_plan_set_mask of a process also makes one allocation of pinned host memory (66 560
+ *   or sparse_conv_plan_set_mask of a process also makes one allocation of pinned host memory (196 608
  *   bytes, into which kernels write the counts that these calls return), held until the process ends;
  *   where it cannot be had, or more than 32 such calls are under way at once, the counts are copied.
  *   `hip_stream` is a hipStream_t passed as void* (NULL = the default stream).

@@ -271,15 +271,38 @@ __global__ void band_rows_kernel(const int32_t* __restrict__ row_idx, const int3
 }
 
 // ------------------------------------------------------------------------------------------------
-// The same tables -- row list, private mask copy, band starts, band-ordered rows, and for one workgroup the slab spans -- in
+// The same tables -- row list, private mask copy, band starts, band-ordered rows -- and the spans of slabs in
 // ONE launch, for maps of up to kTableMostRows rows.  A workgroup owns 1 024 rows and counts the ones in front of them by
 // itself (16-byte loads of a mask that lies in L2) instead of waiting for a pass of its own, so a refresh of a small map is
 // one launch in place of four or five.  Every workgroup leaves what the host wants to know -- its kept rows, the fullest
-// band that ends in its rows, the spans -- in host memory (`result`, four words each), where the host finds it behind the
+// band that ends in its rows, the spans -- in host memory (`result`, kTableWords words each), where the host finds it behind the
 // synchronisation without a copy.
 // ------------------------------------------------------------------------------------------------
 constexpr int kTableThreads = 256, kTableRows = 4 * kTableThreads;
 constexpr int kTableMostRows = 1 << 17, kTableMostWgs = kTableMostRows / kTableRows;
+// Words that a workgroup leaves for the host: kept rows, most kept rows of a band; for tiles of 64, 128 and 256 kept rows the widest span of
+// those inside the segment, the virtual row at which the one open at its end begins and at which the one open at its start ends (-1: none);
+// the virtual row of its last kept row.
+enum { kTableKept, kTableFullest, kTableInner, kTableOpen = kTableInner + 3, kTableClose = kTableOpen + 3, kTableEnd = kTableClose + 3, kTableWords };
+
+// The widest span of a tile of 64, 128 and 256 kept rows, in virtual rows, from the words of all workgroups in order.
+static void table_spans(const int32_t* words, int wgs, int kh, int32_t (&span)[3]) {
+  for (int b = 0; b < 3; ++b) {
+    int open = -1, end = -1;
+    span[b] = 0;
+    for (int i = 0; i < wgs; ++i) {
+      const int32_t* w = words + i * kTableWords;
+      span[b] = std::max(span[b], w[kTableInner + b]);
+      if (w[kTableClose + b] >= 0) {
+        span[b] = std::max(span[b], w[kTableClose + b] + kh - open);
+        open = -1;
+      }
+      if (w[kTableOpen + b] >= 0) open = w[kTableOpen + b];
+      if (w[kTableEnd] >= 0) end = w[kTableEnd];
+    }
+    if (open >= 0) span[b] = std::max(span[b], end + kh - open);      // the last tile, which the kept rows do not fill
+  }
+}
 
 struct TableParams {
   const uint8_t* mask;
@@ -292,12 +315,12 @@ struct TableParams {
 };
 
 __global__ __launch_bounds__(kTableThreads) void row_tables_kernel(const TableParams p) {
-  constexpr int WORDS = kTableRows / 64;
-  __shared__ unsigned long long s_bits[2 * WORDS];          // which rows of the segment, and (for spans) of the one behind it, are kept
-  __shared__ int s_before[2 * WORDS];                       // kept rows in front of each word, counted from the segment's first
-  __shared__ int s_wave[4], s_next[4], s_red[3], s_span[3];
-  constexpr int TILES = 2 * kTableRows / 64 + 2;
-  __shared__ int s_tile[2][TILES];
+  __shared__ unsigned long long s_bits[kTableRows / 64];    // which rows of the segment are kept
+  __shared__ int s_before[kTableRows / 64];                 // kept rows of the segment in front of each word
+  __shared__ int s_wave[4], s_red[3];
+  constexpr int TILES = kTableRows / 64 + 1;                // tiles of 64 kept rows that a segment touches
+  __shared__ int s_tile[2][TILES];                          // virtual rows of their first and last rows (-1: not of this segment)
+  __shared__ int s_out[kTableWords];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int r0 = blockIdx.x * kTableRows;
   const int ho_wo = p.ho * p.wo;
@@ -310,14 +333,6 @@ __global__ __launch_bounds__(kTableThreads) void row_tables_kernel(const TablePa
     const int q = p.period ? r - fast_div(r, p.howo_mul, p.howo_shift) * p.period : r;
     v[it] = r < p.m ? p.mask[q] : (uint8_t)0;
     if (r < p.mask_len) p.copy[r] = v[it];
-  }
-  unsigned char next[4] = {0, 0, 0, 0};
-  if (p.slab_hp) {
-#pragma unroll
-    for (int it = 0; it < 4; ++it) {
-      const int r = r0 + kTableRows + wave * 256 + it * 64 + lane;
-      if (r < p.m) next[it] = p.mask[p.period ? r - fast_div(r, p.howo_mul, p.howo_shift) * p.period : r];
-    }
   }
   auto band_at = [&](int r, int* band, int* first, int* end) {      // rows [first, end) of the band that row r lies in
     const int img = fast_div(r, p.howo_mul, p.howo_shift), pix = r - img * ho_wo;
@@ -361,8 +376,9 @@ __global__ __launch_bounds__(kTableThreads) void row_tables_kernel(const TablePa
     const int img = fast_div(r, p.howo_mul, p.howo_shift), rem = r - img * p.period;
     return (img ? img * kept_in(0, p.period) : 0) + kept_in(0, rem);
   };
-  if (t < 3) s_red[t] = s_span[t] = 0;
+  if (t < 3) s_red[t] = 0;
   if (t < 2 * TILES) s_tile[t / TILES][t % TILES] = -1;
+  if (t < kTableWords) s_out[t] = t >= kTableOpen ? -1 : 0;
   __syncthreads();
   if (r0 > 0) {
     const int to_start = wave_sum(kept_before(start)), to_r0 = wave_sum(start == r0 ? 0 : kept_before(r0));
@@ -379,16 +395,6 @@ __global__ __launch_bounds__(kTableThreads) void row_tables_kernel(const TablePa
     own += __popcll(bits);
   }
   if (lane == 0) s_wave[wave] = own;
-  if (p.slab_hp) {
-    int behind = 0;
-#pragma unroll
-    for (int it = 0; it < 4; ++it) {
-      const unsigned long long bits = __ballot(next[it] != 0);
-      if (lane == 0) { s_bits[WORDS + wave * 4 + it] = bits; s_before[WORDS + wave * 4 + it] = behind; }
-      behind += __popcll(bits);
-    }
-    if (lane == 0) s_next[wave] = behind;
-  }
   __syncthreads();
   int before_wave = 0, total = 0;
   for (int w = 0; w < 4; ++w) {
@@ -396,11 +402,6 @@ __global__ __launch_bounds__(kTableThreads) void row_tables_kernel(const TablePa
     total += s_wave[w];
   }
   if (lane < 4) s_before[wave * 4 + lane] += before_wave;
-  if (p.slab_hp && lane < 4) {
-    int more = total;
-    for (int w = 0; w < wave; ++w) more += s_next[w];
-    s_before[WORDS + wave * 4 + lane] += more;
-  }
   const int start_rank = s_red[0], base = s_red[1];
   __syncthreads();
   auto rank_at = [&](int r) {                  // kept rows in front of row r, a row of the segment or `start`
@@ -408,24 +409,15 @@ __global__ __launch_bounds__(kTableThreads) void row_tables_kernel(const TablePa
     const int q = r - r0;
     return base + s_before[q >> 6] + (int)__popcll(s_bits[q >> 6] & ((1ull << (q & 63)) - 1ull));
   };
-  // For spans: the virtual rows of the first and the last row of every 64 kept ones that lie in this segment or the next.
-  const int in_sight = p.slab_hp ? s_before[2 * WORDS - 1] + (int)__popcll(s_bits[2 * WORDS - 1]) : 0;
-  const bool all_seen = r0 + 2 * kTableRows >= p.m;
-  auto mark = [&](int r, int rank) {
-    const bool first = (rank & 63) == 0, last = (rank & 63) == 63 || (all_seen && rank == base + in_sight - 1);
-    if (!first && !last) return;
+  auto mark = [&](int r, int rank) {           // for spans: a kept row that is the first or the last of 64, or the segment's last
+    const bool first = (rank & 63) == 0, last = (rank & 63) == 63, end = rank == base + total - 1;
+    if (!first && !last && !end) return;
     const int img = fast_div(r, p.howo_mul, p.howo_shift);
     const int vrow = img * p.slab_hp + fast_div(r - img * ho_wo, p.wo_mul, p.wo_shift);
     if (first) s_tile[0][(rank >> 6) - (base >> 6)] = vrow;
     if (last) s_tile[1][(rank >> 6) - (base >> 6)] = vrow;
+    if (end) s_out[kTableEnd] = vrow;
   };
-  if (p.slab_hp) {
-#pragma unroll
-    for (int it = 0; it < 4; ++it) {
-      const int w = WORDS + wave * 4 + it;
-      if (next[it] != 0) mark(r0 + w * 64 + lane, base + s_before[w] + (int)__popcll(s_bits[w] & ((1ull << lane) - 1ull)));
-    }
-  }
   int fullest = 0;
 #pragma unroll
   for (int it = 0; it < 4; ++it) {
@@ -447,34 +439,31 @@ __global__ __launch_bounds__(kTableThreads) void row_tables_kernel(const TablePa
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) fullest = max(fullest, __shfl_xor(fullest, off, 64));
   if (lane == 0) atomicMax(&s_red[2], fullest);
-  const bool last = blockIdx.x == gridDim.x - 1;
-  const int kept = base + total;
   __syncthreads();
-  if (p.slab_hp) {
-    // The tiles of 64, 128 and 256 rows whose first row lies in this segment.  One whose last row is out of sight is more than a
-    // segment of rows long: too wide for any slab.
-    const int tile = (base >> 6) + t, n_last = (base + in_sight - 1) >> 6;
-    if (t < TILES && tile * 64 >= base && tile * 64 < kept) {
-      for (int b = 0; b < 3 && (tile & ((1 << b) - 1)) == 0; ++b) {
-        int end = t + (1 << b) - 1;
-        if (all_seen) end = min(end, n_last - (base >> 6));
-        const int v1 = end < TILES ? s_tile[1][end] : -1;
-        atomicMax(&s_span[b], v1 < 0 ? 0xffff : min(v1 + p.slab_kh - s_tile[0][t], 0xffff));
+  if (p.slab_hp && t < TILES) {
+    // Spans of the tiles of 64, 128 and 256 kept rows that lie in this segment whole.  A tile that crosses the segment's end leaves its
+    // first virtual row there, one that crosses its start its last; the host puts the two together (table_spans).
+    const int unit = (base >> 6) + t;
+    for (int b = 0; b < 3; ++b) {
+      const int n = 1 << b;
+      if ((unit & (n - 1)) == 0 && s_tile[0][t] >= 0) {
+        const int end = t + n - 1 < TILES ? s_tile[1][t + n - 1] : -1;
+        if (end >= 0) atomicMax(&s_out[kTableInner + b], end + p.slab_kh - s_tile[0][t]);
+        else s_out[kTableOpen + b] = s_tile[0][t];
       }
+      if (((unit + 1) & (n - 1)) == 0 && s_tile[1][t] >= 0 && (t + 1 < n || s_tile[0][t + 1 - n] < 0)) s_out[kTableClose + b] = s_tile[1][t];
     }
-    __syncthreads();
   }
   if (t == 0) {
-    int32_t* out = p.result + blockIdx.x * 4;
-    out[0] = total;
-    out[1] = s_red[2];
-    out[2] = s_span[0];                        // (tiles of 64 rows)
-    out[3] = s_span[1] | s_span[2] << 16;      // (of 128 and 256)
-    if (last) {
-      p.kept_out[0] = kept;
-      p.kept_out[1] = p.kept_out[2] = p.kept_out[3] = p.kept_out[4] = 0;
-      if (p.n_bands) p.band_i0[p.n_bands] = kept;
-    }
+    s_out[kTableKept] = total;
+    s_out[kTableFullest] = s_red[2];
+  }
+  __syncthreads();
+  if (t < kTableWords) p.result[blockIdx.x * kTableWords + t] = s_out[t];
+  if (t == 0 && blockIdx.x == gridDim.x - 1) {
+    p.kept_out[0] = base + total;
+    p.kept_out[1] = p.kept_out[2] = p.kept_out[3] = p.kept_out[4] = 0;
+    if (p.n_bands) p.band_i0[p.n_bands] = base + total;
   }
 }
 
@@ -482,7 +471,7 @@ __global__ __launch_bounds__(kTableThreads) void row_tables_kernel(const TablePa
 // (in a way that a capture in another thread is not disturbed by) and held until the process ends.  A call holds a slot from its
 // launch to its synchronisation; one that finds none free (or no such memory), or whose stream is being captured, copies from
 // the device instead.  SPARSE_CONV_HOST_SLOTS=0: always (tests).
-constexpr int kHostSlots = 32, kHostSlotWords = kTableMostWgs * 4;
+constexpr int kHostSlots = 32, kHostSlotWords = kTableMostWgs * kTableWords;
 struct HostSlots {
   std::mutex lock;
   int32_t* base = nullptr;
@@ -760,7 +749,7 @@ static sc_status check_desc(const sc_conv_desc* d, Geometry* g) {
   g->nseg = (int32_t)((g->m + kSeg - 1) / kSeg);
   size_t off = 0;
   g->off_rows = off;   off = align_up(off + (size_t)g->m * 4, 256);
-  g->off_counts = off; off = align_up(off + ((size_t)g->nseg * 4 + 16) * 4, 256);      // (and the words of row_tables_kernel)
+  g->off_counts = off; off = align_up(off + ((size_t)g->nseg * 4 + 16 + (size_t)std::min(g->nseg, kTableMostWgs) * kTableWords) * 4, 256);      // (and the words of row_tables_kernel)
   g->off_kept = off;   off += 256;
   g->off_zeros = off;  off += 256;
   g->off_mask = off;   off = align_up(off + (size_t)g->mask_len, 256);
@@ -2157,7 +2146,7 @@ static sc_status build_row_tables(const sc_conv_desc& d, const Geometry& g, unsi
       SC_HIP(hipGetLastError());
       if (g.depthwise)
         SC_HIP(depthwise_rank(rows, kept_dev, reinterpret_cast<int32_t*>(ws + g.off_band_rows), g.m, stream));
-      if (!slot) SC_HIP(hipMemcpyAsync(copied, counts, sizeof(int32_t) * 4 * wgs, hipMemcpyDeviceToHost, stream));
+      if (!slot) SC_HIP(hipMemcpyAsync(copied, counts, sizeof(int32_t) * kTableWords * wgs, hipMemcpyDeviceToHost, stream));
       SC_HIP(hipStreamSynchronize(stream));
       return SC_OK;
     }();
@@ -2168,12 +2157,12 @@ static sc_status build_row_tables(const sc_conv_desc& d, const Geometry& g, unsi
     const int32_t* res = slot ? slot : copied;
     int kept = 0, fullest = 0;
     for (int i = 0; i < wgs; ++i) {
-      kept += res[4 * i];
-      fullest = std::max(fullest, (int)res[4 * i + 1]);
-      host_vals[2] = std::max(host_vals[2], (int)res[4 * i + 2]);
-      host_vals[3] = std::max(host_vals[3], (int)((uint32_t)res[4 * i + 3] & 0xffffu));
-      host_vals[4] = std::max(host_vals[4], (int)((uint32_t)res[4 * i + 3] >> 16));
+      kept += res[kTableWords * i + kTableKept];
+      fullest = std::max(fullest, (int)res[kTableWords * i + kTableFullest]);
     }
+    int32_t span[3] = {0, 0, 0};
+    if (slab) table_spans(res, wgs, d.kh, span);
+    for (int b = 0; b < 3; ++b) host_vals[2 + b] = span[b];
     if (slot) g_host_slots.give_back(slot);
     host_vals[0] = kept;
     host_vals[1] = fullest;

@@ -61,7 +61,7 @@ def test_band_tables_across_segments(case, mode, monkeypatch):
     assert "band" in B.sparse_conv_plan_kernel(layer.plan, 0)
 
 
-@pytest.mark.parametrize("n,h,w", [(2, 14, 14), (11, 40, 41)])                  # one workgroup's spans, and those of a second launch
+@pytest.mark.parametrize("n,h,w", [(2, 14, 14), (11, 40, 41)])                  # spans inside the share of one workgroup, and across those of several
 def test_slab_spans(n, h, w):
     spec = W.ConvSpec("t", n=n, c_in=64, h=h, w=w, c_out=128, sparsity=0.6)
     layer = check_layer(W.make_conv_inputs(spec, 23), sample_rows=400, options={B.SC_OPT_SLAB: 2})
@@ -71,8 +71,8 @@ def test_slab_spans(n, h, w):
 @pytest.mark.parametrize("case", [
     dict(n=3, c_in=8, h=97, w=211, c_out=8, kh=1, kw=1, pad_h=0, pad_w=0),           # rows alone
     dict(n=9, c_in=32, h=57, w=41, c_out=32, pad_h=1, pad_w=1),                       # band tables
-    dict(n=2, c_in=64, h=14, w=14, c_out=128, slab=True),                             # spans of one workgroup
-    dict(n=11, c_in=64, h=40, w=41, c_out=128, slab=True),                            # and of a second launch, behind the counts
+    dict(n=2, c_in=64, h=14, w=14, c_out=128, slab=True),                             # spans inside one workgroup's share
+    dict(n=11, c_in=64, h=40, w=41, c_out=128, slab=True),                            # and across those of several
 ])
 def test_counts_copied_from_the_device_equal_those_in_host_memory(case, monkeypatch):
     """The path of a call that has no slot of host memory: the same plan, the same bits."""

@@ -14,6 +14,7 @@ from parity import check_layer, row_mask
 from test_gpu_compact import check_compact_output
 from test_gpu_parity import spec_of
 from test_gpu_residual import check as check_residual
+from test_gpu_slab import slab_fits
 
 pytestmark = pytest.mark.gpu
 
@@ -126,3 +127,60 @@ def test_refreshed_filters_reach_the_window_kernel(monkeypatch):
     B.sparse_conv_plan_set_filters(layer.plan, R.to_device(two.w, spec.dtype))
     x = R.to_device(one.x, spec.dtype)
     assert np.array_equal(R.bits_of(layer.sparse(x)), R.bits_of(fresh.sparse(x)))
+
+
+def masks_for_spans(rng, length):
+    """Kept rows that end early, begin late, lie in clumps or far apart, and stand around multiples of 1 024, where a workgroup's
+    share of the row list ends."""
+    half = (rng.random(length) < 0.5).astype(np.uint8)
+    for lo, hi in ((0, length // 2), (0, 700), (length // 2, length), (length // 3, length // 2)):
+        m = np.zeros_like(half)
+        m[lo:hi] = half[lo:hi]
+        yield m
+    yield ((rng.random(length) < 0.9) & (np.arange(length) < length * 2 // 3)).astype(np.uint8)
+    yield ((np.arange(length) // 300) % 2 == 0).astype(np.uint8)
+    yield (np.abs((np.arange(length) + 512) % 1024 - 512) < 40).astype(np.uint8)
+    yield (rng.random(length) < 0.02).astype(np.uint8)
+    m = np.zeros_like(half)
+    m[[0, 1, length - 1]] = 1
+    yield m
+
+
+@pytest.mark.parametrize("n,h,w,mode", [
+    (1, 56, 56, "row"),                # four shares of the list
+    (7, 23, 25, "row"), (5, 31, 11, "spatial"), (60, 9, 8, "row"),      # images across shares
+    (1, 6800, 20, "row"),              # past 2^17 rows: the tables of several launches
+])
+def test_spans_of_tiles_across_the_shares_of_the_row_list(n, h, w, mode, monkeypatch):
+    """The window and the slab kernel run exactly where the widest slab of their tiles fits."""
+    rng = np.random.default_rng(n + h)
+    spec = spec_of(n, 64, h, w, 128, mask_mode=mode, sp=0.5)
+    masks = list(masks_for_spans(rng, spec.mask_len))
+    took = 0
+    for tile in ((64, 64), (128, 64), (256, 128)):
+        monkeypatch.setenv("SPARSE_CONV_WINDOW_TILE", "%dx%d" % tile)
+        layer = R.ConvLayer(spec, np.zeros((128, 3, 3, 64), np.float32), np.zeros(128, np.float32), masks[0], check_count=False)
+        for mask in masks:
+            B.sparse_conv_plan_set_mask(layer.plan, torch.from_numpy(mask).cuda())
+            got = B.sparse_conv_plan_kernel(layer.plan, 0) == "tile_window"
+            assert got == fits(spec, mask, tile)
+            took += got
+            if tile[0] >= 128:
+                B.sparse_conv_plan_set_option(layer.plan, B.SC_OPT_SLAB, tile[0])
+                assert (B.sparse_conv_plan_kernel(layer.plan, 0) == "tile_slab") == slab_fits(spec, mask, tile[0])
+                B.sparse_conv_plan_set_option(layer.plan, B.SC_OPT_SLAB, 0)
+    assert 0 < took < 3 * len(masks)
+
+
+@pytest.mark.parametrize("tile", TILES)
+@pytest.mark.parametrize("n,h,w,cout,sp,mode", [
+    (13, 23, 25, 96, 0.4, "row"),                  # tiles across the shares of the row list
+    (13, 23, 25, 104, 0.1, "spatial"),             # of 256 rows too
+    (1, 6800, 20, 16, 0.1, "row"),                 # past 2^17 rows; more workgroups than compute units in every tile
+])
+def test_window_kernel_on_many_rows(n, h, w, cout, sp, mode, tile, monkeypatch):
+    monkeypatch.setenv("SPARSE_CONV_WINDOW_TILE", "%dx%d" % tile)
+    spec = spec_of(n, 80, h, w, cout, sp=sp, mask_mode=mode)
+    ci = W.make_conv_inputs(spec, 3400)
+    layer = assert_window(check_layer(ci, sample_rows=300), spec, ci.mask, tile)
+    assert B.sparse_conv_plan_kernel(layer.plan, 0) == "tile_window" or (tile[0] == 256 and sp == 0.4)
