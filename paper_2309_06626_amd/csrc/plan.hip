@@ -1392,6 +1392,28 @@ static int window_slab_bytes(const sc_plan* pl, int which, int bm) {
   if (span <= 0 || px > kWinMostPixels) return 0;
   return (int)((px * kWinPitch + 8191) / 8192 * 8192);
 }
+// Predicted microseconds of a run by the plain band kernel (one band a workgroup, a 16-bit layer).  A round of workgroups costs its fixed
+// part, the slabs of filters and input of those that share a compute unit, the rows they store, and the walk of the busiest wavefront: blocks
+// of 32 or 64 rows, K steps of 16, each with an instruction a 32 x 32 block and, where the window shape is not known to the compiler
+// (band_kernel's KH, KW, CPP), a fixed part; beyond the rounds a megabyte of y.  Fitted to 1 256 runs of 628 layers (16 to 160 channels in,
+// 16 to 512 out, maps of 7 to 80, 3 x 3 and 5 x 5): standard deviation 5 % (2 to 6 % in each of the three walks, sparse and dense).
+static double band_us(const sc_plan* pl, int which) {
+  const sc_conv_desc& d = pl->desc;
+  const Geometry& g = pl->geo;
+  const BandPlan& b = which ? pl->band_dense : pl->band;
+  const int cus = device_cus(), rows = which || pl->kept == g.m ? std::min(b.bh, g.ho) * g.wo : b.max_kept;
+  int mi_idx = 0;
+  const double blocks = band_units((double)rows, &mi_idx) / (mi_idx + 1);
+  const int walk = d.kh == 3 && d.kw == 3 ? (d.c_in == 32 ? 1 : d.c_in == 64 ? 2 : 0) : 0;
+  static const double steps[3][2] = {{0.0798, 0.0498}, {0.0025, 0.0533}, {0.0011, 0.0278}};      // fixed part, block of 32 x 32
+  const double k_us = blocks * ((g.k + 15) / 16) * (steps[walk][0] + steps[walk][1] * (mi_idx + 1) * b.ni);
+  const double kb = (double)(b.b_bytes + b.x_bytes) / 1024;
+  const int64_t wgs = (int64_t)b.n_bands * b.n_tiles;
+  const int resident = (int)std::min<size_t>(std::max<size_t>(kLdsLimit / b.lds, 1), 8);
+  auto round_us = [&](int64_t on_cu) { return (which ? 2.77 : 3.74) + on_cu * (0.0151 * kb + 0.0008 * rows * b.ni) + k_us; };
+  const int64_t full = (wgs - 1) / ((int64_t)cus * resident), rest = wgs - full * cus * resident;
+  return full * round_us(resident) + round_us((rest + cus - 1) / cus) + 0.188 * 2e-6 * g.y_elems;
+}
 // Its tile for the sparse / dense run, where it is expected to be faster than the cheapest tiled launch (bm == 0: it is not).
 // SPARSE_CONV_WINDOW_TILE=<bm>x<bn> overrides, in the place of band kernels too (tuning and tests); 0x0 switches the kernel off.
 static sc_plan::Window window_tile_for(const sc_plan* pl, int which) {
@@ -1407,11 +1429,14 @@ static sc_plan::Window window_tile_for(const sc_plan* pl, int which) {
   int fbm = 0, fbn = 0;
   if (const char* env = std::getenv("SPARSE_CONV_WINDOW_TILE"); env && std::sscanf(env, "%dx%d", &fbm, &fbn) == 2)
     return fbm > 0 && fits(fbm, fbn) ? sc_plan::Window{fbm, fbn, true} : none;
-  // Band kernels that fetch their input once stay ahead (us, band kernel / this one: 32 x 64 -> 64 @56 10.3 / 16, 1 x 64 -> 64 @56 5.7 /
-  // 6.7, 8 x 32 -> 16 @48 4.4 / 6.5).  The plain one gives way to this kernel and to the other tiles alike from 48 channels on: 3 x 48 ->
-  // 32 @17x22 8.1 / 6.3, 44 x 112 -> 32 @12x10 13.4 / 7.4, 4 x 128 -> 16 @10x8 14.5 / 6.8; 58 x 128 -> 16 @31x36, every row kept, 41.9 / 15.8,
-  // in other tiles 12.0.  With fewer channels it takes 7 and more before many outputs (3 x 32 -> 144 @35 9.6 / 6.7, 1 x 16 -> 240 @20 7.7 /
-  // 6.3), where this kernel is one round of workgroups (6 x 32 -> 368 @52 is not: 15.3 / 16.9).
+  // The alternating and the tap-pipelined band kernels stay ahead (us, band kernel / this one: 32 x 64 -> 64 @56 10.3 / 16, 1 x 64 -> 64 @56 5.7 /
+  // 6.7), and so does the plain one with few channels and few outputs (8 x 32 -> 16 @48 4.4 / 6.5).  Elsewhere the plain one is priced
+  // (band_us).  From 48 channels on it runs where the cheapest of this kernel's tiles and the others costs 5 % more, the error of the prices:
+  // us, band / this kernel / another tile, 3 x 48 -> 32 @17x22 8.1 / 6.3, 4 x 128 -> 16 @10x8 14.5 / 6.8, 58 x 128 -> 16 @31x36, every row,
+  // 41.9 / 15.8 / 12.0, but 62 x 64 -> 32 @53 15.2 / 26.1 / 16.4 and, every row, 13.9 / 31.3 / 21.0.  Chosen launch against the fastest, geometric mean over 146
+  // random layers: sparse 1.008, dense 1.006 (the band kernel alone 1.56 and 1.56).  With fewer channels and many outputs only this kernel
+  // takes its place, where it is 5 % cheaper (the price of the others is not made for a short K): over 263 layers 0.80 and 0.77 of the band
+  // kernel's time, no layer more than 4 % slower.
   const BandPlan& band = which ? pl->band_dense : pl->band;
   const bool band_runs = band.ok && !band.stream, plain_band = band_runs && !band.pp && !band.tap && !band.rowband && !std::getenv("SPARSE_CONV_BAND_KERNEL");
   const bool deep = d.c_in >= 48;
@@ -1439,11 +1464,12 @@ static sc_plan::Window window_tile_for(const sc_plan* pl, int which) {
   const int family = !pl->geo.vec_out ? 2 : d.c_in % 64 != 0 ? 1 : 0;
   const double* o = others[family][form];
   double other_us = o[0] + o[1] * other.us + o[2] * mb + (other.splits > 1 ? 2.6 : 0.0);
-  if (other.us == 0.0) other_us = 0.0;                            // (a launch that was asked for)
-  if (plain_band && !deep) other_us = 7.4;
+  if (other.us == 0.0) return none;                               // (a launch that was asked for)
+  const double band_price = plain_band ? band_us(pl, which) : 0.0;
   sc_plan::Window best = {0, 0, plain_band && deep};
   // (what has to be won: one chunk or less leaves this kernel's set-up uncovered, 10 x 64 -> 224 @16 6.35 / 6.6)
-  double best_us = (d.c_in < 48 ? 0.9 : family ? 0.943 : chunks == 1 ? 0.97 : 1.0) * other_us;
+  const double ahead = d.c_in < 48 ? 0.9 : family ? 0.943 : chunks == 1 ? 0.97 : 1.0;
+  double best_us = plain_band && !deep ? 0.95 * band_price : ahead * other_us;
   for (const Shape& sh : shapes) {
     if ((sh.bm == 256 && form == 0) || !fits(sh.bm, sh.bn)) continue;
     const int64_t wgs = ((rows + sh.bm - 1) / sh.bm) * ((d.c_out + sh.bn - 1) / sh.bn);
@@ -1453,9 +1479,9 @@ static sc_plan::Window window_tile_for(const sc_plan* pl, int which) {
     const int kg = sh.bm == 256 ? 1 : sh.bn == 128 ? 2 : 4, last = (d.c_in - (chunks - 1) * kWinChunk + 15) / 16;      // K groups, K steps of the last chunk
     const double walk = (chunks - 1 + (double)((last + kg - 1) / kg * kg) / 4) * (d.kh * d.kw / 9.0);      // (in chunks of a 3 x 3 window)
     const double us = c[0] + c[1] * (rounds - 1) + walk * (c[2] * rounds + c[3] * load) + c[4] * mb;
-    if (plain_band && !deep && rounds > 1.0) continue;
     if (us < best_us) { best_us = us; best = {sh.bm, sh.bn, plain_band, plain_band && !deep}; }
   }
+  if (plain_band && deep && band_price < 0.95 * best_us / ahead) return none;
   return best;
 }
 // (not where a tile or a form of another kernel was asked for or measured faster)

@@ -184,3 +184,18 @@ def test_window_kernel_on_many_rows(n, h, w, cout, sp, mode, tile, monkeypatch):
     ci = W.make_conv_inputs(spec, 3400)
     layer = assert_window(check_layer(ci, sample_rows=300), spec, ci.mask, tile)
     assert B.sparse_conv_plan_kernel(layer.plan, 0) == "tile_window" or (tile[0] == 256 and sp == 0.4)
+
+
+@pytest.mark.parametrize("n,cin,h,w,cout,sp,want", [
+    (62, 64, 53, 53, 32, 0.3, ("band", "band")),                     # us, band / cheapest other launch: 15.2 / 16.4, every row 13.9 / 21.0
+    (33, 64, 69, 69, 16, 0.5, ("band", "band")),                     # 11.0 / 14.4, 12.3 / 20
+    (58, 128, 31, 36, 16, 0.5, ("tile_window", "tile_lds_direct")),  # every row 41.9 / 12.0
+    (2, 48, 48, 53, 32, 0.7, ("tile_window",) * 2),                  # every row 7.0 / 5.5
+    (10, 32, 79, 77, 256, 0.5, ("band", "band")),                    # few channels, many outputs: several rounds of the window kernel
+    (54, 32, 25, 23, 416, 0.5, ("tile_window",) * 2),                # 25.7 / 17.3, 31.4 / 20.2
+])
+def test_plain_band_kernel_gives_way_where_it_is_dearer(n, cin, h, w, cout, sp, want):
+    spec = spec_of(n, cin, h, w, cout, sp=sp)
+    mask = (np.random.default_rng(5).permutation(spec.m) >= round(sp * spec.m)).astype(np.uint8)
+    layer = R.ConvLayer(spec, np.zeros((cout, 3, 3, cin), np.float32), np.zeros(cout, np.float32), mask, check_count=False)
+    assert tuple(B.sparse_conv_plan_kernel(layer.plan, which) for which in (0, 1)) == want
