@@ -176,12 +176,13 @@ def plan_shortcut_fusions(ops, layers: Dict[str, "ConvLayer"], row_formats: Opti
                 continue
             plan = layers[conv.spec.name].plan
             plain = B.sparse_conv_plan_kernel(plan, 1 if dense else 0)
-            # the fused launch must not be a step down from the plain one: the same band kernel, or a tiled
-            # kernel where the plain run takes one too (runs with compact operands always do)
+            # the fused launch must not be a step down from the plain one: the same band or window kernel, or a tiled
+            # kernel where the plain run takes one too (runs with compact operands always do).  With few input channels
+            # the window kernel stands in for a band kernel in plain runs alone, and those two never had the sum ride along.
             if not fmt.get(mine, False):
                 if plain in ("band", "band_stream", "band_row_segments", "tile_row_panel"):
                     continue
-                if plain in ("band_alternating", "band_tap") and B.sparse_conv_plan_fused_kernel(plan, 1 if dense else 0) != plain:
+                if plain in ("band_alternating", "band_tap", "tile_window") and B.sparse_conv_plan_fused_kernel(plan, 1 if dense else 0) != plain:
                     continue
             if best is None or position[mine] > position[best[0]]:
                 best = (mine, other)

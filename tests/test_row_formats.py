@@ -58,3 +58,17 @@ def test_dense_shortcut_operand_makes_the_whole_sum_dense(monkeypatch):
     fmt = R.plan_row_formats(ops, layers)
     assert not fmt["b1_p"] and not fmt["b2_out"] and not fmt["b2_p"]
     assert fmt["b2_d"] and fmt["b2_e"] and fmt["b4_out"]
+
+
+def test_sums_ride_along_only_where_the_fused_launch_is_no_step_down(monkeypatch):
+    """A sum stays a launch of its own behind a kernel that has no fused form, and where the fused launch would take another kernel
+    than the plain one took."""
+    spec = lambda name: SimpleNamespace(name=name, groups=1)
+    ops = [W.NetOp("conv", "a", "input", spec=spec("a")), W.NetOp("conv", "b", "a", spec=spec("b")), W.NetOp("add_relu", "sum", "b", "a")]
+    layers = {name: SimpleNamespace(plan=name) for name in ("a", "b")}
+    for plain, fused, rides in (("band", "tile_lds_direct", False), ("band_tap", "band_tap", True), ("band_tap", "tile_window", False),
+                                ("tile_window", "tile_window", True), ("tile_window", "tile_lds_direct", False),
+                                ("tile_window", "tile_masked_store", False), ("tile_masked_store", "tile_lds_direct", True)):
+        monkeypatch.setattr(R.B, "sparse_conv_plan_kernel", lambda plan, which: plain)
+        monkeypatch.setattr(R.B, "sparse_conv_plan_fused_kernel", lambda plan, which: fused)
+        assert R.plan_shortcut_fusions(ops, layers) == ({"sum": ("b", "a", True)} if rides else {}), (plain, fused)
