@@ -230,7 +230,7 @@ const char* sparse_conv_plan_fused_kernel(const sc_plan* plan, int32_t which);
 sc_status sparse_conv_plan_set_tiles(sc_plan* plan, int32_t which, int32_t tile_m, int32_t tile_n);
 
 /*
- * Measured kernel choice.  sparse_conv_plan prices its candidate launches (tile shape, K splits, band or tiled
+ * Measured kernel choice.  sparse_conv_plan prices its candidate launches (tile shape, K splits, band, window or tiled
  * kernel, and for small layers the variant that contracts every row and lets the mask decide at the store) with a
  * model of the device; this call times the serious candidates of the sparse and of the dense run on the caller's
  * real buffers and keeps the fastest of each.  x_dev, bias_dev, y_dev as for sparse_conv_run; y_dev is overwritten

@@ -1125,9 +1125,9 @@ struct sc_plan {
   int stage_tuned;                 // sparse_conv_plan_tune measured that kernel fastest (1) or slower than another (-1); 0: not timed
   bool slab_ok;                    // the layer's geometry admits it
   int slab;                        // 0 = automatic, 1 = never, 2 = wherever it applies, 128 / 256 = with tiles of that many rows
-  struct Window { int bm, bn; bool before_bands, plain_only = false; };
+  struct Window { int bm, bn; bool before_bands, plain_only = false, asked = false; };
   Window window[2];                // tile of the window kernel for the sparse / dense run (bm == 0: another kernel), whether a band kernel gives way,
-                                   // and whether only plain runs take it (the others never went to that band kernel)
+                                   // whether only plain runs take it (the others never went to that band kernel); asked for by the environment
   int slab_span[2][3];             // [sparse, dense run][64-row, 128-row, 256-row tiles]: virtual rows of the widest tile's slab
   Slab slab_auto[2];               // what an automatic launch of the sparse / dense run takes (bm == 0: another kernel)
 };
@@ -1414,21 +1414,23 @@ static double band_us(const sc_plan* pl, int which) {
   const int64_t full = (wgs - 1) / ((int64_t)cus * resident), rest = wgs - full * cus * resident;
   return full * round_us(resident) + round_us((rest + cus - 1) / cus) + 0.188 * 2e-6 * g.y_elems;
 }
+// may it run a tile?  (its slabs fit)
+static bool window_fits(const sc_plan* pl, int which, int bm, int bn) {
+  const int sb = pl->geo.window && window_kernel(kBF16, pl->desc.kh, bm, bn) ? window_slab_bytes(pl, which, bm) : 0;
+  return sb > 0 && window_lds_bytes(bm, bn, sb, (pl->desc.c_in + kWinChunk - 1) / kWinChunk) <= kLdsLimit;
+}
+static constexpr int kWindowTiles[][2] = {{256, 128}, {128, 128}, {128, 64}, {64, 128}, {64, 64}};
 // Its tile for the sparse / dense run, where it is expected to be faster than the cheapest tiled launch (bm == 0: it is not).
 // SPARSE_CONV_WINDOW_TILE=<bm>x<bn> overrides, in the place of band kernels too (tuning and tests); 0x0 switches the kernel off.
 static sc_plan::Window window_tile_for(const sc_plan* pl, int which) {
   const sc_plan::Window none = {0, 0, false};
   const sc_conv_desc& d = pl->desc;
   const int64_t rows = which ? pl->geo.m : pl->kept;
-  if (!pl->geo.window || rows == 0 || !window_kernel(kBF16, d.kh, 64, 64)) return none;
+  if (!pl->geo.window || rows == 0) return none;
   const int chunks = (d.c_in + kWinChunk - 1) / kWinChunk;
-  auto fits = [&](int bm, int bn) {
-    const int sb = window_kernel(kBF16, d.kh, bm, bn) ? window_slab_bytes(pl, which, bm) : 0;
-    return sb > 0 && window_lds_bytes(bm, bn, sb, chunks) <= kLdsLimit;
-  };
   int fbm = 0, fbn = 0;
   if (const char* env = std::getenv("SPARSE_CONV_WINDOW_TILE"); env && std::sscanf(env, "%dx%d", &fbm, &fbn) == 2)
-    return fbm > 0 && fits(fbm, fbn) ? sc_plan::Window{fbm, fbn, true} : none;
+    return fbm > 0 && window_fits(pl, which, fbm, fbn) ? sc_plan::Window{fbm, fbn, true, false, true} : sc_plan::Window{0, 0, false, false, true};
   // The alternating and the tap-pipelined band kernels stay ahead (us, band kernel / this one: 32 x 64 -> 64 @56 10.3 / 16, 1 x 64 -> 64 @56 5.7 /
   // 6.7), and so does the plain one with few channels and few outputs (8 x 32 -> 16 @48 4.4 / 6.5).  Elsewhere the plain one is priced
   // (band_us).  From 48 channels on it runs where the cheapest of this kernel's tiles and the others costs 5 % more, the error of the prices:
@@ -1471,7 +1473,7 @@ static sc_plan::Window window_tile_for(const sc_plan* pl, int which) {
   const double ahead = d.c_in < 48 ? 0.9 : family ? 0.943 : chunks == 1 ? 0.97 : 1.0;
   double best_us = plain_band && !deep ? 0.95 * band_price : ahead * other_us;
   for (const Shape& sh : shapes) {
-    if ((sh.bm == 256 && form == 0) || !fits(sh.bm, sh.bn)) continue;
+    if ((sh.bm == 256 && form == 0) || !window_fits(pl, which, sh.bm, sh.bn)) continue;
     const int64_t wgs = ((rows + sh.bm - 1) / sh.bm) * ((d.c_out + sh.bn - 1) / sh.bn);
     const double load = (double)wgs / cus, rounds = (double)((wgs + cus - 1) / cus);
     if (rounds > 1.0 && sh.bm == 64) continue;      // (set-up and sums again each round: 36 x 128 -> 432 @26x24 in three 24.0 / 30.0)
@@ -2610,6 +2612,8 @@ sc_status sparse_conv_plan_tune(sc_plan* plan, const void* x_dev, const float* b
     if (plan->forced[which] != -1 || rows == 0) continue;
     plan->pick[which] = model_pick(plan, which, rows);
     plan->prefer_tiled[which] = false;
+    plan->slab_auto[which] = sc_plan::Slab{0, 1};
+    plan->window[which] = window_tile_for(plan, which);
     if (time_us(dense, 100, 4) < 0.0) { result = SC_ERR_HIP; break; }     // clocks up before anything is compared
     sc_plan::Pick best_pick = plan->pick[which];
     bool best_tiled = false;
@@ -2624,14 +2628,30 @@ sc_status sparse_conv_plan_tune(sc_plan* plan, const void* x_dev, const float* b
       }
       continue;
     }
+    // the band kernel, where it had given way, and every tile of the window kernel
+    const BandPlan& bsel = dense ? plan->band_dense : plan->band;
+    const bool band_applies = bsel.ok && !bsel.stream;
+    if (plan->geo.window && !plan->window[which].asked && window_is_free(plan, which, rows)) {
+      const sc_plan::Window priced = plan->window[which];
+      sc_plan::Window best_window = priced;
+      auto try_window = [&](sc_plan::Window w) {
+        plan->window[which] = w;
+        const double us = time_us(dense, 40, 3);
+        if (us > 0.0 && us < 0.985 * best_us) { best_us = us; best_window = w; }
+      };
+      if (band_applies && priced.before_bands) try_window({0, 0, false});
+      for (const auto& tile : kWindowTiles)
+        if ((tile[0] != priced.bm || tile[1] != priced.bn) && window_fits(plan, which, tile[0], tile[1]))
+          try_window({tile[0], tile[1], band_applies, band_applies && !bsel.pp && !bsel.tap && plan->desc.c_in < 48});
+      plan->window[which] = best_window;
+    }
     best_tiled = try_tiled(which, &best_pick, &best_us);
     plan->pick[which] = best_pick;
     plan->prefer_tiled[which] = best_tiled;
     // the slab form of the tiled kernel (deep 3x3 layers): both tile heights, the K splits around one workgroup per
     // compute unit; it replaces the choice so far only where it measures faster
-    plan->slab_auto[which] = sc_plan::Slab{0, 1};
-    const BandPlan& bsel = dense ? plan->band_dense : plan->band;
-    if (plan->slab_ok && plan->slab == 0 && plan->split_k == 0 && !(bsel.ok && !bsel.stream && !best_tiled)) {
+    if (plan->slab_ok && plan->slab == 0 && plan->split_k == 0 && !(band_applies && !best_tiled && !bands_give_way(plan, which, rows))) {
+      plan->prefer_tiled[which] = best_tiled || band_applies;      // (or the band kernel would run in its place)
       sc_plan::Slab best_slab = {0, 1};
       for (int bm = 256; bm >= 128; bm >>= 1) {
         if (!slab_buffer_bytes(plan->desc, bm, plan->slab_span[which][span_of(bm)])) continue;
@@ -2650,6 +2670,7 @@ sc_status sparse_conv_plan_tune(sc_plan* plan, const void* x_dev, const float* b
         }
       }
       plan->slab_auto[which] = best_slab;
+      if (!best_slab.bm) plan->prefer_tiled[which] = best_tiled;
     }
   }
   // A sparse run must not lose to the dense run of its own plan: where it still does, try the dense run's tile with

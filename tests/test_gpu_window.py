@@ -10,7 +10,7 @@ import workloads as W
 from oracle import oracle
 from paper_2309_06626_amd import binding as B
 from paper_2309_06626_amd import runtime as R
-from parity import check_layer, row_mask
+from parity import TOL, assert_close, check_layer, row_mask, rows_view
 from test_gpu_compact import check_compact_output
 from test_gpu_parity import spec_of
 from test_gpu_residual import check as check_residual
@@ -199,3 +199,33 @@ def test_plain_band_kernel_gives_way_where_it_is_dearer(n, cin, h, w, cout, sp, 
     mask = (np.random.default_rng(5).permutation(spec.m) >= round(sp * spec.m)).astype(np.uint8)
     layer = R.ConvLayer(spec, np.zeros((cout, 3, 3, cin), np.float32), np.zeros(cout, np.float32), mask, check_count=False)
     assert tuple(B.sparse_conv_plan_kernel(layer.plan, which) for which in (0, 1)) == want
+
+
+@pytest.mark.parametrize("case,before,after", [
+    (dict(n=17, cin=32, h=16, w=17, cout=16, k=5, p=2, sp=0.5), "band", "tile_window"),      # every row 10.3 us / 5.7
+    (dict(n=62, cin=64, h=53, w=53, cout=32, sp=0.3), "band", "band"),                       # 13.9 / 31, in other tiles 21
+    (dict(n=4, cin=64, h=56, w=56, cout=64, sp=0.5), "band_tap", "band_tap"),
+])
+def test_tuning_times_the_window_kernel_and_the_band_kernels(case, before, after):
+    spec = spec_of(dtype="bf16", **case)
+    ci = W.make_conv_inputs(spec, 3500)
+    layer = R.ConvLayer(spec, ci.w, ci.bias, ci.mask)
+    x, y = R.to_device(ci.x, spec.dtype), layer.new_output()
+    assert B.sparse_conv_plan_kernel(layer.plan, 1) == before
+    B.sparse_conv_plan_tune(layer.plan, x, layer.bias, y)
+    assert B.sparse_conv_plan_kernel(layer.plan, 1) == after
+    rows = np.unique(np.random.default_rng(5).integers(0, spec.m, 300)).astype(np.int64)
+    ref, absum = oracle.masked_conv2d_rows(spec, ci.x, ci.w, ci.bias, np.ones_like(ci.mask), rows, want_absum=True)
+    assert_close(rows_view(spec, R.to_host_f32(layer.dense(x)))[rows], ref, absum, TOL["bf16"], "tuned")
+    B.sparse_conv_plan_set_mask(layer.plan, torch.from_numpy(ci.mask).cuda())
+    assert B.sparse_conv_plan_kernel(layer.plan, 1) == after            # (a new mask leaves the dense run's choice)
+
+
+def test_tuning_leaves_a_window_tile_that_was_asked_for(monkeypatch):
+    for tile in ("64x64", "0x0"):
+        monkeypatch.setenv("SPARSE_CONV_WINDOW_TILE", tile)
+        spec = spec_of(17, 32, 16, 17, 16, k=5, p=2)
+        ci = W.make_conv_inputs(spec, 3501)
+        layer = R.ConvLayer(spec, ci.w, ci.bias, ci.mask)
+        B.sparse_conv_plan_tune(layer.plan, R.to_device(ci.x, spec.dtype), layer.bias, layer.new_output())
+        assert all((B.sparse_conv_plan_kernel(layer.plan, which) == "tile_window") == (tile == "64x64") for which in (0, 1))
