@@ -11,6 +11,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
+#include <numeric>
 #include <new>
 
 #include "band_kernel.hpp"
@@ -1350,13 +1351,19 @@ static int slab_buffer_bytes(const sc_conv_desc& d, int bm, int span) {
   const int64_t bytes = ((int64_t)span * (d.w + 2 * d.pad_w) * kSlabPixelBytes + round - 1) / round * round;
   return span > 0 && bytes <= kSlabMostBytes ? (int)bytes : 0;
 }
-// dense run: tiles are runs of bm consecutive pixels
+// dense run: tiles are runs of bm consecutive pixels.  Where they begin in an image repeats after one period, and no tile spans more than one
+// that begins in the last column of some row would (us a plan of 64 x 64 -> 64 @56, all tiles / until one is as wide as that: 130 / 85).
 static int slab_dense_span(const sc_conv_desc& d, const Geometry& g, int bm) {
-  const int hp = d.h + 2 * d.pad_h, ho_wo = g.ho * g.wo;
-  auto vrow = [&](int64_t r) { return (int)(r / ho_wo) * hp + (int)(r % ho_wo) / g.wo; };
-  int span = 0;
-  for (int64_t m0 = 0; m0 < g.m; m0 += bm) span = std::max(span, vrow(std::min<int64_t>(g.m, m0 + bm) - 1) + d.kh - vrow(m0));
-  return span;
+  const uint32_t hp = d.h + 2 * d.pad_h, ho_wo = g.ho * g.wo, wo = g.wo, m = (uint32_t)g.m;
+  auto vrow = [&](uint32_t r) { return r / ho_wo * hp + r % ho_wo / wo; };
+  uint32_t most = 0, span = 0;
+  for (uint32_t q = wo - 1; q < ho_wo; q += wo) most = std::max(most, vrow(q + bm - 1) + d.kh - vrow(q));
+  const uint32_t tiles = (m - 1) / bm + 1, period = ho_wo / std::gcd(ho_wo, (uint32_t)bm);
+  for (uint32_t i = 0; i < std::min(tiles, period) && span < most; ++i) {
+    const uint32_t m0 = i * bm, last = m - m0 > (uint32_t)bm ? m0 + bm - 1 : m - 1;
+    span = std::max(span, vrow(last) + d.kh - vrow(m0));
+  }
+  return (int)span;
 }
 // K splits (by chunks of input channels) of a slab launch with tiles of bm rows: one workgroup per compute unit
 static int slab_splits(const sc_plan* pl, int bm, int64_t rows) {
@@ -1391,6 +1398,12 @@ static int window_slab_bytes(const sc_plan* pl, int which, int bm) {
   const int64_t px = (int64_t)span * (d.w + 2 * d.pad_w);
   if (span <= 0 || px > kWinMostPixels) return 0;
   return (int)((px * kWinPitch + 8191) / 8192 * 8192);
+}
+// Does the band kernel of a run stay, whatever the mask?  The alternating and the tap-pipelined one are ahead of the window kernel (us, band
+// kernel / window kernel: 32 x 64 -> 64 @56 10.3 / 16, 1 x 64 -> 64 @56 5.7 / 6.7), and so is the plain one with few channels and few
+// outputs (8 x 32 -> 16 @48 4.4 / 6.5).
+static bool band_stays(const sc_conv_desc& d, const BandPlan& band) {
+  return band.ok && !band.stream && (band.pp || band.tap || band.rowband || (d.c_in < 48 && d.c_out < 80) || std::getenv("SPARSE_CONV_BAND_KERNEL"));
 }
 // Predicted microseconds of a run by the plain band kernel (one band a workgroup, a 16-bit layer).  A round of workgroups costs its fixed
 // part, the slabs of filters and input of those that share a compute unit, the rows they store, and the walk of the busiest wavefront: blocks
@@ -1431,18 +1444,15 @@ static sc_plan::Window window_tile_for(const sc_plan* pl, int which) {
   int fbm = 0, fbn = 0;
   if (const char* env = std::getenv("SPARSE_CONV_WINDOW_TILE"); env && std::sscanf(env, "%dx%d", &fbm, &fbn) == 2)
     return fbm > 0 && window_fits(pl, which, fbm, fbn) ? sc_plan::Window{fbm, fbn, true, false, true} : sc_plan::Window{0, 0, false, false, true};
-  // The alternating and the tap-pipelined band kernels stay ahead (us, band kernel / this one: 32 x 64 -> 64 @56 10.3 / 16, 1 x 64 -> 64 @56 5.7 /
-  // 6.7), and so does the plain one with few channels and few outputs (8 x 32 -> 16 @48 4.4 / 6.5).  Elsewhere the plain one is priced
-  // (band_us).  From 48 channels on it runs where the cheapest of this kernel's tiles and the others costs 5 % more, the error of the prices:
+  // A plain band kernel that does not stay is priced (band_us).  From 48 channels on it runs where the cheapest of this kernel's tiles and the others costs 5 % more, the error of the prices:
   // us, band / this kernel / another tile, 3 x 48 -> 32 @17x22 8.1 / 6.3, 4 x 128 -> 16 @10x8 14.5 / 6.8, 58 x 128 -> 16 @31x36, every row,
   // 41.9 / 15.8 / 12.0, but 62 x 64 -> 32 @53 15.2 / 26.1 / 16.4 and, every row, 13.9 / 31.3 / 21.0.  Chosen launch against the fastest, geometric mean over 146
   // random layers: sparse 1.008, dense 1.006 (the band kernel alone 1.56 and 1.56).  With fewer channels and many outputs only this kernel
   // takes its place, where it is 5 % cheaper (the price of the others is not made for a short K): over 263 layers 0.80 and 0.77 of the band
   // kernel's time, no layer more than 4 % slower.
   const BandPlan& band = which ? pl->band_dense : pl->band;
-  const bool band_runs = band.ok && !band.stream, plain_band = band_runs && !band.pp && !band.tap && !band.rowband && !std::getenv("SPARSE_CONV_BAND_KERNEL");
-  const bool deep = d.c_in >= 48;
-  if (band_runs && !(plain_band && (deep || d.c_out >= 80))) return none;
+  if (band_stays(d, band)) return none;
+  const bool plain_band = band.ok && !band.stream, deep = d.c_in >= 48;
   // Priced like the other tiled launches (us, MI355X): a launch and its first round of workgroups, every further round, a chunk of 64
   // channels in a round, what a chunk takes longer the more compute units it keeps busy, and a megabyte of y.  Fitted to the runs of 170
   // layers (1 to 8 chunks, 16 to 512 outputs, maps of 7 to 80): standard deviation 4 to 8 %.  The others' price leaves out y and the
@@ -2145,7 +2155,8 @@ static sc_status build_row_tables(const sc_conv_desc& d, const Geometry& g, unsi
   int32_t* rows = reinterpret_cast<int32_t*>(ws + g.off_rows);
   int32_t* kept_dev = reinterpret_cast<int32_t*>(ws + g.off_kept);
   int32_t host_vals[5] = {-1, 0, 0, 0, 0};   // kept count, most kept rows in one band, widest slab of a 64-row / 128-row / 256-row tile
-  const bool slab = slab_geometry_ok(d, g) || g.window;
+  // (where a band kernel stays, tuning asks for the spans itself: two of 24 us of a refresh of a small map, of 58 past 2^17 rows nine)
+  const bool slab = slab_geometry_ok(d, g) || (g.window && (!band_stays(d, bp) || std::getenv("SPARSE_CONV_WINDOW_TILE")));
   // One launch up to 2^17 rows (where a run of rows cut in two leaves both halves a pixel); beyond that every workgroup's
   // count of the rows in front of it costs more than a pass of its own.  Measured per refresh on a
   // 56 x 56 map of one image, us of GPU time: 13 in five launches and a copy, 5 in one.
@@ -2632,6 +2643,17 @@ sc_status sparse_conv_plan_tune(sc_plan* plan, const void* x_dev, const float* b
     const BandPlan& bsel = dense ? plan->band_dense : plan->band;
     const bool band_applies = bsel.ok && !bsel.stream;
     if (plan->geo.window && !plan->window[which].asked && window_is_free(plan, which, rows)) {
+      if (which == 0 && plan->slab_span[0][0] == 0) {      // (the row tables left the spans out)
+        const Geometry& g = plan->geo;
+        const sc_conv_desc& d = plan->desc;
+        int32_t* kept_dev = reinterpret_cast<int32_t*>(plan->ws + g.off_kept);
+        int32_t span[3] = {0, 0, 0};
+        hipLaunchKernelGGL(slab_span_kernel, dim3((unsigned)((g.m + 63) / 64 + 255) / 256), dim3(256), 0, ts,
+                           reinterpret_cast<const int32_t*>(plan->ws + g.off_rows), kept_dev, g.ho * g.wo, g.wo, d.h + 2 * d.pad_h, d.kh, kept_dev + 2);
+        if (hip_failed(hipGetLastError()) || hip_failed(hipMemcpyAsync(span, kept_dev + 2, sizeof(span), hipMemcpyDeviceToHost, ts)) ||
+            hip_failed(hipStreamSynchronize(ts))) { result = SC_ERR_HIP; break; }
+        for (int b = 0; b < 3; ++b) plan->slab_span[0][b] = span[b];
+      }
       const sc_plan::Window priced = plan->window[which];
       sc_plan::Window best_window = priced;
       auto try_window = [&](sc_plan::Window w) {
