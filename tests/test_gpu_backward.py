@@ -226,3 +226,25 @@ def test_float_training_steps_follow_the_oracles_steps():
     assert np.abs(w_dev.cpu().numpy() - w_ref).max() <= 1e-5 * scale
     assert np.abs(b_dev.cpu().numpy() - b_ref).max() <= 1e-5 * max(np.abs(b_ref).max(), 1.0)
     assert np.abs(w_ref - ci.w).max() > 1e-4 * scale          # the steps really moved the weights
+
+
+@pytest.mark.parametrize("window", ["64x64", "0x0"])
+@pytest.mark.parametrize("dtype,shape", [("bf16", (2, 128, 9, 136)), ("f16", (3, 64, 12, 64)), ("bf16", (2, 24, 10, 80))])
+def test_refreshed_filters_reach_the_kernel_of_the_input_gradient(dtype, shape, window, monkeypatch):
+    """A refresh packs the one copy of the filters that the plan's run reads, with the window kernel and without it."""
+    monkeypatch.setenv("SPARSE_CONV_WINDOW_TILE", window)
+    n, c_in, hw, c_out = shape
+    spec = spec_of(n, c_in, hw, c_out, dtype=dtype)
+    one, two = W.make_conv_inputs(spec, 70), W.make_conv_inputs(spec, 71)
+    layer = R.ConvLayer(spec, one.w, one.bias, one.mask)
+    y = R.to_device(oracle.round_storage(oracle.masked_conv2d(spec, one.x, one.w, one.bias, one.mask), dtype), dtype)
+    dy = R.to_device(W.quantize(np.random.default_rng(72).standard_normal(spec.y_shape()).astype(np.float32), dtype), dtype)
+    w2 = R.to_device(two.w, dtype)
+    dx = [torch.full(spec.x_shape(), float("nan"), dtype=B.TORCH_DTYPE[dtype], device="cuda:0") for _ in range(2)]
+    refreshed = B.sparse_conv_backward_plan(layer.plan, layer.w)
+    B.sparse_conv_backward_set_filters(refreshed, w2)
+    for out, plan in zip(dx, (refreshed, B.sparse_conv_backward_plan(layer.plan, w2))):
+        B.sparse_conv_backward_run(plan, None, y, dy, out, None, None)
+    assert np.array_equal(R.bits_of(dx[0]), R.bits_of(dx[1]))
+    ref, _, _, dxa, _ = oracle.masked_conv2d_backward(spec, one.x, two.w, R.to_host_f32(y), R.to_host_f32(dy), one.mask, want_abs=True)
+    assert_close(R.to_host_f32(dx[0]), ref, dxa + 1e-30, TOL[dtype], "dx")
