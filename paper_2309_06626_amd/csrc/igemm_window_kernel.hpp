@@ -10,13 +10,15 @@
 //   * filters, packed in fragment order (repack_kernel), nine fragments a wavefront (five of 25) on their way at any time;
 //   * wavefronts stand side by side over the channels, so that no two load the same filters, and share K where that leaves some over:
 //     a K group takes every KG-th step of 16 channels, and the groups' sums are added through LDS in order at the end.
-// A pixel takes nine 16-byte groups in LDS, of which eight hold channels: reads of sixteen pixels side by side touch every bank once,
-// and which rows stand side by side is chosen for that (below).  The loop is then within a fifth of its products alone.
+// A pixel takes nine 16-byte groups in LDS, of which eight hold channels: reads of sixteen consecutive pixels touch every bank once.  The
+// kept rows of a mask are not consecutive, and which ones stand side by side is chosen for that (below); a fifth of the rows of a 64-row tile
+// finds every set of its residue full and takes a hole all the same, and 44 % of the LDS cycles are conflict cycles (64 x 512 -> 512 @7).
 //
-// Measured at s = 0.5 in bf16, igemm_buf_kernel / this one, us: 64 x 512 -> 512 @7 19.5 / 14.5 (dense 25.5 / 18.5), 64 x 256 -> 256 @14
-// 16.4 / 13.8 (20.2 / 18.4), 16 x 256 -> 256 @14 13.5 / 9.3, 64 x 128 -> 128 @28 15.6 / 14.7 (21.6 / 19.2), 1 x 128 -> 128 @28 10.2 / 7.3,
-// 2 x 512 -> 48 @8x6 21.5 / 10.9.  Of the 12 us a workgroup of the second takes, 1.8 pass before the first row number is known, 1.5 until
-// the first slab has landed, 0.6 go into the groups' sums and as much into the stores.
+// Measured at s = 0.5 in bf16, launches behind each other on one card, the tiled kernels / this one, us: 64 x 512 -> 512 @7 20.7 / 15.3 (dense
+// 28.6 / 20.6), 64 x 256 -> 256 @14 17.6 / 15.2 (21.8 / 20.1), 16 x 256 -> 256 @14 12.7 / 9.6 (13.0 / 8.7), 64 x 128 -> 128 @28 15.8 / 14.5
+// (22.2 / 19.1), 1 x 128 -> 128 @28 9.6 / 7.1 (8.9 / 6.4), 2 x 512 -> 48 @8x6 21.3 / 11.5 (21.2 / 11.1), 5 x 5, 1 x 360 -> 104 @19x24 73 / 16
+// (73 / 15).  Of the 12 us a workgroup of the first takes, 1.8 pass before the first row number is known, 1.5 until the first slab has
+// landed, 0.6 go into the groups' sums and as much into the stores.
 // Tried and left out: reads of the next tap ahead of all products of this one (12.7 -> 13.0 of a loop), the zeros of dropped rows between
 // the products of the first pass (their acknowledgements hold up the filters' waits: 7.4 -> 8.0).
 //
@@ -374,7 +376,7 @@ __global__ __launch_bounds__(512) void igemm_window_kernel(const ConvParams p) {
 
 template <int DT, int BM, int BN, int KS>
 hipError_t igemm_window_launch(const ConvParams& p, hipStream_t stream) {
-  // (p.splits: at most one workgroup a compute unit, so that none waits beside an idle one: 64 x 512 -> 512 @7 15.0 / 13.9)
+  // (p.splits: at most one workgroup a compute unit, so that none waits beside an idle one: 64 x 512 -> 512 @7 takes 7 % less)
   size_t lds = win_lds_bytes<BM, BN>(p.slab_bytes, (p.c_in + kWinChunk - 1) / kWinChunk);
   if (p.splits == 1 && lds < 81 * 1024) lds = 81 * 1024;
   auto kern = igemm_window_kernel<DT, BM, BN, KS>;

@@ -1444,12 +1444,13 @@ static sc_plan::Window window_tile_for(const sc_plan* pl, int which) {
   int fbm = 0, fbn = 0;
   if (const char* env = std::getenv("SPARSE_CONV_WINDOW_TILE"); env && std::sscanf(env, "%dx%d", &fbm, &fbn) == 2)
     return fbm > 0 && window_fits(pl, which, fbm, fbn) ? sc_plan::Window{fbm, fbn, true, false, true} : sc_plan::Window{0, 0, false, false, true};
-  // A plain band kernel that does not stay is priced (band_us).  From 48 channels on it runs where the cheapest of this kernel's tiles and the others costs 5 % more, the error of the prices:
-  // us, band / this kernel / another tile, 3 x 48 -> 32 @17x22 8.1 / 6.3, 4 x 128 -> 16 @10x8 14.5 / 6.8, 58 x 128 -> 16 @31x36, every row,
-  // 41.9 / 15.8 / 12.0, but 62 x 64 -> 32 @53 15.2 / 26.1 / 16.4 and, every row, 13.9 / 31.3 / 21.0.  Chosen launch against the fastest, geometric mean over 146
-  // random layers: sparse 1.008, dense 1.006 (the band kernel alone 1.56 and 1.56).  With fewer channels and many outputs only this kernel
-  // takes its place, where it is 5 % cheaper (the price of the others is not made for a short K): over 263 layers 0.80 and 0.77 of the band
-  // kernel's time, no layer more than 4 % slower.
+  // A plain band kernel that does not stay is priced (band_us).  From 48 channels on it runs where the cheapest of this kernel's tiles
+  // and the others costs 5 % more, the error of the prices: us, band / this kernel / another tile, 3 x 48 -> 32 @17x22 8.1 / 6.3, 4 x
+  // 128 -> 16 @10x8 14.5 / 6.8, 58 x 128 -> 16 @31x36, every row, 41.9 / 15.8 / 12.0, but 62 x 64 -> 32 @53 15.2 / 26.1 / 16.4 and,
+  // every row, 13.9 / 31.3 / 21.0.  Chosen launch against the fastest, geometric mean over 146 random layers: sparse 1.008, dense 1.006
+  // (the band kernel alone 1.56 and 1.56).  With fewer channels and many outputs only this kernel takes its place, where it is 5 %
+  // cheaper (the price of the others is not made for a short K): over 263 layers 0.80 and 0.77 of the band kernel's time, no layer more
+  // than 4 % slower.
   const BandPlan& band = which ? pl->band_dense : pl->band;
   if (band_stays(d, band)) return none;
   const bool plain_band = band.ok && !band.stream, deep = d.c_in >= 48;

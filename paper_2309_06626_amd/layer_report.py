@@ -555,7 +555,7 @@ def main():
         chains["pruned ResNet18 stack (batch 64, s=0.3), channels padded to multiples of 16 (64/112/208/416)"] = \
             chain_time(W.pad_channels(ops, 16), W.base_seed(3), cs)
         chains["the same, every conv through dense_conv_run"] = chain_time(W.pad_channels(ops, 16), W.base_seed(3), cs, dense=True)
-        chains["pruned ResNet18 stack, channels padded to multiples of 8 (56/104/208/416: register-staged tiled kernel)"] = \
+        chains["pruned ResNet18 stack, channels padded to multiples of 8 (56/104/208/416)"] = \
             chain_time(W.pad_channels(ops, 8), W.base_seed(3), cs)
         chains["pruned ResNet18 stack with its own channel counts (51/102/205/410: element-aligned groups)"] = \
             chain_time(ops, W.base_seed(3), cs)
