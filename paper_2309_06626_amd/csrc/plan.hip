@@ -1408,7 +1408,7 @@ static bool band_stays(const sc_conv_desc& d, const BandPlan& band) {
 // Predicted microseconds of a run by the plain band kernel (one band a workgroup, a 16-bit layer).  A round of workgroups costs its fixed
 // part, the slabs of filters and input of those that share a compute unit, the rows they store, and the walk of the busiest wavefront: blocks
 // of 32 or 64 rows, K steps of 16, each with an instruction a 32 x 32 block and, where the window shape is not known to the compiler
-// (band_kernel's KH, KW, CPP), a fixed part; beyond the rounds a megabyte of y.  Fitted to 1 256 runs of 628 layers (16 to 160 channels in,
+// (band_kernel's KH, KW, CPP), a fixed part; beyond the rounds a megabyte of y.  Fitted to 1 604 runs of 802 layers (16 to 160 channels in,
 // 16 to 512 out, maps of 7 to 80, 3 x 3 and 5 x 5): standard deviation 5 % (2 to 6 % in each of the three walks, sparse and dense).
 static double band_us(const sc_plan* pl, int which) {
   const sc_conv_desc& d = pl->desc;
@@ -1418,14 +1418,14 @@ static double band_us(const sc_plan* pl, int which) {
   int mi_idx = 0;
   const double blocks = band_units((double)rows, &mi_idx) / (mi_idx + 1);
   const int walk = d.kh == 3 && d.kw == 3 ? (d.c_in == 32 ? 1 : d.c_in == 64 ? 2 : 0) : 0;
-  static const double steps[3][2] = {{0.0798, 0.0498}, {0.0025, 0.0533}, {0.0011, 0.0278}};      // fixed part, block of 32 x 32
+  static const double steps[3][2] = {{0.0798, 0.0478}, {0.0019, 0.0517}, {0.0034, 0.0239}};      // fixed part, block of 32 x 32
   const double k_us = blocks * ((g.k + 15) / 16) * (steps[walk][0] + steps[walk][1] * (mi_idx + 1) * b.ni);
   const double kb = (double)(b.b_bytes + b.x_bytes) / 1024;
   const int64_t wgs = (int64_t)b.n_bands * b.n_tiles;
   const int resident = (int)std::min<size_t>(std::max<size_t>(kLdsLimit / b.lds, 1), 8);
-  auto round_us = [&](int64_t on_cu) { return (which ? 2.77 : 3.74) + on_cu * (0.0151 * kb + 0.0008 * rows * b.ni) + k_us; };
+  auto round_us = [&](int64_t on_cu) { return (which ? 2.75 : 3.71) + on_cu * (0.0171 * kb + 0.0009 * rows * b.ni) + k_us; };
   const int64_t full = (wgs - 1) / ((int64_t)cus * resident), rest = wgs - full * cus * resident;
-  return full * round_us(resident) + round_us((rest + cus - 1) / cus) + 0.188 * 2e-6 * g.y_elems;
+  return full * round_us(resident) + round_us((rest + cus - 1) / cus) + 0.185 * 2e-6 * g.y_elems;
 }
 // may it run a tile?  (its slabs fit)
 static bool window_fits(const sc_plan* pl, int which, int bm, int bn) {
@@ -1444,13 +1444,13 @@ static sc_plan::Window window_tile_for(const sc_plan* pl, int which) {
   int fbm = 0, fbn = 0;
   if (const char* env = std::getenv("SPARSE_CONV_WINDOW_TILE"); env && std::sscanf(env, "%dx%d", &fbm, &fbn) == 2)
     return fbm > 0 && window_fits(pl, which, fbm, fbn) ? sc_plan::Window{fbm, fbn, true, false, true} : sc_plan::Window{0, 0, false, false, true};
-  // A plain band kernel that does not stay is priced (band_us).  From 48 channels on it runs where the cheapest of this kernel's tiles
-  // and the others costs 5 % more, the error of the prices: us, band / this kernel / another tile, 3 x 48 -> 32 @17x22 8.1 / 6.3, 4 x
-  // 128 -> 16 @10x8 14.5 / 6.8, 58 x 128 -> 16 @31x36, every row, 41.9 / 15.8 / 12.0, but 62 x 64 -> 32 @53 15.2 / 26.1 / 16.4 and,
-  // every row, 13.9 / 31.3 / 21.0.  Chosen launch against the fastest, geometric mean over 146 random layers: sparse 1.008, dense 1.006
-  // (the band kernel alone 1.56 and 1.56).  With fewer channels and many outputs only this kernel takes its place, where it is 5 %
-  // cheaper (the price of the others is not made for a short K): over 263 layers 0.80 and 0.77 of the band kernel's time, no layer more
-  // than 4 % slower.
+  // A plain band kernel that does not stay is priced (band_us).  From 48 channels on it runs where it is cheaper than this kernel's tiles and
+  // the others, by 3 % unless its walk is the unrolled one of 64 channels, whose price is good to 2 % (us, band / this kernel / another tile:
+  // 3 x 48 -> 32 @17x22 8.1 / 6.3, 4 x 128 -> 16 @10x8 14.5 / 6.8, 58 x 128 -> 16 @31x36, every row, 41.9 / 15.8 / 12.0, but 62 x 64 -> 32 @53
+  // 15.2 / 26.1 / 16.4 and, every row, 13.9 / 31.3 / 21.0, 56 x 64 -> 64 @45 at s = 0.25 16.4 / 20.8 / 19.1).  With fewer channels and many
+  // outputs only this kernel takes its place, where it is 5 % cheaper (the price of the others is not made for a short K): over 263 layers
+  // 0.80 and 0.77 of the band kernel's time.  Over 1 790 layers of every kind, of which these rules choose the kernel in most, one sparse
+  // run is 4 % slower than with the kernels without this one, none of the dense ones.
   const BandPlan& band = which ? pl->band_dense : pl->band;
   if (band_stays(d, band)) return none;
   const bool plain_band = band.ok && !band.stream, deep = d.c_in >= 48;
@@ -1494,7 +1494,7 @@ static sc_plan::Window window_tile_for(const sc_plan* pl, int which) {
     const double us = c[0] + c[1] * (rounds - 1) + walk * (c[2] * rounds + c[3] * load) + c[4] * mb;
     if (us < best_us) { best_us = us; best = {sh.bm, sh.bn, plain_band, plain_band && !deep}; }
   }
-  if (plain_band && deep && band_price < 0.95 * best_us / ahead) return none;
+  if (plain_band && deep && band_price < (d.c_in == 64 ? 1.0 : 0.97) * best_us / ahead) return none;
   return best;
 }
 // (not where a tile or a form of another kernel was asked for or measured faster)

@@ -190,9 +190,11 @@ def test_window_kernel_on_many_rows(n, h, w, cout, sp, mode, tile, monkeypatch):
     (62, 64, 53, 53, 32, 0.3, ("band", "band")),                     # us, band / cheapest other launch: 15.2 / 16.4, every row 13.9 / 21.0
     (33, 64, 69, 69, 16, 0.5, ("band", "band")),                     # 11.0 / 14.4, 12.3 / 20
     (58, 128, 31, 36, 16, 0.5, ("tile_window", "tile_lds_direct")),  # every row 41.9 / 12.0
-    (2, 48, 48, 53, 32, 0.7, ("tile_window",) * 2),                  # every row 7.0 / 5.5
+    (2, 48, 48, 53, 32, 0.5, ("tile_window",) * 2),                  # every row 7.0 / 5.5
     (10, 32, 79, 77, 256, 0.5, ("band", "band")),                    # few channels, many outputs: several rounds of the window kernel
     (54, 32, 25, 23, 416, 0.5, ("tile_window",) * 2),                # 25.7 / 17.3, 31.4 / 20.2
+    (48, 64, 55, 55, 16, 0.7, ("band", "band")),                     # 8.5 / 9.1
+    (56, 64, 45, 45, 64, 0.25, ("band", "band")),                    # 16.4 / 19.1
 ])
 def test_plain_band_kernel_gives_way_where_it_is_dearer(n, cin, h, w, cout, sp, want):
     spec = spec_of(n, cin, h, w, cout, sp=sp)
