@@ -234,3 +234,15 @@ def test_tuning_leaves_a_window_tile_that_was_asked_for(monkeypatch):
         layer = R.ConvLayer(spec, ci.w, ci.bias, ci.mask)
         B.sparse_conv_plan_tune(layer.plan, R.to_device(ci.x, spec.dtype), layer.bias, layer.new_output())
         assert all((B.sparse_conv_plan_kernel(layer.plan, which) == "tile_window") == (tile == "64x64") for which in (0, 1))
+
+
+@pytest.mark.parametrize("n,cin,h,w,cout,sp,want", [
+    (17, 32, 14, 15, 40, 0.7, "tile_masked_store"),                  # 6.3 us, in this kernel 7.1 and 7.6
+    (10, 48, 7, 12, 224, 0.7, "tile_masked_store"),                  # 6.6 / 7.2
+    (17, 32, 14, 15, 40, 0.5, "tile_window"),
+])
+def test_sparse_tiles_are_priced_with_the_rows_between_theirs(n, cin, h, w, cout, sp, want):
+    spec = spec_of(n, cin, h, w, cout, sp=sp)
+    mask = (np.random.default_rng(5).permutation(spec.m) >= round(sp * spec.m)).astype(np.uint8)
+    layer = R.ConvLayer(spec, np.zeros((cout, 3, 3, cin), np.float32), np.zeros(cout, np.float32), mask, check_count=False)
+    assert B.sparse_conv_plan_kernel(layer.plan, 0) == want
