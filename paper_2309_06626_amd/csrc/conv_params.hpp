@@ -66,6 +66,7 @@ struct ConvParams {
   // zero-padded image (H + 2 * pad_h, W + 2 * pad_w) and their multiply-shift divisors
   int32_t slab_bytes, slab_hp, slab_wp;
   uint32_t div_hp_mul, div_hp_shift, div_wp_mul, div_wp_shift;
+  int32_t zero_share;      // window launches only: rows of y, kept or not, among which a tile of kept rows writes the zeros
 #ifdef SC_TIMING
   long long* dbg;          // development builds only: per-workgroup phase time stamps
 #endif

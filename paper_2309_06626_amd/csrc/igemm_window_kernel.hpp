@@ -22,7 +22,10 @@
 // Tried and left out: reads of the next tap ahead of all products of this one (12.7 -> 13.0 of a loop), the zeros of dropped rows between
 // the products of the first pass (their acknowledgements hold up the filters' waits: 7.4 -> 8.0).
 //
-// Workgroup = BM kept rows x BN channels, eight wavefronts; zero-fill ownership and the epilogue are those of the other tiled kernels.
+// Workgroup = BM kept rows x BN channels, eight wavefronts; the epilogue is that of the other tiled kernels.  The zeros of the dropped rows are
+// shared out by rows of the map, as many for every tile wherever its kept rows lie: a tile that wrote those up to the next tile's first row,
+// as in the other kernels, had them all where half of a map is dropped in one piece (38 x 160 -> 64 @21x19 with
+// the lower half dropped 30.4 us, now 8.4, with every other row dropped 8.0).
 #pragma once
 #include <type_traits>
 
@@ -72,8 +75,9 @@ __global__ __launch_bounds__(512) void igemm_window_kernel(const ConvParams p) {
   float* s_bias = reinterpret_cast<float*>(s_corner + BM);      // [BN]
   int32_t* s_px = reinterpret_cast<int32_t*>(s_bias + BN);      // [kWinMostPixels] byte offset of a slab pixel in x
   int32_t* s_count = s_px + kWinMostPixels;                     // [16] rows of a residue, then the rows beyond the last set
+  int32_t* s_drops = s_count + 24;                              // [8] dropped rows that a wavefront has found
   int32_t* s_hole = s_count + 32;                               // [BM]
-  int32_t* s_drop = s_hole + BM;                                // [ZERO_ROWS] the first dropped rows this workgroup owns
+  int32_t* s_drop = s_hole + BM;                                // [ZERO_ROWS] the first dropped rows of this workgroup's share
 
   const int nwg = p.m_tiles * p.n_tiles;
   const int per_xcd = (nwg + 7) >> 3;
@@ -88,20 +92,21 @@ __global__ __launch_bounds__(512) void igemm_window_kernel(const ConvParams p) {
   const int hp = p.slab_hp, wp = p.slab_wp;
   T* __restrict__ y = static_cast<T*>(p.y);
 
-  // ---- first round trip: row numbers, the dense rows this workgroup owns, bias; the first filters need none of them ----------------
+  // ---- first round trip: row numbers, the mask of this workgroup's share of the map, bias; the first filters need none of them ----------------
   const int i_last = min(m0 + BM, p.rows) - 1;
   const int r_first = p.row_idx ? p.row_idx[m0] : m0;
   const int r_last = p.row_idx ? p.row_idx[i_last] : i_last;
-  int z_lo = 0, z_hi = p.m_total;
+  const int z_lo = tile_m * p.zero_share, z_hi = (int)min((int64_t)z_lo + p.zero_share, (int64_t)p.m_total);
+  auto mask_of = [&](int r) { return (int)p.mask[p.mask_spatial ? r - fast_div(r, p.div_howo_mul, p.div_howo_shift) * p.ho_wo : r]; };
+  int keeps[2] = {0, 0};                                 // mask of rows z_lo + t and z_lo + 512 + t
   if (p.zero_fill) {
-    if (tile_m != 0) z_lo = r_first;
-    if (m0 + BM < p.rows) z_hi = p.row_idx[m0 + BM];
+    keeps[0] = mask_of(min(z_lo + t, p.m_total - 1));
+    if (p.zero_share > 512) keeps[1] = mask_of(min(z_lo + 512 + t, p.m_total - 1));
   }
-  int my_row = 0, before = -1;                           // row of tile row t, and the kept one in front of it
+  int my_row = 0;                                        // row of tile row t
   if (t < BM) {
     const int i = min(m0 + t, p.rows - 1);
     my_row = p.row_idx ? p.row_idx[i] : i;
-    if (p.zero_fill && i > 0) before = p.row_idx[i - 1];
   }
   float bias_v = 0.0f;
   if (t < BN && p.bias && n0 + t < p.c_out) bias_v = p.bias[n0 + t];
@@ -129,7 +134,6 @@ __global__ __launch_bounds__(512) void igemm_window_kernel(const ConvParams p) {
 
   const int zc = t % CPR, zr = t / CPR;
   const bool fill_ahead = p.zero_fill && !p.residual && (int64_t)p.m_total * p.c_out * EB < ((int64_t)1 << 31);      // (byte offsets of a buffer)
-  const int n_drop = z_hi - z_lo - (i_last + 1 - m0), n_list = p.zero_fill ? min(n_drop, D::ZERO_ROWS) : 0;
   // ---- the slab: a run of pixels of the images with their zero margins (virtual rows of wp pixels, hp of them an image), from the
   // corner of the first row's window to the end of the last one's.  A tap is then one displacement, the same for every row. -----------
   auto corner = [&](int r) {
@@ -176,14 +180,13 @@ __global__ __launch_bounds__(512) void igemm_window_kernel(const ConvParams p) {
   auto lds_barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
   constexpr int SETS = BM / 16;
   int place = -1, spare = 0;
-  if (p.zero_fill && t < BM && m0 + t < p.rows) {
-    // the dropped rows in front of tile row t, and behind the last one: row r is dropped row number r - z_lo - (kept ones before it)
-    int at = max(before + 1, z_lo) - z_lo - t;
-    for (int r = max(before + 1, z_lo); r < my_row && at < D::ZERO_ROWS; ++r, ++at) s_drop[at] = r;
-    if (m0 + t == i_last) {
-      at = my_row + 1 - z_lo - (t + 1);
-      for (int r = my_row + 1; r < z_hi && at < D::ZERO_ROWS; ++r, ++at) s_drop[at] = r;
-    }
+  int n_drop = 0;                                         // dropped rows among the first 1 024 of the share
+  unsigned long long drop_bits[2] = {0, 0};
+  if (p.zero_fill) {
+    asm volatile("" : "+v"(keeps[0]), "+v"(keeps[1]));    // (waited for here, behind the slab's transfers)
+    drop_bits[0] = __ballot(keeps[0] == 0 && z_lo + t < z_hi);
+    drop_bits[1] = __ballot(keeps[1] == 0 && z_lo + 512 + t < z_hi);
+    if (lane == 0) s_drops[wave] = (int)__popcll(drop_bits[0]) | (int)__popcll(drop_bits[1]) << 16;
   }
   if (t < BM) {
     const int k = atomicAdd(&s_count[my_px & 15], 1);
@@ -202,6 +205,23 @@ __global__ __launch_bounds__(512) void igemm_window_kernel(const ConvParams p) {
       found += __popcll(b);
     }
   }
+  if (p.zero_fill) {
+    int in_front[2] = {0, 0}, all = 0;                    // (the counts of rows z_lo + 0 .. 511 and of the 512 behind them in halves of a word)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      if (i == wave) in_front[0] = in_front[1] = all;
+      all += s_drops[i];
+    }
+    n_drop = (all & 0xffff) + (all >> 16);
+    in_front[0] &= 0xffff;
+    in_front[1] = (in_front[1] >> 16) + (all & 0xffff);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int i = in_front[u] + (int)__popcll(drop_bits[u] & ((1ull << lane) - 1ull));
+      if ((drop_bits[u] >> lane & 1) && i < D::ZERO_ROWS) s_drop[i] = z_lo + u * 512 + t;
+    }
+  }
+  const int n_list = min(n_drop, D::ZERO_ROWS);
   lds_barrier();
   if (t < BM) {
     if (place < 0) place = s_hole[spare];
@@ -214,7 +234,7 @@ __global__ __launch_bounds__(512) void igemm_window_kernel(const ConvParams p) {
 #pragma unroll
   for (int mi = 0; mi < MI; ++mi) a_base[mi] = lds0 + (unsigned)s_corner[wm0 + mi * 32 + fp] + (unsigned)((2 * kg + fh) * 16);
 
-  // ---- zeros of the dropped rows this workgroup owns (Alg. 2, mask == 0 branch), the first passes ------------------------------
+  // ---- zeros of the dropped rows of this workgroup's share (Alg. 2, mask == 0 branch), the first passes -------------------------
   if (fill_ahead) {
     const int valid = (min(BN, p.c_out - n0) * EB) >> 4;
 #pragma unroll
@@ -322,7 +342,7 @@ __global__ __launch_bounds__(512) void igemm_window_kernel(const ConvParams p) {
   }
 
   // ---- zero fill: the rows behind the listed ones, and those too where they have not had their zeros yet (a shortcut is fused) --------
-  if (p.zero_fill && (!fill_ahead || n_drop > n_list)) {
+  if (p.zero_fill && (!fill_ahead || n_drop > n_list || z_hi - z_lo > 1024)) {
     const int valid = (min(BN, p.c_out - n0) * EB) >> 4;
     if (zc < valid) {
       const int64_t at0 = (int64_t)n0 * EB + zc * 16;
@@ -340,14 +360,12 @@ __global__ __launch_bounds__(512) void igemm_window_kernel(const ConvParams p) {
           if (zr + u * RPI < n_list)
             sc_store16(reinterpret_cast<v4i*>(ybase + (int64_t)s_drop[zr + u * RPI] * p.c_out * EB), p.residual ? shortcut_alone<DT>(g[u], p.residual_relu) : g[u]);
       }
-      const int z_from = n_drop > n_list ? s_drop[D::ZERO_ROWS - 1] + 1 : z_hi;
+      const int z_from = n_drop > n_list ? s_drop[D::ZERO_ROWS - 1] + 1 : min(z_lo + 1024, z_hi);
       for (int r0 = z_from + zr; r0 < z_hi; r0 += 4 * RPI) {
-        unsigned char m4[4];
+        int m4[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          int r = min(r0 + u * RPI, z_hi - 1);
-          if (p.mask_spatial) r -= fast_div(r, p.div_howo_mul, p.div_howo_shift) * p.ho_wo;
-          m4[u] = p.mask[r];
+          m4[u] = mask_of(min(r0 + u * RPI, z_hi - 1));
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {

@@ -1491,10 +1491,11 @@ static sc_plan::Window window_tile_for(const sc_plan* pl, int which) {
     const double* c = sh.us[form];
     const int kg = sh.bm == 256 ? 1 : sh.bn == 128 ? 2 : 4, last = (d.c_in - (chunks - 1) * kWinChunk + 15) / 16;      // K groups, K steps of the last chunk
     const double walk = (chunks - 1 + (double)((last + kg - 1) / kg * kg) / 4) * (d.kh * d.kw / 9.0);      // (in chunks of a 3 x 3 window)
-    // (from half of the rows on a sparse run also pays for what lies between a tile's rows: the zeros of a gap are listed by one lane, the slab
-    // grows.  us beyond the price in one chunk, 64 x 64: s = 0.6 0.25, 0.7 0.65, 0.8 1.1, 0.9 1.3, 0.95 2.1, the other tiles alike.  17 x 32 ->
-    // 40 @14x15 at s = 0.7 took 7.6, priced 5.9, in another tile 6.3.  The price of 5 x 5 windows, 10 % high, has room for it.)
-    const double between = form == 0 && d.kh == 3 ? std::max(0.0, std::log((double)pl->geo.m / (2.0 * rows))) : 0.0;
+    // (where a tile's share of the map holds more dropped rows than have their zeros written ahead of the products, two thirds for 64 rows, the
+    // others come behind them, and the slab grows.  us beyond the price in one chunk, 64 x 64: s = 0.6 0.0, 0.7 0.5, 0.8 0.6, the other tiles
+    // alike.  17 x 32 -> 40 @14x15 at s = 0.7 takes 6.6 to 6.9, priced 6.0, in another tile 6.3.  The price of 5 x 5 windows, 10 % high, has room for it.)
+    const bool over = form == 0 && d.kh == 3 && pl->geo.m * sh.bm > rows * (2 * sh.bm + 64);
+    const double between = over ? 0.5 + 0.5 * std::max(0.0, std::log((double)pl->geo.m / (3.3 * rows))) : 0.0;
     const double us = c[0] + c[1] * (rounds - 1) + walk * (c[2] * rounds + c[3] * load) + c[4] * mb + between;
     if (us < best_us) { best_us = us; best = {sh.bm, sh.bn, plain_band, plain_band && !deep}; }
   }
@@ -1873,6 +1874,7 @@ static sc_status launch_conv(const sc_plan* pl, bool dense, const void* x, const
     p.w_bytes = (uint32_t)((uint64_t)((d.c_out + 31) / 32) * 32 * d.kh * d.kw * ((d.c_in + kWinChunk - 1) / kWinChunk) * kWinChunk * eb);
     p.vec_out = g.vec_out ? 1 : 2;
     p.slab_bytes = window_slab_bytes(pl, which, win.bm);
+    p.zero_share = (int32_t)((g.m + p.m_tiles - 1) / p.m_tiles);
     p.slab_hp = d.h + 2 * d.pad_h;
     p.slab_wp = d.w + 2 * d.pad_w;
     magic_div((uint32_t)p.slab_hp, &p.div_hp_mul, &p.div_hp_shift);
