@@ -12,7 +12,7 @@
 //     a K group takes every KG-th step of 16 channels, and the groups' sums are added through LDS in order at the end.
 // A pixel takes nine 16-byte groups in LDS, of which eight hold channels: reads of sixteen consecutive pixels touch every bank once.  The
 // kept rows of a mask are not consecutive, and which ones stand side by side is chosen for that (below); a fifth of the rows of a 64-row tile
-// finds every set of its residue full and takes a hole all the same, and 44 % of the LDS cycles are conflict cycles (64 x 512 -> 512 @7).
+// finds every set of its residue full and takes a hole all the same, and 43 % of the LDS cycles are conflict cycles (64 x 512 -> 512 @7).
 //
 // Measured at s = 0.5 in bf16, launches behind each other on one card, the tiled kernels / this one, us: 64 x 512 -> 512 @7 20.7 / 15.3 (dense
 // 28.6 / 20.6), 64 x 256 -> 256 @14 17.6 / 15.2 (21.8 / 20.1), 16 x 256 -> 256 @14 12.7 / 9.6 (13.0 / 8.7), 64 x 128 -> 128 @28 15.8 / 14.5
@@ -24,8 +24,8 @@
 //
 // Workgroup = BM kept rows x BN channels, eight wavefronts; the epilogue is that of the other tiled kernels.  The zeros of the dropped rows are
 // shared out by rows of the map, as many for every tile wherever its kept rows lie: a tile that wrote those up to the next tile's first row,
-// as in the other kernels, had them all where half of a map is dropped in one piece (38 x 160 -> 64 @21x19 with
-// the lower half dropped 30.4 us, now 8.4, with every other row dropped 8.0).
+// as in the other kernels, had them all where half of a map is dropped in one piece (38 x 160 -> 64 @21x19 with the
+// lower half dropped 30.4 us, now 8.1; as many rows dropped here and there 8.2).
 #pragma once
 #include <type_traits>
 
