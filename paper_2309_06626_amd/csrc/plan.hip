@@ -1449,8 +1449,8 @@ static sc_plan::Window window_tile_for(const sc_plan* pl, int which) {
   // 3 x 48 -> 32 @17x22 8.1 / 6.3, 4 x 128 -> 16 @10x8 14.5 / 6.8, 58 x 128 -> 16 @31x36, every row, 41.9 / 15.8 / 12.0, but 62 x 64 -> 32 @53
   // 15.2 / 26.1 / 16.4 and, every row, 13.9 / 31.3 / 21.0, 56 x 64 -> 64 @45 at s = 0.25 16.4 / 20.8 / 19.1).  With fewer channels and many
   // outputs only this kernel takes its place, where it is 5 % cheaper (the price of the others is not made for a short K): over 263 layers
-  // 0.80 and 0.77 of the band kernel's time.  Over 1 790 layers of every kind, of which these rules choose the kernel in most, one sparse
-  // run is 4 % slower than with the kernels without this one, none of the dense ones.
+  // 0.80 and 0.77 of the band kernel's time.  Over 400 layers drawn at random, with rows dropped here and there, in blocks and at the end, the 205 sparse
+  // and 270 dense runs that these rules give to this kernel take 0.58 times the time of the kernels without it, one 1.06 times, the others at most 1.03.
   const BandPlan& band = which ? pl->band_dense : pl->band;
   if (band_stays(d, band)) return none;
   const bool plain_band = band.ok && !band.stream, deep = d.c_in >= 48;
@@ -1496,7 +1496,11 @@ static sc_plan::Window window_tile_for(const sc_plan* pl, int which) {
     // alike.  17 x 32 -> 40 @14x15 at s = 0.7 takes 6.6 to 6.9, priced 6.0, in another tile 6.3.  The price of 5 x 5 windows, 10 % high, has room for it.)
     const bool over = form == 0 && d.kh == 3 && pl->geo.m * sh.bm > rows * (2 * sh.bm + 64);
     const double between = over ? 0.5 + 0.5 * std::max(0.0, std::log((double)pl->geo.m / (3.3 * rows))) : 0.0;
-    const double us = c[0] + c[1] * (rounds - 1) + walk * (c[2] * rounds + c[3] * load) + c[4] * mb + between;
+    // (two prices are low.  Half of the wavefronts of 256 x 128 hold no outputs where there are 64 or fewer: 57 x 48 -> 40 @23x26, every row, 10.4 us,
+    // in other tiles 9.3, 37 x 72 -> 40 @31 13.1 / 12.0, but 60 x 72 -> 40 @45x48 26.1 / 29.0.  And 128 rows and more over every row of one whole
+    // chunk, where much of y goes out at once: 20 x 64 -> 320 @22 9.8 / 9.0, 40 x 64 -> 384 @14 9.9 / 9.3, but 64 x 64 -> 512 @12 12.4 / 14.2.)
+    const double low = sh.bm == 256 && d.c_out <= 64 ? 1.08 : sh.bm >= 128 && form && chunks == 1 && family == 0 ? 1.055 : 1.0;
+    const double us = (c[0] + c[1] * (rounds - 1) + walk * (c[2] * rounds + c[3] * load) + c[4] * mb) * low + between;
     if (us < best_us) { best_us = us; best = {sh.bm, sh.bn, plain_band, plain_band && !deep}; }
   }
   if (plain_band && deep && band_price < (d.c_in == 64 ? 1.0 : 0.97) * best_us / ahead) return none;

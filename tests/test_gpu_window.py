@@ -290,6 +290,20 @@ def test_tuning_leaves_a_window_tile_that_was_asked_for(monkeypatch):
         assert all((B.sparse_conv_plan_kernel(layer.plan, which) == "tile_window") == (tile == "64x64") for which in (0, 1))
 
 
+@pytest.mark.parametrize("n,cin,h,w,cout,want", [
+    (57, 48, 23, 26, 40, "tile_registers"),                          # every row, us, other tiles / this kernel: 9.3 / 10.4
+    (37, 72, 31, 31, 40, "tile_registers"),                          # 12.0 / 13.1
+    (60, 72, 45, 48, 40, "tile_window"),                             # 29.0 / 26.1
+    (20, 64, 22, 22, 320, "tile_lds_direct"),                        # 9.0 / 9.8
+    (40, 64, 14, 14, 384, "tile_lds_direct"),                        # 9.3 / 9.9
+    (64, 64, 12, 12, 512, "tile_window"),                            # 14.2 / 12.4
+])
+def test_dense_runs_take_the_cheaper_kernel(n, cin, h, w, cout, want):
+    spec = spec_of(n, cin, h, w, cout)
+    layer = R.ConvLayer(spec, np.zeros((cout, 3, 3, cin), np.float32), np.zeros(cout, np.float32), np.ones(spec.m, np.uint8), check_count=False)
+    assert B.sparse_conv_plan_kernel(layer.plan, 1) == want
+
+
 @pytest.mark.parametrize("n,cin,h,w,cout,sp,want", [
     (17, 32, 14, 15, 40, 0.7, "tile_masked_store"),                  # 6.3 us, in this kernel 6.6 and 6.9
     (10, 48, 7, 12, 224, 0.7, "tile_masked_store"),                  # 6.6 / 6.7
